@@ -457,6 +457,9 @@ def main():
         return
     layers = [Layer(cg, torch, synth, c, plan_override, psum_fp16=args.psum_fp16) for c in cases]
     torch.cuda.synchronize()
+    if args.ablate:                                     # the ablation builds leave parts of the Psumbook kernel out
+        for L in layers:
+            L.plan.centroid_rows = L.plan.centroid_splits = 0
     if args.phases:
         phases_report(torch, cg, layers)
         return

@@ -109,7 +109,13 @@ typedef struct codegemm_plan {
                             /* 2 (waves = 16, row_words = 2, batch_group = 1, fp32 Psumbook, m <= 2): the */
                             /* last two wavefronts only build, one unit ahead; the other 14 stream,       */
                             /* gather and own the workgroup's 448 rows                                    */
-    int32_t reserved[2];    /* must be zero */
+    int32_t centroid_rows;  /* 0: the Psumbook kernels, as described by the fields above.  32, 64 or 128: */
+                            /* the centroid kernel, which multiplies the centroid vectors themselves with  */
+                            /* x on the matrix cores (no Psumbook; for batches), in blocks of that many    */
+                            /* rows.  The fields above are then only validated; the workspace is sized for */
+                            /* both.  Needs one scale per row or at least 8 sub-vectors per group          */
+    int32_t centroid_splits; /* K ranges of the centroid kernel, >= 1 (clamped like k_splits); 0 when       */
+                            /* centroid_rows = 0                                                            */
 } codegemm_plan;
 
 enum {

@@ -48,10 +48,12 @@ struct Geometry {
     int RPL;        // 8-row words per lane per unit (1, 2 or 4): the workgroup owns 16 * (NW - NB) * RPL rows
                     // (32 * NW * RPL in the batched kernel, BG = 4)
     int BG;         // batch rows per pass over the codes
+    int RB;         // rows of a block of the centroid kernel (32, 64 or 128), or 0: one of the Psumbook kernels
     int NGR;        // ceil(N / 128) granules
     int NBLK;       // row blocks = workgroups along N: NGR over the granules per workgroup, rounded up
     int NKT;        // ceil(J / 32) K tiles
     int NKS;        // workgroups per row block (K ranges)
+    int WKS;        // K ranges the workspace holds partial sums of up to kBatchPerLaunch rows for
     int KPW;        // K tiles per workgroup: ceil(NKT / NKS)
     int NG;         // ceil(B / BG) batch groups
     int Npad;       // NGR * 128
@@ -81,6 +83,7 @@ __host__ __device__ inline size_t packed_offset(int c, int n, int j, int m, int 
 
 int make_geometry(const codegemm_desc* d, const codegemm_plan* plan, Geometry* g);   // status
 size_t workspace_counter_bytes(const Geometry& g);   // the fixed area in front of the partial sums: counters, then pair words
+size_t workspace_need(const Geometry& g);            // bytes of workspace of one launch
 size_t pair_words(const Geometry& g);                // 64-bit words the pairwise reduction of this problem needs; 0: not offered
 int counter_stride(const Geometry& g);               // words between two row blocks' counters; 0: the plan does not fit
 

@@ -4,6 +4,7 @@
 #include <vector>
 
 #include "gemm_batch_impl.h"
+#include "gemm_centroid_impl.h"
 
 namespace cg {
 
@@ -73,6 +74,15 @@ extern "C" void codegemm_set_trace(uint64_t* stamps) { g_trace = stamps; }
 // Kernel instance for a geometry -> launch.  g.NBLK is the number of row blocks of all members of p.
 static int dispatch(const Geometry& g, const GemmParams& p, hipStream_t s)
 {
+    if (g.RB) {
+        switch (g.m) {
+            case 1: return launch_gemm_centroid_m1(g, p, s);
+            case 2: return launch_gemm_centroid_m2(g, p, s);
+            case 3: return launch_gemm_centroid_m3(g, p, s);
+            case 4: return launch_gemm_centroid_m4(g, p, s);
+        }
+        return CODEGEMM_UNSUPPORTED;
+    }
     if (g.BG == 4) {
         switch (g.m) {
             case 1: return g.g > 0 ? launch_gemm_batch_gs_m1(g, p, s) : launch_gemm_batch_m1(g, p, s);
@@ -122,7 +132,7 @@ static void fill_common(GemmParams* p, const Geometry& g, const void* x, void* w
     p->y_fp32 = g.y_fp32 ? 1 : 0;
     p->trace = nullptr;
 #ifdef CODEGEMM_TRACE
-    p->trace = reinterpret_cast<unsigned long long*>(g_trace);
+    if (!g.RB) p->trace = reinterpret_cast<unsigned long long*>(g_trace);   // the centroid kernel has other phases and no stamps
 #endif
     p->ngrp = 1;
     for (int i = 0; i < kMaxGroup; ++i) p->mem[i] = Member{};
@@ -142,7 +152,7 @@ static void fill_member(Member* mm, const Geometry& g, const uint8_t* packed_cod
     mm->blk0 = blk0;
 }
 
-// One launch: at most kBatchPerLaunch batch rows.
+// One launch: at most kBatchPerLaunch batch rows with the Psumbook kernels.
 static int gemm_launch(const codegemm_desc* desc, const codegemm_plan* plan, const void* x,
                        const uint8_t* packed_codes, const void* codebooks, const void* scales,
                        void* y, void* workspace, size_t workspace_bytes, void* stream)
@@ -155,7 +165,7 @@ static int gemm_launch(const codegemm_desc* desc, const codegemm_plan* plan, con
         misaligned(y) || misaligned(workspace))
         return CODEGEMM_INVALID_ARG;
     const size_t cbytes = workspace_counter_bytes(g);
-    const size_t need = cbytes + (size_t)g.B * g.NKS * g.Npad * sizeof(float);
+    const size_t need = workspace_need(g);
     if (workspace_bytes < need) return CODEGEMM_WORKSPACE_TOO_SMALL;
 
     GemmParams p;
@@ -181,6 +191,7 @@ extern "C" int codegemm_gemm(const codegemm_desc* desc, const codegemm_plan* pla
     Geometry g;
     int st = make_geometry(desc, plan, &g);
     if (st) return st;
+    if (g.RB) return gemm_launch(desc, plan, x, packed_codes, codebooks, scales, y, workspace, workspace_bytes, stream);
     if (!x || !y) return CODEGEMM_INVALID_ARG;
     const size_t ysize = g.y_fp32 ? sizeof(float) : sizeof(_Float16);
     for (int b0 = 0; b0 < desc->batch; b0 += kBatchPerLaunch) {
@@ -255,7 +266,7 @@ extern "C" size_t codegemm_grouped_workspace_bytes(const codegemm_desc* desc, co
 {
     Geometry members[kMaxGroup], whole;
     if (group_geometry(desc, plan, out_features, count, members, &whole)) return 0;
-    return workspace_counter_bytes(whole) + (size_t)whole.B * whole.NKS * whole.Npad * sizeof(float);
+    return workspace_need(whole);
 }
 
 extern "C" int codegemm_gemm_grouped(const codegemm_desc* desc, const codegemm_plan* plan, const void* x,
@@ -276,7 +287,7 @@ extern "C" int codegemm_gemm_grouped(const codegemm_desc* desc, const codegemm_p
             return CODEGEMM_INVALID_ARG;
     }
     const size_t cbytes = workspace_counter_bytes(whole);
-    const size_t need = cbytes + (size_t)whole.B * whole.NKS * whole.Npad * sizeof(float);
+    const size_t need = workspace_need(whole);
     if (workspace_bytes < need) return CODEGEMM_WORKSPACE_TOO_SMALL;
 
     GemmParams p;

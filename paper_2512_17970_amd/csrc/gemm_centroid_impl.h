@@ -1,0 +1,500 @@
+// The hot path for batches without a Psumbook: centroid vectors go straight from LDS into the
+// matrix cores.  Included by gemm_centroid_m1.hip .. gemm_centroid_m4.hip.
+//
+// A Psumbook costs 4 bytes of LDS per batch row and code to gather and has to be rebuilt (LDS
+// writes, the slow direction) for every 32 sub-vectors of every row block; a centroid costs 2 v
+// bytes per code whatever the batch, its table never changes, and v_mfma_f32_16x16x32_f16 takes
+// 16 rows x 32 weights of it per instruction.  From two batch rows on that is the cheaper side.
+// W is still never formed: each codebook's centroids are multiplied with x on their own (exact
+// fp16 products, fp32 accumulation), and scales are applied to fp32 sums.
+//
+// Mapping onto the packed code layout (no re-ordering).  In v_mfma_f32_16x16x32_f16 lane l of a
+// wavefront is column i = l % 16 of the weight operand and slice q = l / 16 of the contraction.
+// The columns are row octets of a granule: MFMA u takes row u of every octet, so the 8 rows x 2
+// codebooks of one packed 16-byte entry feed 16 MFMAs and no lane needs another lane's codes.
+// The other operand is x itself, batch rows along its 16 columns.
+// With 8 or 4 batch rows the 16 columns are 8 x 2 or 4 x 4 (batch row, sub-vector), and the
+// weight operand's are 8 x 2 or 4 x 4 (octet, sub-vector): only the result elements where the two
+// sub-vectors agree mean anything, and they are picked and added over the SB = 2 or 4 lanes at the
+// end.  That costs nothing (an instruction takes in 512 weights either way) and puts neighbouring
+// lanes on neighbouring entries: with one octet per lane the loads of a quad of lanes fall into
+// four cache lines and take 64 clocks instead of 16.  For more than 8 batch rows (SB = 1) pairs of
+// loads are made with pairs of lanes along contiguous memory and exchanged in registers.
+//
+// LDS table: rows of 256 bytes, one per code, each centroid repeated in several columns so that
+// the 16 lanes of one LDS cycle read 16 different 16-byte columns whatever the codes are; planes
+// of 64 KB.  The byte address (plane << 16) | (code << 8) | column is one byte-permute, as in the
+// other kernels.  Two codebooks share the rows of a plane with 8 columns each: lanes 8..15 of a
+// row of lanes take the two in the opposite order (their sums do not care), so that at any time
+// half of the lanes read one half of the row; four codebooks of 32-byte vectors do the same with
+// 4 columns and quads of lanes.
+// Measured (random codes, ns per 64-lane read and compute unit): 16 columns of 16 bytes 2.1, 8
+// columns 3.5, 4 columns 7, no copies 26; with the MFMA that consumes it 3.1-3.6, 3.9-4.5, 7.4, 26.
+//
+// The KW wavefronts of a workgroup take consecutive slices of the workgroup's K range for the
+// same rows, and their sums meet in LDS: a matrix needs K ranges on different workgroups (and
+// the exchange through the workspace) only when N / rows does not fill the chip.
+#pragma once
+
+#include "gemm_impl.h"
+
+namespace cg {
+
+typedef __attribute__((address_space(3))) half8_t lds_half8;
+typedef __attribute__((address_space(3))) half4_t lds_half4;
+typedef __attribute__((address_space(3))) float4_t lds_f4;
+
+template <int M, int V>
+struct CentroidTable {
+    static constexpr int kEntry = V == 4 ? 8 : 16;                      // bytes one lookup reads
+    static constexpr int kHalves = V == 16 ? 2 : 1;                     // lookups per centroid (a plane, or set of planes, each)
+    static constexpr int kPlanesPerHalf = V == 16 ? 1 : (M + 1) / 2;
+    static constexpr int kBytes = kHalves * kPlanesPerHalf * 65536;
+    // Lanes that differ in these bits of i take the codebooks of a plane in another order: codebook k of
+    // the program is codebook k ^ order(i) of the lane.
+    static constexpr int kOrderBits = (V == 4 || M == 1) ? 0 : (V == 16 && M == 4) ? 2 : 1;
+    __host__ __device__ static constexpr int plane(int c, int h) { return V == 16 ? h : c / 2; }
+    // region of codebook c in the rows of its plane
+    __host__ __device__ static constexpr int region(int c)
+    {
+        return V == 16 ? (M <= 2 ? (c % 2) * 128 : c * 64) : (c % 2) * 128;
+    }
+    __host__ __device__ static constexpr int columns(int c)
+    {
+        const bool alone = c == M - 1 && (M & 1);                       // the last of an odd number has no partner
+        const int bytes = V == 16 ? (M == 1 ? 256 : M == 2 ? 128 : alone ? 128 : 64) : alone ? 256 : 128;
+        return bytes / kEntry;
+    }
+};
+
+// 2 x 2 transpose of dwords between two registers and the two lanes of each pair.
+__device__ __forceinline__ void pair_transpose(uint32_t& a, uint32_t& b, bool odd)
+{
+    auto swap1 = [](uint32_t v) { return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0xb1, 0xf, 0xf, true); };   // l <-> l ^ 1
+    const uint32_t from_a = swap1(a), from_b = swap1(b);                // before the selects: all lanes take part
+    const uint32_t na = odd ? from_b : a, nb = odd ? b : from_a;
+    a = na;
+    b = nb;
+}
+
+// SB: sub-vectors along the columns of the operands (16 / SB octets per wavefront, 16 / SB batch rows per tile).
+// NT: tiles of batch rows.  RW x KW wavefronts: RW blocks of 128 / SB rows, KW slices of K.  D: steps in the load
+// ring.  GS: group scales; a step (16 sub-vectors, 32 for v = 4) lies in one group.  ONE (SB = 4): one batch row, for
+// which the result elements are arranged so that a lane has one that means something instead of one of four.
+template <int M, int V, int SB, int NT, int RW, int KW, int D, bool GS, bool ONE>
+__global__ void __launch_bounds__(RW * KW * 64) gemm_centroid_kernel(CG_HEAD_PARAMS, const GemmParams pk)
+{
+    const GemmParams p = with_head(pk, hx, hpacked, hcodebooks, hgscales, hK, hNKT, hKPW, hB, hNGR, hmisc);
+    typedef CentroidTable<M, V> T;
+    constexpr int THREADS = RW * KW * kWave;
+    constexpr int OCT = 16 / SB;                       // octets of a wavefront
+    constexpr int RB = 8 * OCT * RW;                   // rows of the workgroup
+    constexpr int BPT = ONE ? 1 : 16 / SB;             // batch rows per tile
+    static_assert(!ONE || (SB == 4 && NT == 1), "one batch row");
+    constexpr int BT = BPT * NT;                       // batch rows of the workgroup
+    constexpr int SPU = V == 4 ? 1 : 2;                // steps per unit of 32 sub-vectors
+    constexpr int R = 4 / SB;                          // rounds per step: 4 SB chunks of 16 bytes of x (v = 16: 32) each
+    constexpr int HALVES = T::kHalves;                 // operands of 8 elements per chunk
+    constexpr int NSB = R * HALVES * M;                // (round, half, codebook) per step: 8 lookups and 8 NT MFMAs each
+    constexpr int PW = V == 4 ? 8 : 4;                 // dwords per lane and round of a part with two codebooks
+    constexpr int WR = PW / 2 * M;                     // .. of all parts
+    constexpr int CHUNK = V == 16 ? 16 : 8;            // elements of x per chunk
+    constexpr int kUnitBytes = kGranuleRows * kSlots * M;
+    constexpr int kOutOfRange = 0x7ffffff0;
+    constexpr uint32_t kRsrcFlags = 0x00020000u;
+    static_assert(RB <= kGranuleRows, "rows of a workgroup lie in one granule");
+
+    extern __shared__ __align__(16) unsigned char smem[];
+    const int tid = threadIdx.x;
+    const int lane = tid & (kWave - 1);
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int rw = wave % RW, kw = wave / RW;
+    const int ks = blockIdx.x;
+    const Member mm = member_of(p, blockIdx.y);
+    const int blk = blockIdx.y - mm.blk0;
+    const int b0 = blockIdx.z * BT;
+    const int kt0 = ks * p.KPW;
+    const int nq = min(p.KPW, p.NKT - kt0);
+    const int q = lane >> 4;
+    // columns of the operands: octet (batch row) and sub-vector; with SB = 1 the loads pair up lanes as with SB = 2
+    // and the exchange leaves octet (batch row) lane % 16 to the lane
+    constexpr int LS = SB == 1 ? 2 : SB;
+    const int ls = lane & (LS - 1), lo = (lane & 15) / LS;
+    const int col_o = (lane & 15) / SB;                // octet of this lane's column
+    const bool odd = lane & 1;
+
+    // Table entries of this thread, requested first: everything waits for them.
+    constexpr int ENTRIES = M * kCentroids * T::kHalves;                // to replicate
+    constexpr int TPE = 2 * ENTRIES <= THREADS ? 2 : 1;                 // threads that share one entry's columns
+    constexpr int EPT = (ENTRIES + THREADS - 1) / THREADS;              // entries per thread
+    typedef typename Frag<V == 4 ? 4 : 16>::type entry_t;               // 8 or 16 bytes
+    entry_t fill[EPT];
+#pragma unroll
+    for (int k = 0; k < EPT; ++k) {
+        const int e = TPE > 1 ? min(tid / TPE, ENTRIES - 1) : min(tid + k * THREADS, ENTRIES - 1);
+        fill[k] = reinterpret_cast<const entry_t*>(mm.codebooks)[e];    // entry e = (codebook, centroid, half) in memory order
+    }
+
+    // This wavefront's steps [s_beg, s_end) of the workgroup's K range.
+    const int total = nq * SPU;
+    const int s_beg = total * kw / KW, s_end = total * (kw + 1) / KW;
+
+    // x: round j of a step, chunk 4 q + SB j + ls of the step's 16 (SB = 1: loads 2 jj and 2 jj + 1 take chunk
+    // 4 q + 2 jj + ls of batch rows 2 lo and 2 lo + 1; after the exchange register r is chunk 4 q + r of row lane % 16)
+    const __amdgpu_buffer_rsrc_t x_rsrc = __builtin_amdgcn_make_buffer_rsrc(
+        const_cast<_Float16*>(p.x + (size_t)b0 * p.K), 0, min(p.B - b0, BT) * p.K * 2, kRsrcFlags);
+    const int xb = ONE ? lane & 3 : lo, xs = ONE ? (lane >> 2) & 3 : ls;           // ONE: batch row innermost
+    const int x_el0 = kt0 * kSlots * V + (4 * q + xs) * CHUNK;
+    const int x_off = ((SB == 1 ? 2 * xb : xb) * p.K + x_el0) * 2;
+    auto load_x = [&](half8_t (&dst)[NT][R][HALVES], int s) {
+#pragma unroll
+        for (int j = 0; j < R; ++j) {
+            const int el = s * (16 * CHUNK) + (SB == 1 ? 2 * (j / 2) : SB * j) * CHUNK;
+            const int at = (s < s_end && x_el0 + el < p.K) ? el * 2 + (SB == 1 ? (j % 2) * p.K * 2 : 0) : kOutOfRange;
+#pragma unroll
+            for (int nt = 0; nt < NT; ++nt)
+#pragma unroll
+                for (int h = 0; h < HALVES; ++h)
+                    dst[nt][j][h] = __builtin_bit_cast(half8_t, __builtin_amdgcn_raw_buffer_load_b128(x_rsrc, x_off + nt * BPT * 2 * p.K + at + 16 * h, 0, 0));
+        }
+    };
+    auto turn_x = [&](half8_t (&xv)[NT][R][HALVES], int s) {
+        if constexpr (V == 4) {                        // an odd number of sub-vectors: the chunk may reach past the end of the row
+#pragma unroll
+            for (int j = 0; j < R; ++j) {
+                const bool past = x_el0 + s * (16 * CHUNK) + (SB == 1 ? 2 * (j / 2) : SB * j) * CHUNK + 4 >= p.K;
+#pragma unroll
+                for (int nt = 0; nt < NT; ++nt) {
+                    u32x4_t t = __builtin_bit_cast(u32x4_t, xv[nt][j][0]);
+                    t.z = past ? 0u : t.z;
+                    t.w = past ? 0u : t.w;
+                    xv[nt][j][0] = __builtin_bit_cast(half8_t, t);
+                }
+            }
+        }
+        if constexpr (SB == 1) {
+#pragma unroll
+            for (int nt = 0; nt < NT; ++nt)
+#pragma unroll
+                for (int j = 0; j < R; j += 2)
+#pragma unroll
+                    for (int h = 0; h < HALVES; ++h) {
+                        u32x4_t a = __builtin_bit_cast(u32x4_t, xv[nt][j][h]), b = __builtin_bit_cast(u32x4_t, xv[nt][j + 1][h]);
+#pragma unroll
+                        for (int k = 0; k < 4; ++k) {
+                            uint32_t ak = a[k], bk = b[k];
+                            pair_transpose(ak, bk, odd);
+                            a[k] = ak;
+                            b[k] = bk;
+                        }
+                        xv[nt][j][h] = __builtin_bit_cast(half8_t, a);
+                        xv[nt][j + 1][h] = __builtin_bit_cast(half8_t, b);
+                    }
+        }
+    };
+    // Codes of round j: octet lo, sub-vector 16 (s % 2) + chunk (v = 4: sub-vectors 2 chunk and 2 chunk + 1), pairs of
+    // loads for SB = 1 as above.
+    const int row0 = blk * RB + rw * (8 * OCT);
+    const int gr = row0 / kGranuleRows;
+    const int oct0 = (row0 % kGranuleRows) / kRowsPerLane;
+    const uint8_t* cbase = mm.packed + ((size_t)min(gr, mm.NGR - 1) * p.NKT + kt0) * kUnitBytes;
+    const __amdgpu_buffer_rsrc_t c_rsrc =
+        __builtin_amdgcn_make_buffer_rsrc(const_cast<uint8_t*>(cbase), 0, gr < mm.NGR ? nq * kUnitBytes : 0, kRsrcFlags);
+    const int c_ent = (oct0 + (SB == 1 ? 2 * lo : lo)) * kSlots + (V == 4 ? 2 : 1) * (4 * q + ls);
+    auto load_codes = [&](uint32_t (&dst)[R][WR], int s) {
+        const int unit = s < s_end ? (s / SPU) * kUnitBytes : kOutOfRange;
+#pragma unroll
+        for (int j = 0; j < R; ++j) {
+            const int ent = c_ent + (V == 4 ? 0 : (s % SPU) * 16) + (V == 4 ? 2 : 1) * (SB == 1 ? 2 * (j / 2) : SB * j) + (SB == 1 ? (j % 2) * kSlots : 0);
+#pragma unroll
+            for (int part = 0; part < (M + 1) / 2; ++part) {
+                uint32_t* w = dst[j] + part * PW;
+                if (2 * part + 1 == M) {               // last part of an odd m: 8 bytes per entry
+                    if constexpr (V == 4) {
+                        const u32x4_t t = __builtin_amdgcn_raw_buffer_load_b128(c_rsrc, unit + part * 8192 + ent * 8, 0, 2);
+                        w[0] = t.x; w[1] = t.y; w[2] = t.z; w[3] = t.w;
+                    } else {
+                        const u32x2_t t = __builtin_amdgcn_raw_buffer_load_b64(c_rsrc, unit + part * 8192 + ent * 8, 0, 2);
+                        w[0] = t.x; w[1] = t.y;
+                    }
+                } else {
+#pragma unroll
+                    for (int g = 0; g < PW / 4; ++g) {
+                        const u32x4_t t = __builtin_amdgcn_raw_buffer_load_b128(c_rsrc, unit + part * 8192 + (ent + g) * 16, 0, 2);
+                        w[4 * g] = t.x; w[4 * g + 1] = t.y; w[4 * g + 2] = t.z; w[4 * g + 3] = t.w;
+                    }
+                }
+            }
+        }
+    };
+    // The exchange of SB = 1, then the lane's order of the codebooks that share a plane.
+    const int order = T::kOrderBits == 2 ? (lane >> 2) & 3 : T::kOrderBits == 1 ? (lane >> 3) & 1 : 0;
+    auto turn_codes = [&](uint32_t (&cw)[R][WR]) {
+        if constexpr (SB == 1) {
+#pragma unroll
+            for (int j = 0; j < R; j += 2)
+#pragma unroll
+                for (int k = 0; k < WR; ++k) pair_transpose(cw[j][k], cw[j + 1][k], odd);
+        }
+        if constexpr (T::kOrderBits > 0) {
+#pragma unroll
+            for (int j = 0; j < R; ++j) {
+#pragma unroll
+                for (int part = 0; part < M / 2; ++part)
+#pragma unroll
+                    for (int k = 0; k < 2; ++k) {
+                        uint32_t* w = cw[j] + part * PW;
+                        const uint32_t a = w[k], b = w[2 + k];
+                        w[k] = (order & 1) ? b : a;
+                        w[2 + k] = (order & 1) ? a : b;
+                    }
+                if constexpr (T::kOrderBits == 2) {
+#pragma unroll
+                    for (int k = 0; k < PW; ++k) {
+                        const uint32_t a = cw[j][k], b = cw[j][PW + k];
+                        cw[j][k] = (order & 2) ? b : a;
+                        cw[j][PW + k] = (order & 2) ? a : b;
+                    }
+                }
+            }
+        }
+    };
+    // group scales of the lane's octet for the group of step s
+    __amdgpu_buffer_rsrc_t s_rsrc;
+    if constexpr (GS) {
+        const uint8_t* base = mm.gscales + ((size_t)min(gr, mm.NGR - 1) * p.NKT + kt0) * p.GPU * 256;
+        s_rsrc = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint8_t*>(base), 0, gr < mm.NGR ? nq * p.GPU * 256 : 0, kRsrcFlags);
+    }
+    auto load_scales = [&](half8_t& dst, int s) {
+        const int o = s < s_end ? ((s / SPU) * p.GPU + (((s % SPU) * 16) >> p.gshift)) * 256 : kOutOfRange;
+        dst = __builtin_bit_cast(half8_t, __builtin_amdgcn_raw_buffer_load_b128(s_rsrc, o + (oct0 + col_o) * 16, 0, 0));
+    };
+
+    half8_t xr[D][NT][R][HALVES];
+    uint32_t w[D][R][WR];
+    half8_t sc[GS ? D : 1];
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int d = 0; d < D; ++d) {
+        load_codes(w[d], s_beg + d);
+        load_x(xr[d], s_beg + d);
+        if constexpr (GS) load_scales(sc[d], s_beg + d);
+    }
+    __builtin_amdgcn_sched_barrier(0);
+
+    // replicate the centroids
+    const uint32_t lds0 = (uint32_t)reinterpret_cast<uintptr_t>((lds_float*)smem);
+#pragma unroll
+    for (int k = 0; k < EPT; ++k) {
+        const int e = TPE > 1 ? tid / TPE : tid + k * THREADS;
+        if (e < ENTRIES) {
+            const int h = e % T::kHalves, code = (e / T::kHalves) % kCentroids, c = e / (T::kHalves * kCentroids);
+            const uint32_t row = lds0 + (uint32_t)(T::plane(c, h) * 65536 + code * 256 + T::region(c));
+            // columns this thread fills, rotated by row so that a wavefront's stores spread over the banks
+            const int cols = T::columns(c), mine = cols / TPE;
+            const int c0 = (TPE > 1 ? (tid % TPE) * mine + tid / TPE : lane);
+            for (int j = 0; j < mine; ++j) {
+                const uint32_t a = row + (uint32_t)((c0 + j) & (cols - 1)) * T::kEntry;
+                if constexpr (V == 4) *reinterpret_cast<lds_half4*>(static_cast<uintptr_t>(a)) = fill[k];
+                else *reinterpret_cast<lds_half8*>(static_cast<uintptr_t>(a)) = fill[k];
+            }
+        }
+    }
+
+    // Result tiles; with group scales the tiles of one step, and the scaled sums of the elements that
+    // mean something beside them.
+    float4_t acc[NT][8];
+    constexpr int TL = 4 / SB;                         // batch rows of a lane per tile
+    float sum[GS ? NT : 1][8][GS ? TL : 1];
+#pragma unroll
+    for (int nt = 0; nt < NT; ++nt)
+#pragma unroll
+        for (int u = 0; u < 8; ++u) {
+            acc[nt][u] = float4_t{0.0f, 0.0f, 0.0f, 0.0f};
+            if constexpr (GS) {
+#pragma unroll
+                for (int t = 0; t < TL; ++t) sum[nt][u][t] = 0.0f;
+            }
+        }
+    // Batch row t of this lane in a result tile, whose row 4 q + e is batch row 4 q + e for SB = 1; batch row 2 q + e / 2,
+    // sub-vector e % 2 for SB = 2; batch row q, sub-vector e for SB = 4: the meaningful elements are those of the column's
+    // own sub-vector.  ONE: batch row e, sub-vector q, meaningful in the lanes whose column has sub-vector q.
+    auto own = [&](const float4_t& r, int t) -> float {
+        if constexpr (SB == 1 || ONE) return r[t];
+        else if constexpr (SB == 2) return odd ? r[2 * t + 1] : r[2 * t];
+        else {
+            const float lo2 = odd ? r[1] : r[0], hi2 = odd ? r[3] : r[2];
+            return (lane & 2) ? hi2 : lo2;
+        }
+    };
+
+    // Lookup bases: plane, region and column of codebook k as this lane orders them, per half.
+    uint32_t base[M][HALVES];
+#pragma unroll
+    for (int k = 0; k < M; ++k) {
+        const bool alone = k == M - 1 && (M & 1);
+        const int c = alone ? k : k ^ order;
+        const uint32_t at = lds0 + (uint32_t)((alone ? T::region(k) : T::kOrderBits == 2 ? c * 64 : T::kOrderBits == 1 ? (c % 2) * T::region(1) : T::region(k)) +
+                                              (lane & (T::columns(k) - 1)) * T::kEntry);
+#pragma unroll
+        for (int h = 0; h < HALVES; ++h) base[k][h] = at + (uint32_t)(T::plane(k, h) << 16);
+    }
+    // Centroid operand of MFMA u in (round, half, codebook) k of a step: row u of the lane's octet.
+    auto fetch = [&](const uint32_t (&cw)[R][WR], int k, int u) -> half8_t {
+        const int c = k % M, h = (k / M) % HALVES, j = k / (M * HALVES);
+        const uint32_t* w = cw[j] + (c / 2) * PW;
+        const bool single = 2 * (c / 2) + 1 == M;
+        const uint32_t sel = 0x0c020000u | (uint32_t)(4 + u % 4) << 8;
+        if constexpr (V == 4) {
+            const uint32_t w0 = single ? w[u / 4] : w[2 * (c % 2) + u / 4], w1 = single ? w[2 + u / 4] : w[4 + 2 * (c % 2) + u / 4];
+            const half4_t lo4 = *reinterpret_cast<const lds_half4*>(static_cast<uintptr_t>(__builtin_amdgcn_perm(w0, base[c][0], sel)));
+            const half4_t hi4 = *reinterpret_cast<const lds_half4*>(static_cast<uintptr_t>(__builtin_amdgcn_perm(w1, base[c][0], sel)));
+            return __builtin_shufflevector(lo4, hi4, 0, 1, 2, 3, 4, 5, 6, 7);
+        } else {
+            const uint32_t w0 = single ? w[u / 4] : w[2 * (c % 2) + u / 4];
+            return *reinterpret_cast<const lds_half8*>(static_cast<uintptr_t>(__builtin_amdgcn_perm(w0, base[c][h], sel)));
+        }
+    };
+
+    __syncthreads();
+
+    // Main loop.  Every MFMA is followed by the lookup that takes its operand's registers, for the same u
+    // of the next (round, half, codebook): eight lookups are in flight while the matrix cores work.
+    half8_t a[8];
+    turn_codes(w[0]);
+#pragma unroll
+    for (int u = 0; u < 8; ++u) a[u] = fetch(w[0], 0, u);
+    for (int s0 = s_beg; s0 < s_end; s0 += D) {
+#pragma unroll
+        for (int d = 0; d < D; ++d) {
+            const int s = s0 + d;
+            turn_codes(w[(d + 1) % D]);
+            if (s < s_end) {
+                turn_x(xr[d], s);
+#pragma unroll
+                for (int k = 0; k < NSB; ++k) {
+#pragma unroll
+                    for (int u = 0; u < 8; ++u) {
+#pragma unroll
+                        for (int nt = 0; nt < NT; ++nt) {
+                            const half8_t xv = xr[d][nt][k / (M * HALVES)][(k / M) % HALVES];
+                            acc[nt][u] = __builtin_amdgcn_mfma_f32_16x16x32_f16(xv, a[u], (GS && k == 0) ? float4_t{} : acc[nt][u], 0, 0, 0);
+                        }
+                        __builtin_amdgcn_sched_barrier(0);         // the lookup after its operand's last use: no second set of registers
+                        a[u] = k + 1 < NSB ? fetch(w[d], k + 1, u) : fetch(w[(d + 1) % D], 0, u);
+                        __builtin_amdgcn_sched_barrier(0);
+                    }
+                }
+                if constexpr (GS) {
+#pragma unroll
+                    for (int u = 0; u < 8; ++u) {
+                        const float f = (float)sc[d][u];
+#pragma unroll
+                        for (int nt = 0; nt < NT; ++nt)
+#pragma unroll
+                            for (int t = 0; t < TL; ++t)
+                                sum[nt][u][t] = __builtin_fmaf(f, own(acc[nt][u], t), sum[nt][u][t]);
+                    }
+                }
+            }
+            load_codes(w[d], s + D);
+            load_x(xr[d], s + D);
+            if constexpr (GS) load_scales(sc[d], s + D);
+        }
+    }
+
+    // Sum over the wavefronts' K slices, one tile of batch rows at a time: partials in LDS
+    // [slice][batch row][RB + 4] (ONE: the four sub-vectors of a slice apart), totals behind
+    // them as [batch row][RB].
+    constexpr int STRIDE = RB + 4;                     // floats; the pad spreads the batch rows over the banks
+    constexpr int SLICES = ONE ? 4 * KW : KW;
+    float* parts = reinterpret_cast<float*>(smem);
+    float* totals = parts + SLICES * BPT * STRIDE;
+    uint32_t* flag = reinterpret_cast<uint32_t*>(totals + BT * RB);
+    __syncthreads();                                   // everyone is done with the table
+#pragma unroll
+    for (int nt = 0; nt < NT; ++nt) {
+        const int nb = min(p.B - b0 - BPT * nt, BPT);  // rows of this tile
+        if (nt > 0) __syncthreads();                   // the previous tile's partials have been read
+#pragma unroll
+        for (int t = 0; t < TL; ++t) {
+            float v[8];
+#pragma unroll
+            for (int u = 0; u < 8; ++u) {
+                v[u] = GS ? sum[GS ? nt : 0][u][GS ? t : 0] : own(acc[nt][u], t);
+                if constexpr (SB >= 2 && !ONE) v[u] = dpp_add<0xb1, 0xf>(v[u]);
+                if constexpr (SB == 4 && !ONE) v[u] = dpp_add<0x4e, 0xf>(v[u]);
+            }
+            const int b = ONE ? 0 : TL * q + t;
+            if (ONE ? (lane & 3) == q : b < nb && (lane & (SB - 1)) == 0) {
+                float* dst = parts + ((ONE ? kw * 4 + q : kw) * BPT + b) * STRIDE + (rw * OCT + col_o) * 8;
+                *reinterpret_cast<float4_t*>(dst) = float4_t{v[0], v[1], v[2], v[3]};
+                *reinterpret_cast<float4_t*>(dst + 4) = float4_t{v[4], v[5], v[6], v[7]};
+            }
+        }
+        __syncthreads();
+        for (int o = tid; o < nb * RB; o += THREADS) {
+            const int b = o / RB, n = o % RB;
+            float t = parts[b * STRIDE + n];
+#pragma unroll
+            for (int k = 1; k < SLICES; ++k) t += parts[(k * BPT + b) * STRIDE + n];
+            totals[(BPT * nt + b) * RB + n] = t;
+        }
+    }
+    finish_block<THREADS, BT, RB>(p, mm, totals, flag, tid, blk, ks, b0);
+}
+
+template <int M, int V, int SB, int NT, int RW, int KW, int D, bool GS, bool ONE = false>
+int launch_gemm_centroid_one(const Geometry& g, const GemmParams& p, hipStream_t stream)
+{
+    auto fn = gemm_centroid_kernel<M, V, SB, NT, RW, KW, D, GS, ONE>;
+    constexpr int RB = 128 / SB * RW, BPT = ONE ? 1 : 16 / SB;
+    if (g.RB != RB || g.BG != BPT * NT) return CODEGEMM_UNSUPPORTED;
+    constexpr size_t stage = (size_t)((ONE ? 4 * KW : KW) * BPT * (RB + 4) + BPT * NT * RB) * sizeof(float) + 64;
+    constexpr size_t table = CentroidTable<M, V>::kBytes;
+    constexpr size_t lds = stage > table ? stage : table;
+    static_assert(lds <= (size_t)kMaxLds, "LDS");
+    int st = set_max_lds(reinterpret_cast<const void*>(fn), lds);
+    if (st != CODEGEMM_OK) return st;
+    const dim3 grid((unsigned)g.NKS, (unsigned)g.NBLK, (unsigned)g.NG);
+    hipLaunchKernelGGL(fn, grid, dim3(RW * KW * kWave), lds, stream, CG_HEAD_ARGS(p), p);
+    return hipGetLastError() == hipSuccess ? CODEGEMM_OK : CODEGEMM_LAUNCH_FAILED;
+}
+
+template <int M, int V, bool GS>
+int launch_gemm_centroid_v(const Geometry& g, const GemmParams& p, hipStream_t stream)
+{
+    switch (g.BG) {
+        case 1:
+            if (g.RB == 128) return launch_gemm_centroid_one<M, V, 4, 1, 4, 2, 4, GS, true>(g, p, stream);
+            if (g.RB == 64) return launch_gemm_centroid_one<M, V, 4, 1, 2, 4, 4, GS, true>(g, p, stream);
+            return launch_gemm_centroid_one<M, V, 4, 1, 1, 8, 4, GS, true>(g, p, stream);
+        case 4:
+            if (g.RB == 128) return launch_gemm_centroid_one<M, V, 4, 1, 4, 2, 4, GS>(g, p, stream);
+            if (g.RB == 64) return launch_gemm_centroid_one<M, V, 4, 1, 2, 4, 4, GS>(g, p, stream);
+            return launch_gemm_centroid_one<M, V, 4, 1, 1, 8, 4, GS>(g, p, stream);
+        case 8:
+            if (g.RB == 128) return launch_gemm_centroid_one<M, V, 2, 1, 2, 4, 4, GS>(g, p, stream);
+            return launch_gemm_centroid_one<M, V, 2, 1, 1, 8, 4, GS>(g, p, stream);
+        case 16: return launch_gemm_centroid_one<M, V, 1, 1, 1, 8, 2, GS>(g, p, stream);
+        case 32:
+            if constexpr (!GS && (V == 8 && M <= 2 || V == 4 && M == 1)) return launch_gemm_centroid_one<M, V, 1, 2, 1, 8, 2, GS>(g, p, stream);
+    }
+    return CODEGEMM_UNSUPPORTED;
+}
+
+template <int M>
+int launch_gemm_centroid_m(const Geometry& g, const GemmParams& p, hipStream_t stream)
+{
+    if (g.v == 16) return g.g > 0 ? launch_gemm_centroid_v<M, 16, true>(g, p, stream) : launch_gemm_centroid_v<M, 16, false>(g, p, stream);
+    if (g.v == 8) return g.g > 0 ? launch_gemm_centroid_v<M, 8, true>(g, p, stream) : launch_gemm_centroid_v<M, 8, false>(g, p, stream);
+    if constexpr (M <= 2) return g.g > 0 ? launch_gemm_centroid_v<M, 4, true>(g, p, stream) : launch_gemm_centroid_v<M, 4, false>(g, p, stream);
+    return CODEGEMM_UNSUPPORTED;
+}
+
+int launch_gemm_centroid_m1(const Geometry& g, const GemmParams& p, hipStream_t stream);
+int launch_gemm_centroid_m2(const Geometry& g, const GemmParams& p, hipStream_t stream);
+int launch_gemm_centroid_m3(const Geometry& g, const GemmParams& p, hipStream_t stream);
+int launch_gemm_centroid_m4(const Geometry& g, const GemmParams& p, hipStream_t stream);
+
+}  // namespace cg

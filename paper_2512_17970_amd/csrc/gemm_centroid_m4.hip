@@ -1,0 +1,6 @@
+// Centroid kernels for m = 4 codebooks (see gemm_centroid_impl.h).
+#include "gemm_centroid_impl.h"
+
+namespace cg {
+int launch_gemm_centroid_m4(const Geometry& g, const GemmParams& p, hipStream_t stream) { return launch_gemm_centroid_m<4>(g, p, stream); }
+}  // namespace cg

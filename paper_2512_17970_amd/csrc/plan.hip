@@ -26,6 +26,29 @@ static int validate_desc(const codegemm_desc* d)
     return CODEGEMM_OK;
 }
 
+// Formats the centroid kernel takes: a group of scales covers at least one of its steps (16 sub-vectors, 32
+// for v = 4), and the codes of a step fit in registers.
+static bool centroid_format(const codegemm_desc* d)
+{
+    if (d->vec_len == 4 && d->num_codebooks > 2) return false;
+    return d->group_size == -1 || d->group_size >= (d->vec_len == 4 ? 32 : 16) * d->vec_len;
+}
+
+// Batch rows of a workgroup of the centroid kernel, and the rows of W that one of its wavefronts owns then.
+static int centroid_batch(const codegemm_desc* d)
+{
+    const int b = d->batch;
+    if (b <= 8) return b == 1 ? 1 : b <= 4 ? 4 : 8;
+    // two tiles of 16 only where their accumulators leave registers for the codes
+    const bool two = d->group_size == -1 && ((d->vec_len == 8 && d->num_codebooks <= 2) || (d->vec_len == 4 && d->num_codebooks == 1));
+    return b > 16 && two ? 32 : 16;
+}
+static int centroid_min_rows(const codegemm_desc* d)
+{
+    const int b = centroid_batch(d);
+    return b <= 4 ? 32 : b == 8 ? 64 : 128;
+}
+
 static int validate_plan(const codegemm_desc* d, const codegemm_plan* p)
 {
     if (p->waves != 8 && p->waves != 14 && p->waves != 16) return CODEGEMM_UNSUPPORTED;
@@ -37,8 +60,14 @@ static int validate_plan(const codegemm_desc* d, const codegemm_plan* p)
     if (p->row_words == 4 && p->waves != 16 && p->batch_group != 4) return CODEGEMM_UNSUPPORTED;
     if (p->k_splits < 1) return CODEGEMM_UNSUPPORTED;
     if (p->batch_group != 1 && p->batch_group != 2 && p->batch_group != 4) return CODEGEMM_UNSUPPORTED;
-    for (int i = 0; i < 2; ++i)
-        if (p->reserved[i]) return CODEGEMM_INVALID_ARG;
+    if (p->centroid_rows == 0) {
+        if (p->centroid_splits != 0) return CODEGEMM_INVALID_ARG;
+    } else {
+        if (p->centroid_rows != 32 && p->centroid_rows != 64 && p->centroid_rows != 128) return CODEGEMM_INVALID_ARG;
+        if (p->centroid_splits < 1) return CODEGEMM_INVALID_ARG;
+        if (!centroid_format(d)) return CODEGEMM_UNSUPPORTED;
+        if (p->centroid_rows < centroid_min_rows(d)) return CODEGEMM_UNSUPPORTED;
+    }
     if (p->build_waves != 0 && p->build_waves != 2) return CODEGEMM_UNSUPPORTED;
     if (p->build_waves == 2) {
         // 14 gathering + 2 building wavefronts: a double-buffered fp32 Psumbook (one or two codebooks); one batch
@@ -68,7 +97,7 @@ static int validate_plan(const codegemm_desc* d, const codegemm_plan* p)
 // to keep up with its share of HBM, so blocks are 512 rows tall when the batch and the
 // number of codebooks leave registers for it; the K ranges are then cut to give close
 // to, but not more than, 256 workgroups.
-static void choose_plan(const codegemm_desc* d, codegemm_plan* p)
+static void choose_psumbook_plan(const codegemm_desc* d, codegemm_plan* p)
 {
     *p = codegemm_plan{};
     const int m = d->num_codebooks;
@@ -198,6 +227,63 @@ static void choose_plan(const codegemm_desc* d, codegemm_plan* p)
     }
 }
 
+// Whether the centroid kernel is the faster one, from sweeps over the workloads' shapes and formats (us, Psumbook
+// kernels / centroid kernel):
+//  * two to eight batch rows: everywhere (v8 m2, batch 2 / 4 / 8: 2048^2 6.1/4.9, 7.6/5.0, 7.8/6.6; 8192->28672
+//    23.9/18.3, 27.3/19.2, 41.5/21.9; v16 m4 at 8192^2 12.3/11.2, 14.3/11.5, 19.9/15.2);
+//  * nine and more: all but the smallest matrices, which leave its 128-row blocks too few and too short (batch 16:
+//    2048^2 8.4/9.4, 4096->1024 8.6/9.6, but 8192->1024 12.9/10.7, 8192->28672 70/25); beyond 32 rows, where the
+//    Psumbook kernels start over for every 32, always;
+//  * one: where 32-row blocks fill half of the chip and its lookups, four times the LDS bytes of the Psumbook's, are not
+//    what bounds the call: v4 m1 g128 4096^2 5.9/5.3, 28672->8192 21.9/15.7 (its centroids are the shortest); v8 m2
+//    4096^2 5.5/4.9, 4096->14336 7.9/7.0, 8192^2 8.0/7.7, but 8192->28672 15.7/17.4, 2048^2 4.8/4.9; three codebooks
+//    (8192^2 10.3/10.6) and v = 16 (4096^2 5.4/7.1) lose.
+static bool prefer_centroid(const codegemm_desc* d)
+{
+    if (!centroid_format(d) || d->out_features > 65535 * 128) return false;     // grid.y
+    const long long codes = (long long)d->num_codebooks * d->out_features * (d->in_features / d->vec_len);
+    if (d->batch > 8) return d->batch > kBatchPerLaunch || codes >= 1500000;
+    if (d->batch > 1) return true;
+    if (d->num_codebooks > 2 || d->vec_len == 16) return false;
+    if (d->vec_len == 4 && d->num_codebooks == 1) return d->out_features >= 4096 || d->in_features >= 8192;
+    return d->out_features >= 4096 && codes * d->vec_len <= (d->group_size > 0 ? 120000000 : 136000000);
+}
+
+static void choose_plan(const codegemm_desc* d, codegemm_plan* p)
+{
+    choose_psumbook_plan(d, p);
+    if (!prefer_centroid(d)) return;
+    const int nkt = ceil_div(d->in_features / d->vec_len, kSlots);
+    const int tile = centroid_batch(d);
+    const int tiles = ceil_div(d->batch, tile);
+    // Block height: as low as the batch allows while there are no more blocks than the chip takes at a time (two
+    // workgroups fit on a compute unit): low blocks need fewer K ranges, and with them the exchange through memory.
+    int rows = 128;
+    if (tile <= 4) rows = ceil_div(d->out_features, 32) <= 320 ? 32 : ceil_div(d->out_features, 64) <= 512 ? 64 : 128;
+    else if (tile == 8) rows = ceil_div(d->out_features, 64) <= 256 ? 64 : 128;
+    const int blocks = ceil_div(d->out_features, rows) * tiles;
+    // K ranges: for up to 4 batch rows 128 workgroups, 256 when that leaves each 48 units or more (14336->4096 v8 m2: two
+    // ranges 7.4, one 8+; 4096^2: one 4.9, two 5.4); for more, 256 as long as a workgroup keeps 2 (4 with 9 or more rows)
+    // units (4096^2 at batch 32: 4 ranges 15.9, 8 ranges 17.6; 8192^2: 4 ranges 20.2, 2 ranges 24.4).
+    int splits;
+    if (tile <= 4) {
+        splits = ceil_div(128, blocks);
+        if (splits * blocks <= 128 && nkt / splits >= 48) splits *= 2;
+    } else {
+        splits = 256 / blocks;
+        const int most = nkt / (tile == 8 ? 2 : 4);
+        if (splits > most) splits = most;
+        if (splits * blocks < 128 && splits < nkt / 2) splits = ceil_div(128, blocks) < nkt / 2 ? ceil_div(128, blocks) : nkt / 2;
+    }
+    // no more workspace than the fields of the Psumbook kernels ask for
+    const long long room = (long long)p->k_splits * (d->batch < kBatchPerLaunch ? d->batch : kBatchPerLaunch) / d->batch;
+    if (splits > room) splits = (int)room;
+    if (splits > nkt) splits = nkt;
+    if (splits < 1) splits = 1;
+    p->centroid_rows = rows;
+    p->centroid_splits = splits;
+}
+
 int make_geometry(const codegemm_desc* d, const codegemm_plan* plan, Geometry* g)
 {
     int st = validate_desc(d);
@@ -209,7 +295,8 @@ int make_geometry(const codegemm_desc* d, const codegemm_plan* plan, Geometry* g
     }
     st = validate_plan(d, plan);
     if (st) return st;
-    g->B = d->batch < kBatchPerLaunch ? d->batch : kBatchPerLaunch;   // larger batches run as several launches
+    // larger batches run as several launches of the Psumbook kernels, as one of the centroid kernels
+    g->B = (d->batch < kBatchPerLaunch || plan->centroid_rows) ? d->batch : kBatchPerLaunch;
     g->K = d->in_features;
     g->N = d->out_features;
     g->v = d->vec_len;
@@ -221,12 +308,22 @@ int make_geometry(const codegemm_desc* d, const codegemm_plan* plan, Geometry* g
     g->BG = plan->batch_group;
     g->psum_fp16 = plan->psum_dtype == CODEGEMM_PSUM_FP16;
     g->NGR = ceil_div(g->N, kGranuleRows);
+    g->RB = plan->centroid_rows;
+    if (g->RB) g->BG = centroid_batch(d);              // batch rows of a workgroup of the centroid kernel
     // rows per workgroup: 16 per wavefront and row word (32 in the batched kernel)
     g->NBLK = ceil_div(g->NGR * kGranuleRows, g->RPL * (g->NW - g->NB) * (g->BG == 4 ? 32 : 16));
+    if (g->RB) g->NBLK = ceil_div(g->N, g->RB);
+    if (g->RB && g->NBLK > 65535) return CODEGEMM_UNSUPPORTED;
     g->NKT = ceil_div(g->J, kSlots);
-    int nks = plan->k_splits < g->NKT ? plan->k_splits : g->NKT;
+    const int want = g->RB ? plan->centroid_splits : plan->k_splits;
+    int nks = want < g->NKT ? want : g->NKT;
     g->KPW = ceil_div(g->NKT, nks);
     g->NKS = ceil_div(g->NKT, g->KPW);          // no empty K range
+    g->WKS = g->NKS;
+    if (g->RB) {                                // workspace as for the Psumbook kernel of the same plan, too
+        const int pks = plan->k_splits < g->NKT ? plan->k_splits : g->NKT;
+        g->WKS = ceil_div(g->NKT, ceil_div(g->NKT, pks));
+    }
     g->NG = ceil_div(g->B, g->BG);
     g->Npad = g->NGR * kGranuleRows;
     if (counter_stride(*g) == 0) return CODEGEMM_UNSUPPORTED;   // > 16384 row blocks x batch groups with several K ranges
@@ -245,6 +342,13 @@ int make_geometry(const codegemm_desc* d, const codegemm_plan* plan, Geometry* g
 size_t workspace_counter_bytes(const Geometry&)
 {
     return (size_t)kCounterAreaWords * sizeof(uint32_t) + kPairAreaBytes;
+}
+
+size_t workspace_need(const Geometry& g)
+{
+    size_t floats = (size_t)(g.B < kBatchPerLaunch ? g.B : kBatchPerLaunch) * g.WKS * g.Npad;
+    if (g.NKS > 1 && (size_t)g.B * g.NKS * g.Npad > floats) floats = (size_t)g.B * g.NKS * g.Npad;
+    return workspace_counter_bytes(g) + floats * sizeof(float);
 }
 
 size_t pair_words(const Geometry& g)
@@ -283,13 +387,13 @@ extern "C" size_t codegemm_workspace_bytes(const codegemm_desc* desc, const code
 {
     Geometry g;
     if (make_geometry(desc, plan, &g)) return 0;
-    size_t bytes = workspace_counter_bytes(g) + (size_t)g.B * g.NKS * g.Npad * sizeof(float);
-    if (desc->batch > kBatchPerLaunch && desc->batch % kBatchPerLaunch) {
+    size_t bytes = workspace_need(g);
+    if (desc->batch > kBatchPerLaunch && desc->batch % kBatchPerLaunch && !g.RB) {
         // the last launch of a large batch has fewer rows and, under the default plan, other K ranges
         codegemm_desc tail = *desc;
         tail.batch = desc->batch % kBatchPerLaunch;
         if (make_geometry(&tail, plan, &g)) return 0;
-        const size_t b2 = workspace_counter_bytes(g) + (size_t)g.B * g.NKS * g.Npad * sizeof(float);
+        const size_t b2 = workspace_need(g);
         if (b2 > bytes) bytes = b2;
     }
     return bytes;

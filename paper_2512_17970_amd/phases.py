@@ -56,6 +56,8 @@ def phase_table(torch, desc, plan, x, packed_codes, codebooks, scales, y, worksp
     tensor larger than the chip's caches that is overwritten just before the traced call, so
     that the call reads its codes from HBM (cold); without it the warm-up calls leave them in
     the memory-side cache."""
+    plan = binding.Plan.from_buffer_copy(plan)         # the phases are those of the Psumbook kernels
+    plan.centroid_rows = plan.centroid_splits = 0
     lib = _trace_lib()
     stream = ctypes.c_void_p(torch.cuda.current_stream().cuda_stream)
 

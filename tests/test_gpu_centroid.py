@@ -1,0 +1,160 @@
+"""GPU parity of the centroid kernel (plans with centroid_rows != 0): every block height, batch tile, format and
+K split against the CPU oracle at the acceptance bar, bit for bit on integer cases, and as a member of a group."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+import synth
+
+pytestmark = pytest.mark.gpu
+
+cg = pytest.importorskip("paper_2512_17970_amd")
+from gpu_util import DeviceLayer, Guarded, check_against_oracle, dev, stream  # noqa: E402
+
+
+def least_rows(B):
+    return 32 if B <= 4 else 64 if B <= 8 else 128
+
+
+def plan_of(case, rows, splits):
+    p = cg.codegemm_default_plan(cg.Desc.make(case.B, case.K, case.N, case.v, case.m, g=case.g))
+    p.centroid_rows, p.centroid_splits = rows, splits
+    return p
+
+
+def run(case, rows, splits, y_fp32=False):
+    print(f"[centroid] {case.name} rows={rows} splits={splits}", flush=True)
+    inp = synth.generate(case)
+    y_ref, T = oracle.gemm(inp.x, inp.codes, inp.codebooks, inp.scales)
+    layer = DeviceLayer(inp, plan=plan_of(case, rows, splits), y_fp32=y_fp32)
+    first = layer.gemm().clone()
+    again = layer.gemm()                                                # on the workspace the first call left
+    torch.cuda.synchronize()
+    assert torch.equal(first, again)
+    rel = check_against_oracle(first.cpu().numpy(), y_ref, T, f"{case.name} rows={rows} splits={splits}")
+    # fp32 output: fp32 sums of K m / v exact products, in order 1e-7 apart; fp16 output: its rounding, 2.8e-4
+    assert rel < (5e-6 if y_fp32 else 6e-4), rel
+    # counters and pair words are all zero again
+    assert not bool(layer.ws[:65536 + (2 << 20)].any().item())
+
+
+FORMATS = [(8, 2, -1), (8, 1, -1), (4, 1, -1), (8, 3, -1), (8, 4, -1), (4, 2, -1), (16, 1, -1), (16, 2, -1), (16, 3, -1), (16, 4, -1),
+           (8, 2, 128), (8, 1, 256), (4, 1, 128), (8, 3, 1024), (4, 2, 512), (8, 4, 128), (16, 2, 256), (16, 3, 512), (16, 4, 1024)]
+
+
+@pytest.mark.parametrize("B", [1, 2, 4, 5, 8, 9, 16, 17, 32, 33])
+@pytest.mark.parametrize("v,m,g", FORMATS)
+def test_formats_and_batches(v, m, g, B):
+    """Every batch tile at its edges; ragged N (not a multiple of 8, 32 or 128), K with a ragged last unit where the
+    scales allow one (an odd number of sub-vectors for v = 4), more K ranges than a wavefront's share of steps."""
+    unit = max(g, 32 * v)
+    K = unit * 5 + (g if g > 0 else 7 * v)
+    for N, splits, fp32 in ((301, 1, True), (130, 3, False), (33, 1000, True)):
+        run(synth.custom_case(K, N, v, m, B, seed=3000 + N + B, g=g), 128, splits, fp32)
+
+
+@pytest.mark.parametrize("rows", [32, 64, 128])
+@pytest.mark.parametrize("splits", [1, 2, 4, 5])
+@pytest.mark.parametrize("B", [1, 3, 7])
+@pytest.mark.parametrize("v,m,g", [(8, 2, -1), (4, 1, 128), (16, 4, -1), (8, 3, 128)])
+def test_block_heights(v, m, g, B, splits, rows):
+    """Blocks of 32 and 64 rows (the batches that have them), ragged at either end of a granule; pairwise words and
+    tickets between the K ranges."""
+    if rows < least_rows(B):
+        pytest.skip("block height not offered for this batch")
+    for N in (rows, rows + 1, 1000):
+        run(synth.custom_case(max(g, 32 * v) * 6, N, v, m, B, seed=3100 + N, g=g), rows, splits)
+
+
+@pytest.mark.parametrize("K,N", [(8, 1), (256, 31), (8 * 33, 128)])
+@pytest.mark.parametrize("B", [1, 4, 6, 12, 20])
+def test_fewer_steps_than_wavefronts(K, N, B):
+    run(synth.custom_case(K, N, 8, 2, B, seed=3200), 128, 1, True)
+
+
+@pytest.mark.parametrize("B", [1, 4, 8, 16, 32])
+def test_integer_cases_are_exact(B):
+    """+-1 and 0/2 codebooks with small integer activations: every sum is an integer that fp32 holds, in any order."""
+    v, K, N = 8, 4096, 700
+    rng = np.random.default_rng(31)
+    i = np.arange(256)[:, None]
+    inp = synth.generate(synth.custom_case(K, N, v, 2, B, seed=3))
+    bits = (i >> np.arange(v)[None, :]) & 1
+    inp.codebooks = np.stack([np.where(bits, 1.0, -1.0), np.where(bits, 2.0, 0.0)]).astype(np.float16)
+    inp.x = rng.integers(-8, 9, (B, K)).astype(np.float16)
+    inp.scales = np.ones(N, np.float16)
+    y_ref, _ = oracle.gemm(inp.x, inp.codes, inp.codebooks, inp.scales)
+    for rows, splits in ((128, 1), (128, 3), (least_rows(B), 2)):
+        y = DeviceLayer(inp, plan=plan_of(inp.case, rows, splits), y_fp32=True).gemm()
+        torch.cuda.synchronize()
+        assert np.array_equal(y.cpu().numpy().astype(np.float64), y_ref), (rows, splits)
+
+
+@pytest.mark.parametrize("B,row", [(3, 1), (6, 4), (13, 0), (20, 19), (70, 33)])
+def test_non_finite_activations_stay_in_their_row(B, row):
+    """The batch rows share instructions (and, up to 8 rows, result tiles whose other elements are discarded): an
+    infinity or NaN in one row of x reaches that row of y alone."""
+    case = synth.custom_case(8 * 32 * 4, 300, 8, 2, B, seed=3300)
+    inp = synth.generate(case)
+    clean = DeviceLayer(inp, plan=plan_of(case, 128, 1)).gemm().clone()
+    inp.x = inp.x.copy()
+    inp.x[row, ::97] = np.inf
+    inp.x[row, 5] = np.nan
+    y = DeviceLayer(inp, plan=plan_of(case, 128, 1)).gemm()
+    torch.cuda.synchronize()
+    others = [b for b in range(B) if b != row]
+    assert torch.equal(y[others], clean[others])
+    assert not bool(torch.isfinite(y[row]).any().item())
+
+
+@pytest.mark.parametrize("B,rows,splits,g", [(1, 32, 1, -1), (1, 64, 2, 128), (4, 32, 3, -1), (8, 64, 4, -1), (16, 128, 2, 128), (32, 128, 5, -1)])
+def test_grouped_members_equal_their_single_calls(B, rows, splits, g):
+    K, Ns = 2048, [300, 130, 65]
+    desc = cg.Desc.make(B, K, sum(Ns), 8, 2, g=g)
+    plan = cg.codegemm_default_plan(desc)
+    plan.centroid_rows, plan.centroid_splits = rows, splits
+    inps = [synth.generate(synth.custom_case(K, n, 8, 2, B, seed=3400 + k, g=g)) for k, n in enumerate(Ns)]
+    layers = []
+    for inp in inps:
+        inp.x = inps[0].x
+        layers.append(DeviceLayer(inp, plan=plan))
+    ws_bytes = cg.codegemm_grouped_workspace_bytes(desc, plan, Ns)
+    ws = Guarded(ws_bytes)
+    cg.codegemm_workspace_init(ws.t, ws_bytes, stream())
+    ys = [layer.new_y() for layer in layers]
+    members = [(n, l.packed, l.codebooks, l.gemm_scales, y) for n, l, y in zip(Ns, layers, ys)]
+    for _ in range(2):
+        cg.codegemm_gemm_grouped(desc, plan, layers[0].x, members, ws.t, ws_bytes, stream())
+        torch.cuda.synchronize()
+        assert ws.intact()
+        for layer, y, inp in zip(layers, ys, inps):
+            layer.check_guards("grouped launch")
+            y_ref, T = oracle.gemm(inp.x, inp.codes, inp.codebooks, inp.scales)
+            check_against_oracle(y.cpu().numpy(), y_ref, T, "grouped member")
+            alone = layer.gemm()
+            torch.cuda.synchronize()
+            assert torch.equal(alone, y)
+
+
+def test_replays_from_a_hip_graph():
+    """Captured calls give the eager bits on every replay, with eager calls on the same workspace in between."""
+    layers = [DeviceLayer(synth.generate(synth.custom_case(K, N, 8, 2, B, seed=3500 + B)), plan=None)
+              for K, N, B in ((4096, 1000, 4), (2048, 700, 16), (1024, 4200, 1))]
+    eager = [l.gemm().clone() for l in layers]
+    outs = [torch.empty_like(e) for e in eager]
+    graph = torch.cuda.CUDAGraph()
+    side = torch.cuda.Stream()
+    side.wait_stream(torch.cuda.current_stream())
+    with torch.cuda.stream(side), torch.cuda.graph(graph, stream=side):
+        for l, y in zip(layers, outs):
+            l.gemm(y, check=False)
+    torch.cuda.current_stream().wait_stream(side)
+    for _ in range(3):
+        for y in outs:
+            y.fill_(float("nan"))
+        graph.replay()
+        torch.cuda.synchronize()
+        for l, y, e in zip(layers, outs, eager):
+            assert torch.equal(y, e)
+            assert torch.equal(l.gemm(), e)
