@@ -49,6 +49,7 @@ struct Geometry {
                     // (32 * NW * RPL in the batched kernel, BG = 4)
     int BG;         // batch rows per pass over the codes
     int RB;         // rows of a block of the centroid kernel (32, 64 or 128), or 0: one of the Psumbook kernels
+    bool prompt;    // more than kBatchPerLaunch batch rows, and enough of them for the prompt kernel (RB != 0 only)
     int NGR;        // ceil(N / 128) granules
     int NBLK;       // row blocks = workgroups along N: NGR over the granules per workgroup, rounded up
     int NKT;        // ceil(J / 32) K tiles
@@ -63,6 +64,13 @@ struct Geometry {
     bool y_fp32;
     bool psum_fp16;  // Psumbook stored as fp16 pairs (plan field psum_dtype)
 };
+
+// Tiles of 16 batch rows of a workgroup of the prompt kernel: 4 where 128 accumulators per lane leave room for the
+// codes, 2 with group scales (sums of their own beside the accumulators) and for wide codes.
+__host__ __device__ constexpr int prompt_tiles(int m, int v, bool group_scales)
+{
+    return group_scales || m >= 3 || (v == 4 && m == 2) ? 2 : 4;
+}
 
 __host__ __device__ inline int ceil_div(int a, int b) { return (a + b - 1) / b; }
 

@@ -483,15 +483,6 @@ int launch_gemm_centroid_v(const Geometry& g, const GemmParams& p, hipStream_t s
     return CODEGEMM_UNSUPPORTED;
 }
 
-template <int M>
-int launch_gemm_centroid_m(const Geometry& g, const GemmParams& p, hipStream_t stream)
-{
-    if (g.v == 16) return g.g > 0 ? launch_gemm_centroid_v<M, 16, true>(g, p, stream) : launch_gemm_centroid_v<M, 16, false>(g, p, stream);
-    if (g.v == 8) return g.g > 0 ? launch_gemm_centroid_v<M, 8, true>(g, p, stream) : launch_gemm_centroid_v<M, 8, false>(g, p, stream);
-    if constexpr (M <= 2) return g.g > 0 ? launch_gemm_centroid_v<M, 4, true>(g, p, stream) : launch_gemm_centroid_v<M, 4, false>(g, p, stream);
-    return CODEGEMM_UNSUPPORTED;
-}
-
 int launch_gemm_centroid_m1(const Geometry& g, const GemmParams& p, hipStream_t stream);
 int launch_gemm_centroid_m2(const Geometry& g, const GemmParams& p, hipStream_t stream);
 int launch_gemm_centroid_m3(const Geometry& g, const GemmParams& p, hipStream_t stream);

@@ -324,6 +324,11 @@ int make_geometry(const codegemm_desc* d, const codegemm_plan* plan, Geometry* g
         const int pks = plan->k_splits < g->NKT ? plan->k_splits : g->NKT;
         g->WKS = ceil_div(g->NKT, ceil_div(g->NKT, pks));
     }
+    // The prompt kernel's workgroups take 1024 rows of W and 64 (with group scales 32) batch rows and all of K: worth it
+    // once they are enough to fill the chip.
+    g->prompt = g->RB && g->B > kBatchPerLaunch && g->v < 16 &&
+                (long long)ceil_div(g->NGR, 8) * ceil_div(g->B, 16 * prompt_tiles(g->m, g->v, d->group_size > 0)) >= 128;
+    if (g->prompt) g->NKS = 1;
     g->NG = ceil_div(g->B, g->BG);
     g->Npad = g->NGR * kGranuleRows;
     if (counter_stride(*g) == 0) return CODEGEMM_UNSUPPORTED;   // > 16384 row blocks x batch groups with several K ranges

@@ -1,0 +1,72 @@
+"""GPU parity of the prompt kernel (default plans with more than 32 batch rows and enough workgroups): formats, ragged
+N, K and batch against the CPU oracle, exact on integer cases, non-finite rows kept apart."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+import synth
+
+pytestmark = pytest.mark.gpu
+
+cg = pytest.importorskip("paper_2512_17970_amd")
+from gpu_util import DeviceLayer, check_against_oracle  # noqa: E402
+
+
+def batch_for(v, m, g, N, extra):
+    """A batch whose tiles of 64 (or 32) rows give at least 128 workgroups of 1024 rows, the last tile ragged."""
+    tile = 32 if g > 0 or m >= 3 or (v == 4 and m == 2) else 64
+    return tile * -(-128 // -(-N // 1024)) - tile + extra
+
+
+@pytest.mark.parametrize("N,extra", [(1031, 1), (2048, 33), (3000, 32)])
+@pytest.mark.parametrize("v,m,g", [(8, 2, -1), (8, 1, -1), (4, 1, -1), (8, 3, -1), (8, 4, -1), (4, 2, -1), (8, 2, 128), (8, 1, 512), (4, 1, 128), (4, 2, 256)])
+def test_formats(v, m, g, N, extra):
+    """K of one to three units with an odd number of steps or a ragged last one; N that 8, 128 or 1024 does not divide
+    (scalar and vector stores of y), both output types."""
+    for units, fp32 in ((1, True), (3, False)):
+        K = max(g, 32 * v) * units + (g if g > 0 else 5 * v)
+        case = synth.custom_case(K, N, v, m, batch_for(v, m, g, N, extra), seed=3600 + N + units, g=g)
+        print(f"[prompt] {case.name}", flush=True)
+        inp = synth.generate(case)
+        y_ref, T = oracle.gemm(inp.x, inp.codes, inp.codebooks, inp.scales)
+        layer = DeviceLayer(inp, y_fp32=fp32)
+        assert layer.plan.centroid_rows
+        y = layer.gemm()
+        torch.cuda.synchronize()
+        rel = check_against_oracle(y.cpu().numpy(), y_ref, T, case.name)
+        assert rel < (5e-6 if fp32 else 6e-4), rel
+
+
+def test_integer_case_is_exact_and_rows_are_independent():
+    v, K, N, B, row = 8, 1024, 1100, 64 * 63 + 7, 77
+    rng = np.random.default_rng(37)
+    i = np.arange(256)[:, None]
+    inp = synth.generate(synth.custom_case(K, N, v, 2, B, seed=4))
+    bits = (i >> np.arange(v)[None, :]) & 1
+    inp.codebooks = np.stack([np.where(bits, 1.0, -1.0), np.where(bits, 2.0, 0.0)]).astype(np.float16)
+    inp.x = rng.integers(-8, 9, (B, K)).astype(np.float16)
+    inp.scales = np.ones(N, np.float16)
+    y_ref, _ = oracle.gemm(inp.x, inp.codes, inp.codebooks, inp.scales)
+    y = DeviceLayer(inp, y_fp32=True).gemm()
+    torch.cuda.synchronize()
+    assert np.array_equal(y.cpu().numpy().astype(np.float64), y_ref)
+    inp.x = inp.x.copy()
+    inp.x[row, 3] = np.nan
+    inp.x[row, 200] = np.inf
+    z = DeviceLayer(inp, y_fp32=True).gemm()
+    torch.cuda.synchronize()
+    others = torch.arange(B, device=z.device) != row
+    assert torch.equal(z[others], y[others])
+    assert not bool(torch.isfinite(z[row]).any().item())
+
+
+@pytest.mark.parametrize("B", [33, 64, 96, 200])
+def test_batches_between_a_launch_and_a_prompt(B):
+    """More than 32 rows but too few workgroups for the prompt kernel: tiles of the centroid kernel along the grid."""
+    for v, m, g in ((8, 2, -1), (4, 1, 128)):
+        inp = synth.generate(synth.custom_case(2048, 515, v, m, B, seed=3700, g=g))
+        y_ref, T = oracle.gemm(inp.x, inp.codes, inp.codebooks, inp.scales)
+        y = DeviceLayer(inp).gemm()
+        torch.cuda.synchronize()
+        check_against_oracle(y.cpu().numpy(), y_ref, T, inp.case.name)
