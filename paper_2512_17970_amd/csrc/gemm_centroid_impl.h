@@ -475,8 +475,16 @@ int launch_gemm_centroid_v(const Geometry& g, const GemmParams& p, hipStream_t s
             return launch_gemm_centroid_one<M, V, 4, 1, 1, 8, 4, GS>(g, p, stream);
         case 8:
             if (g.RB == 128) return launch_gemm_centroid_one<M, V, 2, 1, 2, 4, 4, GS>(g, p, stream);
-            return launch_gemm_centroid_one<M, V, 2, 1, 1, 8, 4, GS>(g, p, stream);
-        case 16: return launch_gemm_centroid_one<M, V, 1, 1, 1, 8, 2, GS>(g, p, stream);
+            if (g.RB == 64) return launch_gemm_centroid_one<M, V, 2, 1, 1, 8, 4, GS>(g, p, stream);
+            if constexpr (V < 16) return launch_gemm_centroid_one<M, V, 4, 2, 1, 8, 3, GS>(g, p, stream);
+            break;
+        case 16:
+            if (g.RB == 128) return launch_gemm_centroid_one<M, V, 1, 1, 1, 8, 2, GS>(g, p, stream);
+            if constexpr (V < 16) {
+                if (g.RB == 64) return launch_gemm_centroid_one<M, V, 2, 2, 1, 8, 2, GS>(g, p, stream);
+                if constexpr (!GS || M == 1) return launch_gemm_centroid_one<M, V, 4, 4, 1, 8, 2, GS>(g, p, stream);
+            }
+            break;
         case 32:
             if constexpr (!GS && (V == 8 && M <= 2 || V == 4 && M == 1)) return launch_gemm_centroid_one<M, V, 1, 2, 1, 8, 2, GS>(g, p, stream);
     }

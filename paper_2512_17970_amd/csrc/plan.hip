@@ -34,19 +34,20 @@ static bool centroid_format(const codegemm_desc* d)
     return d->group_size == -1 || d->group_size >= (d->vec_len == 4 ? 32 : 16) * d->vec_len;
 }
 
-// Batch rows of a workgroup of the centroid kernel, and the rows of W that one of its wavefronts owns then.
-static int centroid_batch(const codegemm_desc* d)
+// Batch rows of a workgroup of the centroid kernel whose blocks have `rows` rows.  A wavefront owns 32, 64 or 128
+// rows and takes 4, 8 or 16 batch rows per MFMA; blocks lower than the batch would have take several MFMAs per lookup.
+static int centroid_batch(const codegemm_desc* d, int rows)
 {
     const int b = d->batch;
     if (b <= 8) return b == 1 ? 1 : b <= 4 ? 4 : 8;
     // two tiles of 16 only where their accumulators leave registers for the codes
     const bool two = d->group_size == -1 && ((d->vec_len == 8 && d->num_codebooks <= 2) || (d->vec_len == 4 && d->num_codebooks == 1));
-    return b > 16 && two ? 32 : 16;
+    return b > 16 && rows == 128 && two ? 32 : 16;
 }
 static int centroid_min_rows(const codegemm_desc* d)
 {
-    const int b = centroid_batch(d);
-    return b <= 4 ? 32 : b == 8 ? 64 : 128;
+    if (d->vec_len < 16) return d->batch > 8 && d->group_size > 0 && d->num_codebooks > 1 ? 64 : 32;   // (registers)
+    return d->batch <= 4 ? 32 : d->batch <= 8 ? 64 : 128;      // v = 16: one MFMA per lookup (registers)
 }
 
 static int validate_plan(const codegemm_desc* d, const codegemm_plan* p)
@@ -229,11 +230,9 @@ static void choose_psumbook_plan(const codegemm_desc* d, codegemm_plan* p)
 
 // Whether the centroid kernel is the faster one, from sweeps over the workloads' shapes and formats (us, Psumbook
 // kernels / centroid kernel):
-//  * two to eight batch rows: everywhere (v8 m2, batch 2 / 4 / 8: 2048^2 6.1/4.9, 7.6/5.0, 7.8/6.6; 8192->28672
-//    23.9/18.3, 27.3/19.2, 41.5/21.9; v16 m4 at 8192^2 12.3/11.2, 14.3/11.5, 19.9/15.2);
-//  * nine and more: all but the smallest matrices, which leave its 128-row blocks too few and too short (batch 16:
-//    2048^2 8.4/9.4, 4096->1024 8.6/9.6, but 8192->1024 12.9/10.7, 8192->28672 70/25); beyond 32 rows, where the
-//    Psumbook kernels start over for every 32, always;
+//  * more than one batch row: everywhere (v8 m2, batch 2 / 4 / 8 / 16: 2048^2 6.1/4.9, 7.6/5.0, 7.8/5.6, 8.3/7.2;
+//    8192->28672 23.9/18.3, 27.3/19.2, 41.5/21.9, 70/25), except v = 16 at nine rows and more, whose 128-row blocks
+//    leave small matrices too few of them (v16 m4 at batch 16: 4096^2 14.8/16.0, 8192^2 31.7/20.6; at 32 19.8/16.6);
 //  * one: where 32-row blocks fill half of the chip and its lookups, four times the LDS bytes of the Psumbook's, are not
 //    what bounds the call: v4 m1 g128 4096^2 5.9/5.3, 28672->8192 21.9/15.7 (its centroids are the shortest); v8 m2
 //    4096^2 5.5/4.9, 4096->14336 7.9/7.0, 8192^2 8.0/7.7, but 8192->28672 15.7/17.4, 2048^2 4.8/4.9; three codebooks
@@ -242,8 +241,7 @@ static bool prefer_centroid(const codegemm_desc* d)
 {
     if (!centroid_format(d) || d->out_features > 65535 * 128) return false;     // grid.y
     const long long codes = (long long)d->num_codebooks * d->out_features * (d->in_features / d->vec_len);
-    if (d->batch > 8) return d->batch > kBatchPerLaunch || codes >= 1500000;
-    if (d->batch > 1) return true;
+    if (d->batch > 1) return d->vec_len < 16 || d->batch <= 8 || d->batch > kBatchPerLaunch || codes >= (d->batch <= 16 ? 6000000 : 4000000);
     if (d->num_codebooks > 2 || d->vec_len == 16) return false;
     if (d->vec_len == 4 && d->num_codebooks == 1) return d->out_features >= 4096 || d->in_features >= 8192;
     return d->out_features >= 4096 && codes * d->vec_len <= (d->group_size > 0 ? 120000000 : 136000000);
@@ -254,26 +252,37 @@ static void choose_plan(const codegemm_desc* d, codegemm_plan* p)
     choose_psumbook_plan(d, p);
     if (!prefer_centroid(d)) return;
     const int nkt = ceil_div(d->in_features / d->vec_len, kSlots);
-    const int tile = centroid_batch(d);
-    const int tiles = ceil_div(d->batch, tile);
-    // Block height: as low as the batch allows while there are no more blocks than the chip takes at a time (two
-    // workgroups fit on a compute unit): low blocks need fewer K ranges, and with them the exchange through memory.
+    const long long codes = (long long)d->num_codebooks * d->out_features * (d->in_features / d->vec_len);
+    const int least = centroid_min_rows(d);
+    auto blocks = [&](int r) { return (long long)ceil_div(d->out_features, r) * ceil_div(d->batch, centroid_batch(d, r)); };
+    // Block height.  Low blocks need fewer K ranges, and with them the exchange through memory; from 5 batch rows on
+    // they cost more MFMAs per lookup (32 rows: one per 4 batch rows, 64: one per 8).  So: as low as fills the chip, and
+    // only for matrices whose lookups are few beside a call's fixed part (v8 m2, us: batch 8, 2048^2 32 rows 5.6, 64 rows
+    // 6.6; 4096^2 6.5 / 7.8; 8192^2 13.6 / 11.1; batch 16, 4096^2 32 rows 9.0, 64 rows 9.5, 128 rows 11.3; 4096->14336
+    // 64 rows 12.5, 128 rows 14.0; 14336->4096 17.0 / 14.0; batch 32, 4096^2 64 rows 10.5, 128 rows 15.8).
     int rows = 128;
-    if (tile <= 4) rows = ceil_div(d->out_features, 32) <= 320 ? 32 : ceil_div(d->out_features, 64) <= 512 ? 64 : 128;
-    else if (tile == 8) rows = ceil_div(d->out_features, 64) <= 256 ? 64 : 128;
-    const int blocks = ceil_div(d->out_features, rows) * tiles;
-    // K ranges: for up to 4 batch rows 128 workgroups, 256 when that leaves each 48 units or more (14336->4096 v8 m2: two
-    // ranges 7.4, one 8+; 4096^2: one 4.9, two 5.4); for more, 256 as long as a workgroup keeps 2 (4 with 9 or more rows)
-    // units (4096^2 at batch 32: 4 ranges 15.9, 8 ranges 17.6; 8192^2: 4 ranges 20.2, 2 ranges 24.4).
-    int splits;
-    if (tile <= 4) {
-        splits = ceil_div(128, blocks);
-        if (splits * blocks <= 128 && nkt / splits >= 48) splits *= 2;
+    if (d->batch <= 4) {
+        rows = blocks(32) <= 320 ? 32 : blocks(64) <= 512 ? 64 : 128;
+    } else if (d->batch <= 8) {
+        if (least == 32 && blocks(32) <= 256 && (d->vec_len == 4 ? codes / 2 : codes) <= 10000000) rows = 32;
+        else if (blocks(64) <= 256) rows = 64;
     } else {
-        splits = 256 / blocks;
-        const int most = nkt / (tile == 8 ? 2 : 4);
+        const long long low = d->batch <= 16 ? 8500000 : 4300000;
+        if (least == 32 && blocks(32) <= (d->batch <= 16 ? 192 : 256) && codes <= low) rows = 32;
+        else if (least <= 64 && blocks(64) <= 256 && (codes <= 8500000 || (d->batch <= 16 && codes <= 16000000 && blocks(64) >= 96))) rows = 64;
+    }
+    // K ranges.  Up to 4 batch rows: 128 workgroups, 256 when that leaves each 48 units or more (14336->4096 v8 m2: two
+    // ranges 7.4, one 8+; 4096^2: one 4.9, two 5.4).  More: 256 as long as every wavefront keeps a step (4096^2 at batch
+    // 8: two ranges 6.5, one 6.8; 2048^2: two 5.6, four, with half of the wavefronts idle, 6.2).
+    const int nb = (int)blocks(rows);
+    int splits;
+    if (d->batch <= 4) {
+        splits = ceil_div(128, nb);
+        if (splits * nb <= 128 && nkt / splits >= 48) splits *= 2;
+    } else {
+        splits = 256 / nb;
+        const int most = nkt * (d->vec_len == 4 ? 1 : 2) / 8;
         if (splits > most) splits = most;
-        if (splits * blocks < 128 && splits < nkt / 2) splits = ceil_div(128, blocks) < nkt / 2 ? ceil_div(128, blocks) : nkt / 2;
     }
     // no more workspace than the fields of the Psumbook kernels ask for
     const long long room = (long long)p->k_splits * (d->batch < kBatchPerLaunch ? d->batch : kBatchPerLaunch) / d->batch;
@@ -309,7 +318,7 @@ int make_geometry(const codegemm_desc* d, const codegemm_plan* plan, Geometry* g
     g->psum_fp16 = plan->psum_dtype == CODEGEMM_PSUM_FP16;
     g->NGR = ceil_div(g->N, kGranuleRows);
     g->RB = plan->centroid_rows;
-    if (g->RB) g->BG = centroid_batch(d);              // batch rows of a workgroup of the centroid kernel
+    if (g->RB) g->BG = centroid_batch(d, g->RB);              // batch rows of a workgroup of the centroid kernel
     // rows per workgroup: 16 per wavefront and row word (32 in the batched kernel)
     g->NBLK = ceil_div(g->NGR * kGranuleRows, g->RPL * (g->NW - g->NB) * (g->BG == 4 ? 32 : 16));
     if (g->RB) g->NBLK = ceil_div(g->N, g->RB);

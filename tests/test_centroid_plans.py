@@ -14,10 +14,12 @@ def test_offered_and_refused():
     assert ws(d, 32, 1) > 0 and ws(d, 64, 2) > 0 and ws(d, 128, 1000) > 0
     for rows, splits in ((16, 1), (96, 1), (256, 1), (128, 0), (128, -1), (0, 1), (-128, 1)):
         assert ws(d, rows, splits) == 0
-    assert ws(cg.Desc.make(8, 4096, 1000, 8, 2), 32, 1) == 0            # a wavefront owns 64 rows from 5 batch rows on
-    assert ws(cg.Desc.make(8, 4096, 1000, 8, 2), 64, 1) > 0
-    assert ws(cg.Desc.make(9, 4096, 1000, 8, 2), 64, 1) == 0            # .. and 128 from 9 on
-    assert ws(cg.Desc.make(9, 4096, 1000, 8, 2), 128, 1) > 0
+    for B in (5, 8, 9, 16, 17, 32, 33):                                 # v = 16 and wide group scales: registers
+        for rows in (32, 64, 128):
+            assert ws(cg.Desc.make(B, 4096, 1000, 8, 2), rows, 1) > 0
+            assert (ws(cg.Desc.make(B, 4096, 1000, 16, 2), rows, 1) > 0) == (rows >= (64 if B <= 8 else 128))
+            assert (ws(cg.Desc.make(B, 4096, 1000, 8, 2, g=128), rows, 1) > 0) == (rows >= (32 if B <= 8 else 64))
+            assert ws(cg.Desc.make(B, 4096, 1000, 4, 1, g=128), rows, 1) > 0
     for v, m, g, ok in ((8, 2, 128, True), (8, 2, 64, False), (4, 1, 128, True), (4, 1, 64, False), (16, 2, 256, True), (16, 2, 128, False),
                         (4, 2, -1, True), (4, 3, -1, False), (16, 4, -1, True)):
         assert (ws(cg.Desc.make(4, 4096, 1000, v, m, g=g), 128, 1) > 0) == ok, (v, m, g)

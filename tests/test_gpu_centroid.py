@@ -13,8 +13,10 @@ cg = pytest.importorskip("paper_2512_17970_amd")
 from gpu_util import DeviceLayer, Guarded, check_against_oracle, dev, stream  # noqa: E402
 
 
-def least_rows(B):
-    return 32 if B <= 4 else 64 if B <= 8 else 128
+def least_rows(B, v=8, m=2, g=-1):
+    if v == 16:
+        return 32 if B <= 4 else 64 if B <= 8 else 128
+    return 64 if B > 8 and g > 0 and m > 1 else 32
 
 
 def plan_of(case, rows, splits):
@@ -56,12 +58,12 @@ def test_formats_and_batches(v, m, g, B):
 
 @pytest.mark.parametrize("rows", [32, 64, 128])
 @pytest.mark.parametrize("splits", [1, 2, 4, 5])
-@pytest.mark.parametrize("B", [1, 3, 7])
-@pytest.mark.parametrize("v,m,g", [(8, 2, -1), (4, 1, 128), (16, 4, -1), (8, 3, 128)])
+@pytest.mark.parametrize("B", [1, 3, 7, 13, 21, 40])
+@pytest.mark.parametrize("v,m,g", [(8, 2, -1), (8, 1, -1), (4, 1, 128), (4, 2, -1), (16, 4, -1), (8, 3, 128), (8, 4, -1)])
 def test_block_heights(v, m, g, B, splits, rows):
     """Blocks of 32 and 64 rows (the batches that have them), ragged at either end of a granule; pairwise words and
     tickets between the K ranges."""
-    if rows < least_rows(B):
+    if rows < least_rows(B, v, m, g):
         pytest.skip("block height not offered for this batch")
     for N in (rows, rows + 1, 1000):
         run(synth.custom_case(max(g, 32 * v) * 6, N, v, m, B, seed=3100 + N, g=g), rows, splits)
@@ -108,7 +110,8 @@ def test_non_finite_activations_stay_in_their_row(B, row):
     assert not bool(torch.isfinite(y[row]).any().item())
 
 
-@pytest.mark.parametrize("B,rows,splits,g", [(1, 32, 1, -1), (1, 64, 2, 128), (4, 32, 3, -1), (8, 64, 4, -1), (16, 128, 2, 128), (32, 128, 5, -1)])
+@pytest.mark.parametrize("B,rows,splits,g", [(1, 32, 1, -1), (1, 64, 2, 128), (4, 32, 3, -1), (8, 64, 4, -1), (6, 32, 1, 128),
+                                             (16, 128, 2, 128), (16, 32, 2, -1), (13, 64, 1, 128), (32, 128, 5, -1), (32, 64, 2, -1)])
 def test_grouped_members_equal_their_single_calls(B, rows, splits, g):
     K, Ns = 2048, [300, 130, 65]
     desc = cg.Desc.make(B, K, sum(Ns), 8, 2, g=g)
