@@ -77,11 +77,21 @@ __device__ __forceinline__ void pair_transpose(uint32_t& a, uint32_t& b, bool od
     b = nb;
 }
 
+// Exchanges two registers' contents between lanes 16 apart: a keeps its rows of lanes 0 and 2 and gets b's there as rows
+// 1 and 3, b gets a's rows 1 and 3 as rows 0 and 2.
+__device__ __forceinline__ void row_exchange(uint32_t& a, uint32_t& b)
+{
+    const auto r = __builtin_amdgcn_permlane16_swap(a, b, false, false);
+    a = r[0];
+    b = r[1];
+}
+
 // SB: sub-vectors along the columns of the operands (16 / SB octets per wavefront, 16 / SB batch rows per tile).
 // NT: tiles of batch rows.  RW x KW wavefronts: RW blocks of 128 / SB rows, KW slices of K.  D: steps in the load
-// ring.  GS: group scales; a step (16 sub-vectors, 32 for v = 4) lies in one group.  ONE (SB = 4): one batch row, for
-// which the result elements are arranged so that a lane has one that means something instead of one of four.
-template <int M, int V, int SB, int NT, int RW, int KW, int D, bool GS, bool ONE>
+// ring.  GS: 0 one scale per row; 1 group scales, a step (16 chunks) lies in one group; 2 groups of 4 or 8 chunks (a
+// chunk is a sub-vector, two for v = 4): every MFMA then contracts over 4 neighbouring chunks instead of chunks 4 apart,
+// and sums are scaled after every round.  ONE (SB = 4): one batch row, for which the result elements are arranged so that a lane has one that means something instead of one of four.
+template <int M, int V, int SB, int NT, int RW, int KW, int D, int GS, bool ONE>
 __global__ void __launch_bounds__(RW * KW * 64) gemm_centroid_kernel(CG_HEAD_PARAMS, const GemmParams pk)
 {
     const GemmParams p = with_head(pk, hx, hpacked, hcodebooks, hgscales, hK, hNKT, hKPW, hB, hNGR, hmisc);
@@ -122,6 +132,16 @@ __global__ void __launch_bounds__(RW * KW * 64) gemm_centroid_kernel(CG_HEAD_PAR
     const int ls = lane & (LS - 1), lo = (lane & 15) / LS;
     const int col_o = (lane & 15) / SB;                // octet of this lane's column
     const bool odd = lane & 1;
+    // Chunk of load j of a step: the lane's part and the load's (chunk_at(j)).  SB = 1: loads 2 i and 2 i + 1 take the same
+    // chunk of two octets (batch rows), exchanged afterwards; GS = 2 moves chunk bits between lanes 16 apart as well.
+    auto lane_chunk = [&](int sv) -> int {             // sv: the lane's place along contiguous memory
+        if constexpr (GS == 2) return SB == 1 ? 4 * (q & 1) + 2 * (q >> 1) + sv : 4 * sv + q;
+        else return 4 * q + sv;
+    };
+    auto chunk_at = [](int j) -> int {
+        if constexpr (SB == 1) return (GS == 2 ? 8 : 2) * (j / 2);
+        else return (GS == 2 ? 4 * SB : SB) * j;
+    };
 
     // Table entries of this thread, requested first: everything waits for them.
     constexpr int ENTRIES = M * kCentroids * T::kHalves;                // to replicate
@@ -139,17 +159,17 @@ __global__ void __launch_bounds__(RW * KW * 64) gemm_centroid_kernel(CG_HEAD_PAR
     const int total = nq * SPU;
     const int s_beg = total * kw / KW, s_end = total * (kw + 1) / KW;
 
-    // x: round j of a step, chunk 4 q + SB j + ls of the step's 16 (SB = 1: loads 2 jj and 2 jj + 1 take chunk
-    // 4 q + 2 jj + ls of batch rows 2 lo and 2 lo + 1; after the exchange register r is chunk 4 q + r of row lane % 16)
+    // x: round j of a step, chunk lane_chunk + chunk_at(j) of the step's 16 (SB = 1: loads 2 i and 2 i + 1 of batch rows
+    // 2 lo and 2 lo + 1; after the exchange register j is chunk 4 q + j, or 4 j + q with GS = 2, of row lane % 16)
     const __amdgpu_buffer_rsrc_t x_rsrc = __builtin_amdgcn_make_buffer_rsrc(
         const_cast<_Float16*>(p.x + (size_t)b0 * p.K), 0, min(p.B - b0, BT) * p.K * 2, kRsrcFlags);
     const int xb = ONE ? lane & 3 : lo, xs = ONE ? (lane >> 2) & 3 : ls;           // ONE: batch row innermost
-    const int x_el0 = kt0 * kSlots * V + (4 * q + xs) * CHUNK;
+    const int x_el0 = kt0 * kSlots * V + lane_chunk(xs) * CHUNK;
     const int x_off = ((SB == 1 ? 2 * xb : xb) * p.K + x_el0) * 2;
     auto load_x = [&](half8_t (&dst)[NT][R][HALVES], int s) {
 #pragma unroll
         for (int j = 0; j < R; ++j) {
-            const int el = s * (16 * CHUNK) + (SB == 1 ? 2 * (j / 2) : SB * j) * CHUNK;
+            const int el = s * (16 * CHUNK) + chunk_at(j) * CHUNK;
             const int at = (s < s_end && x_el0 + el < p.K) ? el * 2 + (SB == 1 ? (j % 2) * p.K * 2 : 0) : kOutOfRange;
 #pragma unroll
             for (int nt = 0; nt < NT; ++nt)
@@ -162,7 +182,7 @@ __global__ void __launch_bounds__(RW * KW * 64) gemm_centroid_kernel(CG_HEAD_PAR
         if constexpr (V == 4) {                        // an odd number of sub-vectors: the chunk may reach past the end of the row
 #pragma unroll
             for (int j = 0; j < R; ++j) {
-                const bool past = x_el0 + s * (16 * CHUNK) + (SB == 1 ? 2 * (j / 2) : SB * j) * CHUNK + 4 >= p.K;
+                const bool past = x_el0 + s * (16 * CHUNK) + chunk_at(j) * CHUNK + 4 >= p.K;
 #pragma unroll
                 for (int nt = 0; nt < NT; ++nt) {
                     u32x4_t t = __builtin_bit_cast(u32x4_t, xv[nt][j][0]);
@@ -184,6 +204,7 @@ __global__ void __launch_bounds__(RW * KW * 64) gemm_centroid_kernel(CG_HEAD_PAR
                         for (int k = 0; k < 4; ++k) {
                             uint32_t ak = a[k], bk = b[k];
                             pair_transpose(ak, bk, odd);
+                            if constexpr (GS == 2) row_exchange(ak, bk);
                             a[k] = ak;
                             b[k] = bk;
                         }
@@ -200,12 +221,12 @@ __global__ void __launch_bounds__(RW * KW * 64) gemm_centroid_kernel(CG_HEAD_PAR
     const uint8_t* cbase = mm.packed + ((size_t)min(gr, mm.NGR - 1) * p.NKT + kt0) * kUnitBytes;
     const __amdgpu_buffer_rsrc_t c_rsrc =
         __builtin_amdgcn_make_buffer_rsrc(const_cast<uint8_t*>(cbase), 0, gr < mm.NGR ? nq * kUnitBytes : 0, kRsrcFlags);
-    const int c_ent = (oct0 + (SB == 1 ? 2 * lo : lo)) * kSlots + (V == 4 ? 2 : 1) * (4 * q + ls);
+    const int c_ent = (oct0 + (SB == 1 ? 2 * lo : lo)) * kSlots + (V == 4 ? 2 : 1) * lane_chunk(ls);
     auto load_codes = [&](uint32_t (&dst)[R][WR], int s) {
         const int unit = s < s_end ? (s / SPU) * kUnitBytes : kOutOfRange;
 #pragma unroll
         for (int j = 0; j < R; ++j) {
-            const int ent = c_ent + (V == 4 ? 0 : (s % SPU) * 16) + (V == 4 ? 2 : 1) * (SB == 1 ? 2 * (j / 2) : SB * j) + (SB == 1 ? (j % 2) * kSlots : 0);
+            const int ent = c_ent + (V == 4 ? 0 : (s % SPU) * 16) + (V == 4 ? 2 : 1) * chunk_at(j) + (SB == 1 ? (j % 2) * kSlots : 0);
 #pragma unroll
             for (int part = 0; part < (M + 1) / 2; ++part) {
                 uint32_t* w = dst[j] + part * PW;
@@ -234,7 +255,10 @@ __global__ void __launch_bounds__(RW * KW * 64) gemm_centroid_kernel(CG_HEAD_PAR
 #pragma unroll
             for (int j = 0; j < R; j += 2)
 #pragma unroll
-                for (int k = 0; k < WR; ++k) pair_transpose(cw[j][k], cw[j + 1][k], odd);
+                for (int k = 0; k < WR; ++k) {
+                    pair_transpose(cw[j][k], cw[j + 1][k], odd);
+                    if constexpr (GS == 2) row_exchange(cw[j][k], cw[j + 1][k]);
+                }
         }
         if constexpr (T::kOrderBits > 0) {
 #pragma unroll
@@ -265,14 +289,21 @@ __global__ void __launch_bounds__(RW * KW * 64) gemm_centroid_kernel(CG_HEAD_PAR
         const uint8_t* base = mm.gscales + ((size_t)min(gr, mm.NGR - 1) * p.NKT + kt0) * p.GPU * 256;
         s_rsrc = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint8_t*>(base), 0, gr < mm.NGR ? nq * p.GPU * 256 : 0, kRsrcFlags);
     }
-    auto load_scales = [&](half8_t& dst, int s) {
-        const int o = s < s_end ? ((s / SPU) * p.GPU + (((s % SPU) * 16) >> p.gshift)) * 256 : kOutOfRange;
-        dst = __builtin_bit_cast(half8_t, __builtin_amdgcn_raw_buffer_load_b128(s_rsrc, o + (oct0 + col_o) * 16, 0, 0));
+    constexpr int SR = GS == 2 ? R : 1;                // scales per step
+    auto load_scales = [&](half8_t (&dst)[SR], int s) {
+#pragma unroll
+        for (int j = 0; j < SR; ++j) {
+            // first sub-vector, in its unit, of the chunks that the lane's column contracts over
+            const int chunk = GS == 2 ? (SB == 1 ? 4 * j : chunk_at(j) + 4 * (lane & (SB - 1))) : 0;
+            const int sub = (s % SPU) * 16 + (V == 4 ? 2 : 1) * chunk;
+            const int o = s < s_end ? ((s / SPU) * p.GPU + (sub >> p.gshift)) * 256 : kOutOfRange;
+            dst[j] = __builtin_bit_cast(half8_t, __builtin_amdgcn_raw_buffer_load_b128(s_rsrc, o + (oct0 + col_o) * 16, 0, 0));
+        }
     };
 
     half8_t xr[D][NT][R][HALVES];
     uint32_t w[D][R][WR];
-    half8_t sc[GS ? D : 1];
+    half8_t sc[GS ? D : 1][SR];
     __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
     for (int d = 0; d < D; ++d) {
@@ -356,6 +387,17 @@ __global__ void __launch_bounds__(RW * KW * 64) gemm_centroid_kernel(CG_HEAD_PAR
         }
     };
 
+    auto add_scaled = [&](const half8_t& scales) {
+#pragma unroll
+        for (int u = 0; u < 8; ++u) {
+            const float f = (float)scales[u];
+#pragma unroll
+            for (int nt = 0; nt < NT; ++nt)
+#pragma unroll
+                for (int t = 0; t < TL; ++t) sum[GS ? nt : 0][u][GS ? t : 0] = __builtin_fmaf(f, own(acc[nt][u], t), sum[GS ? nt : 0][u][GS ? t : 0]);
+        }
+    };
+
     __syncthreads();
 
     // Main loop.  Every MFMA is followed by the lookup that takes its operand's registers, for the same u
@@ -378,24 +420,17 @@ __global__ void __launch_bounds__(RW * KW * 64) gemm_centroid_kernel(CG_HEAD_PAR
 #pragma unroll
                         for (int nt = 0; nt < NT; ++nt) {
                             const half8_t xv = xr[d][nt][k / (M * HALVES)][(k / M) % HALVES];
-                            acc[nt][u] = __builtin_amdgcn_mfma_f32_16x16x32_f16(xv, a[u], (GS && k == 0) ? float4_t{} : acc[nt][u], 0, 0, 0);
+                            acc[nt][u] = __builtin_amdgcn_mfma_f32_16x16x32_f16(xv, a[u], (GS == 1 && k == 0) || (GS == 2 && k % (M * HALVES) == 0) ? float4_t{} : acc[nt][u], 0, 0, 0);
                         }
                         __builtin_amdgcn_sched_barrier(0);         // the lookup after its operand's last use: no second set of registers
                         a[u] = k + 1 < NSB ? fetch(w[d], k + 1, u) : fetch(w[(d + 1) % D], 0, u);
                         __builtin_amdgcn_sched_barrier(0);
                     }
-                }
-                if constexpr (GS) {
-#pragma unroll
-                    for (int u = 0; u < 8; ++u) {
-                        const float f = (float)sc[d][u];
-#pragma unroll
-                        for (int nt = 0; nt < NT; ++nt)
-#pragma unroll
-                            for (int t = 0; t < TL; ++t)
-                                sum[nt][u][t] = __builtin_fmaf(f, own(acc[nt][u], t), sum[nt][u][t]);
+                    if constexpr (GS == 2) {
+                        if (k % (M * HALVES) == M * HALVES - 1) add_scaled(sc[d][k / (M * HALVES)]);
                     }
                 }
+                if constexpr (GS == 1) add_scaled(sc[d][0]);
             }
             load_codes(w[d], s + D);
             load_x(xr[d], s + D);
@@ -444,7 +479,7 @@ __global__ void __launch_bounds__(RW * KW * 64) gemm_centroid_kernel(CG_HEAD_PAR
     finish_block<THREADS, BT, RB>(p, mm, totals, flag, tid, blk, ks, b0);
 }
 
-template <int M, int V, int SB, int NT, int RW, int KW, int D, bool GS, bool ONE = false>
+template <int M, int V, int SB, int NT, int RW, int KW, int D, int GS, bool ONE = false>
 int launch_gemm_centroid_one(const Geometry& g, const GemmParams& p, hipStream_t stream)
 {
     auto fn = gemm_centroid_kernel<M, V, SB, NT, RW, KW, D, GS, ONE>;
@@ -461,7 +496,7 @@ int launch_gemm_centroid_one(const Geometry& g, const GemmParams& p, hipStream_t
     return hipGetLastError() == hipSuccess ? CODEGEMM_OK : CODEGEMM_LAUNCH_FAILED;
 }
 
-template <int M, int V, bool GS>
+template <int M, int V, int GS>
 int launch_gemm_centroid_v(const Geometry& g, const GemmParams& p, hipStream_t stream)
 {
     switch (g.BG) {
@@ -474,15 +509,17 @@ int launch_gemm_centroid_v(const Geometry& g, const GemmParams& p, hipStream_t s
             if (g.RB == 64) return launch_gemm_centroid_one<M, V, 4, 1, 2, 4, 4, GS>(g, p, stream);
             return launch_gemm_centroid_one<M, V, 4, 1, 1, 8, 4, GS>(g, p, stream);
         case 8:
-            if (g.RB == 128) return launch_gemm_centroid_one<M, V, 2, 1, 2, 4, 4, GS>(g, p, stream);
-            if (g.RB == 64) return launch_gemm_centroid_one<M, V, 2, 1, 1, 8, 4, GS>(g, p, stream);
+            if (g.RB == 128) return launch_gemm_centroid_one<M, V, 2, 1, 2, 4, GS == 2 ? 3 : 4, GS>(g, p, stream);
+            if (g.RB == 64) return launch_gemm_centroid_one<M, V, 2, 1, 1, 8, GS == 2 ? 3 : 4, GS>(g, p, stream);
             if constexpr (V < 16) return launch_gemm_centroid_one<M, V, 4, 2, 1, 8, 3, GS>(g, p, stream);
             break;
         case 16:
             if (g.RB == 128) return launch_gemm_centroid_one<M, V, 1, 1, 1, 8, 2, GS>(g, p, stream);
-            if constexpr (V < 16) {
+            if constexpr (V < 16 && (GS < 2 || M == 1)) {
                 if (g.RB == 64) return launch_gemm_centroid_one<M, V, 2, 2, 1, 8, 2, GS>(g, p, stream);
-                if constexpr (!GS || M == 1) return launch_gemm_centroid_one<M, V, 4, 4, 1, 8, 2, GS>(g, p, stream);
+            }
+            if constexpr (V < 16 && (GS == 0 || M == 1)) {
+                if (g.RB == 32) return launch_gemm_centroid_one<M, V, 4, 4, 1, 8, 2, GS>(g, p, stream);
             }
             break;
         case 32:

@@ -16,7 +16,7 @@
 
 namespace cg {
 
-template <int M, int V, int NT, bool GS>
+template <int M, int V, int NT, int GS>
 __global__ void __launch_bounds__(512) gemm_prompt_kernel(CG_HEAD_PARAMS, const GemmParams pk)
 {
     const GemmParams p = with_head(pk, hx, hpacked, hcodebooks, hgscales, hK, hNKT, hKPW, hB, hNGR, hmisc);
@@ -85,12 +85,13 @@ __global__ void __launch_bounds__(512) gemm_prompt_kernel(CG_HEAD_PARAMS, const 
     const uint8_t* cbase = mm.packed + (size_t)min(gr, mm.NGR - 1) * p.NKT * kUnitBytes;
     const __amdgpu_buffer_rsrc_t c_rsrc =
         __builtin_amdgcn_make_buffer_rsrc(const_cast<uint8_t*>(cbase), 0, gr < mm.NGR ? p.NKT * kUnitBytes : 0, kRsrcFlags);
-    const int c_ent = 2 * lo * kSlots + (V == 4 ? 2 : 1) * (4 * q + (lane & 1));
+    // chunk of load j: GS = 2 as in the centroid kernel, every MFMA contracting over 4 neighbouring chunks
+    const int c_ent = 2 * lo * kSlots + (V == 4 ? 2 : 1) * ((GS == 2 ? 4 * (q & 1) + 2 * (q >> 1) : 4 * q) + (lane & 1));
     auto load_codes = [&](uint32_t (&dst)[4][WR], int s) {
         const int unit = (s / SPU) * kUnitBytes;       // past the last unit: zeros
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
-            const int ent = c_ent + (V == 4 ? 0 : (s % SPU) * 16) + (V == 4 ? 2 : 1) * (2 * (j / 2)) + (j % 2) * kSlots;
+            const int ent = c_ent + (V == 4 ? 0 : (s % SPU) * 16) + (V == 4 ? 2 : 1) * ((GS == 2 ? 8 : 2) * (j / 2)) + (j % 2) * kSlots;
 #pragma unroll
             for (int part = 0; part < (M + 1) / 2; ++part) {
                 uint32_t* w = dst[j] + part * PW;
@@ -117,7 +118,10 @@ __global__ void __launch_bounds__(512) gemm_prompt_kernel(CG_HEAD_PARAMS, const 
 #pragma unroll
         for (int j = 0; j < 4; j += 2)
 #pragma unroll
-            for (int k = 0; k < WR; ++k) pair_transpose(cw[j][k], cw[j + 1][k], odd);
+            for (int k = 0; k < WR; ++k) {
+                pair_transpose(cw[j][k], cw[j + 1][k], odd);
+                if constexpr (GS == 2) row_exchange(cw[j][k], cw[j + 1][k]);
+            }
         if constexpr (T::kOrderBits == 1) {
 #pragma unroll
             for (int j = 0; j < 4; ++j)
@@ -137,13 +141,18 @@ __global__ void __launch_bounds__(512) gemm_prompt_kernel(CG_HEAD_PARAMS, const 
         const uint8_t* base = mm.gscales + (size_t)min(gr, mm.NGR - 1) * p.NKT * p.GPU * 256;
         s_rsrc = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint8_t*>(base), 0, gr < mm.NGR ? p.NKT * p.GPU * 256 : 0, kRsrcFlags);
     }
-    auto load_scales = [&](half8_t& dst, int s) {
-        const int o = ((s / SPU) * p.GPU + (((s % SPU) * 16) >> p.gshift)) * 256;
-        dst = __builtin_bit_cast(half8_t, __builtin_amdgcn_raw_buffer_load_b128(s_rsrc, o + i16 * 16, 0, 0));
+    constexpr int SR = GS == 2 ? 4 : 1;                // scales per step
+    auto load_scales = [&](half8_t (&dst)[SR], int s) {
+#pragma unroll
+        for (int j = 0; j < SR; ++j) {
+            const int sub = (s % SPU) * 16 + (V == 4 ? 2 : 1) * 4 * j;  // of the unit
+            const int o = ((s / SPU) * p.GPU + (sub >> p.gshift)) * 256;
+            dst[j] = __builtin_bit_cast(half8_t, __builtin_amdgcn_raw_buffer_load_b128(s_rsrc, o + i16 * 16, 0, 0));
+        }
     };
 
     uint32_t w[2][4][WR];
-    half8_t sc[2];
+    half8_t sc[2][SR];
     __builtin_amdgcn_sched_barrier(0);
     load_x(0);
     load_codes(w[0], 0);
@@ -203,10 +212,20 @@ __global__ void __launch_bounds__(512) gemm_prompt_kernel(CG_HEAD_PARAMS, const 
             return *reinterpret_cast<const lds_half8*>(static_cast<uintptr_t>(__builtin_amdgcn_perm(w0, base[c], sel)));
         }
     };
-    // x operand of (tile nt, round j): chunk 4 q + j of batch row 16 nt + i16
+    auto add_scaled = [&](const half8_t& scales) {
+#pragma unroll
+        for (int u = 0; u < 8; ++u) {
+            const float f = (float)scales[u];
+#pragma unroll
+            for (int nt = 0; nt < NT; ++nt)
+#pragma unroll
+                for (int e = 0; e < 4; ++e) sum[GS ? nt : 0][GS ? u : 0][e] = __builtin_fmaf(f, acc[nt][u][e], sum[GS ? nt : 0][GS ? u : 0][e]);
+        }
+    };
+    // x operand of (tile nt, round j): chunk 4 q + j (GS = 2: 4 j + q) of batch row 16 nt + i16
     const uint32_t xrd = xbase + (uint32_t)(i16 * 256);
     auto x_operand = [&](int s, int nt, int j) -> half8_t {
-        return *reinterpret_cast<const lds_half8*>(static_cast<uintptr_t>(xrd + (uint32_t)((s & 1) * (BT * 256) + nt * 4096) + (uint32_t)(((4 * q + j) ^ i16) * 16)));
+        return *reinterpret_cast<const lds_half8*>(static_cast<uintptr_t>(xrd + (uint32_t)((s & 1) * (BT * 256) + nt * 4096) + (uint32_t)(((GS == 2 ? 4 * j + q : 4 * q + j) ^ i16) * 16)));
     };
 
     __syncthreads();
@@ -232,7 +251,7 @@ __global__ void __launch_bounds__(512) gemm_prompt_kernel(CG_HEAD_PARAMS, const 
                     for (int u = 0; u < 8; ++u) {
 #pragma unroll
                         for (int nt = 0; nt < NT; ++nt)
-                            acc[nt][u] = __builtin_amdgcn_mfma_f32_16x16x32_f16(xv[nt], a[u], (GS && k == 0) ? float4_t{} : acc[nt][u], 0, 0, 0);
+                            acc[nt][u] = __builtin_amdgcn_mfma_f32_16x16x32_f16(xv[nt], a[u], (GS == 1 && k == 0) || (GS == 2 && k % M == 0) ? float4_t{} : acc[nt][u], 0, 0, 0);
                         __builtin_amdgcn_sched_barrier(0);         // the lookup after its operand's last use: no second set of registers
                         a[u] = k + 1 < NSB ? fetch(w[d], k + 1, u) : fetch(w[d ^ 1], 0, u);
                     }
@@ -240,17 +259,11 @@ __global__ void __launch_bounds__(512) gemm_prompt_kernel(CG_HEAD_PARAMS, const 
 #pragma unroll
                         for (int nt = 0; nt < NT; ++nt) xv[nt] = x_operand(s, nt, j + 1);
                     }
-                }
-                if constexpr (GS) {
-#pragma unroll
-                    for (int u = 0; u < 8; ++u) {
-                        const float f = (float)sc[d][u];
-#pragma unroll
-                        for (int nt = 0; nt < NT; ++nt)
-#pragma unroll
-                            for (int e = 0; e < 4; ++e) sum[nt][u][e] = __builtin_fmaf(f, acc[nt][u][e], sum[nt][u][e]);
+                    if constexpr (GS == 2) {
+                        if (k % M == M - 1) add_scaled(sc[d][j]);
                     }
                 }
+                if constexpr (GS == 1) add_scaled(sc[d][0]);
             }
             load_codes(w[d], s + 2);
             if constexpr (GS) load_scales(sc[d], s + 2);
@@ -309,7 +322,7 @@ __global__ void __launch_bounds__(512) gemm_prompt_kernel(CG_HEAD_PARAMS, const 
         }
 }
 
-template <int M, int V, int NT, bool GS>
+template <int M, int V, int NT, int GS>
 int launch_gemm_prompt_one(const Geometry& g, const GemmParams& p, hipStream_t stream)
 {
     auto fn = gemm_prompt_kernel<M, V, NT, GS>;
@@ -322,23 +335,32 @@ int launch_gemm_prompt_one(const Geometry& g, const GemmParams& p, hipStream_t s
     return hipGetLastError() == hipSuccess ? CODEGEMM_OK : CODEGEMM_LAUNCH_FAILED;
 }
 
-template <int M, int V, bool GS>
+template <int M, int V, int GS>
 int launch_gemm_centroid_mv(const Geometry& g, const GemmParams& p, hipStream_t stream)
 {
     if constexpr (V < 16) {
         if (g.prompt) {
-            return launch_gemm_prompt_one<M, V, prompt_tiles(M, V, GS), GS>(g, p, stream);
+            return launch_gemm_prompt_one<M, V, prompt_tiles(M, V, GS != 0), GS>(g, p, stream);
         }
     }
     return launch_gemm_centroid_v<M, V, GS>(g, p, stream);
 }
 
+template <int M, int V>
+int launch_gemm_centroid_mg(const Geometry& g, const GemmParams& p, hipStream_t stream)
+{
+    if (g.g < 0) return launch_gemm_centroid_mv<M, V, 0>(g, p, stream);
+    // a step, 16 chunks, is 16 sub-vectors (32 for v = 4)
+    if (g.gshift >= (V == 4 ? 5 : 4)) return launch_gemm_centroid_mv<M, V, 1>(g, p, stream);
+    return launch_gemm_centroid_mv<M, V, 2>(g, p, stream);
+}
+
 template <int M>
 int launch_gemm_centroid_m(const Geometry& g, const GemmParams& p, hipStream_t stream)
 {
-    if (g.v == 16) return g.g > 0 ? launch_gemm_centroid_mv<M, 16, true>(g, p, stream) : launch_gemm_centroid_mv<M, 16, false>(g, p, stream);
-    if (g.v == 8) return g.g > 0 ? launch_gemm_centroid_mv<M, 8, true>(g, p, stream) : launch_gemm_centroid_mv<M, 8, false>(g, p, stream);
-    if constexpr (M <= 2) return g.g > 0 ? launch_gemm_centroid_mv<M, 4, true>(g, p, stream) : launch_gemm_centroid_mv<M, 4, false>(g, p, stream);
+    if (g.v == 16) return launch_gemm_centroid_mg<M, 16>(g, p, stream);
+    if (g.v == 8) return launch_gemm_centroid_mg<M, 8>(g, p, stream);
+    if constexpr (M <= 2) return launch_gemm_centroid_mg<M, 4>(g, p, stream);
     return CODEGEMM_UNSUPPORTED;
 }
 

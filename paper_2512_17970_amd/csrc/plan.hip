@@ -26,12 +26,12 @@ static int validate_desc(const codegemm_desc* d)
     return CODEGEMM_OK;
 }
 
-// Formats the centroid kernel takes: a group of scales covers at least one of its steps (16 sub-vectors, 32
-// for v = 4), and the codes of a step fit in registers.
+// Formats the centroid kernel takes: a group of scales covers at least what one MFMA contracts over (4 chunks: 4
+// sub-vectors, 8 for v = 4), and the codes of a step fit in registers.
 static bool centroid_format(const codegemm_desc* d)
 {
     if (d->vec_len == 4 && d->num_codebooks > 2) return false;
-    return d->group_size == -1 || d->group_size >= (d->vec_len == 4 ? 32 : 16) * d->vec_len;
+    return d->group_size == -1 || d->group_size >= (d->vec_len == 4 ? 8 : 4) * d->vec_len;
 }
 
 // Batch rows of a workgroup of the centroid kernel whose blocks have `rows` rows.  A wavefront owns 32, 64 or 128
@@ -44,9 +44,17 @@ static int centroid_batch(const codegemm_desc* d, int rows)
     const bool two = d->group_size == -1 && ((d->vec_len == 8 && d->num_codebooks <= 2) || (d->vec_len == 4 && d->num_codebooks == 1));
     return b > 16 && rows == 128 && two ? 32 : 16;
 }
+// Groups shorter than a step of the kernels (16 chunks) flush their sums inside it, with more registers.
+static bool short_groups(const codegemm_desc* d)
+{
+    return d->group_size > 0 && d->group_size < (d->vec_len == 4 ? 32 : 16) * d->vec_len;
+}
 static int centroid_min_rows(const codegemm_desc* d)
 {
-    if (d->vec_len < 16) return d->batch > 8 && d->group_size > 0 && d->num_codebooks > 1 ? 64 : 32;   // (registers)
+    if (d->vec_len < 16) {
+        if (d->batch <= 8 || d->group_size < 0 || d->num_codebooks == 1) return 32;
+        return short_groups(d) ? 128 : 64;                                                     // registers
+    }
     return d->batch <= 4 ? 32 : d->batch <= 8 ? 64 : 128;      // v = 16: one MFMA per lookup (registers)
 }
 
@@ -236,11 +244,19 @@ static void choose_psumbook_plan(const codegemm_desc* d, codegemm_plan* p)
 //  * one: where 32-row blocks fill half of the chip and its lookups, four times the LDS bytes of the Psumbook's, are not
 //    what bounds the call: v4 m1 g128 4096^2 5.9/5.3, 28672->8192 21.9/15.7 (its centroids are the shortest); v8 m2
 //    4096^2 5.5/4.9, 4096->14336 7.9/7.0, 8192^2 8.0/7.7, but 8192->28672 15.7/17.4, 2048^2 4.8/4.9; three codebooks
-//    (8192^2 10.3/10.6) and v = 16 (4096^2 5.4/7.1) lose.
+//    (8192^2 10.3/10.6) and v = 16 (4096^2 5.4/7.1) lose;
+//  * groups shorter than a step cost a flush inside it (v8 m2 g32, batch 2 / 4 / 8 / 16 / 32: 4096^2 7.7/6.0, 9.1/6.3,
+//    12.3/7.3, 15.0/12.2, 21.3/12.8; 8192^2 12.2/9.1, 15.7/9.2, 22.1/12.5, 34/15, 63/21; at 512 297/61 and 871/242).
+//    With several codebooks only 128-row blocks are left from nine rows on, too few of them on small matrices (2048^2,
+//    batch 16: 8.7/10.3), and v = 16 loses at two rows (m3 g64: 4096^2 7.5/8.5, 8192^2 10.4/12.4).
 static bool prefer_centroid(const codegemm_desc* d)
 {
     if (!centroid_format(d) || d->out_features > 65535 * 128) return false;     // grid.y
     const long long codes = (long long)d->num_codebooks * d->out_features * (d->in_features / d->vec_len);
+    if (short_groups(d)) {
+        if (d->batch > 8 && d->batch <= kBatchPerLaunch && d->num_codebooks > 1 && codes < 2500000) return false;
+        if (d->vec_len == 16 && d->batch == 2 && d->num_codebooks > 2) return false;
+    }
     if (d->batch > 1) return d->vec_len < 16 || d->batch <= 8 || d->batch > kBatchPerLaunch || codes >= (d->batch <= 16 ? 6000000 : 4000000);
     if (d->num_codebooks > 2 || d->vec_len == 16) return false;
     if (d->vec_len == 4 && d->num_codebooks == 1) return d->out_features >= 4096 || d->in_features >= 8192;
@@ -269,7 +285,7 @@ static void choose_plan(const codegemm_desc* d, codegemm_plan* p)
     } else {
         const long long low = d->batch <= 16 ? 8500000 : 4300000;
         if (least == 32 && blocks(32) <= (d->batch <= 16 ? 192 : 256) && codes <= low) rows = 32;
-        else if (least <= 64 && blocks(64) <= 256 && (codes <= 8500000 || (d->batch <= 16 && codes <= 16000000 && blocks(64) >= 96))) rows = 64;
+        else if (least <= 64 && !short_groups(d) && blocks(64) <= 256 && (codes <= 8500000 || (d->batch <= 16 && codes <= 16000000 && blocks(64) >= 96))) rows = 64;
     }
     // K ranges.  Up to 4 batch rows: 128 workgroups, 256 when that leaves each 48 units or more (14336->4096 v8 m2: two
     // ranges 7.4, one 8+; 4096^2: one 4.9, two 5.4).  More: 256 as long as every wavefront keeps a step (4096^2 at batch

@@ -19,8 +19,10 @@ def test_offered_and_refused():
             assert ws(cg.Desc.make(B, 4096, 1000, 8, 2), rows, 1) > 0
             assert (ws(cg.Desc.make(B, 4096, 1000, 16, 2), rows, 1) > 0) == (rows >= (64 if B <= 8 else 128))
             assert (ws(cg.Desc.make(B, 4096, 1000, 8, 2, g=128), rows, 1) > 0) == (rows >= (32 if B <= 8 else 64))
+            assert (ws(cg.Desc.make(B, 4096, 1000, 8, 2, g=64), rows, 1) > 0) == (rows >= (32 if B <= 8 else 128))
             assert ws(cg.Desc.make(B, 4096, 1000, 4, 1, g=128), rows, 1) > 0
-    for v, m, g, ok in ((8, 2, 128, True), (8, 2, 64, False), (4, 1, 128, True), (4, 1, 64, False), (16, 2, 256, True), (16, 2, 128, False),
+            assert ws(cg.Desc.make(B, 4096, 1000, 4, 1, g=32), rows, 1) > 0
+    for v, m, g, ok in ((8, 2, 128, True), (8, 2, 32, True), (8, 2, 16, False), (4, 1, 32, True), (4, 1, 16, False), (16, 2, 64, True), (16, 2, 32, False),
                         (4, 2, -1, True), (4, 3, -1, False), (16, 4, -1, True)):
         assert (ws(cg.Desc.make(4, 4096, 1000, v, m, g=g), 128, 1) > 0) == ok, (v, m, g)
     assert ws(cg.Desc.make(2, 512, 65536 * 128, 8, 1), 128, 1) == 0     # more blocks than a grid has
@@ -42,7 +44,9 @@ def test_default_plan_keeps_the_other_kernels_where_they_win():
     assert plan(1, 8192, 28672, 8, 2).centroid_rows == 0 and plan(1, 2048, 2048, 8, 2).centroid_rows == 0
     assert plan(1, 8192, 8192, 16, 4).centroid_rows == 0
     assert (plan(1, 8192, 8192, 8, 2).centroid_rows, plan(1, 8192, 8192, 8, 2).centroid_splits) == (32, 1)
-    assert plan(4, 8192, 8192, 8, 2, 32).centroid_rows == 0             # groups smaller than a step
+    assert plan(4, 8192, 8192, 8, 2, 16).centroid_rows == 0             # groups smaller than an MFMA's contraction
+    assert plan(16, 2048, 2048, 8, 2, 32).centroid_rows == 0 and plan(16, 2048, 2048, 8, 1, 32).centroid_rows != 0
+    assert plan(2, 8192, 8192, 16, 4, 64).centroid_rows == 0 and plan(4, 8192, 8192, 16, 4, 64).centroid_rows != 0
     for B in (2, 8, 32, 500):
         assert plan(B, 8192, 28672, 8, 2).centroid_rows != 0
     assert plan(2, 512, (1 << 24), 8, 1).centroid_rows == 0             # more blocks than a grid has

@@ -16,7 +16,7 @@ from gpu_util import DeviceLayer, Guarded, check_against_oracle, dev, stream  # 
 def least_rows(B, v=8, m=2, g=-1):
     if v == 16:
         return 32 if B <= 4 else 64 if B <= 8 else 128
-    return 64 if B > 8 and g > 0 and m > 1 else 32
+    return 32 if B <= 8 or g < 0 or m == 1 else 64 if g >= 128 else 128
 
 
 def plan_of(case, rows, splits):
@@ -42,7 +42,8 @@ def run(case, rows, splits, y_fp32=False):
 
 
 FORMATS = [(8, 2, -1), (8, 1, -1), (4, 1, -1), (8, 3, -1), (8, 4, -1), (4, 2, -1), (16, 1, -1), (16, 2, -1), (16, 3, -1), (16, 4, -1),
-           (8, 2, 128), (8, 1, 256), (4, 1, 128), (8, 3, 1024), (4, 2, 512), (8, 4, 128), (16, 2, 256), (16, 3, 512), (16, 4, 1024)]
+           (8, 2, 128), (8, 1, 256), (4, 1, 128), (8, 3, 1024), (4, 2, 512), (8, 4, 128), (16, 2, 256), (16, 3, 512), (16, 4, 1024),
+           (8, 2, 64), (8, 2, 32), (8, 1, 32), (8, 3, 64), (8, 4, 32), (4, 1, 64), (4, 1, 32), (4, 2, 32), (16, 1, 128), (16, 2, 64), (16, 4, 64)]
 
 
 @pytest.mark.parametrize("B", [1, 2, 4, 5, 8, 9, 16, 17, 32, 33])
@@ -59,7 +60,7 @@ def test_formats_and_batches(v, m, g, B):
 @pytest.mark.parametrize("rows", [32, 64, 128])
 @pytest.mark.parametrize("splits", [1, 2, 4, 5])
 @pytest.mark.parametrize("B", [1, 3, 7, 13, 21, 40])
-@pytest.mark.parametrize("v,m,g", [(8, 2, -1), (8, 1, -1), (4, 1, 128), (4, 2, -1), (16, 4, -1), (8, 3, 128), (8, 4, -1)])
+@pytest.mark.parametrize("v,m,g", [(8, 2, -1), (8, 1, -1), (4, 1, 128), (4, 2, -1), (16, 4, -1), (8, 3, 128), (8, 4, -1), (8, 2, 32), (8, 1, 64), (4, 1, 32)])
 def test_block_heights(v, m, g, B, splits, rows):
     """Blocks of 32 and 64 rows (the batches that have them), ragged at either end of a granule; pairwise words and
     tickets between the K ranges."""
@@ -111,7 +112,7 @@ def test_non_finite_activations_stay_in_their_row(B, row):
 
 
 @pytest.mark.parametrize("B,rows,splits,g", [(1, 32, 1, -1), (1, 64, 2, 128), (4, 32, 3, -1), (8, 64, 4, -1), (6, 32, 1, 128),
-                                             (16, 128, 2, 128), (16, 32, 2, -1), (13, 64, 1, 128), (32, 128, 5, -1), (32, 64, 2, -1)])
+                                             (16, 128, 2, 128), (16, 32, 2, -1), (3, 32, 1, 32), (11, 128, 2, 64), (13, 64, 1, 128), (32, 128, 5, -1), (32, 64, 2, -1)])
 def test_grouped_members_equal_their_single_calls(B, rows, splits, g):
     K, Ns = 2048, [300, 130, 65]
     desc = cg.Desc.make(B, K, sum(Ns), 8, 2, g=g)

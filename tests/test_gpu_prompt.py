@@ -20,7 +20,7 @@ def batch_for(v, m, g, N, extra):
 
 
 @pytest.mark.parametrize("N,extra", [(1031, 1), (2048, 33), (3000, 32)])
-@pytest.mark.parametrize("v,m,g", [(8, 2, -1), (8, 1, -1), (4, 1, -1), (8, 3, -1), (8, 4, -1), (4, 2, -1), (8, 2, 128), (8, 1, 512), (4, 1, 128), (4, 2, 256)])
+@pytest.mark.parametrize("v,m,g", [(8, 2, -1), (8, 1, -1), (4, 1, -1), (8, 3, -1), (8, 4, -1), (4, 2, -1), (8, 2, 128), (8, 1, 512), (4, 1, 128), (4, 2, 256), (8, 2, 32), (8, 1, 64), (4, 1, 32), (8, 3, 64), (4, 2, 64)])
 def test_formats(v, m, g, N, extra):
     """K of one to three units with an odd number of steps or a ragged last one; N that 8, 128 or 1024 does not divide
     (scalar and vector stores of y), both output types."""
