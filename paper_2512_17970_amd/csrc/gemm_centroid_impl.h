@@ -90,7 +90,15 @@ __device__ __forceinline__ void row_exchange(uint32_t& a, uint32_t& b)
 // NT: tiles of batch rows.  RW x KW wavefronts: RW blocks of 128 / SB rows, KW slices of K.  D: steps in the load
 // ring.  GS: 0 one scale per row; 1 group scales, a step (16 chunks) lies in one group; 2 groups of 4 or 8 chunks (a
 // chunk is a sub-vector, two for v = 4): every MFMA then contracts over 4 neighbouring chunks instead of chunks 4 apart,
-// and sums are scaled after every round.  ONE (SB = 4): one batch row, for which the result elements are arranged so that a lane has one that means something instead of one of four.
+// and sums are scaled after every round; 3 one scale per row, short chains of sums.  ONE (SB = 4): one batch row, for
+// which the result elements are arranged so that a lane has one that means something instead of one of four.
+//
+// GS = 3 is for fp32 output.  Every MFMA on an accumulator rounds it, and a wavefront's share of K is hundreds of them in
+// a row: against 64 bits, up to three times the error of the Psumbook kernels (relative 2-norm, 1e-7: 14336->4096
+// v8 m2 batch 2 1.60 against 1.18, batch 512 3.85 against 1.33), which is lost in the rounding of fp16 output (2.1e-4) but
+// not here.  So MFMAs start from zero, their results are added by the vector units one MFMA later, when they are there,
+// and tiles are added to sums in intervals: 1.08 and 1.12.  It costs 15 to 25 % (8192^2 v8 m2 batch 4 8.3 -> 9.9 us), so
+// fp16 output does without.  Group scales with fp32 output take GS = 2, whose chains are one round long.
 template <int M, int V, int SB, int NT, int RW, int KW, int D, int GS, bool ONE>
 __global__ void __launch_bounds__(RW * KW * 64) gemm_centroid_kernel(CG_HEAD_PARAMS, const GemmParams pk)
 {
@@ -110,8 +118,12 @@ __global__ void __launch_bounds__(RW * KW * 64) gemm_centroid_kernel(CG_HEAD_PAR
     constexpr int WR = PW / 2 * M;                     // .. of all parts
     constexpr int CHUNK = V == 16 ? 16 : 8;            // elements of x per chunk
     constexpr int kUnitBytes = kGranuleRows * kSlots * M;
+    constexpr bool SCALED = GS == 1 || GS == 2;
+    // sums beside the result tiles; GS = 3 adds the tiles to them in intervals, where registers allow it
+    constexpr bool SUMS = SCALED || (GS == 3 && (NT * 4 / SB <= 2 || (SB == 1 && NT == 1)));
     constexpr int kOutOfRange = 0x7ffffff0;
     constexpr uint32_t kRsrcFlags = 0x00020000u;
+    static_assert((KW & (KW - 1)) == 0, "slices are added in pairs");
     static_assert(RB <= kGranuleRows, "rows of a workgroup lie in one granule");
 
     extern __shared__ __align__(16) unsigned char smem[];
@@ -285,7 +297,7 @@ __global__ void __launch_bounds__(RW * KW * 64) gemm_centroid_kernel(CG_HEAD_PAR
     };
     // group scales of the lane's octet for the group of step s
     __amdgpu_buffer_rsrc_t s_rsrc;
-    if constexpr (GS) {
+    if constexpr (SCALED) {
         const uint8_t* base = mm.gscales + ((size_t)min(gr, mm.NGR - 1) * p.NKT + kt0) * p.GPU * 256;
         s_rsrc = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint8_t*>(base), 0, gr < mm.NGR ? nq * p.GPU * 256 : 0, kRsrcFlags);
     }
@@ -303,13 +315,13 @@ __global__ void __launch_bounds__(RW * KW * 64) gemm_centroid_kernel(CG_HEAD_PAR
 
     half8_t xr[D][NT][R][HALVES];
     uint32_t w[D][R][WR];
-    half8_t sc[GS ? D : 1][SR];
+    half8_t sc[SCALED ? D : 1][SR];
     __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
     for (int d = 0; d < D; ++d) {
         load_codes(w[d], s_beg + d);
         load_x(xr[d], s_beg + d);
-        if constexpr (GS) load_scales(sc[d], s_beg + d);
+        if constexpr (SCALED) load_scales(sc[d], s_beg + d);
     }
     __builtin_amdgcn_sched_barrier(0);
 
@@ -336,13 +348,13 @@ __global__ void __launch_bounds__(RW * KW * 64) gemm_centroid_kernel(CG_HEAD_PAR
     // mean something beside them.
     float4_t acc[NT][8];
     constexpr int TL = 4 / SB;                         // batch rows of a lane per tile
-    float sum[GS ? NT : 1][8][GS ? TL : 1];
+    float sum[SUMS ? NT : 1][8][SUMS ? TL : 1];
 #pragma unroll
     for (int nt = 0; nt < NT; ++nt)
 #pragma unroll
         for (int u = 0; u < 8; ++u) {
             acc[nt][u] = float4_t{0.0f, 0.0f, 0.0f, 0.0f};
-            if constexpr (GS) {
+            if constexpr (SUMS) {
 #pragma unroll
                 for (int t = 0; t < TL; ++t) sum[nt][u][t] = 0.0f;
             }
@@ -394,8 +406,19 @@ __global__ void __launch_bounds__(RW * KW * 64) gemm_centroid_kernel(CG_HEAD_PAR
 #pragma unroll
             for (int nt = 0; nt < NT; ++nt)
 #pragma unroll
-                for (int t = 0; t < TL; ++t) sum[GS ? nt : 0][u][GS ? t : 0] = __builtin_fmaf(f, own(acc[nt][u], t), sum[GS ? nt : 0][u][GS ? t : 0]);
+                for (int t = 0; t < TL; ++t) sum[SCALED ? nt : 0][u][SCALED ? t : 0] = __builtin_fmaf(f, own(acc[nt][u], t), sum[SCALED ? nt : 0][u][SCALED ? t : 0]);
         }
+    };
+
+    auto add_up = [&]() {
+#pragma unroll
+        for (int nt = 0; nt < NT; ++nt)
+#pragma unroll
+            for (int u = 0; u < 8; ++u) {
+#pragma unroll
+                for (int t = 0; t < TL; ++t) sum[SUMS ? nt : 0][u][SUMS ? t : 0] += own(acc[nt][u], t);
+                acc[nt][u] = float4_t{0.0f, 0.0f, 0.0f, 0.0f};
+            }
     };
 
     __syncthreads();
@@ -403,6 +426,9 @@ __global__ void __launch_bounds__(RW * KW * 64) gemm_centroid_kernel(CG_HEAD_PAR
     // Main loop.  Every MFMA is followed by the lookup that takes its operand's registers, for the same u
     // of the next (round, half, codebook): eight lookups are in flight while the matrix cores work.
     half8_t a[8];
+    float4_t one[NT], late[NT];                        // GS = 3
+#pragma unroll
+    for (int nt = 0; nt < NT; ++nt) late[nt] = float4_t{0.0f, 0.0f, 0.0f, 0.0f};
     turn_codes(w[0]);
 #pragma unroll
     for (int u = 0; u < 8; ++u) a[u] = fetch(w[0], 0, u);
@@ -420,9 +446,18 @@ __global__ void __launch_bounds__(RW * KW * 64) gemm_centroid_kernel(CG_HEAD_PAR
 #pragma unroll
                         for (int nt = 0; nt < NT; ++nt) {
                             const half8_t xv = xr[d][nt][k / (M * HALVES)][(k / M) % HALVES];
-                            acc[nt][u] = __builtin_amdgcn_mfma_f32_16x16x32_f16(xv, a[u], (GS == 1 && k == 0) || (GS == 2 && k % (M * HALVES) == 0) ? float4_t{} : acc[nt][u], 0, 0, 0);
+                            if constexpr (GS == 3) one[nt] = __builtin_amdgcn_mfma_f32_16x16x32_f16(xv, a[u], float4_t{}, 0, 0, 0);
+                            else acc[nt][u] = __builtin_amdgcn_mfma_f32_16x16x32_f16(xv, a[u], (GS == 1 && k == 0) || (GS == 2 && k % (M * HALVES) == 0) ? float4_t{} : acc[nt][u], 0, 0, 0);
                         }
                         __builtin_amdgcn_sched_barrier(0);         // the lookup after its operand's last use: no second set of registers
+                        if constexpr (GS == 3) {                   // the result before this one, which is there by now
+#pragma unroll
+                            for (int nt = 0; nt < NT; ++nt) {
+                                acc[nt][(u + 7) % 8] += late[nt];
+                                asm volatile("" : "+v"(acc[nt][(u + 7) % 8]));     // here: the compiler would keep the results and add them all later
+                                late[nt] = one[nt];
+                            }
+                        }
                         a[u] = k + 1 < NSB ? fetch(w[d], k + 1, u) : fetch(w[(d + 1) % D], 0, u);
                         __builtin_amdgcn_sched_barrier(0);
                     }
@@ -431,11 +466,19 @@ __global__ void __launch_bounds__(RW * KW * 64) gemm_centroid_kernel(CG_HEAD_PAR
                     }
                 }
                 if constexpr (GS == 1) add_scaled(sc[d][0]);
+                if constexpr (SUMS && !SCALED && SB == 1) add_up();
             }
             load_codes(w[d], s + D);
             load_x(xr[d], s + D);
-            if constexpr (GS) load_scales(sc[d], s + D);
+            if constexpr (SCALED) load_scales(sc[d], s + D);
         }
+        if constexpr (SUMS && !SCALED && SB > 1) add_up();
+    }
+
+    if constexpr (GS == 3) {
+#pragma unroll
+        for (int nt = 0; nt < NT; ++nt) acc[nt][7] += late[nt];
+        if constexpr (SUMS) add_up();
     }
 
     // Sum over the wavefronts' K slices, one tile of batch rows at a time: partials in LDS
@@ -456,7 +499,7 @@ __global__ void __launch_bounds__(RW * KW * 64) gemm_centroid_kernel(CG_HEAD_PAR
             float v[8];
 #pragma unroll
             for (int u = 0; u < 8; ++u) {
-                v[u] = GS ? sum[GS ? nt : 0][u][GS ? t : 0] : own(acc[nt][u], t);
+                v[u] = SUMS ? sum[SUMS ? nt : 0][u][SUMS ? t : 0] : own(acc[nt][u], t);
                 if constexpr (SB >= 2 && !ONE) v[u] = dpp_add<0xb1, 0xf>(v[u]);
                 if constexpr (SB == 4 && !ONE) v[u] = dpp_add<0x4e, 0xf>(v[u]);
             }
@@ -470,10 +513,14 @@ __global__ void __launch_bounds__(RW * KW * 64) gemm_centroid_kernel(CG_HEAD_PAR
         __syncthreads();
         for (int o = tid; o < nb * RB; o += THREADS) {
             const int b = o / RB, n = o % RB;
-            float t = parts[b * STRIDE + n];
+            float t[SLICES];                           // added in pairs: fewer roundings on the way of each
 #pragma unroll
-            for (int k = 1; k < SLICES; ++k) t += parts[(k * BPT + b) * STRIDE + n];
-            totals[(BPT * nt + b) * RB + n] = t;
+            for (int k = 0; k < SLICES; ++k) t[k] = parts[(k * BPT + b) * STRIDE + n];
+#pragma unroll
+            for (int w = SLICES / 2; w > 0; w /= 2)
+#pragma unroll
+                for (int k = 0; k < w; ++k) t[k] += t[k + w];
+            totals[(BPT * nt + b) * RB + n] = t[0];
         }
     }
     finish_block<THREADS, BT, RB>(p, mm, totals, flag, tid, blk, ks, b0);
@@ -515,15 +562,15 @@ int launch_gemm_centroid_v(const Geometry& g, const GemmParams& p, hipStream_t s
             break;
         case 16:
             if (g.RB == 128) return launch_gemm_centroid_one<M, V, 1, 1, 1, 8, 2, GS>(g, p, stream);
-            if constexpr (V < 16 && (GS < 2 || M == 1)) {
+            if constexpr (V < 16 && (GS != 2 || M == 1)) {
                 if (g.RB == 64) return launch_gemm_centroid_one<M, V, 2, 2, 1, 8, 2, GS>(g, p, stream);
             }
-            if constexpr (V < 16 && (GS == 0 || M == 1)) {
+            if constexpr (V < 16 && (GS == 0 || GS == 3 || M == 1)) {
                 if (g.RB == 32) return launch_gemm_centroid_one<M, V, 4, 4, 1, 8, 2, GS>(g, p, stream);
             }
             break;
         case 32:
-            if constexpr (!GS && (V == 8 && M <= 2 || V == 4 && M == 1)) return launch_gemm_centroid_one<M, V, 1, 2, 1, 8, 2, GS>(g, p, stream);
+            if constexpr (GS == 0 && (V == 8 && M <= 2 || V == 4 && M == 1)) return launch_gemm_centroid_one<M, V, 1, 2, 1, 8, 2, GS>(g, p, stream);
     }
     return CODEGEMM_UNSUPPORTED;
 }

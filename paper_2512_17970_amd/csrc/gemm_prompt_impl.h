@@ -1,5 +1,5 @@
 // The centroid kernel for prompts: more than 32 batch rows.  Included by gemm_centroid_m1.hip ..
-// gemm_centroid_m4.hip; mapping, table and lookups as in gemm_centroid_impl.h.
+// gemm_centroid_m4.hip; mapping, table, lookups and the kinds of scales (GS) as in gemm_centroid_impl.h.
 //
 // A lookup is paid once per 64 codes whatever the batch, so with NT tiles of 16 batch rows per
 // wavefront the matrix cores take over as the bound (NT = 4: 64 lookups, 256 MFMAs per step and
@@ -8,8 +8,8 @@
 // step (16 chunks of 16 bytes, 128 elements) of 16 NT batch rows, double-buffered, one barrier per
 // step.  Measured: 8192^2 v8 m2 at batch 2048 366 us, 64 launches of 32 rows before 2584 (the two
 // codebooks make it 550 GFLOP of MFMAs: 1.50 PFLOP/s; this instruction alone, in registers, reaches
-// 1.87 on this card); 4096->28672 v4 m1 g128 at batch 500 126 us, 1519 before.  Chunk c of row r lies at column c ^ (r % 16) of its 256-byte row, so that both the stores
-// (16 lanes along a row) and the operand reads (16 lanes down 16 rows) touch 16 different columns.
+// 1.87 on this card); 4096->28672 v4 m1 g128 at batch 500 121 us, 1519 before.  Chunk c of
+// row r lies at column c ^ (r % 16) of its 256-byte row, so that both the stores (16 lanes along a row) and the operand reads (16 lanes down 16 rows) touch 16 different columns.
 #pragma once
 
 #include "gemm_centroid_impl.h"
@@ -31,6 +31,10 @@ __global__ void __launch_bounds__(512) gemm_prompt_kernel(CG_HEAD_PARAMS, const 
     constexpr int BT = 16 * NT;                        // batch rows of the workgroup
     constexpr int XL = BT * 16 / THREADS;              // chunks of x this thread moves per step
     constexpr int kUnitBytes = kGranuleRows * kSlots * M;
+    constexpr bool SCALED = GS == 1 || GS == 2;
+    // GS = 3 adds its tiles to the sums after every step (8192^2 v8 m2, batch 512: 285 us, every eight 295), except for
+    // two codebooks of v = 4, which spill there (537 us, every eight steps 430).
+    constexpr bool SELDOM = V == 4 && M == 2;
     constexpr int kOutOfRange = 0x7ffffff0;
     constexpr uint32_t kRsrcFlags = 0x00020000u;
     static_assert(BT * 16 % THREADS == 0, "whole chunks per thread");
@@ -137,7 +141,7 @@ __global__ void __launch_bounds__(512) gemm_prompt_kernel(CG_HEAD_PARAMS, const 
         }
     };
     __amdgpu_buffer_rsrc_t s_rsrc;
-    if constexpr (GS) {
+    if constexpr (SCALED) {
         const uint8_t* base = mm.gscales + (size_t)min(gr, mm.NGR - 1) * p.NKT * p.GPU * 256;
         s_rsrc = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint8_t*>(base), 0, gr < mm.NGR ? p.NKT * p.GPU * 256 : 0, kRsrcFlags);
     }
@@ -156,9 +160,9 @@ __global__ void __launch_bounds__(512) gemm_prompt_kernel(CG_HEAD_PARAMS, const 
     __builtin_amdgcn_sched_barrier(0);
     load_x(0);
     load_codes(w[0], 0);
-    if constexpr (GS) load_scales(sc[0], 0);
+    if constexpr (SCALED) load_scales(sc[0], 0);
     load_codes(w[1], 1);
-    if constexpr (GS) load_scales(sc[1], 1);
+    if constexpr (SCALED) load_scales(sc[1], 1);
     __builtin_amdgcn_sched_barrier(0);
 
 #pragma unroll
@@ -219,8 +223,17 @@ __global__ void __launch_bounds__(512) gemm_prompt_kernel(CG_HEAD_PARAMS, const 
 #pragma unroll
             for (int nt = 0; nt < NT; ++nt)
 #pragma unroll
-                for (int e = 0; e < 4; ++e) sum[GS ? nt : 0][GS ? u : 0][e] = __builtin_fmaf(f, acc[nt][u][e], sum[GS ? nt : 0][GS ? u : 0][e]);
+                for (int e = 0; e < 4; ++e) sum[SCALED ? nt : 0][SCALED ? u : 0][e] = __builtin_fmaf(f, acc[nt][u][e], sum[SCALED ? nt : 0][SCALED ? u : 0][e]);
         }
+    };
+    auto add_up = [&]() {
+#pragma unroll
+        for (int nt = 0; nt < NT; ++nt)
+#pragma unroll
+            for (int u = 0; u < 8; ++u) {
+                sum[GS ? nt : 0][GS ? u : 0] += acc[nt][u];
+                acc[nt][u] = float4_t{0.0f, 0.0f, 0.0f, 0.0f};
+            }
     };
     // x operand of (tile nt, round j): chunk 4 q + j (GS = 2: 4 j + q) of batch row 16 nt + i16
     const uint32_t xrd = xbase + (uint32_t)(i16 * 256);
@@ -231,6 +244,8 @@ __global__ void __launch_bounds__(512) gemm_prompt_kernel(CG_HEAD_PARAMS, const 
     __syncthreads();
 
     half8_t a[8], xv[NT];
+    static_assert(NT % 2 == 0, "tiles");
+    float4_t late[2] = {float4_t{0.0f, 0.0f, 0.0f, 0.0f}, float4_t{0.0f, 0.0f, 0.0f, 0.0f}};       // GS = 3
     turn_codes(w[0]);
 #pragma unroll
     for (int u = 0; u < 8; ++u) a[u] = fetch(w[0], 0, u);
@@ -250,8 +265,18 @@ __global__ void __launch_bounds__(512) gemm_prompt_kernel(CG_HEAD_PARAMS, const 
 #pragma unroll
                     for (int u = 0; u < 8; ++u) {
 #pragma unroll
-                        for (int nt = 0; nt < NT; ++nt)
-                            acc[nt][u] = __builtin_amdgcn_mfma_f32_16x16x32_f16(xv[nt], a[u], (GS == 1 && k == 0) || (GS == 2 && k % M == 0) ? float4_t{} : acc[nt][u], 0, 0, 0);
+                        for (int nt = 0; nt < NT; ++nt) {
+                            if constexpr (GS == 3) {               // added two instructions later, when it is there
+                                const float4_t one = __builtin_amdgcn_mfma_f32_16x16x32_f16(xv[nt], a[u], float4_t{}, 0, 0, 0);
+                                __builtin_amdgcn_sched_barrier(0);
+                                const int n = (u * NT + nt + 8 * NT - 2) % (8 * NT);
+                                acc[n % NT][n / NT] += late[nt % 2];
+                                asm volatile("" : "+v"(acc[n % NT][n / NT]));      // here: the compiler would keep the results and add them all later
+                                late[nt % 2] = one;
+                            } else {
+                                acc[nt][u] = __builtin_amdgcn_mfma_f32_16x16x32_f16(xv[nt], a[u], (GS == 1 && k == 0) || (GS == 2 && k % M == 0) ? float4_t{} : acc[nt][u], 0, 0, 0);
+                            }
+                        }
                         __builtin_amdgcn_sched_barrier(0);         // the lookup after its operand's last use: no second set of registers
                         a[u] = k + 1 < NSB ? fetch(w[d], k + 1, u) : fetch(w[d ^ 1], 0, u);
                     }
@@ -264,19 +289,29 @@ __global__ void __launch_bounds__(512) gemm_prompt_kernel(CG_HEAD_PARAMS, const 
                     }
                 }
                 if constexpr (GS == 1) add_scaled(sc[d][0]);
+                if constexpr (GS == 3 && !SELDOM) add_up();
             }
             load_codes(w[d], s + 2);
-            if constexpr (GS) load_scales(sc[d], s + 2);
+            if constexpr (SCALED) load_scales(sc[d], s + 2);
             __syncthreads();
 #pragma unroll
             for (int nt = 0; nt < NT; ++nt) xv[nt] = x_operand(s + 1, nt, 0);
         }
+        if constexpr (GS == 3 && SELDOM) {
+            if ((s0 & 6) == 6) add_up();
+        }
+    }
+
+    if constexpr (GS == 3) {
+        acc[NT - 2][7] += late[0];
+        acc[NT - 1][7] += late[1];
+        add_up();
     }
 
     // Lane (i16, q): rows 8 i16 .. + 7 of the granule, batch rows 16 nt + 4 q + e.
     const int n0 = gr * kGranuleRows + i16 * kRowsPerLane;
     float scale[8];
-    if constexpr (GS) {
+    if constexpr (SCALED) {
 #pragma unroll
         for (int u = 0; u < 8; ++u) scale[u] = 1.0f;
     } else {
@@ -349,9 +384,9 @@ int launch_gemm_centroid_mv(const Geometry& g, const GemmParams& p, hipStream_t 
 template <int M, int V>
 int launch_gemm_centroid_mg(const Geometry& g, const GemmParams& p, hipStream_t stream)
 {
-    if (g.g < 0) return launch_gemm_centroid_mv<M, V, 0>(g, p, stream);
+    if (g.g < 0) return p.y_fp32 ? launch_gemm_centroid_mv<M, V, 3>(g, p, stream) : launch_gemm_centroid_mv<M, V, 0>(g, p, stream);
     // a step, 16 chunks, is 16 sub-vectors (32 for v = 4)
-    if (g.gshift >= (V == 4 ? 5 : 4)) return launch_gemm_centroid_mv<M, V, 1>(g, p, stream);
+    if (!p.y_fp32 && g.gshift >= (V == 4 ? 5 : 4)) return launch_gemm_centroid_mv<M, V, 1>(g, p, stream);
     return launch_gemm_centroid_mv<M, V, 2>(g, p, stream);
 }
 

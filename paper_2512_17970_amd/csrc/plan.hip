@@ -41,13 +41,13 @@ static int centroid_batch(const codegemm_desc* d, int rows)
     const int b = d->batch;
     if (b <= 8) return b == 1 ? 1 : b <= 4 ? 4 : 8;
     // two tiles of 16 only where their accumulators leave registers for the codes
-    const bool two = d->group_size == -1 && ((d->vec_len == 8 && d->num_codebooks <= 2) || (d->vec_len == 4 && d->num_codebooks == 1));
+    const bool two = d->group_size == -1 && !(d->flags & CODEGEMM_FLAG_Y_FP32) && ((d->vec_len == 8 && d->num_codebooks <= 2) || (d->vec_len == 4 && d->num_codebooks == 1));
     return b > 16 && rows == 128 && two ? 32 : 16;
 }
 // Groups shorter than a step of the kernels (16 chunks) flush their sums inside it, with more registers.
 static bool short_groups(const codegemm_desc* d)
 {
-    return d->group_size > 0 && d->group_size < (d->vec_len == 4 ? 32 : 16) * d->vec_len;
+    return d->group_size > 0 && (d->group_size < (d->vec_len == 4 ? 32 : 16) * d->vec_len || (d->flags & CODEGEMM_FLAG_Y_FP32));
 }
 static int centroid_min_rows(const codegemm_desc* d)
 {
@@ -243,12 +243,14 @@ static void choose_psumbook_plan(const codegemm_desc* d, codegemm_plan* p)
 //    leave small matrices too few of them (v16 m4 at batch 16: 4096^2 14.8/16.0, 8192^2 31.7/20.6; at 32 19.8/16.6);
 //  * one: where 32-row blocks fill half of the chip and its lookups, four times the LDS bytes of the Psumbook's, are not
 //    what bounds the call: v4 m1 g128 4096^2 5.9/5.3, 28672->8192 21.9/15.7 (its centroids are the shortest); v8 m2
-//    4096^2 5.5/4.9, 4096->14336 7.9/7.0, 8192^2 8.0/7.7, but 8192->28672 15.7/17.4, 2048^2 4.8/4.9; three codebooks
+//    4096^2 5.5/4.9, 4096->14336 7.9/7.0, a tie at 8192^2, but 8192->28672 15.7/17.4, 2048^2 4.8/4.9; three codebooks
 //    (8192^2 10.3/10.6) and v = 16 (4096^2 5.4/7.1) lose;
 //  * groups shorter than a step cost a flush inside it (v8 m2 g32, batch 2 / 4 / 8 / 16 / 32: 4096^2 7.7/6.0, 9.1/6.3,
 //    12.3/7.3, 15.0/12.2, 21.3/12.8; 8192^2 12.2/9.1, 15.7/9.2, 22.1/12.5, 34/15, 63/21; at 512 297/61 and 871/242).
 //    With several codebooks only 128-row blocks are left from nine rows on, too few of them on small matrices (2048^2,
-//    batch 16: 8.7/10.3), and v = 16 loses at two rows (m3 g64: 4096^2 7.5/8.5, 8192^2 10.4/12.4).
+//    batch 16: 8.7/10.3), and v = 16 loses at two rows (m3 g64: 4096^2 7.5/8.5, 8192^2 10.4/12.4);
+//  * fp32 output pays for its short chains of sums: two codebooks at one row (8192^2 7.9/9.3, 4096^2 5.4/5.8) and v = 16 on
+//    small matrices, at two rows or with many codebooks lose (m4 8192^2 batch 2 12.5/16.5, 4 15.0/17.4, 12 31/26).
 static bool prefer_centroid(const codegemm_desc* d)
 {
     if (!centroid_format(d) || d->out_features > 65535 * 128) return false;     // grid.y
@@ -257,10 +259,13 @@ static bool prefer_centroid(const codegemm_desc* d)
         if (d->batch > 8 && d->batch <= kBatchPerLaunch && d->num_codebooks > 1 && codes < 2500000) return false;
         if (d->vec_len == 16 && d->batch == 2 && d->num_codebooks > 2) return false;
     }
+    const bool fp32 = d->flags & CODEGEMM_FLAG_Y_FP32;
+    if (fp32 && d->vec_len == 16 && d->batch <= kBatchPerLaunch && (codes < 6000000 || d->batch == 2 || (d->batch <= 8 && d->num_codebooks > 2))) return false;
     if (d->batch > 1) return d->vec_len < 16 || d->batch <= 8 || d->batch > kBatchPerLaunch || codes >= (d->batch <= 16 ? 6000000 : 4000000);
     if (d->num_codebooks > 2 || d->vec_len == 16) return false;
+    if (fp32 && d->group_size < 0 && d->num_codebooks > 1) return false;
     if (d->vec_len == 4 && d->num_codebooks == 1) return d->out_features >= 4096 || d->in_features >= 8192;
-    return d->out_features >= 4096 && codes * d->vec_len <= (d->group_size > 0 ? 120000000 : 136000000);
+    return d->out_features >= 4096 && codes * d->vec_len <= 120000000;
 }
 
 static void choose_plan(const codegemm_desc* d, codegemm_plan* p)
@@ -352,7 +357,7 @@ int make_geometry(const codegemm_desc* d, const codegemm_plan* plan, Geometry* g
     // The prompt kernel's workgroups take 1024 rows of W and 64 (with group scales 32) batch rows and all of K: worth it
     // once they are enough to fill the chip.
     g->prompt = g->RB && g->B > kBatchPerLaunch && g->v < 16 &&
-                (long long)ceil_div(g->NGR, 8) * ceil_div(g->B, 16 * prompt_tiles(g->m, g->v, d->group_size > 0)) >= 128;
+                (long long)ceil_div(g->NGR, 8) * ceil_div(g->B, 16 * prompt_tiles(g->m, g->v, d->group_size > 0 || (d->flags & CODEGEMM_FLAG_Y_FP32))) >= 128;
     if (g->prompt) g->NKS = 1;
     g->NG = ceil_div(g->B, g->BG);
     g->Npad = g->NGR * kGranuleRows;

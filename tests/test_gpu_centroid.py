@@ -94,6 +94,21 @@ def test_integer_cases_are_exact(B):
         assert np.array_equal(y.cpu().numpy().astype(np.float64), y_ref), (rows, splits)
 
 
+@pytest.mark.parametrize("v,m,g,B,rows", [(8, 2, -1, 3, 128), (8, 2, -1, 7, 64), (8, 3, -1, 40, 128), (4, 1, -1, 64, 128), (16, 2, -1, 12, 128), (8, 2, 512, 20, 128)])
+def test_fp32_output_keeps_chains_of_sums_short(v, m, g, B, rows):
+    """A chain of n roundings to 2^-24 ends with a relative error of 2^-24 sqrt(n / 6) (uniform, partial sums growing as
+    sqrt): 2e-7 for n = 64.  With all of a wavefront's MFMAs on one accumulator (K m / 256, here 224 to 336 over 32
+    products each, which round more than once) 40 rows of this K show 3.8e-7 to 4.7e-7.  With group scales the chains have
+    a sum per round (K / 256: 56), so half of the K."""
+    case = synth.custom_case(28672 if g < 0 else 14336, 256, v, m, B, seed=3250, g=g)
+    inp = synth.generate(case)
+    y_ref, _ = oracle.gemm(inp.x, inp.codes, inp.codebooks, inp.scales)
+    y = DeviceLayer(inp, plan=plan_of(case, rows, 1), y_fp32=True).gemm()
+    torch.cuda.synchronize()
+    err = np.linalg.norm(y.cpu().numpy() - y_ref) / np.linalg.norm(y_ref)
+    assert err < 2e-7, err
+
+
 @pytest.mark.parametrize("B,row", [(3, 1), (6, 4), (13, 0), (20, 19), (70, 33)])
 def test_non_finite_activations_stay_in_their_row(B, row):
     """The batch rows share instructions (and, up to 8 rows, result tiles whose other elements are discarded): an
