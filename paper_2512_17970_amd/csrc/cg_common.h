@@ -27,7 +27,7 @@ constexpr int kCounterAreaWords = 16384;   // 64 KB
 // finds and leaves all zero like the counters.  Calls whose words do not fit use the ticket and the fp32 partials.
 constexpr size_t kPairAreaBytes = 2u << 20;
 constexpr int kMaxLds = 160 * 1024; // LDS per workgroup on gfx950
-constexpr int kBatchPerLaunch = 32;         // batch rows one launch of a gather kernel takes; more rows = more launches
+constexpr int kBatchPerLaunch = 32;         // batch rows one launch of a Psumbook kernel takes; more rows = more launches, or one of the centroid kernel
 constexpr int kMaxBatch = 65535;            // grid limit of the comparator (one grid row per batch row)
 constexpr int kMaxInFeatures = 1 << 22;     // K: a workgroup's code range (K/v/32 units of 4096 m bytes) and a row of
                                             // x stay below 2^31 bytes, which the 32-bit buffer offsets require

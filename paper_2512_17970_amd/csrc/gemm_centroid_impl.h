@@ -96,8 +96,8 @@ __device__ __forceinline__ void row_exchange(uint32_t& a, uint32_t& b)
 // GS = 3 is for fp32 output.  Every MFMA on an accumulator rounds it, and a wavefront's share of K is hundreds of them in
 // a row: against 64 bits, up to three times the error of the Psumbook kernels (relative 2-norm, 1e-7: 14336->4096
 // v8 m2 batch 2 1.60 against 1.18, batch 512 3.85 against 1.33), which is lost in the rounding of fp16 output (2.1e-4) but
-// not here.  So MFMAs start from zero, their results are added by the vector units one MFMA later, when they are there,
-// and tiles are added to sums in intervals: 1.08 and 1.12.  It costs 15 to 25 % (8192^2 v8 m2 batch 4 8.3 -> 9.9 us), so
+// not here.  So a result tile takes at most 4 MFMAs in a row and is then added to sums of its own: 1.14 and 1.37.  It
+// costs 5 to 10 % (8192^2 v8 m2 batch 4 8.3 -> 8.7 us; adding every MFMA's result with vector instructions: 9.9), so
 // fp16 output does without.  Group scales with fp32 output take GS = 2, whose chains are one round long.
 template <int M, int V, int SB, int NT, int RW, int KW, int D, int GS, bool ONE>
 __global__ void __launch_bounds__(RW * KW * 64) gemm_centroid_kernel(CG_HEAD_PARAMS, const GemmParams pk)
@@ -119,8 +119,11 @@ __global__ void __launch_bounds__(RW * KW * 64) gemm_centroid_kernel(CG_HEAD_PAR
     constexpr int CHUNK = V == 16 ? 16 : 8;            // elements of x per chunk
     constexpr int kUnitBytes = kGranuleRows * kSlots * M;
     constexpr bool SCALED = GS == 1 || GS == 2;
-    // sums beside the result tiles; GS = 3 adds the tiles to them in intervals, where registers allow it
-    constexpr bool SUMS = SCALED || (GS == 3 && (NT * 4 / SB <= 2 || (SB == 1 && NT == 1)));
+    // GS = 3: MFMAs in a row on a result tile before it is added to the sums: a divisor of a step's, or several steps'
+    // of the ring
+    constexpr int CHAIN = NSB % 4 == 0 ? 4 : NSB % 3 == 0 ? 3 : NSB == 2 ? (D % 2 ? 2 : 4) : D % 4 == 0 ? 4 : D % 3 == 0 ? 3 : 2;
+    constexpr bool ACROSS = NSB < CHAIN;               // chains reach over several steps
+    static_assert(NSB % CHAIN == 0 || (D * NSB) % CHAIN == 0 && CHAIN % NSB == 0, "chains");
     constexpr int kOutOfRange = 0x7ffffff0;
     constexpr uint32_t kRsrcFlags = 0x00020000u;
     static_assert((KW & (KW - 1)) == 0, "slices are added in pairs");
@@ -348,13 +351,13 @@ __global__ void __launch_bounds__(RW * KW * 64) gemm_centroid_kernel(CG_HEAD_PAR
     // mean something beside them.
     float4_t acc[NT][8];
     constexpr int TL = 4 / SB;                         // batch rows of a lane per tile
-    float sum[SUMS ? NT : 1][8][SUMS ? TL : 1];
+    float sum[GS ? NT : 1][8][GS ? TL : 1];
 #pragma unroll
     for (int nt = 0; nt < NT; ++nt)
 #pragma unroll
         for (int u = 0; u < 8; ++u) {
             acc[nt][u] = float4_t{0.0f, 0.0f, 0.0f, 0.0f};
-            if constexpr (SUMS) {
+            if constexpr (GS) {
 #pragma unroll
                 for (int t = 0; t < TL; ++t) sum[nt][u][t] = 0.0f;
             }
@@ -414,11 +417,9 @@ __global__ void __launch_bounds__(RW * KW * 64) gemm_centroid_kernel(CG_HEAD_PAR
 #pragma unroll
         for (int nt = 0; nt < NT; ++nt)
 #pragma unroll
-            for (int u = 0; u < 8; ++u) {
+            for (int u = 0; u < 8; ++u)
 #pragma unroll
-                for (int t = 0; t < TL; ++t) sum[SUMS ? nt : 0][u][SUMS ? t : 0] += own(acc[nt][u], t);
-                acc[nt][u] = float4_t{0.0f, 0.0f, 0.0f, 0.0f};
-            }
+                for (int t = 0; t < TL; ++t) sum[GS ? nt : 0][u][GS ? t : 0] += own(acc[nt][u], t);
     };
 
     __syncthreads();
@@ -426,9 +427,6 @@ __global__ void __launch_bounds__(RW * KW * 64) gemm_centroid_kernel(CG_HEAD_PAR
     // Main loop.  Every MFMA is followed by the lookup that takes its operand's registers, for the same u
     // of the next (round, half, codebook): eight lookups are in flight while the matrix cores work.
     half8_t a[8];
-    float4_t one[NT], late[NT];                        // GS = 3
-#pragma unroll
-    for (int nt = 0; nt < NT; ++nt) late[nt] = float4_t{0.0f, 0.0f, 0.0f, 0.0f};
     turn_codes(w[0]);
 #pragma unroll
     for (int u = 0; u < 8; ++u) a[u] = fetch(w[0], 0, u);
@@ -446,39 +444,39 @@ __global__ void __launch_bounds__(RW * KW * 64) gemm_centroid_kernel(CG_HEAD_PAR
 #pragma unroll
                         for (int nt = 0; nt < NT; ++nt) {
                             const half8_t xv = xr[d][nt][k / (M * HALVES)][(k / M) % HALVES];
-                            if constexpr (GS == 3) one[nt] = __builtin_amdgcn_mfma_f32_16x16x32_f16(xv, a[u], float4_t{}, 0, 0, 0);
-                            else acc[nt][u] = __builtin_amdgcn_mfma_f32_16x16x32_f16(xv, a[u], (GS == 1 && k == 0) || (GS == 2 && k % (M * HALVES) == 0) ? float4_t{} : acc[nt][u], 0, 0, 0);
+                            acc[nt][u] = __builtin_amdgcn_mfma_f32_16x16x32_f16(xv, a[u], (GS == 1 && k == 0) || (GS == 2 && k % (M * HALVES) == 0) || (GS == 3 && (d * NSB + k) % CHAIN == 0) ? float4_t{} : acc[nt][u], 0, 0, 0);
                         }
                         __builtin_amdgcn_sched_barrier(0);         // the lookup after its operand's last use: no second set of registers
-                        if constexpr (GS == 3) {                   // the result before this one, which is there by now
-#pragma unroll
-                            for (int nt = 0; nt < NT; ++nt) {
-                                acc[nt][(u + 7) % 8] += late[nt];
-                                asm volatile("" : "+v"(acc[nt][(u + 7) % 8]));     // here: the compiler would keep the results and add them all later
-                                late[nt] = one[nt];
-                            }
-                        }
                         a[u] = k + 1 < NSB ? fetch(w[d], k + 1, u) : fetch(w[(d + 1) % D], 0, u);
                         __builtin_amdgcn_sched_barrier(0);
+                    }
+                    if constexpr (GS == 3) {
+                        if (!ACROSS && (d * NSB + k) % CHAIN == CHAIN - 1) add_up();
                     }
                     if constexpr (GS == 2) {
                         if (k % (M * HALVES) == M * HALVES - 1) add_scaled(sc[d][k / (M * HALVES)]);
                     }
                 }
                 if constexpr (GS == 1) add_scaled(sc[d][0]);
-                if constexpr (SUMS && !SCALED && SB == 1) add_up();
+            } else if constexpr (GS == 3 && ACROSS) {
+                // no step: nothing to add where a chain would have started in it
+                bool starts = false;
+#pragma unroll
+                for (int k = 0; k < NSB; ++k) starts |= (d * NSB + k) % CHAIN == 0;
+                if (starts) {
+#pragma unroll
+                    for (int nt = 0; nt < NT; ++nt)
+#pragma unroll
+                        for (int u = 0; u < 8; ++u) acc[nt][u] = float4_t{0.0f, 0.0f, 0.0f, 0.0f};
+                }
+            }
+            if constexpr (GS == 3 && ACROSS) {
+                if (((d + 1) * NSB) % CHAIN == 0) add_up();
             }
             load_codes(w[d], s + D);
             load_x(xr[d], s + D);
             if constexpr (SCALED) load_scales(sc[d], s + D);
         }
-        if constexpr (SUMS && !SCALED && SB > 1) add_up();
-    }
-
-    if constexpr (GS == 3) {
-#pragma unroll
-        for (int nt = 0; nt < NT; ++nt) acc[nt][7] += late[nt];
-        if constexpr (SUMS) add_up();
     }
 
     // Sum over the wavefronts' K slices, one tile of batch rows at a time: partials in LDS
@@ -499,7 +497,7 @@ __global__ void __launch_bounds__(RW * KW * 64) gemm_centroid_kernel(CG_HEAD_PAR
             float v[8];
 #pragma unroll
             for (int u = 0; u < 8; ++u) {
-                v[u] = SUMS ? sum[SUMS ? nt : 0][u][SUMS ? t : 0] : own(acc[nt][u], t);
+                v[u] = GS ? sum[GS ? nt : 0][u][GS ? t : 0] : own(acc[nt][u], t);
                 if constexpr (SB >= 2 && !ONE) v[u] = dpp_add<0xb1, 0xf>(v[u]);
                 if constexpr (SB == 4 && !ONE) v[u] = dpp_add<0x4e, 0xf>(v[u]);
             }
@@ -565,7 +563,7 @@ int launch_gemm_centroid_v(const Geometry& g, const GemmParams& p, hipStream_t s
             if constexpr (V < 16 && (GS != 2 || M == 1)) {
                 if (g.RB == 64) return launch_gemm_centroid_one<M, V, 2, 2, 1, 8, 2, GS>(g, p, stream);
             }
-            if constexpr (V < 16 && (GS == 0 || GS == 3 || M == 1)) {
+            if constexpr (V < 16 && (GS == 0 || M == 1)) {
                 if (g.RB == 32) return launch_gemm_centroid_one<M, V, 4, 4, 1, 8, 2, GS>(g, p, stream);
             }
             break;

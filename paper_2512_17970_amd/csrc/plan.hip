@@ -52,7 +52,8 @@ static bool short_groups(const codegemm_desc* d)
 static int centroid_min_rows(const codegemm_desc* d)
 {
     if (d->vec_len < 16) {
-        if (d->batch <= 8 || d->group_size < 0 || d->num_codebooks == 1) return 32;
+        if (d->batch <= 8 || d->num_codebooks == 1) return 32;
+        if (d->group_size < 0) return d->flags & CODEGEMM_FLAG_Y_FP32 ? 64 : 32;
         return short_groups(d) ? 128 : 64;                                                     // registers
     }
     return d->batch <= 4 ? 32 : d->batch <= 8 ? 64 : 128;      // v = 16: one MFMA per lookup (registers)
@@ -249,8 +250,8 @@ static void choose_psumbook_plan(const codegemm_desc* d, codegemm_plan* p)
 //    12.3/7.3, 15.0/12.2, 21.3/12.8; 8192^2 12.2/9.1, 15.7/9.2, 22.1/12.5, 34/15, 63/21; at 512 297/61 and 871/242).
 //    With several codebooks only 128-row blocks are left from nine rows on, too few of them on small matrices (2048^2,
 //    batch 16: 8.7/10.3), and v = 16 loses at two rows (m3 g64: 4096^2 7.5/8.5, 8192^2 10.4/12.4);
-//  * fp32 output pays for its short chains of sums: two codebooks at one row (8192^2 7.9/9.3, 4096^2 5.4/5.8) and v = 16 on
-//    small matrices, at two rows or with many codebooks lose (m4 8192^2 batch 2 12.5/16.5, 4 15.0/17.4, 12 31/26).
+//  * fp32 output pays for its short chains of sums: v = 16 loses on small matrices, at two rows (m2 8192^2 8.4/9.4) and
+//    with many codebooks, whose sums spill (m4 8192^2, batch 512: 817/936); two codebooks at one row gain nothing.
 static bool prefer_centroid(const codegemm_desc* d)
 {
     if (!centroid_format(d) || d->out_features > 65535 * 128) return false;     // grid.y
@@ -260,7 +261,7 @@ static bool prefer_centroid(const codegemm_desc* d)
         if (d->vec_len == 16 && d->batch == 2 && d->num_codebooks > 2) return false;
     }
     const bool fp32 = d->flags & CODEGEMM_FLAG_Y_FP32;
-    if (fp32 && d->vec_len == 16 && d->batch <= kBatchPerLaunch && (codes < 6000000 || d->batch == 2 || (d->batch <= 8 && d->num_codebooks > 2))) return false;
+    if (fp32 && d->vec_len == 16 && (d->num_codebooks > 3 || (d->batch <= kBatchPerLaunch && (codes < 6000000 || d->batch == 2 || d->num_codebooks > 2)))) return false;
     if (d->batch > 1) return d->vec_len < 16 || d->batch <= 8 || d->batch > kBatchPerLaunch || codes >= (d->batch <= 16 ? 6000000 : 4000000);
     if (d->num_codebooks > 2 || d->vec_len == 16) return false;
     if (fp32 && d->group_size < 0 && d->num_codebooks > 1) return false;

@@ -13,10 +13,10 @@ cg = pytest.importorskip("paper_2512_17970_amd")
 from gpu_util import DeviceLayer, Guarded, check_against_oracle, dev, stream  # noqa: E402
 
 
-def least_rows(B, v=8, m=2, g=-1):
+def least_rows(B, v=8, m=2, g=-1, fp32=False):
     if v == 16:
         return 32 if B <= 4 else 64 if B <= 8 else 128
-    return 32 if B <= 8 or g < 0 or m == 1 else 64 if g >= 128 else 128
+    return 32 if B <= 8 or m == 1 or (g < 0 and not fp32) else 64 if g >= 128 or g < 0 else 128
 
 
 def plan_of(case, rows, splits):
@@ -88,7 +88,7 @@ def test_integer_cases_are_exact(B):
     inp.x = rng.integers(-8, 9, (B, K)).astype(np.float16)
     inp.scales = np.ones(N, np.float16)
     y_ref, _ = oracle.gemm(inp.x, inp.codes, inp.codebooks, inp.scales)
-    for rows, splits in ((128, 1), (128, 3), (least_rows(B), 2)):
+    for rows, splits in ((128, 1), (128, 3), (least_rows(B, fp32=True), 2)):
         y = DeviceLayer(inp, plan=plan_of(inp.case, rows, splits), y_fp32=True).gemm()
         torch.cuda.synchronize()
         assert np.array_equal(y.cpu().numpy().astype(np.float64), y_ref), (rows, splits)
