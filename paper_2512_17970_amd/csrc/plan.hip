@@ -252,16 +252,37 @@ static void choose_psumbook_plan(const codegemm_desc* d, codegemm_plan* p)
 //    batch 16: 8.7/10.3), and v = 16 loses at two rows (m3 g64: 4096^2 7.5/8.5, 8192^2 10.4/12.4);
 //  * fp32 output pays for its short chains of sums: v = 16 loses on small matrices, at two rows (m2 8192^2 8.4/9.4) and
 //    with many codebooks, whose sums spill (m4 8192^2, batch 512: 817/936); two codebooks at one row gain nothing.
+//  * the Psumbook kernels also keep what 26 000 random sizes showed them to win (gains below are Psumbook time / centroid
+//    time, geometric mean): a second, nearly empty round of blocks (more than 256 of 32 rows, or of 64) at one row with
+//    v8 m2 group scales 0.78, v8 m1 0.91, and from two to four rows with v16 m4 0.75 to 0.91; one row, short K with group
+//    scales 0.92; two rows, short K on high matrices 0.88; five to 23 rows with v16 on small matrices 0.76 to 0.97.
 static bool prefer_centroid(const codegemm_desc* d)
 {
     if (!centroid_format(d) || d->out_features > 65535 * 128) return false;     // grid.y
     const long long codes = (long long)d->num_codebooks * d->out_features * (d->in_features / d->vec_len);
     if (short_groups(d)) {
-        if (d->batch > 8 && d->batch <= kBatchPerLaunch && d->num_codebooks > 1 && codes < 2500000) return false;
+        if (d->batch > 8 && d->batch <= kBatchPerLaunch && d->num_codebooks > 1 && codes < 4000000) return false;
         if (d->vec_len == 16 && d->batch == 2 && d->num_codebooks > 2) return false;
     }
     const bool fp32 = d->flags & CODEGEMM_FLAG_Y_FP32;
     if (fp32 && d->vec_len == 16 && (d->num_codebooks > 3 || (d->batch <= kBatchPerLaunch && (codes < 6000000 || d->batch == 2 || d->num_codebooks > 2)))) return false;
+    const int n32 = ceil_div(d->out_features, 32), n64 = ceil_div(d->out_features, 64), v = d->vec_len, m = d->num_codebooks;
+    const bool second = (n32 > 256 && n32 <= 320) || n64 > 256, grouped = d->group_size > 0;
+    if (d->batch == 1) {
+        if (v == 8 && n64 > 256) return false;
+        if (v == 4 && grouped && second && n64 <= 320) return false;
+        if (v == 8 && grouped && second) return false;
+        if (v == 8 && m == 2 && grouped && d->in_features > 8192 && n32 > 128) return false;
+        if (grouped && (v == 8 || n64 > 256) && d->in_features < 1024) return false;
+    } else if (d->batch <= 4) {
+        if (v == 16 && m >= 3 && second) return false;
+        if (d->batch == 2 && v == 8 && m >= 2 && second && (d->in_features < 2048 || (grouped && n64 <= 256))) return false;
+        if (d->batch == 2 && m == 1 && grouped && d->out_features < 2048) return false;
+    } else if (d->batch <= kBatchPerLaunch) {
+        if (v == 16 && m >= 3 && (d->batch <= 8 ? n64 <= 64 : d->batch < 24 && codes < 10000000)) return false;
+        if (d->batch > 8 && v == 8 && m >= 2 && (grouped ? n64 <= 18 : fp32 && n64 < 24)) return false;
+        if (d->batch > 16 && fp32 && d->in_features < 1024) return false;
+    }
     if (d->batch > 1) return d->vec_len < 16 || d->batch <= 8 || d->batch > kBatchPerLaunch || codes >= (d->batch <= 16 ? 6000000 : 4000000);
     if (d->num_codebooks > 2 || d->vec_len == 16) return false;
     if (fp32 && d->group_size < 0 && d->num_codebooks > 1) return false;
