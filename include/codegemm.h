@@ -63,8 +63,9 @@ enum {
 
 /* Problem descriptor (host struct). */
 typedef struct codegemm_desc {
-    int32_t batch;          /* B, 1..65535; more than 32 rows run as several   */
-                            /* launches of up to 32 rows on the same stream    */
+    int32_t batch;          /* B, 1..65535; more than 32 rows are one launch    */
+                            /* of the centroid kernel, or launches of up to 32  */
+                            /* rows of the Psumbook kernels on the same stream  */
     int32_t in_features;    /* K, a positive multiple of vec_len, <= 2^22      */
     int32_t out_features;   /* N, 1..2^24                                      */
     int32_t vec_len;        /* v: 4, 8 or 16                                   */
@@ -113,7 +114,8 @@ typedef struct codegemm_plan {
                             /* the centroid kernel, which multiplies the centroid vectors themselves with  */
                             /* x on the matrix cores (no Psumbook; for batches), in blocks of that many    */
                             /* rows.  The fields above are then only validated; the workspace is sized for */
-                            /* both.  Needs one scale per row or at least 8 sub-vectors per group          */
+                            /* both.  Needs one scale per row or groups of at least 4 sub-vectors (8 for   */
+                            /* v = 4), and for v = 4 at most two codebooks                                 */
     int32_t centroid_splits; /* K ranges of the centroid kernel, >= 1 (clamped like k_splits); 0 when       */
                             /* centroid_rows = 0                                                            */
 } codegemm_plan;
@@ -215,8 +217,8 @@ int codegemm_psumbook_build(const codegemm_desc *desc, const void *x, const void
  * `packed_codes` is the output of codegemm_pack_codes.  `scales` is the
  * canonical [N] array when group_size = -1 and the output of
  * codegemm_pack_scales otherwise.
- * fp16 inputs, fp32 Psumbook (built on the matrix cores: fp16 products are exact
- * in fp32) and fp32 accumulation, y rounded to nearest-even fp16 (or stored as
+ * fp16 inputs, fp32 partial sums of exact fp16 products (a Psumbook, or for most
+ * batches centroids times x on the matrix cores: centroid_rows) and fp32 accumulation, y rounded to nearest-even fp16 (or stored as
  * fp32 under CODEGEMM_FLAG_Y_FP32).  Every sum is taken in a fixed order (also
  * across K ranges), so results are bit-reproducible.
  * `workspace` holds at least codegemm_workspace_bytes() bytes and has been
