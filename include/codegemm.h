@@ -112,12 +112,17 @@ typedef struct codegemm_plan {
                             /* gather and own the workgroup's 448 rows                                    */
     int32_t centroid_rows;  /* 0: the Psumbook kernels, as described by the fields above.  32, 64 or 128: */
                             /* the centroid kernel, which multiplies the centroid vectors themselves with  */
-                            /* x on the matrix cores (no Psumbook; for batches), in blocks of that many    */
-                            /* rows.  The fields above are then only validated; the workspace is sized for */
-                            /* both.  Needs one scale per row or groups of at least 4 sub-vectors (8 for   */
-                            /* v = 4), and for v = 4 at most two codebooks                                 */
-    int32_t centroid_splits; /* K ranges of the centroid kernel, >= 1 (clamped like k_splits); 0 when       */
-                            /* centroid_rows = 0                                                            */
+                            /* x on the matrix cores (no Psumbook; for batches), in blocks of at least     */
+                            /* that many rows: 64 or 128 where the problem's registers (v = 16, or 9 and   */
+                            /* more batch rows with m >= 2 and group scales or fp32 output) or its grid    */
+                            /* (millions of output rows) need higher ones.  The fields above are then only */
+                            /* validated; the workspace is sized for both.  Formats that the centroid      */
+                            /* kernel does not take (groups of fewer than 4 sub-vectors, 8 for v = 4; v = 4 */
+                            /* with three or four codebooks) run the Psumbook kernels as described above,  */
+                            /* so one plan serves every batch size, output type and group size of a layer  */
+    int32_t centroid_splits; /* K ranges of the centroid kernel, >= 1 (clamped like k_splits, and above 32 */
+                            /* batch rows so that the partial sums fit into those of a 32-row call); 0     */
+                            /* when centroid_rows = 0                                                      */
 } codegemm_plan;
 
 enum {

@@ -28,6 +28,8 @@ constexpr int kCounterAreaWords = 16384;   // 64 KB
 constexpr size_t kPairAreaBytes = 2u << 20;
 constexpr int kMaxLds = 160 * 1024; // LDS per workgroup on gfx950
 constexpr int kBatchPerLaunch = 32;         // batch rows one launch of a Psumbook kernel takes; more rows = more launches, or one of the centroid kernel
+constexpr int kMaxGroup = 4;                // layers one grouped launch can hold
+constexpr int kMaxRowBlocks = 65535 - (kMaxGroup - 1);   // of the centroid kernel (grid.y); every further member of a launch may add a ragged block
 constexpr int kMaxBatch = 65535;            // grid limit of the comparator (one grid row per batch row)
 constexpr int kMaxInFeatures = 1 << 22;     // K: a workgroup's code range (K/v/32 units of 4096 m bytes) and a row of
                                             // x stay below 2^31 bytes, which the 32-bit buffer offsets require
@@ -54,7 +56,7 @@ struct Geometry {
     int NBLK;       // row blocks = workgroups along N: NGR over the granules per workgroup, rounded up
     int NKT;        // ceil(J / 32) K tiles
     int NKS;        // workgroups per row block (K ranges)
-    int WKS;        // K ranges the workspace holds partial sums of up to kBatchPerLaunch rows for
+    int WKS;        // K ranges the workspace holds partial sums of up to kBatchPerLaunch rows for; more rows: NKS * B <= WKS * kBatchPerLaunch, or NKS = 1
     int KPW;        // K tiles per workgroup: ceil(NKT / NKS)
     int NG;         // ceil(B / BG) batch groups
     int Npad;       // NGR * 128
@@ -89,6 +91,7 @@ __host__ __device__ inline size_t packed_offset(int c, int n, int j, int m, int 
     return off;
 }
 
+void resolve_centroid(const codegemm_desc* d, long long n, codegemm_plan* p);        // the centroid fields as they hold for n rows of d's format
 int make_geometry(const codegemm_desc* d, const codegemm_plan* plan, Geometry* g);   // status
 size_t workspace_counter_bytes(const Geometry& g);   // the fixed area in front of the partial sums: counters, then pair words
 size_t workspace_need(const Geometry& g);            // bytes of workspace of one launch

@@ -49,8 +49,6 @@
 
 namespace cg {
 
-constexpr int kMaxGroup = 4;     // layers one grouped launch can hold
-
 // What differs between the layers of one launch: a plain call has one member, a grouped call
 // (layers that share x and the format, e.g. the q, k and v projections) up to kMaxGroup, whose
 // row blocks follow each other along grid.y.

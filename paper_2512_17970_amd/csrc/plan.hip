@@ -59,6 +59,25 @@ static int centroid_min_rows(const codegemm_desc* d)
     return d->batch <= 4 ? 32 : d->batch <= 8 ? 64 : 128;      // v = 16: one MFMA per lookup (registers)
 }
 
+// A plan made for one batch, output type or format of a layer serves the others too, as its Psumbook fields do: blocks
+// become as high as this problem's registers and grid ask for, and where the centroid kernel does not take the format
+// the Psumbook fields hold.  K ranges are cut to what the ticket counters and, above kBatchPerLaunch rows, the partial
+// sums of a launch of that many rows have room for.
+void resolve_centroid(const codegemm_desc* d, long long n, codegemm_plan* p)
+{
+    if (p->centroid_rows == 0) return;
+    int rows = p->centroid_rows > centroid_min_rows(d) ? p->centroid_rows : centroid_min_rows(d);
+    auto blocks = [&]() { return (n + rows - 1) / rows; };
+    while (rows < 128 && blocks() > kMaxRowBlocks) rows *= 2;
+    if (!centroid_format(d) || blocks() > kMaxRowBlocks) {
+        p->centroid_rows = p->centroid_splits = 0;
+        return;
+    }
+    p->centroid_rows = rows;
+    const long long groups = ceil_div(d->batch, centroid_batch(d, rows));
+    if ((blocks() + kMaxGroup - 1) * groups > kCounterAreaWords) p->centroid_splits = 1;
+}
+
 static int validate_plan(const codegemm_desc* d, const codegemm_plan* p)
 {
     if (p->waves != 8 && p->waves != 14 && p->waves != 16) return CODEGEMM_UNSUPPORTED;
@@ -75,8 +94,6 @@ static int validate_plan(const codegemm_desc* d, const codegemm_plan* p)
     } else {
         if (p->centroid_rows != 32 && p->centroid_rows != 64 && p->centroid_rows != 128) return CODEGEMM_INVALID_ARG;
         if (p->centroid_splits < 1) return CODEGEMM_INVALID_ARG;
-        if (!centroid_format(d)) return CODEGEMM_UNSUPPORTED;
-        if (p->centroid_rows < centroid_min_rows(d)) return CODEGEMM_UNSUPPORTED;
     }
     if (p->build_waves != 0 && p->build_waves != 2) return CODEGEMM_UNSUPPORTED;
     if (p->build_waves == 2) {
@@ -258,7 +275,7 @@ static void choose_psumbook_plan(const codegemm_desc* d, codegemm_plan* p)
 //    scales 0.92; two rows, short K on high matrices 0.88; five to 23 rows with v16 on small matrices 0.76 to 0.97.
 static bool prefer_centroid(const codegemm_desc* d)
 {
-    if (!centroid_format(d) || d->out_features > 65535 * 128) return false;     // grid.y
+    if (!centroid_format(d) || d->out_features > kMaxRowBlocks * 128) return false;
     const long long codes = (long long)d->num_codebooks * d->out_features * (d->in_features / d->vec_len);
     if (short_groups(d)) {
         if (d->batch > 8 && d->batch <= kBatchPerLaunch && d->num_codebooks > 1 && codes < 4000000) return false;
@@ -347,6 +364,9 @@ int make_geometry(const codegemm_desc* d, const codegemm_plan* plan, Geometry* g
     }
     st = validate_plan(d, plan);
     if (st) return st;
+    codegemm_plan fitted = *plan;
+    resolve_centroid(d, d->out_features, &fitted);
+    plan = &fitted;
     // larger batches run as several launches of the Psumbook kernels, as one of the centroid kernels
     g->B = (d->batch < kBatchPerLaunch || plan->centroid_rows) ? d->batch : kBatchPerLaunch;
     g->K = d->in_features;
@@ -365,17 +385,19 @@ int make_geometry(const codegemm_desc* d, const codegemm_plan* plan, Geometry* g
     // rows per workgroup: 16 per wavefront and row word (32 in the batched kernel)
     g->NBLK = ceil_div(g->NGR * kGranuleRows, g->RPL * (g->NW - g->NB) * (g->BG == 4 ? 32 : 16));
     if (g->RB) g->NBLK = ceil_div(g->N, g->RB);
-    if (g->RB && g->NBLK > 65535) return CODEGEMM_UNSUPPORTED;
     g->NKT = ceil_div(g->J, kSlots);
-    const int want = g->RB ? plan->centroid_splits : plan->k_splits;
-    int nks = want < g->NKT ? want : g->NKT;
-    g->KPW = ceil_div(g->NKT, nks);
-    g->NKS = ceil_div(g->NKT, g->KPW);          // no empty K range
-    g->WKS = g->NKS;
+    auto ranges = [&](int want) {               // no empty K range
+        const int nks = want < g->NKT ? want : g->NKT;
+        return ceil_div(g->NKT, ceil_div(g->NKT, nks));
+    };
+    g->NKS = g->WKS = ranges(plan->k_splits);
     if (g->RB) {                                // workspace as for the Psumbook kernel of the same plan, too
-        const int pks = plan->k_splits < g->NKT ? plan->k_splits : g->NKT;
-        g->WKS = ceil_div(g->NKT, ceil_div(g->NKT, pks));
+        g->NKS = ranges(plan->centroid_splits);
+        if (g->NKS > g->WKS) g->WKS = g->NKS;
+        const int room = kBatchPerLaunch * g->WKS / g->B;
+        if (g->B > kBatchPerLaunch && g->NKS > room) g->NKS = ranges(room > 0 ? room : 1);
     }
+    g->KPW = ceil_div(g->NKT, g->NKS);
     // The prompt kernel's workgroups take 1024 rows of W and 64 (with group scales 32) batch rows and all of K: worth it
     // once they are enough to fill the chip.
     g->prompt = g->RB && g->B > kBatchPerLaunch && g->v < 16 &&
@@ -403,8 +425,7 @@ size_t workspace_counter_bytes(const Geometry&)
 
 size_t workspace_need(const Geometry& g)
 {
-    size_t floats = (size_t)(g.B < kBatchPerLaunch ? g.B : kBatchPerLaunch) * g.WKS * g.Npad;
-    if (g.NKS > 1 && (size_t)g.B * g.NKS * g.Npad > floats) floats = (size_t)g.B * g.NKS * g.Npad;
+    const size_t floats = (size_t)(g.B < kBatchPerLaunch ? g.B : kBatchPerLaunch) * g.WKS * g.Npad;
     return workspace_counter_bytes(g) + floats * sizeof(float);
 }
 

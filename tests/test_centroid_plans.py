@@ -14,18 +14,50 @@ def test_offered_and_refused():
     assert ws(d, 32, 1) > 0 and ws(d, 64, 2) > 0 and ws(d, 128, 1000) > 0
     for rows, splits in ((16, 1), (96, 1), (256, 1), (128, 0), (128, -1), (0, 1), (-128, 1)):
         assert ws(d, rows, splits) == 0
-    for B in (5, 8, 9, 16, 17, 32, 33):                                 # v = 16 and wide group scales: registers
-        for rows in (32, 64, 128):
-            assert ws(cg.Desc.make(B, 4096, 1000, 8, 2), rows, 1) > 0
-            assert (ws(cg.Desc.make(B, 4096, 1000, 16, 2), rows, 1) > 0) == (rows >= (64 if B <= 8 else 128))
-            assert (ws(cg.Desc.make(B, 4096, 1000, 8, 2, g=128), rows, 1) > 0) == (rows >= (32 if B <= 8 else 64))
-            assert (ws(cg.Desc.make(B, 4096, 1000, 8, 2, g=64), rows, 1) > 0) == (rows >= (32 if B <= 8 else 128))
-            assert ws(cg.Desc.make(B, 4096, 1000, 4, 1, g=128), rows, 1) > 0
-            assert ws(cg.Desc.make(B, 4096, 1000, 4, 1, g=32), rows, 1) > 0
-    for v, m, g, ok in ((8, 2, 128, True), (8, 2, 32, True), (8, 2, 16, False), (4, 1, 32, True), (4, 1, 16, False), (16, 2, 64, True), (16, 2, 32, False),
-                        (4, 2, -1, True), (4, 3, -1, False), (16, 4, -1, True)):
-        assert (ws(cg.Desc.make(4, 4096, 1000, v, m, g=g), 128, 1) > 0) == ok, (v, m, g)
-    assert ws(cg.Desc.make(2, 512, 65536 * 128, 8, 1), 128, 1) == 0     # more blocks than a grid has
+    # more blocks than a grid has: the Psumbook fields hold, whose K ranges need more counters than there are here
+    assert ws(cg.Desc.make(2, 512, 65536 * 128, 8, 1), 128, 1) == 0
+    assert ws(cg.Desc.make(2, 512, 65536 * 128, 8, 1), 128, 1, (8, 1, 1, 4)) > 0
+
+
+BATCHES = (1, 2, 4, 5, 8, 9, 16, 17, 32, 33, 64, 500)
+
+
+@pytest.mark.parametrize("v,m", [(8, 2), (8, 1), (8, 3), (8, 4), (4, 1), (4, 2), (4, 3), (16, 1), (16, 2), (16, 4)])
+def test_a_plan_serves_every_batch_output_type_and_group_size(v, m):
+    """A plan chosen for one batch of a layer was always accepted for the others (the Psumbook fields are): blocks grow
+    where 32 rows do not fit, formats without the centroid kernel fall back to the Psumbook fields.  The workspace is that
+    of the Psumbook fields throughout, so it grows with the batch alone and one of the largest batch serves them all."""
+    groups = (-1, 32 * v, 16 * v, 8 * v, 4 * v, 2 * v, v)
+    for K, N in ((32 * v * 20, 1000), (32 * v * 8, 4096), (32 * v * 80, 300)):
+        for g0 in groups[:5]:
+            for B0 in BATCHES:
+                for fp32 in (False, True):
+                    p = cg.codegemm_default_plan(cg.Desc.make(B0, K, N, v, m, y_fp32=fp32, g=g0))
+                    if not p.centroid_rows:
+                        continue
+                    q = cg.Plan.from_buffer_copy(p)
+                    q.centroid_rows = q.centroid_splits = 0
+                    for g in groups:
+                        last = 0
+                        for B in BATCHES:
+                            d = cg.Desc.make(B, K, N, v, m, y_fp32=not fp32, g=g)
+                            need = cg.codegemm_workspace_bytes(d, q)
+                            assert cg.codegemm_workspace_bytes(d, p) == need >= last, (B0, g0, B, g, p)
+                            if need and B <= 32:
+                                assert cg.codegemm_grouped_workspace_bytes(d, p, [N - 100, 70, 30]) == cg.codegemm_grouped_workspace_bytes(d, q, [N - 100, 70, 30]) > 0
+                            last = need
+
+
+def test_plans_of_small_layers_fit_large_ones():
+    """Blocks of 32 rows would be more than a grid has, or than there are ticket counters for several K ranges."""
+    p = cg.codegemm_default_plan(cg.Desc.make(2, 8192, 512, 8, 2))
+    assert p.centroid_rows == 32 and p.centroid_splits > 1
+    p.k_splits = 1
+    for N in (1 << 19, (1 << 19) + 1, 1 << 20, 1 << 22, 1 << 24):
+        d = cg.Desc.make(2, 8192, N, 8, 2)
+        assert cg.codegemm_workspace_bytes(d, p) > 0
+        if N < 1 << 24:                                                # the Psumbook kernels' row blocks of a group end at 65535
+            assert cg.codegemm_grouped_workspace_bytes(d, p, [N - 1000, 900, 99, 1]) > 0
 
 
 @pytest.mark.parametrize("v,m,g", [(8, 2, -1), (4, 1, 128), (8, 1, -1), (8, 3, -1), (16, 4, -1), (8, 2, 128), (8, 2, 32), (4, 4, -1)])

@@ -156,6 +156,26 @@ def test_grouped_members_equal_their_single_calls(B, rows, splits, g):
             assert torch.equal(alone, y)
 
 
+@pytest.mark.parametrize("B0", [1, 3, 12, 200])
+@pytest.mark.parametrize("v,m,g0", [(8, 2, 128), (8, 2, -1), (8, 1, 32), (4, 1, 128), (8, 3, -1), (16, 2, -1), (4, 2, -1)])
+def test_default_plans_at_other_batches(v, m, g0, B0):
+    """The default plan of one batch, kept for other batches, output types and groups of the same layer: blocks that are
+    raised from 32 rows to what those need, formats that fall back to the Psumbook fields, batches above one launch."""
+    K, N = 32 * v * 5, 4100 if B0 == 1 else 700
+    plan = cg.codegemm_default_plan(cg.Desc.make(B0, K, N, v, m, g=g0))
+    if not plan.centroid_rows:
+        pytest.skip("the Psumbook kernels' plan")
+    for B, g, fp32 in ((1, -1, True), (4, g0, True), (9, g0, False), (16, 4 * v, False), (20, -1, True), (33, 8 * v, True), (70, 2 * v, False), (5, v, True), (150, g0, False)):
+        case = synth.custom_case(K, N, v, m, B, seed=3450 + B, g=g)
+        print(f"[kept plan] {case.name} fp32={fp32} {plan}", flush=True)
+        inp = synth.generate(case)
+        y_ref, T = oracle.gemm(inp.x, inp.codes, inp.codebooks, inp.scales)
+        y = DeviceLayer(inp, plan=plan, y_fp32=fp32).gemm()
+        torch.cuda.synchronize()
+        rel = check_against_oracle(y.cpu().numpy(), y_ref, T, case.name)
+        assert rel < (5e-6 if fp32 else 6e-4), rel
+
+
 def test_replays_from_a_hip_graph():
     """Captured calls give the eager bits on every replay, with eager calls on the same workspace in between."""
     layers = [DeviceLayer(synth.generate(synth.custom_case(K, N, 8, 2, B, seed=3500 + B)), plan=None)
