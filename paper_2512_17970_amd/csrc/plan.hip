@@ -61,19 +61,20 @@ static int centroid_min_rows(const codegemm_desc* d)
 
 // A plan made for one batch, output type or format of a layer serves the others too, as its Psumbook fields do: blocks
 // become as high as this problem's registers and grid ask for, and where the centroid kernel does not take the format
-// the Psumbook fields hold.  K ranges are cut to what the ticket counters and, above kBatchPerLaunch rows, the partial
-// sums of a launch of that many rows have room for.
+// the Psumbook fields hold, and so they do for an fp16 Psumbook.  There are no more K ranges than k_splits, and than the
+// ticket counters and, above kBatchPerLaunch rows, the partial sums of a launch of that many rows have room for.
 void resolve_centroid(const codegemm_desc* d, long long n, codegemm_plan* p)
 {
     if (p->centroid_rows == 0) return;
     int rows = p->centroid_rows > centroid_min_rows(d) ? p->centroid_rows : centroid_min_rows(d);
     auto blocks = [&]() { return (n + rows - 1) / rows; };
     while (rows < 128 && blocks() > kMaxRowBlocks) rows *= 2;
-    if (!centroid_format(d) || blocks() > kMaxRowBlocks) {
+    if (!centroid_format(d) || p->psum_dtype == CODEGEMM_PSUM_FP16 || blocks() > kMaxRowBlocks) {
         p->centroid_rows = p->centroid_splits = 0;
         return;
     }
     p->centroid_rows = rows;
+    if (p->centroid_splits > p->k_splits) p->centroid_splits = p->k_splits;
     const long long groups = ceil_div(d->batch, centroid_batch(d, rows));
     if ((blocks() + kMaxGroup - 1) * groups > kCounterAreaWords) p->centroid_splits = 1;
 }
@@ -391,9 +392,8 @@ int make_geometry(const codegemm_desc* d, const codegemm_plan* plan, Geometry* g
         return ceil_div(g->NKT, ceil_div(g->NKT, nks));
     };
     g->NKS = g->WKS = ranges(plan->k_splits);
-    if (g->RB) {                                // workspace as for the Psumbook kernel of the same plan, too
+    if (g->RB) {                                // within the workspace of the Psumbook kernel of the same plan
         g->NKS = ranges(plan->centroid_splits);
-        if (g->NKS > g->WKS) g->WKS = g->NKS;
         const int room = kBatchPerLaunch * g->WKS / g->B;
         if (g->B > kBatchPerLaunch && g->NKS > room) g->NKS = ranges(room > 0 ? room : 1);
     }

@@ -48,6 +48,15 @@ def test_a_plan_serves_every_batch_output_type_and_group_size(v, m):
                             last = need
 
 
+def test_k_splits_bounds_the_workspace_of_an_edited_default_plan():
+    d = cg.Desc.make(2, 4096, 512, 8, 2)
+    p = cg.codegemm_default_plan(d)
+    assert p.centroid_rows and p.centroid_splits > 2
+    for k in (1, 2):
+        p.k_splits = k
+        assert cg.codegemm_workspace_bytes(d, p) == 65536 + (2 << 20) + 2 * k * 512 * 4
+
+
 def test_plans_of_small_layers_fit_large_ones():
     """Blocks of 32 rows would be more than a grid has, or than there are ticket counters for several K ranges."""
     p = cg.codegemm_default_plan(cg.Desc.make(2, 8192, 512, 8, 2))

@@ -22,6 +22,7 @@ def least_rows(B, v=8, m=2, g=-1, fp32=False):
 def plan_of(case, rows, splits):
     p = cg.codegemm_default_plan(cg.Desc.make(case.B, case.K, case.N, case.v, case.m, g=case.g))
     p.centroid_rows, p.centroid_splits = rows, splits
+    p.k_splits = max(p.k_splits, splits)                                # which bounds them
     return p
 
 
@@ -133,6 +134,7 @@ def test_grouped_members_equal_their_single_calls(B, rows, splits, g):
     desc = cg.Desc.make(B, K, sum(Ns), 8, 2, g=g)
     plan = cg.codegemm_default_plan(desc)
     plan.centroid_rows, plan.centroid_splits = rows, splits
+    plan.k_splits = max(plan.k_splits, splits)
     inps = [synth.generate(synth.custom_case(K, n, 8, 2, B, seed=3400 + k, g=g)) for k, n in enumerate(Ns)]
     layers = []
     for inp in inps:
@@ -174,6 +176,22 @@ def test_default_plans_at_other_batches(v, m, g0, B0):
         torch.cuda.synchronize()
         rel = check_against_oracle(y.cpu().numpy(), y_ref, T, case.name)
         assert rel < (5e-6 if fp32 else 6e-4), rel
+
+
+def test_fp16_psumbook_of_a_default_plan():
+    """psum_dtype = 1 on a default plan that has centroid_rows: the fp16 Psumbook, bit for bit that of the same plan
+    without them, and not the centroid kernel's result."""
+    case = synth.custom_case(1024, 4100, 8, 2, 1, seed=3470)
+    inp = synth.generate(case)
+    plans = [cg.codegemm_default_plan(cg.Desc.make(1, case.K, case.N, 8, 2)) for _ in range(3)]
+    assert plans[0].centroid_rows and plans[0].batch_group == 1
+    plans[0].psum_dtype = plans[1].psum_dtype = cg.binding.PSUM_FP16
+    plans[1].centroid_rows = plans[1].centroid_splits = 0
+    ys = []
+    for plan in plans:
+        ys.append(DeviceLayer(inp, plan=plan, y_fp32=True).gemm())
+        torch.cuda.synchronize()
+    assert torch.equal(ys[0], ys[1]) and not torch.equal(ys[0], ys[2])
 
 
 def test_replays_from_a_hip_graph():
