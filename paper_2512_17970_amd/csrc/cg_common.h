@@ -68,10 +68,10 @@ struct Geometry {
 };
 
 // Tiles of 16 batch rows of a workgroup of the prompt kernel: 4 where 128 accumulators per lane leave room for the
-// codes, 2 with sums of their own beside the accumulators (group scales, fp32 output) and for wide codes.
-__host__ __device__ constexpr int prompt_tiles(int m, int v, bool sums)
+// codes, 2 with sums of their own beside the accumulators (group scales) and for wide codes.
+__host__ __device__ constexpr int prompt_tiles(int m, int v, bool grouped)
 {
-    return sums || m >= 3 || (v == 4 && m == 2) ? 2 : 4;
+    return grouped || m >= 3 || (v == 4 && m == 2) ? 2 : 4;
 }
 
 __host__ __device__ inline int ceil_div(int a, int b) { return (a + b - 1) / b; }

@@ -90,15 +90,21 @@ __device__ __forceinline__ void row_exchange(uint32_t& a, uint32_t& b)
 // NT: tiles of batch rows.  RW x KW wavefronts: RW blocks of 128 / SB rows, KW slices of K.  D: steps in the load
 // ring.  GS: 0 one scale per row; 1 group scales, a step (16 chunks) lies in one group; 2 groups of 4 or 8 chunks (a
 // chunk is a sub-vector, two for v = 4): every MFMA then contracts over 4 neighbouring chunks instead of chunks 4 apart,
-// and sums are scaled after every round; 3 one scale per row, short chains of sums.  ONE (SB = 4): one batch row, for
-// which the result elements are arranged so that a lane has one that means something instead of one of four.
+// and sums are scaled after every round; 3 and 4 fp32 output, short chains of sums, with one scale per row and with group
+// scales (chunks as for 2).  ONE (SB = 4): one batch row, for which the result elements are arranged so that a lane has
+// one that means something instead of one of four.
 //
-// GS = 3 is for fp32 output.  Every MFMA on an accumulator rounds it, and a wavefront's share of K is hundreds of them in
-// a row: against 64 bits, up to three times the error of the Psumbook kernels (relative 2-norm, 1e-7: 14336->4096
-// v8 m2 batch 2 1.60 against 1.18, batch 512 3.85 against 1.33), which is lost in the rounding of fp16 output (2.1e-4) but
-// not here.  So a result tile takes at most 4 MFMAs in a row and is then added to sums of its own: 1.14 and 1.37.  It
-// costs 5 to 10 % (8192^2 v8 m2 batch 4 8.3 -> 8.7 us; adding every MFMA's result with vector instructions: 9.9), so
-// fp16 output does without.  Group scales with fp32 output take GS = 2, whose chains are one round long.
+// GS = 3 and 4.  Every MFMA on an accumulator rounds it, and a wavefront's share of K is hundreds of them in a row: up to
+// four times the error of the Psumbook kernels against 64 bits, which is lost in the rounding of fp16 output (2.1e-4) but
+// not here.  Measured on random operands (relative rms, 1e-7): an MFMA of 32 products 0.44, two on one accumulator 0.57,
+// four 0.76; the Psumbook's 8 products 0.31.  The Psumbook kernels spread K over 32 lanes (16 in the batched kernel) and
+// their K ranges, more than the sub-vectors, slices and ranges here, so chains have to be shorter and sums have a second
+// level.  A result tile takes two MFMAs (GS = 4: one, the tiles of a round being added before they are scaled; two above 8
+// batch rows and the whole round for v = 4, whose Psumbook adds twice as often) and is then added to sums of its own, which
+// go to totals after 8 to 12 additions.  Error against that of the Psumbook plan of the same call, fp32 output, geometric
+// mean over some hundred random sizes per format and power of two of K: at most 1.00, 0.4 to 0.9 from K = 4096 on
+// (8192^2, batch 512, 1e-7: v8 m2 1.06 against 1.32, v8 m1 g128 0.95 against 1.24, v8 m2 g32 1.01 against 1.60).  It costs
+// up to 10 % against chains of four (8192^2 v8 m2 batch 4 11.2 -> 11.1 us, 4120->11111 v8 m3 batch 5 16.0 -> 16.9).
 template <int M, int V, int SB, int NT, int RW, int KW, int D, int GS, bool ONE>
 __global__ void __launch_bounds__(RW * KW * 64) gemm_centroid_kernel(CG_HEAD_PARAMS, const GemmParams pk)
 {
@@ -118,12 +124,18 @@ __global__ void __launch_bounds__(RW * KW * 64) gemm_centroid_kernel(CG_HEAD_PAR
     constexpr int WR = PW / 2 * M;                     // .. of all parts
     constexpr int CHUNK = V == 16 ? 16 : 8;            // elements of x per chunk
     constexpr int kUnitBytes = kGranuleRows * kSlots * M;
-    constexpr bool SCALED = GS == 1 || GS == 2;
-    // GS = 3: MFMAs in a row on a result tile before it is added to the sums: a divisor of a step's, or several steps'
-    // of the ring
-    constexpr int CHAIN = NSB % 4 == 0 ? 4 : NSB % 3 == 0 ? 3 : NSB == 2 ? (D % 2 ? 2 : 4) : D % 4 == 0 ? 4 : D % 3 == 0 ? 3 : 2;
-    constexpr bool ACROSS = NSB < CHAIN;               // chains reach over several steps
-    static_assert(NSB % CHAIN == 0 || (D * NSB) % CHAIN == 0 && CHAIN % NSB == 0, "chains");
+    constexpr bool SCALED = GS == 1 || GS == 2 || GS == 4;
+    constexpr bool NEAR = GS == 2 || GS == 4;          // an MFMA contracts over 4 neighbouring chunks
+    constexpr bool SHORT = GS >= 3;
+    constexpr int ROUND = NEAR ? M * HALVES : NSB;     // (half, codebook) of a round, which share a scale
+    // MFMAs in a row on a result tile, before it is added to the sums; the tile starts and ends with them
+    constexpr int LINK = GS == 3 ? 2 : GS == 4 && V > 4 ? (SB > 1 ? 1 : 2) : ROUND;
+    auto starts = [](int k) constexpr -> bool { return GS != 0 && k % ROUND % LINK == 0; };
+    auto ends = [](int k) constexpr -> bool { return GS != 0 && (k % ROUND % LINK == LINK - 1 || k % ROUND == ROUND - 1); };
+    constexpr bool PARTS = GS == 4 && LINK == 1 && ROUND > 1;       // the tiles of a round are added before they are scaled
+    // SHORT: the sums are moved to the totals after 8 to 12 additions: every step, or every few turns of the ring
+    constexpr int ADDS = (NSB / ROUND) * (PARTS ? 1 : (ROUND + LINK - 1) / LINK);            // per step
+    constexpr int TURNS = ADDS >= 8 ? 0 : D * ADDS >= 8 ? 1 : D * ADDS >= 4 ? 2 : 4;
     constexpr int kOutOfRange = 0x7ffffff0;
     constexpr uint32_t kRsrcFlags = 0x00020000u;
     static_assert((KW & (KW - 1)) == 0, "slices are added in pairs");
@@ -150,12 +162,12 @@ __global__ void __launch_bounds__(RW * KW * 64) gemm_centroid_kernel(CG_HEAD_PAR
     // Chunk of load j of a step: the lane's part and the load's (chunk_at(j)).  SB = 1: loads 2 i and 2 i + 1 take the same
     // chunk of two octets (batch rows), exchanged afterwards; GS = 2 moves chunk bits between lanes 16 apart as well.
     auto lane_chunk = [&](int sv) -> int {             // sv: the lane's place along contiguous memory
-        if constexpr (GS == 2) return SB == 1 ? 4 * (q & 1) + 2 * (q >> 1) + sv : 4 * sv + q;
+        if constexpr (NEAR) return SB == 1 ? 4 * (q & 1) + 2 * (q >> 1) + sv : 4 * sv + q;
         else return 4 * q + sv;
     };
     auto chunk_at = [](int j) -> int {
-        if constexpr (SB == 1) return (GS == 2 ? 8 : 2) * (j / 2);
-        else return (GS == 2 ? 4 * SB : SB) * j;
+        if constexpr (SB == 1) return (NEAR ? 8 : 2) * (j / 2);
+        else return (NEAR ? 4 * SB : SB) * j;
     };
 
     // Table entries of this thread, requested first: everything waits for them.
@@ -219,7 +231,7 @@ __global__ void __launch_bounds__(RW * KW * 64) gemm_centroid_kernel(CG_HEAD_PAR
                         for (int k = 0; k < 4; ++k) {
                             uint32_t ak = a[k], bk = b[k];
                             pair_transpose(ak, bk, odd);
-                            if constexpr (GS == 2) row_exchange(ak, bk);
+                            if constexpr (NEAR) row_exchange(ak, bk);
                             a[k] = ak;
                             b[k] = bk;
                         }
@@ -272,7 +284,7 @@ __global__ void __launch_bounds__(RW * KW * 64) gemm_centroid_kernel(CG_HEAD_PAR
 #pragma unroll
                 for (int k = 0; k < WR; ++k) {
                     pair_transpose(cw[j][k], cw[j + 1][k], odd);
-                    if constexpr (GS == 2) row_exchange(cw[j][k], cw[j + 1][k]);
+                    if constexpr (NEAR) row_exchange(cw[j][k], cw[j + 1][k]);
                 }
         }
         if constexpr (T::kOrderBits > 0) {
@@ -304,12 +316,12 @@ __global__ void __launch_bounds__(RW * KW * 64) gemm_centroid_kernel(CG_HEAD_PAR
         const uint8_t* base = mm.gscales + ((size_t)min(gr, mm.NGR - 1) * p.NKT + kt0) * p.GPU * 256;
         s_rsrc = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint8_t*>(base), 0, gr < mm.NGR ? nq * p.GPU * 256 : 0, kRsrcFlags);
     }
-    constexpr int SR = GS == 2 ? R : 1;                // scales per step
+    constexpr int SR = NEAR ? R : 1;                // scales per step
     auto load_scales = [&](half8_t (&dst)[SR], int s) {
 #pragma unroll
         for (int j = 0; j < SR; ++j) {
             // first sub-vector, in its unit, of the chunks that the lane's column contracts over
-            const int chunk = GS == 2 ? (SB == 1 ? 4 * j : chunk_at(j) + 4 * (lane & (SB - 1))) : 0;
+            const int chunk = NEAR ? (SB == 1 ? 4 * j : chunk_at(j) + 4 * (lane & (SB - 1))) : 0;
             const int sub = (s % SPU) * 16 + (V == 4 ? 2 : 1) * chunk;
             const int o = s < s_end ? ((s / SPU) * p.GPU + (sub >> p.gshift)) * 256 : kOutOfRange;
             dst[j] = __builtin_bit_cast(half8_t, __builtin_amdgcn_raw_buffer_load_b128(s_rsrc, o + (oct0 + col_o) * 16, 0, 0));
@@ -347,11 +359,11 @@ __global__ void __launch_bounds__(RW * KW * 64) gemm_centroid_kernel(CG_HEAD_PAR
         }
     }
 
-    // Result tiles; with group scales the tiles of one step, and the scaled sums of the elements that
-    // mean something beside them.
+    // Result tiles; with group scales or fp32 output those of one chain, and the (scaled) sums of the elements
+    // that mean something beside them.
     float4_t acc[NT][8];
     constexpr int TL = 4 / SB;                         // batch rows of a lane per tile
-    float sum[GS ? NT : 1][8][GS ? TL : 1];
+    float sum[GS ? NT : 1][8][GS ? TL : 1], total_of[SHORT ? NT : 1][8][SHORT ? TL : 1], part[PARTS ? NT : 1][8][PARTS ? TL : 1];
 #pragma unroll
     for (int nt = 0; nt < NT; ++nt)
 #pragma unroll
@@ -359,7 +371,10 @@ __global__ void __launch_bounds__(RW * KW * 64) gemm_centroid_kernel(CG_HEAD_PAR
             acc[nt][u] = float4_t{0.0f, 0.0f, 0.0f, 0.0f};
             if constexpr (GS) {
 #pragma unroll
-                for (int t = 0; t < TL; ++t) sum[nt][u][t] = 0.0f;
+                for (int t = 0; t < TL; ++t) {
+                    sum[nt][u][t] = 0.0f;
+                    if constexpr (SHORT) total_of[nt][u][t] = 0.0f;
+                }
             }
         }
     // Batch row t of this lane in a result tile, whose row 4 q + e is batch row 4 q + e for SB = 1; batch row 2 q + e / 2,
@@ -409,17 +424,50 @@ __global__ void __launch_bounds__(RW * KW * 64) gemm_centroid_kernel(CG_HEAD_PAR
 #pragma unroll
             for (int nt = 0; nt < NT; ++nt)
 #pragma unroll
-                for (int t = 0; t < TL; ++t) sum[SCALED ? nt : 0][u][SCALED ? t : 0] = __builtin_fmaf(f, own(acc[nt][u], t), sum[SCALED ? nt : 0][u][SCALED ? t : 0]);
+                for (int t = 0; t < TL; ++t) {
+                    float& x = sum[SCALED ? nt : 0][u][SCALED ? t : 0];
+                    x = __builtin_fmaf(f, PARTS ? part[PARTS ? nt : 0][u][PARTS ? t : 0] : own(acc[nt][u], t), x);
+                    if constexpr (SHORT) asm volatile("" : "+v"(x));
+                }
         }
     };
 
+    auto add_part = [&](bool first) {
+#pragma unroll
+        for (int nt = 0; nt < NT; ++nt)
+#pragma unroll
+            for (int u = 0; u < 8; ++u)
+#pragma unroll
+                for (int t = 0; t < TL; ++t) {
+                    float& x = part[PARTS ? nt : 0][u][PARTS ? t : 0];
+                    const float r = own(acc[nt][u], t);
+                    x = first ? r : x + r;
+                    asm volatile("" : "+v"(x));
+                }
+    };
     auto add_up = [&]() {
 #pragma unroll
         for (int nt = 0; nt < NT; ++nt)
 #pragma unroll
             for (int u = 0; u < 8; ++u)
 #pragma unroll
-                for (int t = 0; t < TL; ++t) sum[GS ? nt : 0][u][GS ? t : 0] += own(acc[nt][u], t);
+                for (int t = 0; t < TL; ++t) {
+                    float& x = sum[GS ? nt : 0][u][GS ? t : 0];
+                    x += own(acc[nt][u], t);
+                    asm volatile("" : "+v"(x));        // here: the compiler would keep the tiles and add them all later
+                }
+    };
+
+    auto move_up = [&]() {
+#pragma unroll
+        for (int nt = 0; nt < NT; ++nt)
+#pragma unroll
+            for (int u = 0; u < 8; ++u)
+#pragma unroll
+                for (int t = 0; t < TL; ++t) {
+                    total_of[SHORT ? nt : 0][u][SHORT ? t : 0] += sum[GS ? nt : 0][u][GS ? t : 0];
+                    sum[GS ? nt : 0][u][GS ? t : 0] = 0.0f;
+                }
     };
 
     __syncthreads();
@@ -430,6 +478,7 @@ __global__ void __launch_bounds__(RW * KW * 64) gemm_centroid_kernel(CG_HEAD_PAR
     turn_codes(w[0]);
 #pragma unroll
     for (int u = 0; u < 8; ++u) a[u] = fetch(w[0], 0, u);
+    int turn = 0;
     for (int s0 = s_beg; s0 < s_end; s0 += D) {
 #pragma unroll
         for (int d = 0; d < D; ++d) {
@@ -444,40 +493,29 @@ __global__ void __launch_bounds__(RW * KW * 64) gemm_centroid_kernel(CG_HEAD_PAR
 #pragma unroll
                         for (int nt = 0; nt < NT; ++nt) {
                             const half8_t xv = xr[d][nt][k / (M * HALVES)][(k / M) % HALVES];
-                            acc[nt][u] = __builtin_amdgcn_mfma_f32_16x16x32_f16(xv, a[u], (GS == 1 && k == 0) || (GS == 2 && k % (M * HALVES) == 0) || (GS == 3 && (d * NSB + k) % CHAIN == 0) ? float4_t{} : acc[nt][u], 0, 0, 0);
+                            acc[nt][u] = __builtin_amdgcn_mfma_f32_16x16x32_f16(xv, a[u], starts(k) ? float4_t{} : acc[nt][u], 0, 0, 0);
                         }
                         __builtin_amdgcn_sched_barrier(0);         // the lookup after its operand's last use: no second set of registers
                         a[u] = k + 1 < NSB ? fetch(w[d], k + 1, u) : fetch(w[(d + 1) % D], 0, u);
                         __builtin_amdgcn_sched_barrier(0);
                     }
-                    if constexpr (GS == 3) {
-                        if (!ACROSS && (d * NSB + k) % CHAIN == CHAIN - 1) add_up();
-                    }
-                    if constexpr (GS == 2) {
-                        if (k % (M * HALVES) == M * HALVES - 1) add_scaled(sc[d][k / (M * HALVES)]);
+                    if (ends(k)) {
+                        if constexpr (GS == 3) add_up();
+                        if constexpr (PARTS) add_part(k % ROUND == 0);
+                        if constexpr (SCALED) if (!PARTS || k % ROUND == ROUND - 1) add_scaled(sc[d][NEAR ? k / ROUND : 0]);
                     }
                 }
-                if constexpr (GS == 1) add_scaled(sc[d][0]);
-            } else if constexpr (GS == 3 && ACROSS) {
-                // no step: nothing to add where a chain would have started in it
-                bool starts = false;
-#pragma unroll
-                for (int k = 0; k < NSB; ++k) starts |= (d * NSB + k) % CHAIN == 0;
-                if (starts) {
-#pragma unroll
-                    for (int nt = 0; nt < NT; ++nt)
-#pragma unroll
-                        for (int u = 0; u < 8; ++u) acc[nt][u] = float4_t{0.0f, 0.0f, 0.0f, 0.0f};
-                }
             }
-            if constexpr (GS == 3 && ACROSS) {
-                if (((d + 1) * NSB) % CHAIN == 0) add_up();
-            }
+            if constexpr (SHORT && TURNS == 0) move_up();
             load_codes(w[d], s + D);
             load_x(xr[d], s + D);
             if constexpr (SCALED) load_scales(sc[d], s + D);
         }
+        if constexpr (SHORT && TURNS > 0) {
+            if (++turn % TURNS == 0) move_up();
+        }
     }
+    if constexpr (SHORT) move_up();
 
     // Sum over the wavefronts' K slices, one tile of batch rows at a time: partials in LDS
     // [slice][batch row][RB + 4] (ONE: the four sub-vectors of a slice apart), totals behind
@@ -497,7 +535,7 @@ __global__ void __launch_bounds__(RW * KW * 64) gemm_centroid_kernel(CG_HEAD_PAR
             float v[8];
 #pragma unroll
             for (int u = 0; u < 8; ++u) {
-                v[u] = GS ? sum[GS ? nt : 0][u][GS ? t : 0] : own(acc[nt][u], t);
+                v[u] = SHORT ? total_of[SHORT ? nt : 0][u][SHORT ? t : 0] : GS ? sum[GS ? nt : 0][u][GS ? t : 0] : own(acc[nt][u], t);
                 if constexpr (SB >= 2 && !ONE) v[u] = dpp_add<0xb1, 0xf>(v[u]);
                 if constexpr (SB == 4 && !ONE) v[u] = dpp_add<0x4e, 0xf>(v[u]);
             }
@@ -554,13 +592,13 @@ int launch_gemm_centroid_v(const Geometry& g, const GemmParams& p, hipStream_t s
             if (g.RB == 64) return launch_gemm_centroid_one<M, V, 4, 1, 2, 4, 4, GS>(g, p, stream);
             return launch_gemm_centroid_one<M, V, 4, 1, 1, 8, 4, GS>(g, p, stream);
         case 8:
-            if (g.RB == 128) return launch_gemm_centroid_one<M, V, 2, 1, 2, 4, GS == 2 ? 3 : 4, GS>(g, p, stream);
-            if (g.RB == 64) return launch_gemm_centroid_one<M, V, 2, 1, 1, 8, GS == 2 ? 3 : 4, GS>(g, p, stream);
+            if (g.RB == 128) return launch_gemm_centroid_one<M, V, 2, 1, 2, 4, GS == 2 || GS == 4 ? 3 : 4, GS>(g, p, stream);
+            if (g.RB == 64) return launch_gemm_centroid_one<M, V, 2, 1, 1, 8, GS == 2 || GS == 4 ? 3 : 4, GS>(g, p, stream);
             if constexpr (V < 16) return launch_gemm_centroid_one<M, V, 4, 2, 1, 8, 3, GS>(g, p, stream);
             break;
         case 16:
             if (g.RB == 128) return launch_gemm_centroid_one<M, V, 1, 1, 1, 8, 2, GS>(g, p, stream);
-            if constexpr (V < 16 && (GS != 2 || M == 1)) {
+            if constexpr (V < 16 && ((GS != 2 && GS != 4) || M == 1)) {
                 if (g.RB == 64) return launch_gemm_centroid_one<M, V, 2, 2, 1, 8, 2, GS>(g, p, stream);
             }
             if constexpr (V < 16 && (GS == 0 || M == 1)) {
@@ -568,7 +606,7 @@ int launch_gemm_centroid_v(const Geometry& g, const GemmParams& p, hipStream_t s
             }
             break;
         case 32:
-            if constexpr (GS == 0 && (V == 8 && M <= 2 || V == 4 && M == 1)) return launch_gemm_centroid_one<M, V, 1, 2, 1, 8, 2, GS>(g, p, stream);
+            if constexpr (GS == 0 && ((V == 8 && M <= 2) || (V == 4 && M == 1))) return launch_gemm_centroid_one<M, V, 1, 2, 1, 8, 2, GS>(g, p, stream);
     }
     return CODEGEMM_UNSUPPORTED;
 }

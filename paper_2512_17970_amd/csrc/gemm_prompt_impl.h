@@ -1,4 +1,5 @@
-// The centroid kernel for prompts: more than 32 batch rows.  Included by gemm_centroid_m1.hip ..
+// The centroid kernel for prompts: more than 32 batch rows, fp16 output (fp32 output needs sums that there are no registers
+// for here, and a spread of K over wavefronts: the centroid kernel's tiles along the grid).  Included by gemm_centroid_m1.hip ..
 // gemm_centroid_m4.hip; mapping, table, lookups and the kinds of scales (GS) as in gemm_centroid_impl.h.
 //
 // A lookup is paid once per 64 codes whatever the batch, so with NT tiles of 16 batch rows per
@@ -31,10 +32,7 @@ __global__ void __launch_bounds__(512) gemm_prompt_kernel(CG_HEAD_PARAMS, const 
     constexpr int BT = 16 * NT;                        // batch rows of the workgroup
     constexpr int XL = BT * 16 / THREADS;              // chunks of x this thread moves per step
     constexpr int kUnitBytes = kGranuleRows * kSlots * M;
-    constexpr bool SCALED = GS == 1 || GS == 2;
-    // GS = 3 adds its tiles to the sums after every step (8192^2 v8 m2, batch 512: 285 us, every eight 295), except for
-    // two codebooks of v = 4, which spill there (537 us, every eight steps 430).
-    constexpr bool SELDOM = V == 4 && M == 2;
+    constexpr bool SCALED = GS != 0;
     constexpr int kOutOfRange = 0x7ffffff0;
     constexpr uint32_t kRsrcFlags = 0x00020000u;
     static_assert(BT * 16 % THREADS == 0, "whole chunks per thread");
@@ -223,17 +221,8 @@ __global__ void __launch_bounds__(512) gemm_prompt_kernel(CG_HEAD_PARAMS, const 
 #pragma unroll
             for (int nt = 0; nt < NT; ++nt)
 #pragma unroll
-                for (int e = 0; e < 4; ++e) sum[SCALED ? nt : 0][SCALED ? u : 0][e] = __builtin_fmaf(f, acc[nt][u][e], sum[SCALED ? nt : 0][SCALED ? u : 0][e]);
+                for (int e = 0; e < 4; ++e) sum[GS ? nt : 0][GS ? u : 0][e] = __builtin_fmaf(f, acc[nt][u][e], sum[GS ? nt : 0][GS ? u : 0][e]);
         }
-    };
-    auto add_up = [&]() {
-#pragma unroll
-        for (int nt = 0; nt < NT; ++nt)
-#pragma unroll
-            for (int u = 0; u < 8; ++u) {
-                sum[GS ? nt : 0][GS ? u : 0] += acc[nt][u];
-                acc[nt][u] = float4_t{0.0f, 0.0f, 0.0f, 0.0f};
-            }
     };
     // x operand of (tile nt, round j): chunk 4 q + j (GS = 2: 4 j + q) of batch row 16 nt + i16
     const uint32_t xrd = xbase + (uint32_t)(i16 * 256);
@@ -244,8 +233,6 @@ __global__ void __launch_bounds__(512) gemm_prompt_kernel(CG_HEAD_PARAMS, const 
     __syncthreads();
 
     half8_t a[8], xv[NT];
-    static_assert(NT % 2 == 0, "tiles");
-    float4_t late[2] = {float4_t{0.0f, 0.0f, 0.0f, 0.0f}, float4_t{0.0f, 0.0f, 0.0f, 0.0f}};       // GS = 3
     turn_codes(w[0]);
 #pragma unroll
     for (int u = 0; u < 8; ++u) a[u] = fetch(w[0], 0, u);
@@ -266,16 +253,7 @@ __global__ void __launch_bounds__(512) gemm_prompt_kernel(CG_HEAD_PARAMS, const 
                     for (int u = 0; u < 8; ++u) {
 #pragma unroll
                         for (int nt = 0; nt < NT; ++nt) {
-                            if constexpr (GS == 3) {               // added two instructions later, when it is there
-                                const float4_t one = __builtin_amdgcn_mfma_f32_16x16x32_f16(xv[nt], a[u], float4_t{}, 0, 0, 0);
-                                __builtin_amdgcn_sched_barrier(0);
-                                const int n = (u * NT + nt + 8 * NT - 2) % (8 * NT);
-                                acc[n % NT][n / NT] += late[nt % 2];
-                                asm volatile("" : "+v"(acc[n % NT][n / NT]));      // here: the compiler would keep the results and add them all later
-                                late[nt % 2] = one;
-                            } else {
-                                acc[nt][u] = __builtin_amdgcn_mfma_f32_16x16x32_f16(xv[nt], a[u], (GS == 1 && k == 0) || (GS == 2 && k % M == 0) ? float4_t{} : acc[nt][u], 0, 0, 0);
-                            }
+                            acc[nt][u] = __builtin_amdgcn_mfma_f32_16x16x32_f16(xv[nt], a[u], (GS == 1 && k == 0) || (GS == 2 && k % M == 0) ? float4_t{} : acc[nt][u], 0, 0, 0);
                         }
                         __builtin_amdgcn_sched_barrier(0);         // the lookup after its operand's last use: no second set of registers
                         a[u] = k + 1 < NSB ? fetch(w[d], k + 1, u) : fetch(w[d ^ 1], 0, u);
@@ -289,7 +267,6 @@ __global__ void __launch_bounds__(512) gemm_prompt_kernel(CG_HEAD_PARAMS, const 
                     }
                 }
                 if constexpr (GS == 1) add_scaled(sc[d][0]);
-                if constexpr (GS == 3 && !SELDOM) add_up();
             }
             load_codes(w[d], s + 2);
             if constexpr (SCALED) load_scales(sc[d], s + 2);
@@ -297,15 +274,6 @@ __global__ void __launch_bounds__(512) gemm_prompt_kernel(CG_HEAD_PARAMS, const 
 #pragma unroll
             for (int nt = 0; nt < NT; ++nt) xv[nt] = x_operand(s + 1, nt, 0);
         }
-        if constexpr (GS == 3 && SELDOM) {
-            if ((s0 & 6) == 6) add_up();
-        }
-    }
-
-    if constexpr (GS == 3) {
-        acc[NT - 2][7] += late[0];
-        acc[NT - 1][7] += late[1];
-        add_up();
     }
 
     // Lane (i16, q): rows 8 i16 .. + 7 of the granule, batch rows 16 nt + 4 q + e.
@@ -330,29 +298,16 @@ __global__ void __launch_bounds__(512) gemm_prompt_kernel(CG_HEAD_PARAMS, const 
             float v[8];
 #pragma unroll
             for (int u = 0; u < 8; ++u) v[u] = (GS ? sum[GS ? nt : 0][GS ? u : 0][e] : acc[nt][u][e]) * scale[u];
-            const size_t at = (size_t)b * mm.N + n0;
-            if (p.y_fp32) {
-                float* y = static_cast<float*>(mm.y) + at;
-                if (whole && (mm.N & 3) == 0) {        // 16-byte stores need every row of y aligned
-                    *reinterpret_cast<float4_t*>(y) = float4_t{v[0], v[1], v[2], v[3]};
-                    *reinterpret_cast<float4_t*>(y + 4) = float4_t{v[4], v[5], v[6], v[7]};
-                } else {
+            _Float16* y = static_cast<_Float16*>(mm.y) + (size_t)b * mm.N + n0;
+            if (whole && (mm.N & 7) == 0) {            // 16-byte stores need every row of y aligned
+                half8_t h;
 #pragma unroll
-                    for (int u = 0; u < 8; ++u)
-                        if (n0 + u < mm.N) y[u] = v[u];
-                }
+                for (int u = 0; u < 8; ++u) h[u] = (_Float16)v[u];
+                *reinterpret_cast<half8_t*>(y) = h;
             } else {
-                _Float16* y = static_cast<_Float16*>(mm.y) + at;
-                if (whole && (mm.N & 7) == 0) {
-                    half8_t h;
 #pragma unroll
-                    for (int u = 0; u < 8; ++u) h[u] = (_Float16)v[u];
-                    *reinterpret_cast<half8_t*>(y) = h;
-                } else {
-#pragma unroll
-                    for (int u = 0; u < 8; ++u)
-                        if (n0 + u < mm.N) y[u] = (_Float16)v[u];
-                }
+                for (int u = 0; u < 8; ++u)
+                    if (n0 + u < mm.N) y[u] = (_Float16)v[u];
             }
         }
 }
@@ -373,7 +328,7 @@ int launch_gemm_prompt_one(const Geometry& g, const GemmParams& p, hipStream_t s
 template <int M, int V, int GS>
 int launch_gemm_centroid_mv(const Geometry& g, const GemmParams& p, hipStream_t stream)
 {
-    if constexpr (V < 16) {
+    if constexpr (V < 16 && GS <= 2) {
         if (g.prompt) {
             return launch_gemm_prompt_one<M, V, prompt_tiles(M, V, GS != 0), GS>(g, p, stream);
         }
@@ -384,9 +339,10 @@ int launch_gemm_centroid_mv(const Geometry& g, const GemmParams& p, hipStream_t 
 template <int M, int V>
 int launch_gemm_centroid_mg(const Geometry& g, const GemmParams& p, hipStream_t stream)
 {
-    if (g.g < 0) return p.y_fp32 ? launch_gemm_centroid_mv<M, V, 3>(g, p, stream) : launch_gemm_centroid_mv<M, V, 0>(g, p, stream);
+    if (p.y_fp32) return g.g < 0 ? launch_gemm_centroid_mv<M, V, 3>(g, p, stream) : launch_gemm_centroid_mv<M, V, 4>(g, p, stream);
+    if (g.g < 0) return launch_gemm_centroid_mv<M, V, 0>(g, p, stream);
     // a step, 16 chunks, is 16 sub-vectors (32 for v = 4)
-    if (!p.y_fp32 && g.gshift >= (V == 4 ? 5 : 4)) return launch_gemm_centroid_mv<M, V, 1>(g, p, stream);
+    if (g.gshift >= (V == 4 ? 5 : 4)) return launch_gemm_centroid_mv<M, V, 1>(g, p, stream);
     return launch_gemm_centroid_mv<M, V, 2>(g, p, stream);
 }
 

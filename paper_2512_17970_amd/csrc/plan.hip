@@ -269,7 +269,8 @@ static void choose_psumbook_plan(const codegemm_desc* d, codegemm_plan* p)
 //    With several codebooks only 128-row blocks are left from nine rows on, too few of them on small matrices (2048^2,
 //    batch 16: 8.7/10.3), and v = 16 loses at two rows (m3 g64: 4096^2 7.5/8.5, 8192^2 10.4/12.4);
 //  * fp32 output pays for its short chains of sums: v = 16 loses on small matrices, at two rows (m2 8192^2 8.4/9.4) and
-//    with many codebooks, whose sums spill (m4 8192^2, batch 512: 817/936); two codebooks at one row gain nothing.
+//    with three and four codebooks, and above 8 rows its 16 products per sum leave it less exact than the Psumbook
+//    kernels (1.04 to 1.08 of their error below K = 8192); two codebooks at one row gain nothing.
 //  * the Psumbook kernels also keep what 26 000 random sizes showed them to win (gains below are Psumbook time / centroid
 //    time, geometric mean): a second, nearly empty round of blocks (more than 256 of 32 rows, or of 64) at one row with
 //    v8 m2 group scales 0.78, v8 m1 0.91, and from two to four rows with v16 m4 0.75 to 0.91; one row, short K with group
@@ -283,7 +284,7 @@ static bool prefer_centroid(const codegemm_desc* d)
         if (d->vec_len == 16 && d->batch == 2 && d->num_codebooks > 2) return false;
     }
     const bool fp32 = d->flags & CODEGEMM_FLAG_Y_FP32;
-    if (fp32 && d->vec_len == 16 && (d->num_codebooks > 3 || (d->batch <= kBatchPerLaunch && (codes < 6000000 || d->batch == 2 || d->num_codebooks > 2)))) return false;
+    if (fp32 && d->vec_len == 16 && (d->batch > 8 || codes < 6000000 || d->batch == 2 || d->num_codebooks > 2)) return false;
     const int n32 = ceil_div(d->out_features, 32), n64 = ceil_div(d->out_features, 64), v = d->vec_len, m = d->num_codebooks;
     const bool second = (n32 > 256 && n32 <= 320) || n64 > 256, grouped = d->group_size > 0;
     if (d->batch == 1) {
@@ -399,9 +400,10 @@ int make_geometry(const codegemm_desc* d, const codegemm_plan* plan, Geometry* g
     }
     g->KPW = ceil_div(g->NKT, g->NKS);
     // The prompt kernel's workgroups take 1024 rows of W and 64 (with group scales 32) batch rows and all of K: worth it
-    // once they are enough to fill the chip.
-    g->prompt = g->RB && g->B > kBatchPerLaunch && g->v < 16 &&
-                (long long)ceil_div(g->NGR, 8) * ceil_div(g->B, 16 * prompt_tiles(g->m, g->v, d->group_size > 0 || (d->flags & CODEGEMM_FLAG_Y_FP32))) >= 128;
+    // once they are enough to fill the chip.  fp32 output needs shorter sums than it has (8192^2 v8 m1 g128 batch 512: 2.9e-7
+    // of 64 bits, tiles of the centroid kernel 0.95e-7, Psumbook kernels 1.24e-7; 141, 156 and 493 us).
+    g->prompt = g->RB && g->B > kBatchPerLaunch && g->v < 16 && !(d->flags & CODEGEMM_FLAG_Y_FP32) &&
+                (long long)ceil_div(g->NGR, 8) * ceil_div(g->B, 16 * prompt_tiles(g->m, g->v, d->group_size > 0)) >= 128;
     if (g->prompt) g->NKS = 1;
     g->NG = ceil_div(g->B, g->BG);
     g->Npad = g->NGR * kGranuleRows;

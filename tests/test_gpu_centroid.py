@@ -215,3 +215,35 @@ def test_replays_from_a_hip_graph():
         for l, y, e in zip(layers, outs, eager):
             assert torch.equal(y, e)
             assert torch.equal(l.gemm(), e)
+
+
+def exact_on_gpu(layer, inp):
+    """The oracle's sum, dequantized and multiplied in float64 on the GPU (some thousand rows of W at a time): the sizes
+    below would take the CPU minutes."""
+    c, out = inp.case, []
+    books = layer.codebooks.double()
+    for n0 in range(0, c.N, 1024):
+        codes, s = layer.codes[:, n0:n0 + 1024].long(), layer.scales[n0:n0 + 1024].double()
+        W = sum(books[i][codes[i]] for i in range(c.m)).reshape(codes.shape[1], c.K)
+        out.append(layer.x.double() @ (W * (s[:, None] if c.g < 0 else s.repeat_interleave(c.g, dim=1))).t())
+    return torch.cat(out, dim=1)
+
+
+@pytest.mark.parametrize("v,m,g,B,K,N", [
+    (8, 2, -1, 2, 1024, 8192), (8, 4, -1, 2, 1024, 8192), (8, 3, 64, 3, 1024, 8192), (8, 2, 32, 2, 512, 8192), (8, 1, -1, 1, 5120, 16000),
+    (8, 1, 128, 2, 28672, 5000), (8, 2, -1, 16, 768, 4096), (4, 2, -1, 12, 512, 4096), (8, 4, -1, 64, 27648, 811), (16, 1, -1, 64, 1024, 1000),
+    (16, 2, -1, 200, 26624, 1190), (8, 2, 64, 100, 1024, 1500), (8, 3, 64, 200, 2048, 700), (4, 1, 32, 500, 28672, 700),
+    (8, 1, 128, 512, 8192, 8192), (8, 2, 32, 512, 4096, 8192), (4, 1, 128, 1024, 4096, 4096), (8, 1, -1, 600, 14336, 8192), (4, 2, -1, 512, 1536, 8192)])
+def test_fp32_output_is_no_further_from_64_bits_than_the_psumbook_kernels(v, m, g, B, K, N):
+    """The default plan against the same plan without centroid_rows.  Each error is a root mean square over B N >= 16384
+    outputs, so known to 1 / sqrt(2 B N) < 0.6 %: 3 % above is more than three standard deviations of their ratio."""
+    case = synth.custom_case(K, N, v, m, B, seed=3260 + B, g=g)
+    inp = synth.generate(case)
+    layer = DeviceLayer(inp, y_fp32=True)
+    ref = exact_on_gpu(layer, inp)
+    err = lambda y: ((y.double() - ref).norm() / ref.norm()).item()
+    now = err(layer.gemm())
+    print(f"[fp32 error] {case.name} {layer.plan} {now:.3e}", flush=True)
+    layer.plan.centroid_rows = layer.plan.centroid_splits = 0
+    then = err(layer.gemm())
+    assert now <= 1.03 * then, (now, then)
