@@ -255,58 +255,65 @@ static void choose_psumbook_plan(const codegemm_desc* d, codegemm_plan* p)
     }
 }
 
-// Whether the centroid kernel is the faster one, from sweeps over the workloads' shapes and formats (us, Psumbook
-// kernels / centroid kernel):
-//  * more than one batch row: everywhere (v8 m2, batch 2 / 4 / 8 / 16: 2048^2 6.1/4.9, 7.6/5.0, 7.8/5.6, 8.3/7.2;
-//    8192->28672 23.9/18.3, 27.3/19.2, 41.5/21.9, 70/25), except v = 16 at nine rows and more, whose 128-row blocks
-//    leave small matrices too few of them (v16 m4 at batch 16: 4096^2 14.8/16.0, 8192^2 31.7/20.6; at 32 19.8/16.6);
-//  * one: where 32-row blocks fill half of the chip and its lookups, four times the LDS bytes of the Psumbook's, are not
-//    what bounds the call: v4 m1 g128 4096^2 5.9/5.3, 28672->8192 21.9/15.7 (its centroids are the shortest); v8 m2
-//    4096^2 5.5/4.9, 4096->14336 7.9/7.0, a tie at 8192^2, but 8192->28672 15.7/17.4, 2048^2 4.8/4.9; three codebooks
-//    (8192^2 10.3/10.6) and v = 16 (4096^2 5.4/7.1) lose;
-//  * groups shorter than a step cost a flush inside it (v8 m2 g32, batch 2 / 4 / 8 / 16 / 32: 4096^2 7.7/6.0, 9.1/6.3,
-//    12.3/7.3, 15.0/12.2, 21.3/12.8; 8192^2 12.2/9.1, 15.7/9.2, 22.1/12.5, 34/15, 63/21; at 512 297/61 and 871/242).
-//    With several codebooks only 128-row blocks are left from nine rows on, too few of them on small matrices (2048^2,
-//    batch 16: 8.7/10.3), and v = 16 loses at two rows (m3 g64: 4096^2 7.5/8.5, 8192^2 10.4/12.4);
+// Rows of a block of the centroid kernel for up to 4 batch rows: as low as one round of 256 workgroups allows.  A second
+// round that few blocks are left for costs as much as a full one: 257 to 320 blocks of 32 rows take 1.09 to 1.42 times as
+// long as half as many of 64 rows, 257 to 448 of 64 rows 1.04 to 1.35 times as long as of 128 (random sizes, all formats).
+static int low_rows(int n) { return ceil_div(n, 32) <= 256 ? 32 : ceil_div(n, 64) <= 256 ? 64 : 128; }
+
+// Whether the centroid kernel is the faster one, from 61 000 random sizes at up to 4 batch rows, 43 000 at 5 to 32 and
+// 17 000 above (times: Psumbook kernels / centroid kernel).  Its cost is the lookups of one workgroup, rows times K of a
+// block, four times the LDS bytes of the Psumbook's; the Psumbook kernels cut K finer and fill the chip at any height.
+//  * One row: where that work is small.  Ratio at 32-row blocks on more than half of the chip (64 rows: at half the K,
+//    128 at a quarter): v8 m2 1.2 at K = 2000, 1.1 at 4000, 1.1 at 7000, 1.0 at 16000; v8 m1 1.2, 1.2, 1.15, 1.05; v4 m1
+//    (the shortest centroids) 1.3, 1.3, 1.25, 1.2, below 1 from 128-row blocks with K = 8000 on unless a step lies in
+//    one group.  8192^2 v8 m2 ties and is left out.  fp32 output of v8 m2 group scales: half of the work; with one scale
+//    per row it gains nothing.  v8 group scales tie below K = 1024; three codebooks and v = 16 lose.
+//  * Two to four rows: everywhere (v8 m2, 2 / 4 rows: 1.4 / 1.7; v4 m1 1.5 / 1.8), but for v8 with group scales or fp32
+//    output on blocks of 64 and 128 rows that fill less than three quarters of the chip, from a work of 128 x 8192 on
+//    (two rows, v8 m1 g128: 0.75 to 0.97 at K = 8300 to 28000 and 16400 to 18000 rows), and v16 with three or four codebooks, whose lookups read 32
+//    bytes (two rows, v16 m4: 1.2 below K = 4000, 0.95 to 1.05 at 8000, 0.8 to 0.9 from 16000 on).
+//  * Groups shorter than a step cost a flush inside it.  With several codebooks only 128-row blocks are left from nine
+//    rows on, too few of them on small matrices (v8 m2 g32 2048^2, batch 16: 8.7/10.3 us), and v = 16 loses at two rows.
 //  * fp32 output pays for its short chains of sums: v = 16 loses on small matrices, at two rows (m2 8192^2 8.4/9.4) and
 //    with three and four codebooks, and above 8 rows its 16 products per sum leave it less exact than the Psumbook
-//    kernels (1.04 to 1.08 of their error below K = 8192); two codebooks at one row gain nothing.
-//  * the Psumbook kernels also keep what 26 000 random sizes showed them to win (gains below are Psumbook time / centroid
-//    time, geometric mean): a second, nearly empty round of blocks (more than 256 of 32 rows, or of 64) at one row with
-//    v8 m2 group scales 0.78, v8 m1 0.91, and from two to four rows with v16 m4 0.75 to 0.91; one row, short K with group
-//    scales 0.92; two rows, short K on high matrices 0.88; five to 23 rows with v16 on small matrices 0.76 to 0.97.
+//    kernels (1.04 to 1.08 of their error below K = 8192).
+//  * 5 to 32 rows: v16 on small matrices (0.76 to 0.97; m4 at batch 16: 4096^2 14.8/16.0, 8192^2 31.7/20.6), blocks of v8
+//    that are too few when they have to be 128 rows (group scales: up to 1100 rows; fp32 output: 1500), and short K with
+//    fp32 output above 16 rows.
+//  * More: everywhere (33 to 64 rows 2.4, to 128 3.2, to 512 4.4, to 2048 6 and more; no size of 17 000 lost 1 %).
 static bool prefer_centroid(const codegemm_desc* d)
 {
     if (!centroid_format(d) || d->out_features > kMaxRowBlocks * 128) return false;
-    const long long codes = (long long)d->num_codebooks * d->out_features * (d->in_features / d->vec_len);
+    const int v = d->vec_len, m = d->num_codebooks, batch = d->batch, K = d->in_features, N = d->out_features;
+    const bool fp32 = d->flags & CODEGEMM_FLAG_Y_FP32, grouped = d->group_size > 0;
+    const long long codes = (long long)m * N * (K / v);
     if (short_groups(d)) {
-        if (d->batch > 8 && d->batch <= kBatchPerLaunch && d->num_codebooks > 1 && codes < 4000000) return false;
-        if (d->vec_len == 16 && d->batch == 2 && d->num_codebooks > 2) return false;
+        if (batch > 8 && batch <= kBatchPerLaunch && m > 1 && codes < 4000000) return false;
+        if (v == 16 && batch == 2 && m > 2) return false;
     }
-    const bool fp32 = d->flags & CODEGEMM_FLAG_Y_FP32;
-    if (fp32 && d->vec_len == 16 && (d->batch > 8 || codes < 6000000 || d->batch == 2 || d->num_codebooks > 2)) return false;
-    const int n32 = ceil_div(d->out_features, 32), n64 = ceil_div(d->out_features, 64), v = d->vec_len, m = d->num_codebooks;
-    const bool second = (n32 > 256 && n32 <= 320) || n64 > 256, grouped = d->group_size > 0;
-    if (d->batch == 1) {
-        if (v == 8 && n64 > 256) return false;
-        if (v == 4 && grouped && second && n64 <= 320) return false;
-        if (v == 8 && grouped && second) return false;
-        if (v == 8 && m == 2 && grouped && d->in_features > 8192 && n32 > 128) return false;
-        if (grouped && (v == 8 || n64 > 256) && d->in_features < 1024) return false;
-    } else if (d->batch <= 4) {
-        if (v == 16 && m >= 3 && second) return false;
-        if (d->batch == 2 && v == 8 && m >= 2 && second && (d->in_features < 2048 || (grouped && n64 <= 256))) return false;
-        if (d->batch == 2 && m == 1 && grouped && d->out_features < 2048) return false;
-    } else if (d->batch <= kBatchPerLaunch) {
-        if (v == 16 && m >= 3 && (d->batch <= 8 ? n64 <= 64 : d->batch < 24 && codes < 10000000)) return false;
-        if (d->batch > 8 && v == 8 && m >= 2 && (grouped ? n64 <= 18 : fp32 && n64 < 24)) return false;
-        if (d->batch > 16 && fp32 && d->in_features < 1024) return false;
+    if (fp32 && v == 16 && (batch > 8 || codes < 6000000 || batch == 2 || m > 2)) return false;
+    if (batch > kBatchPerLaunch) return true;
+    if (batch <= 4) {
+        const int rows = low_rows(N), nb = ceil_div(N, rows);
+        const long long work = (long long)rows * K;
+        if (batch == 1) {
+            if (m > 2 || v == 16 || (fp32 && !grouped && m > 1)) return false;
+            if (v == 4 && m == 1) return (N >= 4096 || K >= 8192) && ((grouped && !short_groups(d)) || work < 32 * 24576);
+            if (N < 4096 || (grouped && v == 8 && K < 1024)) return false;
+            if (m == 1) return work <= 32 * 12288;
+            return K < 8192 && work <= 32 * (fp32 ? 4096 : 8192);
+        }
+        if (v == 16) return m < 3 || work <= (nb >= 192 ? 128 * 8192 : batch == 2 ? 64 * 4096 : 64 * 8192);
+        if (v == 8 && nb < 192 && (grouped || fp32)) return work <= 128 * (batch > 2 ? 14336 : fp32 || m == 1 ? 8192 : 16384);
+        return true;
     }
-    if (d->batch > 1) return d->vec_len < 16 || d->batch <= 8 || d->batch > kBatchPerLaunch || codes >= (d->batch <= 16 ? 6000000 : 4000000);
-    if (d->num_codebooks > 2 || d->vec_len == 16) return false;
-    if (fp32 && d->group_size < 0 && d->num_codebooks > 1) return false;
-    if (d->vec_len == 4 && d->num_codebooks == 1) return d->out_features >= 4096 || d->in_features >= 8192;
-    return d->out_features >= 4096 && codes * d->vec_len <= 120000000;
+    const int n64 = ceil_div(N, 64);
+    if (v == 16) {
+        if (m >= 3 && (batch <= 8 ? n64 <= 64 : batch < 24 && codes < 10000000)) return false;
+        return batch <= 8 || codes >= (batch <= 16 ? 6000000 : 4000000);
+    }
+    if (batch > 8 && v == 8 && m >= 2 && (grouped ? n64 <= 18 : fp32 && n64 < 24)) return false;
+    return !(batch > 16 && fp32 && K < 1024);
 }
 
 static void choose_plan(const codegemm_desc* d, codegemm_plan* p)
@@ -324,7 +331,7 @@ static void choose_plan(const codegemm_desc* d, codegemm_plan* p)
     // 64 rows 12.5, 128 rows 14.0; 14336->4096 17.0 / 14.0; batch 32, 4096^2 64 rows 10.5, 128 rows 15.8).
     int rows = 128;
     if (d->batch <= 4) {
-        rows = blocks(32) <= 320 ? 32 : blocks(64) <= 512 ? 64 : 128;
+        rows = low_rows(d->out_features);
     } else if (d->batch <= 8) {
         if (least == 32 && blocks(32) <= 256 && (d->vec_len == 4 ? codes / 2 : codes) <= 10000000) rows = 32;
         else if (blocks(64) <= 256) rows = 64;
@@ -333,21 +340,27 @@ static void choose_plan(const codegemm_desc* d, codegemm_plan* p)
         if (least == 32 && blocks(32) <= (d->batch <= 16 ? 192 : 256) && codes <= low) rows = 32;
         else if (least <= 64 && !short_groups(d) && blocks(64) <= 256 && (codes <= 8500000 || (d->batch <= 16 && codes <= 16000000 && blocks(64) >= 96))) rows = 64;
     }
-    // K ranges.  Up to 4 batch rows: 128 workgroups, 256 when that leaves each 48 units or more (14336->4096 v8 m2: two
-    // ranges 7.4, one 8+; 4096^2: one 4.9, two 5.4).  More: 256 as long as every wavefront keeps a step (4096^2 at batch
-    // 8: two ranges 6.5, one 6.8; 2048^2: two 5.6, four, with half of the wavefronts idle, 6.2).
+    // K ranges.  Up to 4 batch rows: powers of two (others meet through the ticket, 1 us more than two or four pairwise:
+    // three ranges are 10 % slower than two or four at any K), up to 256 workgroups, as long as a range is worth its
+    // exchange.  One / two ranges break even at K = 4300 (time ratio 0.88 at 512 to 1500, 0.98 at 4096, 1.05 at 5000, 1.2
+    // at 14000), two / four at 6500 (0.92 up to 3000, 1.02 at 8192, 1.1 at 14000), four / eight at 9000 (1.02, 1.06 at
+    // 14000, 1.14 from 16000), for 16 to 128 blocks and all formats alike.  More rows: 256 workgroups as long as every
+    // wavefront keeps a step (4096^2 at batch 8: two ranges 6.5, one 6.8; 2048^2: two 5.6, four, with half of the
+    // wavefronts idle, 6.2).
     const int nb = (int)blocks(rows);
+    auto even = [&](int n) { return ceil_div(nkt, ceil_div(nkt, n)) == n; };       // cuts into n ranges, none empty
+    // no more workspace than the fields of the Psumbook kernels ask for
+    const long long room = (long long)p->k_splits * (d->batch < kBatchPerLaunch ? d->batch : kBatchPerLaunch) / d->batch;
     int splits;
     if (d->batch <= 4) {
-        splits = ceil_div(128, nb);
-        if (splits * nb <= 128 && nkt / splits >= 48) splits *= 2;
+        splits = 1;
+        while (2 * splits * nb <= 256 && d->in_features >= 2 * splits * (splits == 1 ? 2304 : splits == 2 ? 1792 : 1536)) splits *= 2;
+        while (splits > 1 && (splits > room || splits > nkt || !even(splits))) splits /= 2;
     } else {
         splits = 256 / nb;
         const int most = nkt * (d->vec_len == 4 ? 1 : 2) / 8;
         if (splits > most) splits = most;
     }
-    // no more workspace than the fields of the Psumbook kernels ask for
-    const long long room = (long long)p->k_splits * (d->batch < kBatchPerLaunch ? d->batch : kBatchPerLaunch) / d->batch;
     if (splits > room) splits = (int)room;
     if (splits > nkt) splits = nkt;
     if (splits < 1) splits = 1;

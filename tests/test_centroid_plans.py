@@ -49,7 +49,7 @@ def test_a_plan_serves_every_batch_output_type_and_group_size(v, m):
 
 
 def test_k_splits_bounds_the_workspace_of_an_edited_default_plan():
-    d = cg.Desc.make(2, 4096, 512, 8, 2)
+    d = cg.Desc.make(2, 16384, 512, 8, 2)
     p = cg.codegemm_default_plan(d)
     assert p.centroid_rows and p.centroid_splits > 2
     for k in (1, 2):
