@@ -297,7 +297,10 @@ __global__ void __launch_bounds__(512) gemm_prompt_kernel(CG_HEAD_PARAMS, const 
             if (b >= p.B || n0 >= mm.N) continue;
             float v[8];
 #pragma unroll
-            for (int u = 0; u < 8; ++u) v[u] = (GS ? sum[GS ? nt : 0][GS ? u : 0][e] : acc[nt][u][e]) * scale[u];
+            for (int u = 0; u < 8; ++u) {
+                v[u] = (GS ? sum[GS ? nt : 0][GS ? u : 0][e] : acc[nt][u][e]) * scale[u];
+                asm volatile("" : "+v"(v[u]));         // an fp32 product, as in the other kernels: the compiler would round it to fp16 at once
+            }
             _Float16* y = static_cast<_Float16*>(mm.y) + (size_t)b * mm.N + n0;
             if (whole && (mm.N & 7) == 0) {            // 16-byte stores need every row of y aligned
                 half8_t h;
