@@ -129,7 +129,7 @@ __global__ void __launch_bounds__(RW * KW * 64) gemm_centroid_kernel(CG_HEAD_PAR
     constexpr bool SHORT = GS >= 3;
     constexpr int ROUND = NEAR ? M * HALVES : NSB;     // (half, codebook) of a round, which share a scale
     // MFMAs in a row on a result tile, before it is added to the sums; the tile starts and ends with them
-    constexpr int LINK = GS == 3 ? 2 : GS == 4 && V > 4 ? (SB > 1 ? 1 : 2) : ROUND;
+    constexpr int LINK = GS == 3 ? (M == 3 && SB == 2 ? 3 : 2) : GS == 4 && V > 4 ? (SB > 1 ? 1 : 2) : ROUND;
     auto starts = [](int k) constexpr -> bool { return GS != 0 && k % ROUND % LINK == 0; };
     auto ends = [](int k) constexpr -> bool { return GS != 0 && (k % ROUND % LINK == LINK - 1 || k % ROUND == ROUND - 1); };
     constexpr bool PARTS = GS == 4 && LINK == 1 && ROUND > 1;       // the tiles of a round are added before they are scaled
