@@ -16,6 +16,16 @@ def stream() -> int:
     return torch.cuda.current_stream().cuda_stream
 
 
+def plans_of(case, y_fp32=False):
+    """The default plan and, where it takes the centroid kernel, the same plan for the Psumbook kernels."""
+    plan = cg.codegemm_default_plan(cg.Desc.make(case.B, case.K, case.N, case.v, case.m, y_fp32=y_fp32, g=case.g))
+    if not plan.centroid_rows:
+        return [plan]
+    psumbook = cg.Plan.from_buffer_copy(plan)
+    psumbook.centroid_rows = psumbook.centroid_splits = 0
+    return [plan, psumbook]
+
+
 GUARD = 4096          # bytes of canary on each side of every buffer a kernel writes
 PATTERN = 0xA5
 
@@ -118,3 +128,15 @@ def check_against_oracle(y_gpu: np.ndarray, y_ref: np.ndarray, T: np.ndarray, wh
     bad = err > 1e-2 * T + 1e-30
     assert not bad.any(), f"{what}: {bad.sum()} elements exceed 1e-2*sum|terms| (max err {err.max():.3e})"
     return float(max(np.linalg.norm(y[b] - y_ref[b]) / max(np.linalg.norm(y_ref[b]), 1e-300) for b in range(y.shape[0])))
+
+
+def exact_on_gpu(layer, inp):
+    """The oracle's sum, dequantized and multiplied in float64 on the GPU (some thousand rows of W at a time): the sizes
+    below would take the CPU minutes."""
+    c, out = inp.case, []
+    books = layer.codebooks.double()
+    for n0 in range(0, c.N, 1024):
+        codes, s = layer.codes[:, n0:n0 + 1024].long(), layer.scales[n0:n0 + 1024].double()
+        W = sum(books[i][codes[i]] for i in range(c.m)).reshape(codes.shape[1], c.K)
+        out.append(layer.x.double() @ (W * (s[:, None] if c.g < 0 else s.repeat_interleave(c.g, dim=1))).t())
+    return torch.cat(out, dim=1)

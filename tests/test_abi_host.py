@@ -85,10 +85,14 @@ def test_host_pack_is_the_documented_layout_and_roundtrips():
 
 
 def test_large_batches_are_accepted_and_sized_by_their_largest_launch():
-    """More than 32 batch rows run as consecutive launches of up to 32: the workspace is that of the larger
-    of a 32-row launch and the remainder's, the default plan that of a 32-row launch."""
+    """More than 32 batch rows are one launch of the centroid kernel or consecutive launches of up to 32 rows of the Psumbook
+    kernels: the workspace is that of the larger of a 32-row launch and, for the latter, the remainder's; the Psumbook fields
+    of the default plan are those of a 32-row launch."""
     d32, d70, d1 = cg.Desc.make(32, 4096, 4096, 8, 2), cg.Desc.make(70, 4096, 4096, 8, 2), cg.Desc.make(6, 4096, 4096, 8, 2)
     assert cg.codegemm_workspace_bytes(d70) == max(cg.codegemm_workspace_bytes(d32), cg.codegemm_workspace_bytes(d1))
+    e32, e70, e6 = (cg.Desc.make(B, 4096, 4096, 8, 2, g=16) for B in (32, 70, 6))      # launches of 32, 32 and 6 rows
+    assert not cg.codegemm_default_plan(e70).centroid_rows
+    assert cg.codegemm_workspace_bytes(e70) == max(cg.codegemm_workspace_bytes(e32), cg.codegemm_workspace_bytes(e6))
     p70, p32 = cg.codegemm_default_plan(d70), cg.codegemm_default_plan(d32)
     assert (p70.waves, p70.row_words, p70.k_splits, p70.batch_group) == (p32.waves, p32.row_words, p32.k_splits, p32.batch_group)
     assert cg.codegemm_packed_codes_bytes(d70) == cg.codegemm_packed_codes_bytes(d32)

@@ -10,13 +10,13 @@ import synth
 pytestmark = pytest.mark.gpu
 
 cg = pytest.importorskip("paper_2512_17970_amd")
-from gpu_util import DeviceLayer, Guarded, check_against_oracle, dev, stream  # noqa: E402
+from gpu_util import DeviceLayer, Guarded, check_against_oracle, dev, exact_on_gpu, stream  # noqa: E402
 
 
 def least_rows(B, v=8, m=2, g=-1, fp32=False):
     if v == 16:
         return 32 if B <= 4 else 64 if B <= 8 else 128
-    return 32 if B <= 8 or m == 1 or (g < 0 and not fp32) else 64 if g >= 128 or g < 0 else 128
+    return 32 if B <= 8 or m == 1 or (g < 0 and not fp32) else 64 if g < 0 or (g >= 128 and not fp32) else 128
 
 
 def plan_of(case, rows, splits):
@@ -64,11 +64,38 @@ def test_formats_and_batches(v, m, g, B):
 @pytest.mark.parametrize("v,m,g", [(8, 2, -1), (8, 1, -1), (4, 1, 128), (4, 2, -1), (16, 4, -1), (8, 3, 128), (8, 4, -1), (8, 2, 32), (8, 1, 64), (4, 1, 32)])
 def test_block_heights(v, m, g, B, splits, rows):
     """Blocks of 32 and 64 rows (the batches that have them), ragged at either end of a granule; pairwise words and
-    tickets between the K ranges."""
+    tickets between the K ranges; both output types (fp32 output has kernels of its own)."""
     if rows < least_rows(B, v, m, g):
         pytest.skip("block height not offered for this batch")
-    for N in (rows, rows + 1, 1000):
-        run(synth.custom_case(max(g, 32 * v) * 6, N, v, m, B, seed=3100 + N, g=g), rows, splits)
+    for fp32 in (False, True):
+        if rows < least_rows(B, v, m, g, fp32):
+            continue
+        for N in (rows, rows + 1, 1000):
+            run(synth.custom_case(max(g, 32 * v) * 6, N, v, m, B, seed=3100 + N, g=g), rows, splits, fp32)
+
+
+@pytest.mark.parametrize("B,rows", [(1, 32), (1, 128), (2, 32), (2, 64), (3, 128), (6, 32), (6, 64), (8, 128), (12, 32), (12, 64), (16, 128), (40, 128)])
+@pytest.mark.parametrize("v,m,g", [(4, 1, -1), (8, 1, -1), (16, 1, -1), (8, 2, -1), (8, 3, -1), (4, 2, 64), (8, 1, 64), (8, 2, 128), (8, 3, 32), (16, 2, 64)])
+def test_fp32_sums_at_every_length_of_a_slice(v, m, g, B, rows):
+    """fp32 output: chains, sums and totals with slices of K that end at every place of the load ring and of the moves
+    from sums to totals: 0, 1, 2 .. 10 steps per wavefront, 40 and more, an odd number of sub-vectors.  A sum of n
+    additions rounded to 2^-24 has an error of about 0.25e-7 sqrt(n / 2), two levels of at most 12 and 10 of them after
+    0.6e-7 for a chain 0.9e-7, the tree over slices, lanes and ranges below 1e-7 more: 2e-7, and half as much again
+    for a row of few outputs."""
+    if rows < least_rows(B, v, m, g, True):
+        pytest.skip("block height not offered for this batch")
+    step = 16 * v if v > 4 else 128                                     # elements of K
+    unit = max(g, v)
+    for steps in (1, 7, 8, 12, 17, 25, 32, 42, 50, 58, 66, 83, 333):
+        K = -(-steps * step // unit) * unit - (unit if g > 0 or steps > 1 else 0) * (steps % 2)
+        case = synth.custom_case(max(K, unit), 70, v, m, B, seed=3150 + steps, g=g)
+        print(f"[slices] {case.name} rows={rows}", flush=True)
+        inp = synth.generate(case)
+        y_ref, _ = oracle.gemm(inp.x, inp.codes, inp.codebooks, inp.scales)
+        y = DeviceLayer(inp, plan=plan_of(case, rows, 1), y_fp32=True).gemm()
+        torch.cuda.synchronize()
+        err = np.linalg.norm(y.cpu().numpy() - y_ref) / np.linalg.norm(y_ref)
+        assert err < 3e-7, (case.name, err)
 
 
 @pytest.mark.parametrize("K,N", [(8, 1), (256, 31), (8 * 33, 128)])
@@ -215,18 +242,6 @@ def test_replays_from_a_hip_graph():
         for l, y, e in zip(layers, outs, eager):
             assert torch.equal(y, e)
             assert torch.equal(l.gemm(), e)
-
-
-def exact_on_gpu(layer, inp):
-    """The oracle's sum, dequantized and multiplied in float64 on the GPU (some thousand rows of W at a time): the sizes
-    below would take the CPU minutes."""
-    c, out = inp.case, []
-    books = layer.codebooks.double()
-    for n0 in range(0, c.N, 1024):
-        codes, s = layer.codes[:, n0:n0 + 1024].long(), layer.scales[n0:n0 + 1024].double()
-        W = sum(books[i][codes[i]] for i in range(c.m)).reshape(codes.shape[1], c.K)
-        out.append(layer.x.double() @ (W * (s[:, None] if c.g < 0 else s.repeat_interleave(c.g, dim=1))).t())
-    return torch.cat(out, dim=1)
 
 
 @pytest.mark.parametrize("v,m,g,B,K,N", [

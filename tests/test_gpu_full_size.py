@@ -11,7 +11,7 @@ import synth
 pytestmark = pytest.mark.gpu
 
 cg = pytest.importorskip("paper_2512_17970_amd")
-from gpu_util import DeviceLayer, check_against_oracle  # noqa: E402
+from gpu_util import DeviceLayer, check_against_oracle, plans_of  # noqa: E402
 
 ALL = [c for cases in synth.workloads().values() for c in cases]
 
@@ -39,16 +39,18 @@ def test_full_size_default_plan(case):
 
 @pytest.mark.parametrize("B,expect", [(2, (16, 2, 4)), (4, (16, 2, 4))])
 def test_small_batch_on_a_large_matrix_takes_the_batched_kernel(B, expect):
-    """Default plan for 2 and 4 batch rows at 8192 -> 28672: the batched kernel with 1024-row blocks."""
+    """The Psumbook fields of the default plan for 2 and 4 batch rows at 8192 -> 28672: the batched kernel with 1024-row
+    blocks (the plan itself takes the centroid kernel there)."""
     case = synth.custom_case(8192, 28672, 8, 2, B, seed=4100 + B)
     inp = synth.generate(case)
     y_ref, T = oracle.gemm(inp.x, inp.codes, inp.codebooks, inp.scales)
-    layer = DeviceLayer(inp)
-    assert (layer.plan.waves, layer.plan.row_words, layer.plan.batch_group) == expect, layer.plan
-    y = layer.gemm()
-    torch.cuda.synchronize()
-    rel = check_against_oracle(y.cpu().numpy(), y_ref, T, f"batch {B} default plan")
-    assert rel < 6e-4
+    default, psumbook = plans_of(case)
+    assert (psumbook.waves, psumbook.row_words, psumbook.batch_group) == expect, psumbook
+    for plan in (default, psumbook):
+        y = DeviceLayer(inp, plan=plan).gemm()
+        torch.cuda.synchronize()
+        rel = check_against_oracle(y.cpu().numpy(), y_ref, T, f"batch {B} {plan}")
+        assert rel < 6e-4
 
 
 def test_fp32_output_accuracy_at_70b_shape():

@@ -78,9 +78,13 @@ def test_grouped_plans(waves, row_words, k_splits, psum, build):
     (1024, (1000, 896), 4, 1, 8, 32, (16, 2, 1, 4, 0, 2)),
 ])
 def test_grouped_batched_kernel(K, Ns, v, m, B, g, plan):
-    """Groups through the batched kernel (4 batch rows per pass)."""
+    """Groups through the batched kernel (4 batch rows per pass), and under default plans through the centroid kernel
+    where those take it."""
     pl = run_group(K, list(Ns), v, m, B, g, plan=None if plan is None else cg.Plan.make(*plan), seed=7200 + B)
     assert pl.batch_group == 4, pl
+    if pl.centroid_rows:
+        pl.centroid_rows = pl.centroid_splits = 0
+        run_group(K, list(Ns), v, m, B, g, plan=pl, seed=7200 + B)
 
 
 @pytest.mark.parametrize("plan", [(8, 1, 4, 1), (16, 2, 4, 2), (16, 2, 2, 1)])

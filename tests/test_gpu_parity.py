@@ -10,7 +10,7 @@ from oracle.pack_layout import pack_reference
 pytestmark = pytest.mark.gpu
 
 cg = pytest.importorskip("paper_2512_17970_amd")
-from gpu_util import DeviceLayer, Guarded, check_against_oracle, dev, stream  # noqa: E402
+from gpu_util import DeviceLayer, Guarded, check_against_oracle, dev, plans_of, stream  # noqa: E402
 
 
 def say(msg):
@@ -322,11 +322,13 @@ def test_sign_codebook_bit_exact(lo):
     inp.x = rng.integers(-8, 9, (B, K)).astype(np.float16)
     inp.scales = np.ones(N, np.float16)
     y_ref, _ = oracle.gemm(inp.x, inp.codes, inp.codebooks, inp.scales)
-    layer = DeviceLayer(inp, y_fp32=True)
-    y = layer.gemm()
+    for plan in plans_of(case, True):
+        layer = DeviceLayer(inp, plan=plan, y_fp32=True)
+        y = layer.gemm()
+        torch.cuda.synchronize()
+        assert np.array_equal(y.cpu().numpy().astype(np.float64), y_ref)
     yd = layer.dequant()
     torch.cuda.synchronize()
-    assert np.array_equal(y.cpu().numpy().astype(np.float64), y_ref)
     assert np.array_equal(yd.cpu().numpy().astype(np.float64), y_ref)
 
 
@@ -362,27 +364,37 @@ def test_diagnostic_build_gives_the_same_output_and_a_monotone_timeline():
         assert 0 < by["output stored"]["max_us"] < 1000
 
 
-@pytest.mark.parametrize("B,K,N,v,m,g", [(70, 1024, 600, 8, 2, -1), (33, 4 * 200, 257, 4, 1, 32), (64, 2048, 130, 16, 3, -1)])
-def test_batches_above_one_launch(B, K, N, v, m, g):
-    """More than 32 batch rows: consecutive launches of up to 32 rows that share the workspace."""
-    run_case(synth.custom_case(K, N, v, m, B, seed=606 + B, g=g))
+@pytest.mark.parametrize("B,K,N,v,m,g,fp32,centroid", [
+    (70, 1024, 600, 8, 2, -1, False, True), (33, 4 * 200, 257, 4, 1, 32, False, True), (64, 2048, 130, 16, 3, -1, False, True),
+    (70, 2048, 600, 8, 2, 16, False, False), (33, 4 * 300, 257, 4, 4, -1, True, False), (97, 2048, 700, 16, 4, -1, True, False),
+    (65, 1024, 300, 8, 1, 8, True, False)])
+def test_batches_above_one_launch(B, K, N, v, m, g, fp32, centroid):
+    """More than 32 batch rows: one launch of the centroid kernel by default where it takes the format, and consecutive
+    launches of up to 32 rows (the last ragged) of the Psumbook kernels, which share the workspace: by default for formats
+    without the centroid kernel, else for the plan without centroid_rows."""
+    case = synth.custom_case(K, N, v, m, B, seed=606 + B, g=g)
+    plans = plans_of(case, fp32)
+    assert (plans[0].centroid_rows != 0) == centroid and plans[-1].centroid_rows == 0
+    for plan in plans:
+        run_case(case, plan=plan, y_fp32=fp32, dequant=plan is plans[0])
 
 
 @pytest.mark.parametrize("fill", [0, 255, 128])
 def test_constant_codes_extreme_indices(fill):
     """Every code the same index (0, 255 and 128: the ends of the table and the sign bit of the code
     byte): all lanes of a half-wavefront read one Psumbook row, and the byte-permute address assembly
-    sees its extreme values.  Batch 1, 2 (code words reused for a second Psumbook) and 5 (batched kernel)."""
-    for (v, m, B) in [(8, 2, 1), (4, 1, 1), (8, 3, 2), (16, 4, 1), (8, 2, 5)]:
+    sees its extreme values.  Batch 1, 2 (code words reused for a second Psumbook) and 5 (batched kernel), and
+    the centroid kernel where the default plan takes it."""
+    for (v, m, B) in [(8, 2, 1), (4, 1, 1), (8, 3, 2), (16, 4, 1), (8, 2, 5), (16, 4, 3), (4, 2, 20)]:
         case = synth.custom_case(v * 32 * 9 + v * 3, 777, v, m, B, seed=400 + fill)
         inp = synth.generate(case)
         inp.codes = np.full_like(inp.codes, fill)
         say(f"[constant codes {fill}] {case.name}")
         y_ref, T = oracle.gemm(inp.x, inp.codes, inp.codebooks, inp.scales)
-        layer = DeviceLayer(inp)
-        y = layer.gemm()
-        torch.cuda.synchronize()
-        check_against_oracle(y.cpu().numpy(), y_ref, T, f"constant codes {fill} {case.name}")
+        for plan in plans_of(case):
+            y = DeviceLayer(inp, plan=plan).gemm()
+            torch.cuda.synchronize()
+            check_against_oracle(y.cpu().numpy(), y_ref, T, f"constant codes {fill} {case.name} {plan}")
 
 
 def test_wide_dynamic_range_inputs():
@@ -399,14 +411,15 @@ def test_wide_dynamic_range_inputs():
         inp.codebooks = (np.sign(rng.standard_normal(inp.codebooks.shape)) * cmag).astype(np.float16)
         say(f"[dynamic range] {case.name}")
         y_ref, T = oracle.gemm(inp.x, inp.codes, inp.codebooks, inp.scales)
-        layer = DeviceLayer(inp, y_fp32=True)
-        y = layer.gemm()
-        torch.cuda.synchronize()
-        got = y.cpu().numpy().astype(np.float64)
-        assert np.all(np.isfinite(got))
-        assert np.all(np.abs(got - y_ref) <= 1e-5 * T + 1e-30)           # fp32 accumulation: ~K*2^-24 of sum|terms| at worst
-        for b in range(case.B):
-            assert np.linalg.norm(got[b] - y_ref[b]) <= 1e-3 * np.linalg.norm(y_ref[b])
+        for plan in plans_of(case, True):
+            layer = DeviceLayer(inp, plan=plan, y_fp32=True)
+            y = layer.gemm()
+            torch.cuda.synchronize()
+            got = y.cpu().numpy().astype(np.float64)
+            assert np.all(np.isfinite(got))
+            assert np.all(np.abs(got - y_ref) <= 1e-5 * T + 1e-30)       # fp32 accumulation: ~K*2^-24 of sum|terms| at worst
+            for b in range(case.B):
+                assert np.linalg.norm(got[b] - y_ref[b]) <= 1e-3 * np.linalg.norm(y_ref[b])
         yd = layer.dequant()
         torch.cuda.synchronize()
         assert np.all(np.abs(yd.cpu().numpy().astype(np.float64) - y_ref) <= 1e-5 * T + 1e-30)

@@ -1,5 +1,6 @@
-"""GPU parity of the prompt kernel (default plans with more than 32 batch rows and enough workgroups): formats, ragged
-N, K and batch against the CPU oracle, exact on integer cases, non-finite rows kept apart."""
+"""GPU parity of calls with many batch rows under default plans: the prompt kernel (fp16 output, enough workgroups) and the
+centroid kernel's tiles (fp32 output, or fewer): formats, ragged N, K and batch against the CPU oracle, exact on integer
+cases, non-finite rows kept apart."""
 import numpy as np
 import pytest
 import torch
@@ -10,7 +11,7 @@ import synth
 pytestmark = pytest.mark.gpu
 
 cg = pytest.importorskip("paper_2512_17970_amd")
-from gpu_util import DeviceLayer, check_against_oracle  # noqa: E402
+from gpu_util import DeviceLayer, check_against_oracle, exact_on_gpu  # noqa: E402
 
 
 def batch_for(v, m, g, N, extra):
@@ -23,8 +24,8 @@ def batch_for(v, m, g, N, extra):
 @pytest.mark.parametrize("v,m,g", [(8, 2, -1), (8, 1, -1), (4, 1, -1), (8, 3, -1), (8, 4, -1), (4, 2, -1), (8, 2, 128), (8, 1, 512), (4, 1, 128), (4, 2, 256), (8, 2, 32), (8, 1, 64), (4, 1, 32), (8, 3, 64), (4, 2, 64)])
 def test_formats(v, m, g, N, extra):
     """K of one to three units with an odd number of steps or a ragged last one; N that 8, 128 or 1024 does not divide
-    (scalar and vector stores of y), both output types."""
-    for units, fp32 in ((1, True), (3, False)):
+    (scalar and vector stores of y); fp16 output through the prompt kernel, fp32 output through tiles."""
+    for units, fp32 in ((1, True), (1, False), (3, False)):
         K = max(g, 32 * v) * units + (g if g > 0 else 5 * v)
         case = synth.custom_case(K, N, v, m, batch_for(v, m, g, N, extra), seed=3600 + N + units, g=g)
         print(f"[prompt] {case.name}", flush=True)
@@ -48,17 +49,36 @@ def test_integer_case_is_exact_and_rows_are_independent():
     inp.x = rng.integers(-8, 9, (B, K)).astype(np.float16)
     inp.scales = np.ones(N, np.float16)
     y_ref, _ = oracle.gemm(inp.x, inp.codes, inp.codebooks, inp.scales)
-    y = DeviceLayer(inp, y_fp32=True).gemm()
-    torch.cuda.synchronize()
-    assert np.array_equal(y.cpu().numpy().astype(np.float64), y_ref)
+    y = {}
+    for fp32 in (True, False):
+        y[fp32] = DeviceLayer(inp, y_fp32=fp32).gemm()
+        torch.cuda.synchronize()
+        assert np.array_equal(y[fp32].cpu().numpy(), y_ref.astype(np.float32 if fp32 else np.float16))
     inp.x = inp.x.copy()
     inp.x[row, 3] = np.nan
     inp.x[row, 200] = np.inf
-    z = DeviceLayer(inp, y_fp32=True).gemm()
-    torch.cuda.synchronize()
-    others = torch.arange(B, device=z.device) != row
-    assert torch.equal(z[others], y[others])
-    assert not bool(torch.isfinite(z[row]).any().item())
+    for fp32 in (True, False):
+        z = DeviceLayer(inp, y_fp32=fp32).gemm()
+        torch.cuda.synchronize()
+        others = torch.arange(B, device=z.device) != row
+        assert torch.equal(z[others], y[fp32][others])
+        assert not bool(torch.isfinite(z[row]).any().item())
+
+
+@pytest.mark.parametrize("steps", [20, 21, 64, 65])
+@pytest.mark.parametrize("v,m,g", [(8, 2, -1), (4, 1, -1), (4, 2, -1), (8, 3, -1), (8, 2, 32), (8, 1, 128), (4, 1, 128)])
+def test_long_k(v, m, g, steps):
+    """Many turns of the double-buffered loop, odd and even, against float64: fp16 output (its rounding: 2.1e-4) and fp32
+    output through tiles (two levels of short sums: below 1.3e-7 in these formats, 2e-7 the bound of its other tests)."""
+    K, N = 128 * steps, 1500
+    case = synth.custom_case(K, N, v, m, batch_for(v, m, g, N, 5), seed=3650 + steps, g=g)
+    print(f"[prompt] {case.name}", flush=True)
+    inp = synth.generate(case)
+    for fp32, bound in ((False, 3e-4), (True, 2e-7)):
+        layer = DeviceLayer(inp, y_fp32=fp32)
+        ref = exact_on_gpu(layer, inp)
+        err = ((layer.gemm().double() - ref).norm() / ref.norm()).item()
+        assert err < bound, (fp32, err)
 
 
 @pytest.mark.parametrize("B", [33, 64, 96, 200])

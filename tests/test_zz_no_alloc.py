@@ -12,7 +12,7 @@ import synth
 pytestmark = pytest.mark.gpu
 
 cg = pytest.importorskip("paper_2512_17970_amd")
-from gpu_util import DeviceLayer, check_against_oracle, stream  # noqa: E402
+from gpu_util import DeviceLayer, check_against_oracle, plans_of, stream  # noqa: E402
 
 
 def static_call(layer):
@@ -25,9 +25,11 @@ def static_call(layer):
 def test_static_workspace_entry_point_matches_the_workspace_one():
     cases = [synth.custom_case(8 * 32 * 9, 1500, 8, 2, 1, seed=901),            # several K ranges
              synth.custom_case(8 * 32 * 3, 300, 8, 2, 1, seed=902),             # smaller, right after
-             synth.custom_case(4 * 32 * 5 + 8, 700, 4, 1, 6, seed=903),         # batched kernel, ragged K
+             synth.custom_case(4 * 32 * 5 + 8, 700, 4, 1, 6, seed=903),         # centroid kernel, ragged K
+             synth.custom_case(4 * 32 * 5 + 8, 700, 4, 1, 6, seed=903),         # batched kernel
              synth.custom_case(2048, 1030, 8, 2, 2, seed=904, g=64)]            # group scales
-    plans = [cg.Plan.make(8, 2, 3, 1), cg.Plan.make(8, 1, 3, 1), None, None]
+    plans = [cg.Plan.make(8, 2, 3, 1), cg.Plan.make(8, 1, 3, 1), *plans_of(cases[2]), None]
+    assert plans[2].centroid_rows and not plans[3].centroid_rows
     layers = []
     for case, plan in zip(cases, plans):
         print(f"[static] {case.name} plan={plan}", flush=True)
