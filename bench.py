@@ -60,7 +60,8 @@ def parse():
                     help="time an ablation build of the library instead (libcodegemm_ablate_<mask>.so; outputs are wrong on "
                          "purpose): 2 no gather, 4 no Psumbook build after the first, 8 no exchange between workgroups; "
                          "6, 8 and 14 are built by default")
-    ap.add_argument("--plan", default="", help="override plan for every shape: waves,row_words,k_splits[,batch_group[,psum_dtype]] (psum_dtype 1 = fp16 Psumbook)")
+    ap.add_argument("--plan", default="", help="override plan for every shape: waves,row_words,k_splits[,batch_group[,psum_dtype"
+                    "[,build_waves[,centroid_rows,centroid_splits]]]] (psum_dtype 1 = fp16 Psumbook)")
     ap.add_argument("--psum-fp16", action="store_true",
                     help="every shape's default plan with the Psumbook stored as fp16 (batch 1; the group-scale shapes that "
                          "default to 16 wavefronts x 2 row words run with 1 row word)")
@@ -368,7 +369,7 @@ def phases_report(torch, cg, layers):
 
 
 def sweep_report(torch, cg, synth, cases, launch):
-    """Cold time of every offered plan shape and a range of K-split counts, per shape."""
+    """Cold time of every offered plan shape of both kinds of kernels and a range of K-split counts, per shape."""
     out = {}
     for case in cases:
         d = cg.Desc.make(case.B, case.K, case.N, case.v, case.m, g=case.g)
@@ -398,11 +399,35 @@ def sweep_report(torch, cg, synth, cases, launch):
                 log(f"  {case.name} waves={waves}{'(14+2)' if bw else ''} row_words={rw} k_splits={ks} psum={'fp16' if psum else 'fp32'} workgroups={nblk * ks}: {us:.2f} us")
                 del L
                 torch.cuda.empty_cache()
+        # the centroid kernel: block heights and K ranges (a height is raised where the problem needs a higher one)
+        takes = not (case.v == 4 and case.m > 2) and (case.g < 0 or case.g >= (8 if case.v == 4 else 4) * case.v)
+        for rows in (32, 64, 128) if takes else ():
+            for ks in (1, 2, 3, 4, 6, 8, 16, 32):
+                if ks > nkt or -(-case.N // rows) * ks > 1024:
+                    continue
+                plan = cg.Plan.from_buffer_copy(default)
+                plan.centroid_rows, plan.centroid_splits, plan.k_splits = rows, ks, max(ks, default.k_splits)
+                L = Layer(cg, torch, synth, case, plan, copies_bytes=COLD_BYTES // 2)
+                call = graph_of(torch, L.gemm, 50).replay if launch == "graph" else (lambda L=L: [L.gemm() for _ in range(50)])
+                call(); call()
+                us = min(time_region(torch, call, 1) for _ in range(4)) * 1e3 / 50
+                res.append({"centroid_rows": rows, "centroid_splits": ks, "workgroups": -(-case.N // rows) * ks, "us_cold": us})
+                log(f"  {case.name} centroid_rows={rows} centroid_splits={ks} workgroups={-(-case.N // rows) * ks}: {us:.2f} us")
+                del L
+                torch.cuda.empty_cache()
         res.sort(key=lambda r: r["us_cold"])
         out[case.name] = {"default": repr(default), "plans": res}
-        log(f"BEST {case.name}: " + ", ".join(f"({r['waves']},{r['row_words']},{r['k_splits']},{r['psum_dtype']}) {r['us_cold']:.2f}" for r in res[:3])
-            + f"   default {default}")
+        name = lambda r: (f"centroid {r['centroid_rows']},{r['centroid_splits']}" if "centroid_rows" in r else
+                          f"{r['waves']},{r['row_words']},{r['k_splits']},{r['psum_dtype']}")
+        log(f"BEST {case.name}: " + ", ".join(f"({name(r)}) {r['us_cold']:.2f}" for r in res[:3]) + f"   default {default}")
     print(json.dumps({"sweep": out}))
+
+
+def kernel_of(plan, batch):
+    """Name of the kernel that a layer runs under its plan."""
+    if plan.centroid_rows and plan.psum_dtype == 0:
+        return "cg::gemm_centroid_kernel" if batch <= 32 else "cg::gemm_centroid_kernel or cg::gemm_prompt_kernel"
+    return "cg::gemm_batch_kernel" if plan.batch_group == 4 else "cg::gemm_kernel"
 
 
 def read_traffic(key):
@@ -483,11 +508,20 @@ def main():
     launches = len(layers) * args.steps
     value = step_bytes / (ms_per_step * 1e-3) * 1e-9
     us_per_launch = ms * 1e3 / launches
+    def operands_of(kernels, layers):
+        kinds = ["centroids times x on the matrix cores"] if any("centroid" in k for k in kernels) else []
+        if any("centroid" not in k for k in kernels):
+            kinds.append("f16 Psumbook" if any(L.plan.psum_dtype for L in layers) else "f32 Psumbook")
+        return " or ".join(kinds)
+
+    kernels = sorted({kernel_of(L.plan, L.case.B) for L in layers})
+    recorded = kernels == ["cg::gemm_kernel"]              # what the recorded traffic is of
     roofline = {"bound": "hbm", "achieved": value, "peak": HBM_PEAK_GBPS, "unit": "GB/s",
-                "frac": value / HBM_PEAK_GBPS, "traffic": read_traffic(key),
+                "frac": value / HBM_PEAK_GBPS, "traffic": read_traffic(key) if recorded else None,
                 "traffic_source": "profiles/gemm_kernel_hbm_traffic_pmc.txt: separate rocprofv3 --pmc runs of this "
-                                  "command (FETCH_SIZE, WRITE_SIZE), not measured in this run",
-                "kernel": "cg::gemm_kernel", "avg_launch_us": us_per_launch,
+                                  "command (FETCH_SIZE, WRITE_SIZE), not measured in this run" if recorded else
+                                  "not recorded for these kernels",
+                "kernel": ", ".join(kernels), "avg_launch_us": us_per_launch,
                 "algorithmic_bytes_per_launch": step_bytes / len(layers)}
     out = {
         "metric": "effective HBM GB/s on compressed bytes, Llama-3-70B layer shapes, bs=1, 2-bit (us/call in config)",
@@ -495,7 +529,7 @@ def main():
         "ms_per_step": ms_per_step, "higher_is_better": True, "scaling": "weak", "vs_baseline": None,
         "dtype": "f32", "data": "synthetic",
         "config": {"workload": f"{key}: " + ", ".join(c.name for c in cases),
-                   "calls_per_step": len(layers), "operands": f"f16 x, codebooks, scales; u8 codes; {'f16' if args.psum_fp16 else 'f32'} Psumbook, f32 accumulation; f16 y", "us_per_step": ms_per_step * 1e3,
+                   "calls_per_step": len(layers), "operands": f"f16 x, codebooks, scales; u8 codes; {operands_of(kernels, layers)}, f32 accumulation; f16 y", "us_per_step": ms_per_step * 1e3,
                    "timed_runs": len(runs), "us_per_step_min": min(runs) / args.steps * 1e3,
                    "us_per_step_max": max(runs) / args.steps * 1e3, "launch": args.launch,
                    "cold_copies_bytes_per_shape": COLD_BYTES},
