@@ -244,7 +244,8 @@ int codegemm_gemm(const codegemm_desc *desc, const codegemm_plan *plan,
  * layers share in_features, the format (v, m, group_size), the batch and the
  * flags; each has its own out_features, packed codes, codebooks, scales and y.
  * Member i's result is bit-identical to codegemm_gemm on that layer alone with
- * the same plan.
+ * the same plan (but for a plan with centroid_rows whose blocks or K ranges the
+ * summed height does not allow: above two million rows, or 16384 blocks).
  *   desc->out_features   the SUM of the members' out_features (checked);
  *   plan                 applies to every member; NULL = codegemm_default_plan(desc),
  *                        which suits since the launch fills the chip like one

@@ -51,7 +51,7 @@ struct Geometry {
                     // (32 * NW * RPL in the batched kernel, BG = 4)
     int BG;         // batch rows per pass over the codes
     int RB;         // rows of a block of the centroid kernel (32, 64 or 128), or 0: one of the Psumbook kernels
-    bool prompt;    // more than kBatchPerLaunch batch rows, and enough of them for the prompt kernel (RB != 0 only)
+    bool prompt;    // the prompt kernel: RB != 0, fp16 output, more than kBatchPerLaunch batch rows and enough of them
     int NGR;        // ceil(N / 128) granules
     int NBLK;       // row blocks = workgroups along N: NGR over the granules per workgroup, rounded up
     int NKT;        // ceil(J / 32) K tiles
