@@ -4,13 +4,14 @@
 //
 // A lookup is paid once per 64 codes whatever the batch, so with NT tiles of 16 batch rows per
 // wavefront the matrix cores take over as the bound (NT = 4: 32 lookups, 64 for v = 4, and 128 MFMAs
-// per step and codebook; counters at 8192^2 v8 m2 batch 2048: matrix cores 83 % busy, LDS 33 %).  Each of the 8 wavefronts owns 128 rows and streams through the whole of K, there is
-// nothing to sum across wavefronts or workgroups, and x is staged in LDS for all of them: one
-// step (16 chunks of 16 bytes, 128 elements) of 16 NT batch rows, double-buffered, one barrier per
+// per step and codebook; counters at 8192^2 v8 m2 batch 2048: matrix cores 83 % busy, LDS 33 %).  Each
+// of the 8 wavefronts owns 128 rows and streams through the whole of K, there is nothing to sum
+// across wavefronts or workgroups, and x is staged in LDS for all of them: one step (16 chunks of 16 bytes, 128 elements) of 16 NT batch rows, double-buffered, one barrier per
 // step.  Measured: 8192^2 v8 m2 at batch 2048 366 us, 64 launches of 32 rows before 2584 (the two
 // codebooks make it 550 GFLOP of MFMAs: 1.50 PFLOP/s; this instruction alone, in registers, reaches
 // 1.87 on this card); 4096->28672 v4 m1 g128 at batch 500 121 us, 1519 before.  Chunk c of
-// row r lies at column c ^ (r % 16) of its 256-byte row, so that both the stores (16 lanes along a row) and the operand reads (16 lanes down 16 rows) touch 16 different columns.
+// row r lies at column c ^ (r % 16) of its 256-byte row, so that the stores (16 lanes along a row) and the operand reads (16
+// lanes down 16 rows) touch 16 different columns each; the reads still count 4 conflict cycles each (8 LDS cycles, not 4).
 #pragma once
 
 #include "gemm_centroid_impl.h"
