@@ -80,6 +80,26 @@ def test_default_plan_asks_for_no_more_workspace(v, m, g):
             assert cg.codegemm_workspace_bytes(d, p) == cg.codegemm_workspace_bytes(d) <= cg.codegemm_workspace_bytes(d, q), (B, K, N)
 
 
+@pytest.mark.parametrize("v,m,g", [(8, 2, -1), (4, 1, 128), (4, 1, 32), (8, 1, -1), (8, 3, -1), (16, 4, -1), (8, 2, 128), (8, 2, 32)])
+def test_default_blocks_and_ranges_of_few_rows(v, m, g):
+    """Up to 4 batch rows: one round of 256 workgroups wherever a block height allows it, K ranges that are powers of two and
+    all of one length but the last (two and four meet pairwise, three, five or seven would take the slower ticket)."""
+    seen = set()
+    for B in (1, 2, 3, 4):
+        for N in (512, 700, 1300, 1500, 2000, 2900, 4096, 8192, 8193, 10000, 14336, 16384, 17000, 20000, 28672):
+            for K in (512, 1024, 2560, 4096, 5120, 7168, 9216, 12288, 18944, 28672):
+                for fp32 in (False, True):
+                    p = cg.codegemm_default_plan(cg.Desc.make(B, K, N, v, m, y_fp32=fp32, g=g))
+                    if not p.centroid_rows:
+                        continue
+                    blocks, s, nkt = -(-N // p.centroid_rows), p.centroid_splits, -(-(K // v) // 32)
+                    assert blocks <= 256 or p.centroid_rows == 128, (B, K, N, p)
+                    assert p.centroid_rows == 32 or -(-N // (p.centroid_rows // 2)) > 256, (B, K, N, p)
+                    assert s & (s - 1) == 0 and -(-nkt // -(-nkt // s)) == s and (s == 1 or s * blocks <= 256), (B, K, N, p)
+                    seen.add((p.centroid_rows, s))
+    assert {r for r, _ in seen} == {32, 64, 128} and {1, 2, 4, 8} <= {s for _, s in seen}
+
+
 def test_default_plan_keeps_the_other_kernels_where_they_win():
     plan = lambda B, K, N, v, m, g=-1: cg.codegemm_default_plan(cg.Desc.make(B, K, N, v, m, g=g))
     assert plan(1, 8192, 28672, 8, 2).centroid_rows == 0 and plan(1, 2048, 2048, 8, 2).centroid_rows == 0
