@@ -99,10 +99,10 @@ __device__ __forceinline__ void row_exchange(uint32_t& a, uint32_t& b)
 // not here.  Measured on random operands (relative rms, 1e-7): an MFMA of 32 products 0.44, two on one accumulator 0.57,
 // four 0.76; the Psumbook's 8 products 0.31.  The Psumbook kernels spread K over 32 lanes (16 in the batched kernel) and
 // their K ranges, more than the sub-vectors, slices and ranges here, so chains have to be shorter and sums have a second
-// level.  A result tile takes two MFMAs (GS = 4: one, the tiles of a round being added before they are scaled; two above 8
-// batch rows and the whole round for v = 4, whose Psumbook adds twice as often) and is then added to sums of its own, which
+// level.  A result tile takes two MFMAs (three codebooks at 5 to 8 rows: three; GS = 4: one, the tiles of a round being added
+// before they are scaled; two above 8 batch rows and the whole round for v = 4, whose Psumbook adds twice as often) and is then added to sums of its own, which
 // go to totals after 8 to 16 additions.  Error against that of the Psumbook plan of the same call, fp32 output, geometric
-// mean over some hundred random sizes per format and power of two of K: at most 1.00, 0.4 to 0.9 from K = 4096 on
+// mean over some hundred random sizes per format and power of two of K: at most 1.00, 0.4 to 0.95 from K = 4096 on
 // (8192^2, batch 512, 1e-7: v8 m2 1.06 against 1.32, v8 m1 g128 0.95 against 1.24, v8 m2 g32 1.01 against 1.60).  It costs
 // up to 10 % against chains of four (8192^2 v8 m2 batch 4 11.2 -> 11.1 us, 4120->11111 v8 m3 batch 5 13.60 -> 13.80).
 template <int M, int V, int SB, int NT, int RW, int KW, int D, int GS, bool ONE>
@@ -133,8 +133,8 @@ __global__ void __launch_bounds__(RW * KW * 64) gemm_centroid_kernel(CG_HEAD_PAR
     auto starts = [](int k) constexpr -> bool { return GS != 0 && k % ROUND % LINK == 0; };
     auto ends = [](int k) constexpr -> bool { return GS != 0 && (k % ROUND % LINK == LINK - 1 || k % ROUND == ROUND - 1); };
     constexpr bool PARTS = GS == 4 && LINK == 1 && ROUND > 1;       // the tiles of a round are added before they are scaled
-    // SHORT: the sums are moved to the totals after 8 to 12 additions (SB = 2, with more wavefronts and lanes to spread K
-    // over than SB = 1 and fewer batch rows to pay for it than SB = 4: 12 to 16): every step, or every few turns of the ring
+    // SHORT: the sums are moved to the totals after 8 to 12 additions (SB = 2, whose error leaves room for it: 12 to 16):
+    // every step, or every few turns of the ring
     constexpr int ADDS = (NSB / ROUND) * (PARTS ? 1 : (ROUND + LINK - 1) / LINK);            // per step
     constexpr int AIM = SB == 2 ? 16 : 8;
     constexpr int TURNS = ADDS >= AIM ? 0 : D * ADDS >= AIM ? 1 : D * ADDS >= AIM / 2 ? 2 : 4;
