@@ -564,6 +564,19 @@ __global__ void __launch_bounds__(RW * KW * 64) gemm_centroid_kernel(CG_HEAD_PAR
     finish_block<THREADS, BT, RB>(p, mm, totals, flag, tid, blk, ks, b0);
 }
 
+// Steps in the load ring of the kernels with one tile of batch rows: four, but three or two where that is what brings a lane's
+// registers down to 128.  One or two codebooks of short vectors take 64 KB of LDS, so two workgroups then share a compute unit, and
+// each fills the other's first loads, table and exchange (v8 m2 g128, 4 rows, two rounds of 128-row blocks at 57344 rows: 134
+// registers 46.4 us, 122 registers 38.2; v4 m1 g128, 8 rows, 4096->28672, 164 and 124: 13.3 and 12.6).  Where both depths fit, the
+// deeper one wins (8B block, v4 m1 g128, one row: three steps 30.4 us, four 28.8).
+__host__ __device__ constexpr int centroid_ring(int m, int v, int sb, int gs, bool one)
+{
+    const bool shared = v < 16 && m <= 2;              // the table leaves room for a second workgroup
+    if (sb == 4) return shared && (m == 2 ? gs == 1 || (gs == 2 && v == 8) : !one && (gs == 4 || (v == 4 && gs == 2))) ? 3 : 4;
+    if (shared && m == 1 && v == 4 && gs <= 1) return gs == 1 ? 2 : 3;
+    return gs == 2 || gs == 4 ? 3 : 4;
+}
+
 template <int M, int V, int SB, int NT, int RW, int KW, int D, int GS, bool ONE = false>
 int launch_gemm_centroid_one(const Geometry& g, const GemmParams& p, hipStream_t stream)
 {
@@ -584,18 +597,19 @@ int launch_gemm_centroid_one(const Geometry& g, const GemmParams& p, hipStream_t
 template <int M, int V, int GS>
 int launch_gemm_centroid_v(const Geometry& g, const GemmParams& p, hipStream_t stream)
 {
+    constexpr int D1 = centroid_ring(M, V, 4, GS, true), D4 = centroid_ring(M, V, 4, GS, false), D2 = centroid_ring(M, V, 2, GS, false);
     switch (g.BG) {
         case 1:
-            if (g.RB == 128) return launch_gemm_centroid_one<M, V, 4, 1, 4, 2, 4, GS, true>(g, p, stream);
-            if (g.RB == 64) return launch_gemm_centroid_one<M, V, 4, 1, 2, 4, 4, GS, true>(g, p, stream);
-            return launch_gemm_centroid_one<M, V, 4, 1, 1, 8, 4, GS, true>(g, p, stream);
+            if (g.RB == 128) return launch_gemm_centroid_one<M, V, 4, 1, 4, 2, D1, GS, true>(g, p, stream);
+            if (g.RB == 64) return launch_gemm_centroid_one<M, V, 4, 1, 2, 4, D1, GS, true>(g, p, stream);
+            return launch_gemm_centroid_one<M, V, 4, 1, 1, 8, D1, GS, true>(g, p, stream);
         case 4:
-            if (g.RB == 128) return launch_gemm_centroid_one<M, V, 4, 1, 4, 2, 4, GS>(g, p, stream);
-            if (g.RB == 64) return launch_gemm_centroid_one<M, V, 4, 1, 2, 4, 4, GS>(g, p, stream);
-            return launch_gemm_centroid_one<M, V, 4, 1, 1, 8, 4, GS>(g, p, stream);
+            if (g.RB == 128) return launch_gemm_centroid_one<M, V, 4, 1, 4, 2, D4, GS>(g, p, stream);
+            if (g.RB == 64) return launch_gemm_centroid_one<M, V, 4, 1, 2, 4, D4, GS>(g, p, stream);
+            return launch_gemm_centroid_one<M, V, 4, 1, 1, 8, D4, GS>(g, p, stream);
         case 8:
-            if (g.RB == 128) return launch_gemm_centroid_one<M, V, 2, 1, 2, 4, GS == 2 || GS == 4 ? 3 : 4, GS>(g, p, stream);
-            if (g.RB == 64) return launch_gemm_centroid_one<M, V, 2, 1, 1, 8, GS == 2 || GS == 4 ? 3 : 4, GS>(g, p, stream);
+            if (g.RB == 128) return launch_gemm_centroid_one<M, V, 2, 1, 2, 4, D2, GS>(g, p, stream);
+            if (g.RB == 64) return launch_gemm_centroid_one<M, V, 2, 1, 1, 8, D2, GS>(g, p, stream);
             if constexpr (V < 16) return launch_gemm_centroid_one<M, V, 4, 2, 1, 8, 3, GS>(g, p, stream);
             break;
         case 16:
