@@ -51,6 +51,7 @@ struct Geometry {
                     // (32 * NW * RPL in the batched kernel, BG = 4)
     int BG;         // batch rows per pass over the codes
     int RB;         // rows of a block of the centroid kernel (32, 64 or 128), or 0: one of the Psumbook kernels
+    bool staged;    // the centroid kernel with codes and x staged in LDS (RB = 128)
     bool prompt;    // the prompt kernel: RB != 0, fp16 output, more than kBatchPerLaunch batch rows and enough of them
     int NGR;        // ceil(N / 128) granules
     int NBLK;       // row blocks = workgroups along N: NGR over the granules per workgroup, rounded up
@@ -92,7 +93,8 @@ __host__ __device__ inline size_t packed_offset(int c, int n, int j, int m, int 
 }
 
 void resolve_centroid(const codegemm_desc* d, long long n, codegemm_plan* p);        // the centroid fields as they hold for n rows of d's format
-int make_geometry(const codegemm_desc* d, const codegemm_plan* plan, Geometry* g);   // status
+void raise_to_staged(const codegemm_desc* d, long long n, codegemm_plan* p);         // taller blocks where the staged kernel is the faster one
+int make_geometry(const codegemm_desc* d, const codegemm_plan* plan, Geometry* g, bool fitted_plan = false);   // status; fitted_plan: the two above have been applied
 size_t workspace_counter_bytes(const Geometry& g);   // the fixed area in front of the partial sums: counters, then pair words
 size_t workspace_need(const Geometry& g);            // bytes of workspace of one launch
 size_t pair_words(const Geometry& g);                // 64-bit words the pairwise reduction of this problem needs; 0: not offered

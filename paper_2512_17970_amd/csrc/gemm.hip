@@ -244,10 +244,11 @@ static int group_geometry(const codegemm_desc* desc, const codegemm_plan* plan, 
     for (int i = 0; i < count; ++i) total += out_features[i];
     codegemm_plan fitted = *plan;                      // to the whole launch, so that all members run the same kernel
     resolve_centroid(desc, total, &fitted);
+    raise_to_staged(desc, total, &fitted);
     for (int i = 0; i < count; ++i) {
         codegemm_desc d = *desc;
         d.out_features = out_features[i];
-        const int st = make_geometry(&d, &fitted, &members[i]);
+        const int st = make_geometry(&d, &fitted, &members[i], true);
         if (st) return st;
     }
     if (total != desc->out_features) return CODEGEMM_INVALID_ARG;

@@ -15,6 +15,7 @@
 #pragma once
 
 #include "gemm_centroid_impl.h"
+#include "gemm_staged_impl.h"
 
 namespace cg {
 
@@ -336,6 +337,9 @@ int launch_gemm_centroid_mv(const Geometry& g, const GemmParams& p, hipStream_t 
         if (g.prompt) {
             return launch_gemm_prompt_one<M, V, prompt_tiles(M, V, GS != 0), GS>(g, p, stream);
         }
+    }
+    if constexpr (GS <= 1 && ((V == 8 && M <= 2) || (V == 4 && M == 1))) {
+        if (g.staged) return launch_gemm_staged<M, V, GS>(g, p, stream);
     }
     return launch_gemm_centroid_v<M, V, GS>(g, p, stream);
 }

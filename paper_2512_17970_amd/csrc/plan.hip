@@ -59,6 +59,43 @@ static int centroid_min_rows(const codegemm_desc* d)
     return d->batch <= 4 ? 32 : d->batch <= 8 ? 64 : 128;      // v = 16: one MFMA per lookup (registers)
 }
 
+// Batch rows of a workgroup of the kernel that stages codes and x in LDS, or 0: the centroid kernel.  Blocks of 128 rows, fp16
+// output, one or two codebooks of short vectors, groups that hold a step of 16 chunks.  `range` is the K of a workgroup.  Measured
+// (us back to back, centroid kernel / here; 128-row blocks):
+//  * Up to 4 rows with group scales: 8192->28672 v8 m2 22.2 / 19.1, v8 m1 16.0 / 13.6, v4 m1 17.0 / 15.9, 28672->8192 v8 m2 in four
+//    ranges 22.6 / 19.5; with little K the centroid kernel's second workgroup on a compute unit is worth more (2048->28672 8.6 /
+//    8.8, 8192->8192 in four ranges 10.5 / 10.9).  One scale per row ties or loses (33.7 / 35.4): nothing is picked or scaled there.
+//  * 5 to 16 rows, in tiles of 16 (of 8 when v8 m1 has group scales, whose 16 rows do not fit): 8192->28672 v8 m2 8 rows 23.6 / 22.0, g128
+//    25.6 / 23.3; 4096->28672 v8 m2 16 rows 16.2 / 14.9, v4 m1 13.8 / 11.5, g128 14.4 / 12.4.
+//  * 17 to 32 rows: two tiles of 16 where they fit (4096->28672 v8 m2 24.1 / 22.0, v4 m1 19.7 / 15.9), one per workgroup with
+//    group scales.
+static int staged_batch(const codegemm_desc* d, int rows, int range)
+{
+    const int v = d->vec_len, m = d->num_codebooks, b = d->batch;
+    const bool grouped = d->group_size > 0, wide = v == 8 && m == 1;
+    if (rows != 128 || (d->flags & CODEGEMM_FLAG_Y_FP32) || short_groups(d) || !((v == 8 && m <= 2) || (v == 4 && m == 1))) return 0;
+    if (b <= 4) return b > 1 && grouped && range >= 3072 ? 4 : 0;
+    if (wide && grouped) return b <= 8 ? 8 : 0;
+    if (b <= 16 || grouped) return 16;
+    return wide ? 0 : 32;
+}
+
+// 2 to 4 rows with group scales: blocks of 128 rows in two or four K ranges on the staged kernel instead of lower ones on the
+// centroid kernel, where these fill the chip and leave every workgroup a long K (3200 random sizes, 160 to 256 workgroups, time
+// here / of the lower blocks at 4096, 6144, 8192, 10240 and 12288 elements per workgroup: v8 m1 0.99, 0.92, 0.88, 0.85, 0.83; v8 m2 1.03, 0.98,
+// 0.94, 0.93, 0.91; v4 m1 1.08 to 1.0: left out).  n: rows of all layers of a launch.
+void raise_to_staged(const codegemm_desc* d, long long n, codegemm_plan* p)
+{
+    if (p->centroid_rows == 0 || p->centroid_rows == 128 || d->batch < 2 || d->vec_len != 8 || d->group_size < 0) return;
+    const long long blocks = (n + 127) / 128;
+    const int splits = 4 * blocks <= 256 ? 4 : 2, nkt = ceil_div(d->in_features / d->vec_len, kSlots);
+    if (d->batch > 4 || splits * blocks < 160 || splits * blocks > 256 || splits > p->k_splits || splits > nkt) return;
+    const int range = ceil_div(nkt, splits) * kSlots * d->vec_len;
+    if (range < (d->num_codebooks == 1 ? 6144 : 7168) || !staged_batch(d, 128, range)) return;
+    p->centroid_rows = 128;
+    p->centroid_splits = splits;
+}
+
 // A plan made for one batch, output type or format of a layer serves the others too, as its Psumbook fields do: blocks
 // become as high as this problem's registers and grid ask for, and where the centroid kernel does not take the format
 // the Psumbook fields hold, and so they do for an fp16 Psumbook.  There are no more K ranges than k_splits, and than the
@@ -368,7 +405,7 @@ static void choose_plan(const codegemm_desc* d, codegemm_plan* p)
     p->centroid_splits = splits;
 }
 
-int make_geometry(const codegemm_desc* d, const codegemm_plan* plan, Geometry* g)
+int make_geometry(const codegemm_desc* d, const codegemm_plan* plan, Geometry* g, bool fitted_plan)
 {
     int st = validate_desc(d);
     if (st) return st;
@@ -381,6 +418,7 @@ int make_geometry(const codegemm_desc* d, const codegemm_plan* plan, Geometry* g
     if (st) return st;
     codegemm_plan fitted = *plan;
     resolve_centroid(d, d->out_features, &fitted);
+    if (!fitted_plan) raise_to_staged(d, d->out_features, &fitted);
     plan = &fitted;
     // larger batches run as several launches of the Psumbook kernels, as one of the centroid kernels
     g->B = (d->batch < kBatchPerLaunch || plan->centroid_rows) ? d->batch : kBatchPerLaunch;
@@ -412,6 +450,9 @@ int make_geometry(const codegemm_desc* d, const codegemm_plan* plan, Geometry* g
         if (g->B > kBatchPerLaunch && g->NKS > room) g->NKS = ranges(room > 0 ? room : 1);
     }
     g->KPW = ceil_div(g->NKT, g->NKS);
+    const int staged = g->RB ? staged_batch(d, g->RB, g->KPW * kSlots * g->v) : 0;
+    g->staged = staged != 0;
+    if (staged) g->BG = staged;
     // The prompt kernel's workgroups take 1024 rows of W and 64 (with group scales 32) batch rows and all of K: worth it
     // once they are enough to fill the chip.  fp32 output needs shorter sums than it has (8192^2 v8 m1 g128 batch 512: 2.9e-7
     // of 64 bits, tiles of the centroid kernel 0.95e-7, Psumbook kernels 1.24e-7; 141, 156 and 493 us).

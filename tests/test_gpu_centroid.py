@@ -262,3 +262,31 @@ def test_fp32_output_is_no_further_from_64_bits_than_the_psumbook_kernels(v, m, 
     layer.plan.centroid_rows = layer.plan.centroid_splits = 0
     then = err(layer.gemm())
     assert now <= 1.03 * then, (now, then)
+
+
+@pytest.mark.parametrize("v,m,g,B", [(8, 2, -1, 5), (8, 2, -1, 16), (8, 2, -1, 17), (8, 2, -1, 33), (4, 1, -1, 7), (4, 1, -1, 32), (8, 1, -1, 16), (8, 2, 128, 2), (8, 2, 256, 4),
+                                     (8, 2, 128, 9), (8, 1, 128, 3), (8, 1, 256, 8), (4, 1, 128, 4), (4, 1, 128, 16), (4, 1, 256, 20)])
+def test_staged_operands(v, m, g, B):
+    """128-row blocks, fp16 output: codes and x pass through a ring of stages (8 or 16 chunks of 16 bytes of x) in LDS.  Slices of 0, 1,
+    2 .. stages per wavefront, a last stage that the rows of x end inside of (at every number of chunks, half a chunk for v = 4)
+    or that lies wholly behind them, K ranges (from 3072 elements on with up to 4 rows, else the centroid kernel), ragged N."""
+    unit = max(g, v)
+    Ks = [v, 32 * v, 3072, 3072 + 64 * v, 8192] + [2048 + c * v for c in (1, 2, 7, 9, 15, 17, 31, 33)]
+    for K in sorted({max(unit, K // unit * unit) for K in Ks}):
+        case = synth.custom_case(K, 200, v, m, B, seed=3400 + K, g=g)
+        for splits in (1, 2, 5):
+            run(case, 128, splits)
+
+
+def test_staged_operands_leave_the_neighbours_of_x_alone():
+    """The last row of x is followed by other memory, here NaN: what a stage reads past the end of a row counts for nothing."""
+    for v, m, K, B in ((8, 2, 1032, 6), (8, 1, 1096, 13), (4, 1, 1028, 16), (8, 2, 2056, 31)):
+        inp = synth.generate(synth.custom_case(K, 130, v, m, B, seed=3500 + K))
+        y_ref, T = oracle.gemm(inp.x, inp.codes, inp.codebooks, inp.scales)
+        layer = DeviceLayer(inp, plan=plan_of(inp.case, 128, 1))
+        wide = torch.full((B * K + 4096,), float("nan"), dtype=torch.float16, device="cuda")
+        wide[:B * K] = torch.from_numpy(inp.x.reshape(-1)).cuda()
+        layer.x = wide[:B * K].view(B, K)
+        y = layer.gemm()
+        torch.cuda.synchronize()
+        check_against_oracle(y.cpu().numpy(), y_ref, T, inp.case.name)
