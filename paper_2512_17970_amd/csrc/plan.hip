@@ -1,4 +1,6 @@
 // Host-side logic: argument validation, launch plan, buffer sizes, status strings.
+#include <initializer_list>
+
 #include "cg_common.h"
 
 namespace cg {
@@ -353,6 +355,35 @@ static bool prefer_centroid(const codegemm_desc* d)
     return !(batch > 16 && fp32 && K < 1024);
 }
 
+// Microseconds of a call of 5 to 32 rows in blocks of `rows` rows and `splits` K ranges, for the formats of the staged kernel: a
+// fixed part, a workgroup's K at a rate per format and kernel, once per round of 256 workgroups, and the exchange between the
+// ranges (two and four pairwise where their words fit, else by the ticket).  Fitted to 8000 random sizes under every height and
+// 1, 2, 3, 4, 6 and 8 ranges, some 60 000 times; the spread of one format and height about its line is 3 to 9 %.
+static float batch_cost(const codegemm_desc* d, int rows, int splits)
+{
+    // us per 1024 elements of K: blocks of 32, 64 and 128 rows with up to 8 rows / more; two tiles of 16 in one workgroup
+    struct Rate { float h[3][2], two; };
+    static const Rate rates[3][2] = {                  // v4 m1, v8 m1, v8 m2; one scale per row / group scales
+        {{{{0.47f, 0.93f}, {0.95f, 1.28f}, {1.30f, 1.51f}}, 2.15f}, {{{0.59f, 1.24f}, {1.08f, 1.40f}, {1.47f, 1.48f}}, 0.0f}},
+        {{{{0.41f, 0.89f}, {0.63f, 1.01f}, {1.00f, 1.10f}}, 2.44f}, {{{0.57f, 1.11f}, {0.75f, 1.20f}, {1.08f, 1.40f}}, 0.0f}},
+        {{{{0.68f, 1.43f}, {1.02f, 1.59f}, {1.82f, 1.82f}}, 2.84f}, {{{0.85f, 1.71f}, {1.17f, 1.84f}, {1.94f, 1.98f}}, 0.0f}}};
+    static const float fixed[3][2] = {{1.8f, 2.7f}, {2.3f, 3.1f}, {3.25f, 3.8f}};
+    const int b = d->batch, height = rows == 32 ? 0 : rows == 64 ? 1 : 2, more = b > 8;
+    const bool two = rows == 128 && b > 16 && d->group_size < 0;
+    const int nkt = ceil_div(d->in_features / d->vec_len, kSlots), tiles = b <= 16 || two ? 1 : 2;
+    const int units = ceil_div(nkt, splits < nkt ? splits : nkt);
+    splits = ceil_div(nkt, units);
+    const Rate& r = rates[d->vec_len == 4 ? 0 : d->num_codebooks][d->group_size > 0];
+    const float stream = (two ? r.two : r.h[height][more]) * (float)(units * kSlots * d->vec_len) * (1.0f / 1024) + (two ? 5.9f : fixed[height][more]);
+    const long long workgroups = (long long)ceil_div(d->out_features, rows) * tiles * splits;
+    const bool pairs = (splits == 2 || splits == 4) &&
+                       (long long)b * (splits - 1) * ceil_div(d->out_features, kGranuleRows) * kGranuleRows * 8 <= (long long)kPairAreaBytes;
+    float exchange = 0.0f;
+    if (pairs) exchange = splits == 2 ? (rows == 128 && more ? 1.7f : 0.8f) : !more ? 1.3f : rows == 128 ? 2.0f : 1.5f;
+    else if (splits > 1) exchange = !more ? (rows == 128 ? 2.75f : 2.0f) + 0.1f * splits : rows < 128 ? 2.9f : two ? 5.5f : 4.0f;
+    return 2.5f + (float)((workgroups + 255) / 256) * stream + exchange;
+}
+
 static void choose_plan(const codegemm_desc* d, codegemm_plan* p)
 {
     choose_psumbook_plan(d, p);
@@ -401,6 +432,23 @@ static void choose_plan(const codegemm_desc* d, codegemm_plan* p)
     if (splits > room) splits = (int)room;
     if (splits > nkt) splits = nkt;
     if (splits < 1) splits = 1;
+    // 5 to 32 rows of the staged kernel's formats: another height or number of ranges where the costs say that it is worth 8 %, more
+    // than they err.  On the sizes they were fitted to that is 1.6 % (17 to 32 rows) to 0.8 % in the mean, up to a factor of 1.6
+    // (8400->4096 v8 m2, 32 rows: 128-row blocks in seven ranges 24.0 us, 64-row blocks in two 14.6); 32 of 7900 lose 2 % or more.
+    if (d->batch > 4 && d->batch <= kBatchPerLaunch && !(d->flags & CODEGEMM_FLAG_Y_FP32) && !short_groups(d) &&
+        ((d->vec_len == 8 && d->num_codebooks <= 2) || (d->vec_len == 4 && d->num_codebooks == 1))) {
+        const int most = nkt * (d->vec_len == 4 ? 1 : 2) / 8;
+        float least_cost = (d->batch > 16 ? 0.95f : 0.92f) * batch_cost(d, rows, splits);
+        for (int r = least; r <= 128; r *= 2)
+            for (int n : {1, 2, 3, 4, 6, 8}) {
+                if (n > 1 && (n * blocks(r) > 256 || n > most || n > room || n > nkt)) break;
+                const float cost = batch_cost(d, r, n);
+                if (cost >= least_cost) continue;
+                least_cost = cost;
+                rows = r;
+                splits = n;
+            }
+    }
     p->centroid_rows = rows;
     p->centroid_splits = splits;
 }
