@@ -72,8 +72,12 @@ struct Geometry {
 // codes, 2 with sums of their own beside the accumulators (group scales) and for wide codes.
 __host__ __device__ constexpr int prompt_tiles(int m, int v, bool grouped)
 {
-    return grouped || m >= 3 || (v == 4 && m == 2) ? 2 : 4;
+    return (grouped && !(v == 4 && m == 1)) || m >= 3 || (v == 4 && m == 2) ? 2 : 4;
 }
+
+// Granules of a workgroup of the prompt kernel, 8 wavefronts: one each, or one for two where four tiles are paid for with half of
+// the rows (v4 m1 with group scales, see there).  It is also the number of rows of an octet that a wavefront takes.
+__host__ __device__ constexpr int prompt_granules(int m, int v, bool grouped) { return grouped && v == 4 && m == 1 ? 4 : 8; }
 
 __host__ __device__ inline int ceil_div(int a, int b) { return (a + b - 1) / b; }
 

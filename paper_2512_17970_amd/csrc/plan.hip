@@ -501,11 +501,11 @@ int make_geometry(const codegemm_desc* d, const codegemm_plan* plan, Geometry* g
     const int staged = g->RB ? staged_batch(d, g->RB, g->KPW * kSlots * g->v) : 0;
     g->staged = staged != 0;
     if (staged) g->BG = staged;
-    // The prompt kernel's workgroups take 1024 rows of W and 64 (with group scales 32) batch rows and all of K: worth it
+    // The prompt kernel's workgroups take 1024 rows of W and 64 (with group scales 32) batch rows, or 512 and 64 (v4 m1), and all of K: worth it
     // once they are enough to fill the chip.  fp32 output needs shorter sums than it has (8192^2 v8 m1 g128 batch 512: 2.9e-7
     // of 64 bits, tiles of the centroid kernel 0.95e-7, Psumbook kernels 1.24e-7; 141, 156 and 493 us).
     g->prompt = g->RB && g->B > kBatchPerLaunch && g->v < 16 && !(d->flags & CODEGEMM_FLAG_Y_FP32) &&
-                (long long)ceil_div(g->NGR, 8) * ceil_div(g->B, 16 * prompt_tiles(g->m, g->v, d->group_size > 0)) >= 128;
+                (long long)ceil_div(g->NGR, 8) * ceil_div(g->B, d->group_size > 0 ? 32 : 16 * prompt_tiles(g->m, g->v, false)) >= 128;
     if (g->prompt) g->NKS = 1;
     g->NG = ceil_div(g->B, g->BG);
     g->Npad = g->NGR * kGranuleRows;

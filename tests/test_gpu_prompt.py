@@ -104,3 +104,18 @@ def test_fp16_output_rounds_the_fp32_product():
     acc = inp.x[:, :1].astype(np.float32) * inp.codebooks[0, inp.codes[0, :, 0], 0].astype(np.float32)
     want = (acc * inp.scales.astype(np.float32)).astype(np.float16)
     assert np.array_equal(y.cpu().numpy(), want)
+
+
+@pytest.mark.parametrize("g", [32, 64, 128, 512])
+@pytest.mark.parametrize("N,extra", [(1024, 0), (1025, 1), (1028, 17), (1156, 31), (1502, 16), (4093, 2)])
+def test_half_octets(N, extra, g):
+    """v = 4, one codebook, group scales: two wavefronts share a granule, each with 4 rows of every octet and 64 batch rows.  Heights that end
+    in either half, at 4 and at 8 rows, within a workgroup's first granule or its last; odd numbers of steps and sub-vectors."""
+    for K in (max(g, 128), max(g, 128) * 3, 1024 + g):
+        case = synth.custom_case(K, N, 4, 1, batch_for(4, 1, g, N, extra), seed=3700 + N + K, g=g)
+        print(f"[prompt] {case.name}", flush=True)
+        inp = synth.generate(case)
+        y_ref, T = oracle.gemm(inp.x, inp.codes, inp.codebooks, inp.scales)
+        y = DeviceLayer(inp).gemm()
+        torch.cuda.synchronize()
+        assert check_against_oracle(y.cpu().numpy(), y_ref, T, case.name) < 6e-4
