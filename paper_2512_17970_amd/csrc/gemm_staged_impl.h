@@ -10,7 +10,8 @@
 // exchange what they loaded (SB = 1).  Here the memory pipeline writes codes, x and scales to LDS by itself (buffer_load .. lds),
 // in runs of 128 bytes that the lanes read back in any arrangement: all 16 columns are octets, an accumulator holds the whole
 // contraction of its 16 x 16 tile, and neither loads nor exchanges take registers.  Vector instructions per lookup, v8 m2 g128,
-// four rows: 4.1 -> 1.7.
+// four rows: 4.1 -> 1.9.  The table lies at the start of the LDS and the rings behind it, so that an address is one byte-permute (the other
+// way round cost an addition per lookup, 3 to 9 % of a call).
 //
 // Measured (us, back to back; before -> here): see staged_batch in plan.hip.
 //
@@ -64,8 +65,9 @@ struct StagedShape {
     static constexpr int kScalesAt = kXAt + NT * kXTile;
     static constexpr int kStage = kScalesAt + (GS ? 256 : 0);
     static constexpr int kRing = kStage * D;
-    static constexpr int kTableAt = kRing * kWaves;    // behind the rings, which keeps them below 64 KB + 32 KB
-    static constexpr int kLds = kTableAt + CentroidTable<M, V>::kBytes;
+    // The rings lie behind the table: a lookup's address is then the byte-permute alone, without an addition per lookup.
+    static constexpr int kRingAt = CentroidTable<M, V>::kBytes;
+    static constexpr int kLds = kRingAt + kRing * kWaves;
     static constexpr int kStep = 4 / kRounds;          // stages per step of 16 chunks
     // Requests of stage t (counted from a step's first; scales come with that one), and of stages t .. t + n - 1.
     static constexpr int loads(int t) { return 2 + kXLoads + (GS && t % kStep == 0 ? 1 : 0); }
@@ -113,7 +115,7 @@ __global__ void __launch_bounds__(512) gemm_staged_kernel(CG_HEAD_PARAMS, const 
     const int nq = min(p.KPW, p.NKT - kt0);
     const int q = lane >> 4, i16 = lane & 15;
     const uint32_t lds0 = (uint32_t)reinterpret_cast<uintptr_t>((lds_float*)smem);
-    const uint32_t ring = lds0 + (uint32_t)(wave * S::kRing);
+    const uint32_t ring = lds0 + (uint32_t)(S::kRingAt + wave * S::kRing);
 
     // This wavefront's stages of the workgroup's K range (whole steps with group scales).
     constexpr int ALIGN = GS ? SPS : 1;
@@ -128,10 +130,10 @@ __global__ void __launch_bounds__(512) gemm_staged_kernel(CG_HEAD_PARAMS, const 
         for (int k = 0; k < T::kBytes / 1024 / KW; ++k) {
             const int at = (k * KW + wave) * 1024;
             const int code = at / 256 + (lane >> 4), c = M == 2 ? (lane & 15) >> 3 : 0;
-            load_to_lds<false>(lds0 + (uint32_t)(S::kTableAt + at), (c * kCentroids + code) * 16, t_rsrc, 0);
+            load_to_lds<false>(lds0 + (uint32_t)at, (c * kCentroids + code) * 16, t_rsrc, 0);
         }
     } else if (wave < M * kCentroids * V * 2 / 1024) {
-        load_to_lds<false>(lds0 + (uint32_t)(S::kTableAt + wave * 1024), wave * 1024 + lane * 16, buffer_words(mm.codebooks, M * kCentroids * V * 2), 0);
+        load_to_lds<false>(lds0 + (uint32_t)(wave * 1024), wave * 1024 + lane * 16, buffer_words(mm.codebooks, M * kCentroids * V * 2), 0);
     }
 
     const u32x4_t c_rsrc = buffer_words(mm.packed + ((size_t)blk * p.NKT + kt0) * kUnitBytes, nq * kUnitBytes);
@@ -187,9 +189,9 @@ __global__ void __launch_bounds__(512) gemm_staged_kernel(CG_HEAD_PARAMS, const 
         wait_requests<S::loads(0, D)>();
         __syncthreads();
         // two threads per centroid, columns rotated by row so that a wavefront's stores spread over the banks
-        const half4_t c = *reinterpret_cast<const lds_half4*>(static_cast<uintptr_t>(lds0 + (uint32_t)(S::kTableAt + tid / 2 * 8)));
+        const half4_t c = *reinterpret_cast<const lds_half4*>(static_cast<uintptr_t>(lds0 + (uint32_t)(tid / 2 * 8)));
         __syncthreads();                               // everyone has its centroid: the table takes their place
-        const uint32_t row = lds0 + (uint32_t)(S::kTableAt + tid / 2 * 256);
+        const uint32_t row = lds0 + (uint32_t)(tid / 2 * 256);
 #pragma unroll
         for (int j = 0; j < 16; ++j)
             *reinterpret_cast<lds_half4*>(static_cast<uintptr_t>(row + (uint32_t)(((tid & 1) * 16 + tid / 2 + j) & 31) * 8)) = c;
@@ -210,7 +212,7 @@ __global__ void __launch_bounds__(512) gemm_staged_kernel(CG_HEAD_PARAMS, const 
     const int order = M == 2 ? (lane >> 3) & 1 : 0;
     uint32_t base[M];
 #pragma unroll
-    for (int k = 0; k < M; ++k) base[k] = (uint32_t)((M == 2 ? (k ^ order) * 128 : 0) + (lane & (T::columns(k) - 1)) * T::kEntry);
+    for (int k = 0; k < M; ++k) base[k] = lds0 + (uint32_t)((M == 2 ? (k ^ order) * 128 : 0) + (lane & (T::columns(k) - 1)) * T::kEntry);
     // Where the lane finds the codes of octet i16, chunk 4 r + q, and x of batch row i16 % BR, the same chunk.
     uint32_t c_at[R], x_at[R];
     const int xr = i16 & (BR - 1);
@@ -262,11 +264,11 @@ __global__ void __launch_bounds__(512) gemm_staged_kernel(CG_HEAD_PARAMS, const 
         const int c = k % M, r = k / M;
         const uint32_t sel = 0x0c020000u | (uint32_t)(4 + u % 4) << 8;
         if constexpr (V == 4) {
-            const half4_t lo4 = *reinterpret_cast<const lds_half4*>(static_cast<uintptr_t>(lds0 + __builtin_amdgcn_perm(w[r][u / 4], base[0], sel) + S::kTableAt));
-            const half4_t hi4 = *reinterpret_cast<const lds_half4*>(static_cast<uintptr_t>(lds0 + __builtin_amdgcn_perm(w[r][2 + u / 4], base[0], sel) + S::kTableAt));
+            const half4_t lo4 = *reinterpret_cast<const lds_half4*>(static_cast<uintptr_t>(__builtin_amdgcn_perm(w[r][u / 4], base[0], sel)));
+            const half4_t hi4 = *reinterpret_cast<const lds_half4*>(static_cast<uintptr_t>(__builtin_amdgcn_perm(w[r][2 + u / 4], base[0], sel)));
             return __builtin_shufflevector(lo4, hi4, 0, 1, 2, 3, 4, 5, 6, 7);
         } else {
-            return *reinterpret_cast<const lds_half8*>(static_cast<uintptr_t>(lds0 + __builtin_amdgcn_perm(w[r][2 * c + u / 4], base[c], sel) + S::kTableAt));
+            return *reinterpret_cast<const lds_half8*>(static_cast<uintptr_t>(__builtin_amdgcn_perm(w[r][2 * c + u / 4], base[c], sel)));
         }
     };
     auto add_scaled = [&](const half8_t& scales) {
