@@ -426,7 +426,8 @@ def sweep_report(torch, cg, synth, cases, launch):
 def kernel_of(plan, batch):
     """Name of the kernel that a layer runs under its plan."""
     if plan.centroid_rows and plan.psum_dtype == 0:
-        return "cg::gemm_centroid_kernel" if batch <= 32 else "cg::gemm_centroid_kernel or cg::gemm_prompt_kernel"
+        # by block height, format and output: batches of 128-row blocks with staged operands, large ones of many workgroups
+        return "cg::gemm_centroid_kernel" + (" or cg::gemm_staged_kernel" if batch > 1 else "") + (" or cg::gemm_prompt_kernel" if batch > 32 else "")
     return "cg::gemm_batch_kernel" if plan.batch_group == 4 else "cg::gemm_kernel"
 
 

@@ -64,12 +64,13 @@ static int centroid_min_rows(const codegemm_desc* d)
 // Batch rows of a workgroup of the kernel that stages codes and x in LDS, or 0: the centroid kernel.  Blocks of 128 rows, fp16
 // output, one or two codebooks of short vectors, groups that hold a step of 16 chunks.  `range` is the K of a workgroup.  Measured
 // (us back to back, centroid kernel / here; 128-row blocks):
-//  * Up to 4 rows with group scales: 8192->28672 v8 m2 22.2 / 19.1, v8 m1 16.0 / 13.6, v4 m1 17.0 / 15.9, 28672->8192 v8 m2 in four
-//    ranges 22.6 / 19.5; with little K the centroid kernel's second workgroup on a compute unit is worth more (2048->28672 8.6 /
-//    8.8, 8192->8192 in four ranges 10.5 / 10.9).  One scale per row ties or loses (33.7 / 35.4): nothing is picked or scaled there.
-//  * 5 to 16 rows, in tiles of 16 (of 8 when v8 m1 has group scales, whose 16 rows do not fit): 8192->28672 v8 m2 8 rows 23.6 / 22.0, g128
-//    25.6 / 23.3; 4096->28672 v8 m2 16 rows 16.2 / 14.9, v4 m1 13.8 / 11.5, g128 14.4 / 12.4.
-//  * 17 to 32 rows: two tiles of 16 where they fit (4096->28672 v8 m2 24.1 / 22.0, v4 m1 19.7 / 15.9), one per workgroup with
+//  * Up to 4 rows with group scales: 8192->28672 v8 m2 23.3 / 20.0, v8 m1 15.2 / 12.4, v4 m1 17.1 / 15.2, 28672->8192 v8 m2 in four
+//    ranges 23.9 / 20.0; with little K the centroid kernel's second workgroup on a compute unit makes up for it (2048->28672 8.6 /
+//    8.8, 8192->8192 in four ranges 10.5 / 10.9, with 5 % more time per lookup than now).  One scale per row ties or loses (8192->57344
+//    34.4 / 35.9, 4096->28672 11.6 / 12.1): nothing is picked or scaled there.
+//  * 5 to 16 rows, in tiles of 16 (of 8 when v8 m1 has group scales, whose 16 rows do not fit): 8192->28672 v8 m2 8 rows 21.5 / 20.3, g128
+//    24.5 / 21.1; 4096->28672 16 rows v8 m2 16.0 / 13.8, v4 m1 14.2 / 11.6, g128 14.5 / 12.4.
+//  * 17 to 32 rows: two tiles of 16 where they fit (4096->28672 v8 m2 23.2 / 20.6, v4 m1 20.0 / 16.3), one per workgroup with
 //    group scales.
 static int staged_batch(const codegemm_desc* d, int rows, int range)
 {
