@@ -241,6 +241,9 @@ __global__ void __launch_bounds__(512) gemm_prompt_kernel(CG_HEAD_PARAMS, const 
             return *reinterpret_cast<const lds_half8*>(static_cast<uintptr_t>(__builtin_amdgcn_perm(w0, base[c], sel)));
         }
     };
+    // Beside MFMAs, and the next codes turned late, but for v4 m2 with short groups, where both spill (2048->8192 g32, batch 512: 100
+    // us, 90 with the sums behind the MFMAs and the codes turned first).
+    constexpr bool BESIDE = !(V == 4 && M == 2 && GS == 2);
     auto add_scaled = [&](const half8_t& scales, int u) {
         const float f = (float)scales[u];
 #pragma unroll
@@ -268,12 +271,13 @@ __global__ void __launch_bounds__(512) gemm_prompt_kernel(CG_HEAD_PARAMS, const 
             const int s = s0 + d;                      // (an odd number of steps ends with one whose codes and x are zero)
             store_x(s + 1);
             load_x(s + 2);
+            if constexpr (!BESIDE) turn_codes(w[d ^ 1]);
             if (s < steps) {
 #pragma unroll
                 for (int k = 0; k < NSB; ++k) {
                     const int j = k / M;
                     const bool closes = (GS == 1 && k == NSB - 1) || (GS == 2 && k % M == M - 1);      // a chain of sums
-                    if (k == NSB - 1) turn_codes(w[d ^ 1]);            // asked for a step ago
+                    if (BESIDE && k == NSB - 1) turn_codes(w[d ^ 1]);  // asked for a step ago
 #pragma unroll
                     for (int u = 0; u < UR; ++u) {
 #pragma unroll
@@ -282,13 +286,16 @@ __global__ void __launch_bounds__(512) gemm_prompt_kernel(CG_HEAD_PARAMS, const 
                         }
                         __builtin_amdgcn_sched_barrier(0);         // the lookup after its operand's last use: no second set of registers
                         a[u] = k + 1 < NSB ? fetch(w[d], k + 1, u) : fetch(w[d ^ 1], 0, u);
-                        if (closes && u > 0) add_scaled(sc[d][GS == 2 ? j : 0], u - 1);    // beside the MFMAs of row u
+                        if (BESIDE && closes && u > 0) add_scaled(sc[d][GS == 2 ? j : 0], u - 1);    // beside the MFMAs of row u
                     }
                     if (k % M == M - 1 && j < 3) {
 #pragma unroll
                         for (int nt = 0; nt < NT; ++nt) xv[nt] = x_operand(s, nt, j + 1);
                     }
-                    if (closes) add_scaled(sc[d][GS == 2 ? j : 0], UR - 1);
+                    if (closes) {
+#pragma unroll
+                        for (int u = BESIDE ? UR - 1 : 0; u < UR; ++u) add_scaled(sc[d][GS == 2 ? j : 0], u);
+                    }
                 }
             }
             load_codes(w[d], s + 2);
