@@ -115,9 +115,7 @@ typedef struct codegemm_plan {
                             /* x on the matrix cores (no Psumbook; for batches), in blocks of at least     */
                             /* that many rows: 64 or 128 where the problem's registers (v = 16, or 9 and   */
                             /* more batch rows with m >= 2 and group scales or fp32 output) or its grid    */
-                            /* (millions of output rows) need higher ones, 128 also where that height in    */
-                            /* two or four K ranges is the faster way (2 to 4 batch rows, group scales,     */
-                            /* v = 8, m <= 2, long K).  Of the fields above, k_splits                       */
+                            /* (millions of output rows) need higher ones.  Of the fields above, k_splits   */
                             /* then bounds the K ranges (and with them the workspace) and psum_dtype = 1   */
                             /* selects the Psumbook kernel all the same; the others are only validated.    */
                             /* Formats that the centroid kernel does not take (groups of fewer than 4      */
@@ -125,7 +123,6 @@ typedef struct codegemm_plan {
                             /* Psumbook kernels as described above, so one plan serves every batch size,   */
                             /* output type and group size of a layer                                       */
     int32_t centroid_splits; /* K ranges of the centroid kernel, >= 1 (clamped like k_splits, to k_splits, */
-                            /* raised with the blocks,                                                      */
                             /* and above 32 batch rows so that the partial sums fit into those of a 32-row */
                             /* call); 0 when centroid_rows = 0                                             */
 } codegemm_plan;

@@ -97,8 +97,9 @@ __host__ __device__ inline size_t packed_offset(int c, int n, int j, int m, int 
 }
 
 void resolve_centroid(const codegemm_desc* d, long long n, codegemm_plan* p);        // the centroid fields as they hold for n rows of d's format
-void raise_to_staged(const codegemm_desc* d, long long n, codegemm_plan* p);         // taller blocks where the staged kernel is the faster one
-int make_geometry(const codegemm_desc* d, const codegemm_plan* plan, Geometry* g, bool fitted_plan = false);   // status; fitted_plan: the two above have been applied
+int make_geometry(const codegemm_desc* d, const codegemm_plan* plan, Geometry* g);   // status
+int group_geometry(const codegemm_desc* desc, const codegemm_plan* plan, const int32_t* out_features,
+                   int count, Geometry* members, Geometry* whole);                   // status; a launch of several layers
 size_t workspace_counter_bytes(const Geometry& g);   // the fixed area in front of the partial sums: counters, then pair words
 size_t workspace_need(const Geometry& g);            // bytes of workspace of one launch
 size_t pair_words(const Geometry& g);                // 64-bit words the pairwise reduction of this problem needs; 0: not offered

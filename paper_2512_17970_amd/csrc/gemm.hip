@@ -226,44 +226,6 @@ extern "C" int codegemm_gemm_static(const codegemm_desc* desc, const codegemm_pl
 
 // ---- several layers that share x in one launch ----------------------------------------------
 
-// Geometry of the members of a group under one plan, and the geometry of the whole launch (row
-// blocks summed).  The plan has to suit every member, and a launch takes at most kBatchPerLaunch rows.
-static int group_geometry(const codegemm_desc* desc, const codegemm_plan* plan, const int32_t* out_features,
-                          int count, Geometry* members, Geometry* whole)
-{
-    if (!desc || !out_features) return CODEGEMM_INVALID_ARG;
-    if (count < 1 || count > kMaxGroup) return CODEGEMM_INVALID_ARG;
-    if (desc->batch > kBatchPerLaunch) return CODEGEMM_UNSUPPORTED;
-    codegemm_plan of_sum;
-    if (!plan) {   // the default plan of one layer of the summed height, for every member
-        const int st = codegemm_default_plan(desc, &of_sum);
-        if (st) return st;
-        plan = &of_sum;
-    }
-    long long total = 0;
-    for (int i = 0; i < count; ++i) total += out_features[i];
-    codegemm_plan fitted = *plan;                      // to the whole launch, so that all members run the same kernel
-    resolve_centroid(desc, total, &fitted);
-    raise_to_staged(desc, total, &fitted);
-    for (int i = 0; i < count; ++i) {
-        codegemm_desc d = *desc;
-        d.out_features = out_features[i];
-        const int st = make_geometry(&d, &fitted, &members[i], true);
-        if (st) return st;
-    }
-    if (total != desc->out_features) return CODEGEMM_INVALID_ARG;
-    *whole = members[0];
-    whole->N = (int)total;
-    whole->NBLK = 0; whole->NGR = 0; whole->Npad = 0;
-    for (int i = 0; i < count; ++i) {
-        whole->NBLK += members[i].NBLK;
-        whole->NGR += members[i].NGR;
-        whole->Npad += members[i].Npad;
-    }
-    if (whole->NBLK > 65535 || counter_stride(*whole) == 0) return CODEGEMM_UNSUPPORTED;
-    return CODEGEMM_OK;
-}
-
 extern "C" size_t codegemm_grouped_workspace_bytes(const codegemm_desc* desc, const codegemm_plan* plan,
                                                    const int32_t* out_features, int32_t count)
 {

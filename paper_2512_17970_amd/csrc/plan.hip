@@ -86,16 +86,17 @@ static int staged_batch(const codegemm_desc* d, int rows, int range)
 // 2 to 4 rows with group scales: blocks of 128 rows in two or four K ranges on the staged kernel instead of lower ones on the
 // centroid kernel, where these fill the chip and leave every workgroup a long K (3200 random sizes, 160 to 256 workgroups, time
 // here / of the lower blocks at 4096, 6144, 8192, 10240 and 12288 elements per workgroup: v8 m1 0.99, 0.92, 0.88, 0.85, 0.83; v8 m2 1.03, 0.98,
-// 0.94, 0.93, 0.91; v4 m1 1.08 to 1.0: left out).  n: rows of all layers of a launch.
-void raise_to_staged(const codegemm_desc* d, long long n, codegemm_plan* p)
+// 0.94, 0.93, 0.91; v4 m1 1.08 to 1.0: left out).  It belongs to the choice of the default plan: a group's members and their
+// layers alone then follow the same fields, and a plan that asks for lower blocks gets them.
+static void raise_to_staged(const codegemm_desc* d, codegemm_plan* p)
 {
-    if (p->centroid_rows == 0 || p->centroid_rows == 128 || d->batch < 2 || d->vec_len != 8 || d->group_size < 0) return;
-    const long long blocks = (n + 127) / 128;
+    if (p->centroid_rows == 128 || d->batch < 2 || d->vec_len != 8 || d->group_size < 0) return;
+    const long long blocks = ceil_div(d->out_features, kGranuleRows);
     const int splits = 4 * blocks <= 256 ? 4 : 2, nkt = ceil_div(d->in_features / d->vec_len, kSlots);
     if (d->batch > 4 || splits * blocks < 160 || splits * blocks > 256 || splits > p->k_splits || splits > nkt) return;
     const int range = ceil_div(nkt, splits) * kSlots * d->vec_len;
-    if (range < (d->num_codebooks == 1 ? 6144 : 7168) || !staged_batch(d, 128, range)) return;
-    p->centroid_rows = 128;
+    if (range < (d->num_codebooks == 1 ? 6144 : 7168) || !staged_batch(d, kGranuleRows, range)) return;
+    p->centroid_rows = kGranuleRows;
     p->centroid_splits = splits;
 }
 
@@ -452,9 +453,10 @@ static void choose_plan(const codegemm_desc* d, codegemm_plan* p)
     }
     p->centroid_rows = rows;
     p->centroid_splits = splits;
+    raise_to_staged(d, p);
 }
 
-int make_geometry(const codegemm_desc* d, const codegemm_plan* plan, Geometry* g, bool fitted_plan)
+int make_geometry(const codegemm_desc* d, const codegemm_plan* plan, Geometry* g)
 {
     int st = validate_desc(d);
     if (st) return st;
@@ -467,7 +469,6 @@ int make_geometry(const codegemm_desc* d, const codegemm_plan* plan, Geometry* g
     if (st) return st;
     codegemm_plan fitted = *plan;
     resolve_centroid(d, d->out_features, &fitted);
-    if (!fitted_plan) raise_to_staged(d, d->out_features, &fitted);
     plan = &fitted;
     // larger batches run as several launches of the Psumbook kernels, as one of the centroid kernels
     g->B = (d->batch < kBatchPerLaunch || plan->centroid_rows) ? d->batch : kBatchPerLaunch;
@@ -520,6 +521,43 @@ int make_geometry(const codegemm_desc* d, const codegemm_plan* plan, Geometry* g
         g->GPU = ratio >= kSlots ? 1 : kSlots / ratio;
         while ((1 << g->gshift) < ratio && g->gshift < 5) ++g->gshift;
     }
+    return CODEGEMM_OK;
+}
+
+// Geometry of the members of a group under one plan, and the geometry of the whole launch (row
+// blocks summed).  The plan has to suit every member, and a launch takes at most kBatchPerLaunch rows.
+int group_geometry(const codegemm_desc* desc, const codegemm_plan* plan, const int32_t* out_features,
+                   int count, Geometry* members, Geometry* whole)
+{
+    if (!desc || !out_features) return CODEGEMM_INVALID_ARG;
+    if (count < 1 || count > kMaxGroup) return CODEGEMM_INVALID_ARG;
+    if (desc->batch > kBatchPerLaunch) return CODEGEMM_UNSUPPORTED;
+    codegemm_plan of_sum;
+    if (!plan) {   // the default plan of one layer of the summed height, for every member
+        const int st = codegemm_default_plan(desc, &of_sum);
+        if (st) return st;
+        plan = &of_sum;
+    }
+    long long total = 0;
+    for (int i = 0; i < count; ++i) total += out_features[i];
+    codegemm_plan fitted = *plan;                      // to the whole launch, so that all members run the same kernel
+    resolve_centroid(desc, total, &fitted);
+    for (int i = 0; i < count; ++i) {
+        codegemm_desc d = *desc;
+        d.out_features = out_features[i];
+        const int st = make_geometry(&d, &fitted, &members[i]);
+        if (st) return st;
+    }
+    if (total != desc->out_features) return CODEGEMM_INVALID_ARG;
+    *whole = members[0];
+    whole->N = (int)total;
+    whole->NBLK = 0; whole->NGR = 0; whole->Npad = 0;
+    for (int i = 0; i < count; ++i) {
+        whole->NBLK += members[i].NBLK;
+        whole->NGR += members[i].NGR;
+        whole->Npad += members[i].Npad;
+    }
+    if (whole->NBLK > 65535 || counter_stride(*whole) == 0) return CODEGEMM_UNSUPPORTED;
     return CODEGEMM_OK;
 }
 

@@ -80,10 +80,12 @@ def test_default_plan_asks_for_no_more_workspace(v, m, g):
             assert cg.codegemm_workspace_bytes(d, p) == cg.codegemm_workspace_bytes(d) <= cg.codegemm_workspace_bytes(d, q), (B, K, N)
 
 
-@pytest.mark.parametrize("v,m,g", [(8, 2, -1), (4, 1, 128), (4, 1, 32), (8, 1, -1), (8, 3, -1), (16, 4, -1), (8, 2, 128), (8, 2, 32)])
+@pytest.mark.parametrize("v,m,g", [(8, 2, -1), (4, 1, 128), (4, 1, 32), (8, 1, -1), (8, 1, 128), (8, 3, -1), (16, 4, -1), (8, 2, 128), (8, 2, 32)])
 def test_default_blocks_and_ranges_of_few_rows(v, m, g):
     """Up to 4 batch rows: one round of 256 workgroups wherever a block height allows it, K ranges that are powers of two and
-    all of one length but the last (two and four meet pairwise, three, five or seven would take the slower ticket)."""
+    all of one length but the last (two and four meet pairwise, three, five or seven would take the slower ticket).  Blocks are
+    as low as that allows, but for 2 to 4 rows with v = 8, at most two codebooks, fp16 output and groups of at least 16 chunks, where
+    128-row blocks in two or four ranges that come to 160 to 256 workgroups with a K of 6144 (two codebooks: 7168) or more each take over."""
     seen = set()
     for B in (1, 2, 3, 4):
         for N in (512, 700, 1300, 1500, 2000, 2900, 4096, 8192, 8193, 10000, 14336, 16384, 17000, 20000, 28672):
@@ -94,10 +96,34 @@ def test_default_blocks_and_ranges_of_few_rows(v, m, g):
                         continue
                     blocks, s, nkt = -(-N // p.centroid_rows), p.centroid_splits, -(-(K // v) // 32)
                     assert blocks <= 256 or p.centroid_rows == 128, (B, K, N, p)
-                    assert p.centroid_rows == 32 or -(-N // (p.centroid_rows // 2)) > 256, (B, K, N, p)
+                    tall = -(-N // 128)
+                    ranges = 4 if 4 * tall <= 256 else 2
+                    if (2 <= B <= 4 and v == 8 and m <= 2 and g >= 128 and not fp32 and 160 <= ranges * tall <= 256
+                            and -(-nkt // ranges) * 32 * v >= (6144 if m == 1 else 7168)):
+                        assert (p.centroid_rows, s) == (128, ranges), (B, K, N, p)
+                    else:
+                        assert p.centroid_rows == 32 or -(-N // (p.centroid_rows // 2)) > 256, (B, K, N, p)
                     assert s & (s - 1) == 0 and -(-nkt // -(-nkt // s)) == s and (s == 1 or s * blocks <= 256), (B, K, N, p)
                     seen.add((p.centroid_rows, s))
     assert {r for r, _ in seen} == {32, 64, 128} and {1, 2, 4, 8} <= {s for _, s in seen}
+
+
+@pytest.mark.parametrize("m,K,N,want", [
+    (2, 28672, 8192, (128, 4)), (2, 28672, 8193, (64, 1)),             # 4 x 64 workgroups, one block more
+    (2, 28672, 5120, (128, 4)), (2, 28672, 4992, (32, 1)),             # 160 workgroups, 156
+    (2, 28672, 10240, (128, 2)), (2, 28672, 10112, (64, 1)),           # two ranges: 160 workgroups, 158
+    (2, 28672, 16384, (128, 2)), (2, 28672, 16385, (0, 0)),            # two ranges: 256 workgroups; 129 blocks are the Psumbook kernels'
+    (2, 14336, 16384, (128, 2)), (2, 13824, 16384, (64, 1)),           # K of a workgroup: 7168, 6912
+    (1, 12288, 16384, (128, 2)), (1, 11776, 16384, (64, 1)),           # .. 6144, 5888
+])
+def test_tall_blocks_of_few_rows(m, K, N, want):
+    for B in (2, 3, 4):
+        p = cg.codegemm_default_plan(cg.Desc.make(B, K, N, 8, m, g=128))
+        assert (p.centroid_rows, p.centroid_splits) == want and p.k_splits >= want[1]
+    for kept in (cg.Desc.make(4, K, N, 8, m), cg.Desc.make(4, K, N, 8, m, g=64), cg.Desc.make(4, K, N, 8, m, g=128, y_fp32=True), cg.Desc.make(4, K, N, 8, 3, g=128)):
+        p = cg.codegemm_default_plan(kept)
+        if N <= 16384:
+            assert p.centroid_rows in (32, 64), (kept, p)
 
 
 def test_default_plan_keeps_the_other_kernels_where_they_win():

@@ -206,3 +206,10 @@ def test_grouped_rejects_bad_arguments():
     with pytest.raises(cg.CodegemmError):                                                  # null member pointer
         cg.codegemm_gemm_grouped(desc, plan, buf, [(512, buf, None, buf, buf), (256, buf, buf, buf, buf)], buf, buf.numel(), stream())
     torch.cuda.synchronize()
+
+
+@pytest.mark.parametrize("K,Ns,m,B", [(12288, (12288, 1536, 1536), 1, 4), (28672, (4096, 4096), 2, 3)])
+def test_grouped_at_few_rows_and_long_k(K, Ns, m, B):
+    """Group scales, 2 to 4 rows: the default plan of the sum takes 128-row blocks in two or four K ranges, and so do the members alone."""
+    plan = run_group(K, list(Ns), 8, m, B, 128, seed=7700)
+    assert plan.centroid_rows == 128 and plan.centroid_splits == (2 if m == 1 else 4)

@@ -1,0 +1,85 @@
+"""The launch geometry behind a plan, as the library derives it (host code of the built library, no kernel is launched):
+members of a group and the same layers alone, and what default plans of few rows run."""
+import os
+import random
+import shutil
+import subprocess
+
+import pytest
+
+import paper_2512_17970_amd as cg
+from paper_2512_17970_amd import build
+
+HERE = os.path.dirname(os.path.abspath(__file__))
+
+pytestmark = pytest.mark.skipif(shutil.which(build.HIPCC) is None, reason="no hipcc")
+
+
+@pytest.fixture(scope="module")
+def geometry(tmp_path_factory):
+    """A function: problem lines -> per problem (status, members, alone), the latter two lists of dicts."""
+    cg.load()                                                      # built if it is not there
+    exe = str(tmp_path_factory.mktemp("geometry") / "geometry_lines")
+    subprocess.run([build.HIPCC, "--offload-host-only", "-O1", "-std=c++17", "-Wno-unused-result", "-I", os.path.join(build.ROOT, "include"), "-I", build.CSRC,
+                    os.path.join(HERE, "host", "geometry_lines.cpp"), "-o", exe, "-L", build.PKG, "-l:" + os.path.basename(build.LIB), "-Wl,-rpath," + build.PKG], check=True)
+
+    def run(lines):
+        out = subprocess.run([exe], input="\n".join(lines) + "\n", check=True, capture_output=True, text=True).stdout.splitlines()
+        res = []
+        for line in out:
+            word, rest = line.split(" ", 1)
+            if word == "group":
+                res.append((int(rest), [], []))
+            else:
+                res[-1][1 if word == "member" else 2].append({k: int(v) for k, v in (f.split("=") for f in rest.split())})
+        assert len(res) == len(lines)
+        return res
+    return run
+
+
+def line(B, K, Ns, v, m, g, fp32=0, plan_batch=None, plan=None):
+    tail = [plan_batch or B] if plan is None else [0, *plan]
+    return " ".join(str(t) for t in (B, K, v, m, g, fp32, len(Ns), *Ns, *tail))
+
+
+def same(member, alone):
+    """What decides the bits: the kernel, its tiles and how K is cut.  (Two or four ranges meet in the same order by either protocol.)"""
+    skip = {"pairs"}
+    return {k: x for k, x in member.items() if k not in skip} == {k: x for k, x in alone.items() if k not in skip}
+
+
+def test_group_members_and_single_calls_run_alike(geometry):
+    rng = random.Random(5)
+    problems = []
+    for B, K, Ns, v, m, g in ((4, 28672, (4096, 4096), 8, 2, 128), (4, 12288, (12288, 1536, 1536), 8, 1, 128), (3, 16384, (8192, 1024, 1024), 8, 2, 128)):
+        problems.append((B, K, Ns, v, m, g, 0, None, None))
+    for _ in range(4000):
+        v, m = rng.choice([(8, 1), (8, 2), (8, 2), (8, 3), (4, 1), (4, 2), (16, 2), (16, 4)])
+        g = rng.choice([-1, 4 * v, 16 * v, 128, 256])
+        if g > 0 and g < v:
+            g = v
+        unit = max(v, g)
+        K = unit * max(1, int(2 ** rng.uniform(9, 15)) // unit)
+        n0 = int(2 ** rng.uniform(7, 15))
+        Ns = [n0] + [max(1, n0 // rng.choice([1, 2, 4, 8])) for _ in range(rng.randrange(4))]
+        B = rng.choice([1, 2, 3, 4, 4, 5, 8, 12, 16, 24, 32])
+        plan = None
+        if rng.random() < 0.3:
+            k = rng.choice([1, 2, 3, 4, 8])
+            plan = (8, 1, k, 4, 0, 0, rng.choice([32, 64, 128]), rng.randint(1, 8))
+        problems.append((B, K, Ns, v, m, g, rng.randrange(2), rng.choice([None, None, 1, 4, 32]), plan))
+    raised = 0
+    for p, (st, members, alone) in zip(problems, geometry([line(*p) for p in problems])):
+        assert st == 0, p
+        for a, b in zip(members, alone):
+            assert same(a, b), (p, a, b)
+            raised += a["staged"] and a["bg"] == 4 and a["rows"] == 128
+    assert raised > 30                                              # the long K that 128-row blocks at 2 to 4 rows take
+
+
+def test_explicit_block_heights_of_few_rows_are_kept(geometry):
+    """8192 rows and K = 28672 at 4 rows, where the default plan takes 128-row blocks in four ranges: lower ones when asked for."""
+    for rows in (32, 64, 128):
+        for splits in (1, 2, 3, 4):
+            [(st, members, _)] = geometry([line(4, 28672, [8192], 8, 2, 128, plan=(16, 1, 6, 4, 0, 0, rows, splits))])
+            assert st == 0 and (members[0]["rows"], members[0]["nks"]) == (rows, splits)
