@@ -97,7 +97,8 @@ __host__ __device__ inline size_t packed_offset(int c, int n, int j, int m, int 
 }
 
 void resolve_centroid(const codegemm_desc* d, long long n, codegemm_plan* p);        // the centroid fields as they hold for n rows of d's format
-int make_geometry(const codegemm_desc* d, const codegemm_plan* plan, Geometry* g);   // status
+// Status.  launch_plan: `plan` with its centroid fields resolved for the launch that d is a member of.
+int make_geometry(const codegemm_desc* d, const codegemm_plan* plan, Geometry* g, const codegemm_plan* launch_plan = nullptr);
 int group_geometry(const codegemm_desc* desc, const codegemm_plan* plan, const int32_t* out_features,
                    int count, Geometry* members, Geometry* whole);                   // status; a launch of several layers
 size_t workspace_counter_bytes(const Geometry& g);   // the fixed area in front of the partial sums: counters, then pair words

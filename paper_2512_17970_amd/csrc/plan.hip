@@ -456,7 +456,7 @@ static void choose_plan(const codegemm_desc* d, codegemm_plan* p)
     raise_to_staged(d, p);
 }
 
-int make_geometry(const codegemm_desc* d, const codegemm_plan* plan, Geometry* g)
+int make_geometry(const codegemm_desc* d, const codegemm_plan* plan, Geometry* g, const codegemm_plan* launch_plan)
 {
     int st = validate_desc(d);
     if (st) return st;
@@ -467,7 +467,7 @@ int make_geometry(const codegemm_desc* d, const codegemm_plan* plan, Geometry* g
     }
     st = validate_plan(d, plan);
     if (st) return st;
-    codegemm_plan fitted = *plan;
+    codegemm_plan fitted = launch_plan ? *launch_plan : *plan;
     resolve_centroid(d, d->out_features, &fitted);
     plan = &fitted;
     // larger batches run as several launches of the Psumbook kernels, as one of the centroid kernels
@@ -540,12 +540,13 @@ int group_geometry(const codegemm_desc* desc, const codegemm_plan* plan, const i
     }
     long long total = 0;
     for (int i = 0; i < count; ++i) total += out_features[i];
-    codegemm_plan fitted = *plan;                      // to the whole launch, so that all members run the same kernel
+    codegemm_plan fitted = *plan;                      // to the whole launch, so that all members run the same kernel;
+                                                       // what is validated is the plan as given: fitting mends invalid fields
     resolve_centroid(desc, total, &fitted);
     for (int i = 0; i < count; ++i) {
         codegemm_desc d = *desc;
         d.out_features = out_features[i];
-        const int st = make_geometry(&d, &fitted, &members[i]);
+        const int st = make_geometry(&d, plan, &members[i], &fitted);
         if (st) return st;
     }
     if (total != desc->out_features) return CODEGEMM_INVALID_ARG;

@@ -19,6 +19,17 @@ def test_offered_and_refused():
     assert ws(cg.Desc.make(2, 512, 65536 * 128, 8, 1), 128, 1, (8, 1, 1, 4)) > 0
 
 
+@pytest.mark.parametrize("g", [-1, 128, 8])
+def test_a_group_refuses_the_plans_that_a_layer_refuses(g):
+    """The plan as given is what counts: raising blocks, cutting ranges or falling back to the Psumbook fields must not make a valid one of it."""
+    for B, K, heights in ((4, 4096, [700, 300]), (4, 28672, [4096, 4096])):
+        d = cg.Desc.make(B, K, sum(heights), 8, 2, g=g)
+        for rows, splits in ((32, 0), (64, -1), (128, 0), (16, 1), (31, 1), (96, 1), (-128, 1), (1, 1), (0, 1)):
+            assert ws(d, rows, splits) == 0
+            assert cg.codegemm_grouped_workspace_bytes(d, cg.Plan.make(8, 1, 4, 4, 0, 0, rows, splits), heights) == 0, (g, rows, splits)
+        assert cg.codegemm_grouped_workspace_bytes(d, cg.Plan.make(8, 1, 4, 4, 0, 0, 32, 1), heights) > 0
+
+
 BATCHES = (1, 2, 4, 5, 8, 9, 16, 17, 32, 33, 64, 500)
 
 
