@@ -577,9 +577,12 @@ size_t pair_words(const Geometry& g)
 {
     // Measured per level: one add that returns, on every output of the launch at once, takes 0.8-0.9 us, the ticket
     // protocol 1.9 us whatever the number of ranges: two ranges gain 0.95 us, four 0.2 us, eight lose 0.35 us.
-    // The batched kernel, with four times the outputs per workgroup, takes it for two ranges (8192->28672, batch 8:
-    // 54.1 -> 53.1 us).
-    if (g.NKS != 2 && (g.NKS != 4 || g.BG == 4)) return 0;
+    // The batched kernel, with four times the outputs per workgroup, takes it for two ranges only (8192->28672, batch 8:
+    // 54.1 -> 53.1 us).  The centroid kernels take it for four as well, at 4 rows too, where a workgroup has no more outputs than the
+    // gather kernel's (ticket / pairs: 28672->8192 v8 m2 g128, 4 rows 21.6 / 20.9; 14336->2048 v8 m2, 2 rows 6.08 / 5.93; 33 sizes
+    // at 2 to 4 rows 1.011 to 0.969, 0.991 in the mean).
+    const bool batched = g.RB == 0 && g.BG == 4;
+    if (g.NKS != 2 && (g.NKS != 4 || batched)) return 0;
     return (size_t)g.B * (g.NKS - 1) * g.Npad;
 }
 

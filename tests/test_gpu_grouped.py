@@ -96,6 +96,12 @@ def test_grouped_and_single_calls_agree_across_reduction_protocols(plan):
     run_group(1024, Ns, 8, 1, 2, -1, plan=cg.Plan.make(*plan), seed=7300)
 
 
+@pytest.mark.parametrize("rows,K,B,g", [(32, 2048, 3, -1), (128, 12288, 4, 128)])
+def test_grouped_and_single_calls_agree_across_reduction_protocols_at_few_rows(rows, K, B, g):
+    """The same with blocks of the centroid and the staged kernel in four ranges: B x 3 x 8 bytes per padded row, 15 000 rows fit."""
+    run_group(K, [15000, 15000], 8, 1, B, g, plan=cg.Plan.make(8, 1, 4, 4, 0, 0, rows, 4), seed=7350)
+
+
 def test_grouped_null_plan_is_the_default_plan_of_the_sum():
     K, Ns = 2048, [900, 300, 300]
     desc = cg.Desc.make(1, K, sum(Ns), 8, 2)

@@ -83,3 +83,14 @@ def test_explicit_block_heights_of_few_rows_are_kept(geometry):
         for splits in (1, 2, 3, 4):
             [(st, members, _)] = geometry([line(4, 28672, [8192], 8, 2, 128, plan=(16, 1, 6, 4, 0, 0, rows, splits))])
             assert st == 0 and (members[0]["rows"], members[0]["nks"]) == (rows, splits)
+
+
+def test_two_and_four_ranges_of_the_centroid_kernels_meet_pairwise(geometry):
+    """At every batch; the batched Psumbook kernel, which takes 4 rows per pass too, combines four ranges through the ticket."""
+    for B in (1, 2, 4, 5, 8, 16, 32):
+        for splits, words in ((1, 0), (2, 1), (3, 0), (4, 3), (8, 0)):
+            [(st, members, alone)] = geometry([line(B, 8192, [1000], 8, 2, 128, plan=(8, 1, 8, 4, 0, 0, 128, splits))])
+            assert st == 0 and alone[0]["nks"] == splits and alone[0]["pairs"] == members[0]["pairs"] == B * words * 1024, (B, splits)
+    for splits, words in ((2, 1), (4, 0)):
+        [(st, _, alone)] = geometry([line(8, 8192, [1000], 8, 2, 128, plan=(8, 1, splits, 4, 0, 0, 0, 0))])
+        assert st == 0 and alone[0]["pairs"] == 8 * words * 1024
