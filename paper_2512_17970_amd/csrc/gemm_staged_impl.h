@@ -31,21 +31,25 @@ namespace cg {
 typedef __attribute__((address_space(3))) u32x2_t lds_u2;
 typedef __attribute__((address_space(3))) u32x4_t lds_u4;
 
-// Descriptor of `bytes` bytes at `base` (uniform) as the four words that inline assembly takes.
+// Descriptor of `bytes` bytes at `base` (uniform) as the four words that inline assembly takes.  The compiler does not count wait states
+// into inline assembly, and a buffer instruction needs five behind a vector instruction that wrote its scalar operands.
 __device__ __forceinline__ u32x4_t buffer_words(const void* base, int bytes)
 {
     const uint64_t a = reinterpret_cast<uint64_t>(base);
-    return u32x4_t{(uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)a), (uint32_t)__builtin_amdgcn_readfirstlane((int)((uint32_t)(a >> 32) & 0xffffu)),
-                   (uint32_t)__builtin_amdgcn_readfirstlane(bytes), 0x00020000u};
+    u32x4_t words = {(uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)a), (uint32_t)__builtin_amdgcn_readfirstlane((int)((uint32_t)(a >> 32) & 0xffffu)),
+                     (uint32_t)__builtin_amdgcn_readfirstlane(bytes), 0x00020000u};
+    asm volatile("s_nop 4" : "+s"(words));
+    return words;
 }
 
 // 16 bytes per active lane from voff + soff of the buffer to LDS byte address lds + 16 lane.  A voff past the end of the
-// buffer reads nothing, but counts as a request.
+// buffer reads nothing, but counts as a request.  The LDS address goes through m0, which the compiler sets (as a clobber it would be
+// kept just as safe, with a warning per request: the register is reserved); one wait state lies between.
 template <bool STREAM>
 __device__ __forceinline__ void load_to_lds(uint32_t lds, int voff, u32x4_t rsrc, int soff)
 {
-    if constexpr (STREAM) asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen nt lds" :: "s"(lds), "v"(voff), "s"(rsrc), "s"(soff) : "memory");
-    else asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds" :: "s"(lds), "v"(voff), "s"(rsrc), "s"(soff) : "memory");
+    if constexpr (STREAM) asm volatile("s_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen nt lds" :: "{m0}"(lds), "v"(voff), "s"(rsrc), "s"(soff) : "memory");
+    else asm volatile("s_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds" :: "{m0}"(lds), "v"(voff), "s"(rsrc), "s"(soff) : "memory");
 }
 
 template <int N>
