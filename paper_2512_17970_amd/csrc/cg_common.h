@@ -53,6 +53,7 @@ struct Geometry {
     int RB;         // rows of a block of the centroid kernel (32, 64 or 128), or 0: one of the Psumbook kernels
     bool staged;    // the centroid kernel with codes and x staged in LDS (RB = 128)
     bool prompt;    // the prompt kernel: RB != 0, fp16 output, more than kBatchPerLaunch batch rows and enough of them
+    bool half;      // .. with two wavefronts to a granule (v = 4, one codebook, group scales)
     int NGR;        // ceil(N / 128) granules
     int NBLK;       // row blocks = workgroups along N: NGR over the granules per workgroup, rounded up
     int NKT;        // ceil(J / 32) K tiles
@@ -70,14 +71,7 @@ struct Geometry {
 
 // Tiles of 16 batch rows of a workgroup of the prompt kernel: 4 where 128 accumulators per lane leave room for the
 // codes, 2 with sums of their own beside the accumulators (group scales) and for wide codes.
-__host__ __device__ constexpr int prompt_tiles(int m, int v, bool grouped)
-{
-    return (grouped && !(v == 4 && m == 1)) || m >= 3 || (v == 4 && m == 2) ? 2 : 4;
-}
-
-// Granules of a workgroup of the prompt kernel, 8 wavefronts: one each, or one for two where four tiles are paid for with half of
-// the rows (v4 m1 with group scales, see there).  It is also the number of rows of an octet that a wavefront takes.
-__host__ __device__ constexpr int prompt_granules(int m, int v, bool grouped) { return grouped && v == 4 && m == 1 ? 4 : 8; }
+__host__ __device__ constexpr int prompt_tiles(int m, int v, bool grouped) { return grouped || m >= 3 || (v == 4 && m == 2) ? 2 : 4; }
 
 __host__ __device__ inline int ceil_div(int a, int b) { return (a + b - 1) / b; }
 

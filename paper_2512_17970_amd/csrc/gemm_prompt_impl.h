@@ -363,7 +363,10 @@ int launch_gemm_centroid_mv(const Geometry& g, const GemmParams& p, hipStream_t 
 {
     if constexpr (V < 16 && GS <= 2) {
         if (g.prompt) {
-            return launch_gemm_prompt_one<M, V, prompt_tiles(M, V, GS != 0), GS, prompt_granules(M, V, GS != 0)>(g, p, stream);
+            if constexpr (V == 4 && M == 1 && GS != 0) {
+                if (g.half) return launch_gemm_prompt_one<M, V, 4, GS, 4>(g, p, stream);
+            }
+            return launch_gemm_prompt_one<M, V, prompt_tiles(M, V, GS != 0), GS, 8>(g, p, stream);
         }
     }
     if constexpr (GS <= 1 && ((V == 8 && M <= 2) || (V == 4 && M == 1))) {

@@ -503,12 +503,17 @@ int make_geometry(const codegemm_desc* d, const codegemm_plan* plan, Geometry* g
     const int staged = g->RB ? staged_batch(d, g->RB, g->KPW * kSlots * g->v) : 0;
     g->staged = staged != 0;
     if (staged) g->BG = staged;
-    // The prompt kernel's workgroups take 1024 rows of W and 64 (with group scales 32) batch rows, or 512 and 64 (v4 m1), and all of K: worth it
-    // once they are enough to fill the chip.  fp32 output needs shorter sums than it has (8192^2 v8 m1 g128 batch 512: 2.9e-7
+    // The prompt kernel's workgroups take 1024 rows of W and 64 (with group scales 32) batch rows, or half of the rows and twice the batch rows,
+    // and all of K: worth it once they are enough to fill the chip.  fp32 output needs shorter sums than it has (8192^2 v8 m1 g128 batch 512: 2.9e-7
     // of 64 bits, tiles of the centroid kernel 0.95e-7, Psumbook kernels 1.24e-7; 141, 156 and 493 us).
     g->prompt = g->RB && g->B > kBatchPerLaunch && g->v < 16 && !(d->flags & CODEGEMM_FLAG_Y_FP32) &&
-                (long long)ceil_div(g->NGR, 8) * ceil_div(g->B, d->group_size > 0 ? 32 : 16 * prompt_tiles(g->m, g->v, false)) >= 128;
+                (long long)ceil_div(g->NGR, 8) * ceil_div(g->B, 16 * prompt_tiles(g->m, g->v, d->group_size > 0)) >= 128;
     if (g->prompt) g->NKS = 1;
+    // Two wavefronts to a granule make tiles of 512 x 64 of those of 1024 x 32 and take 0.92 of their time (1500 random sizes, 1 to 6
+    // rounds of 256 workgroups), but where they are too many for as few rounds (28672 rows, 257 to 288 batch rows: 280 and 252): the
+    // other way round is then 1.4 to 1.7 times as fast.
+    auto rounds = [&](int granules, int rows) { return ((long long)ceil_div(g->NGR, granules) * ceil_div(g->B, rows) + 255) / 256; };
+    g->half = g->prompt && g->v == 4 && g->m == 1 && d->group_size > 0 && 12 * rounds(4, 64) <= 13 * rounds(8, 32);
     g->NG = ceil_div(g->B, g->BG);
     g->Npad = g->NGR * kGranuleRows;
     if (counter_stride(*g) == 0) return CODEGEMM_UNSUPPORTED;   // > 16384 row blocks x batch groups with several K ranges

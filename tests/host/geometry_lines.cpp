@@ -1,7 +1,7 @@
 // Reads problems from standard input and prints the launch geometry that the library derives for them, one line per layer:
 //   batch K v m g fp32 count N1 .. Ncount B0 [the eight fields of a plan, if B0 is 0]
-// The plan is the default one of the summed height at batch B0, or the given one.  For each problem: a line "group STATUS" and,
-// when that is 0, a line per member in the group and a line per member alone.
+// The plan is the default one of the summed height at batch B0, or the given one.  For each problem: a line "group STATUS", and per
+// layer a line as a member of the group, when that is 0 (groups end at 32 rows), and one alone.
 #include <cstdio>
 
 #include "cg_common.h"
@@ -10,8 +10,8 @@ using namespace cg;
 
 static void print(const char* what, const Geometry& g)
 {
-    std::printf("%s N=%d rows=%d staged=%d prompt=%d bg=%d nblk=%d nks=%d kpw=%d waves=%d build=%d words=%d pairs=%zu\n", what, g.N, g.RB, (int)g.staged,
-                (int)g.prompt, g.BG, g.NBLK, g.NKS, g.KPW, g.NW, g.NB, g.RPL, pair_words(g));
+    std::printf("%s N=%d rows=%d staged=%d prompt=%d half=%d bg=%d nblk=%d nks=%d kpw=%d waves=%d build=%d words=%d pairs=%zu\n", what, g.N, g.RB, (int)g.staged,
+                (int)g.prompt, (int)g.half, g.BG, g.NBLK, g.NKS, g.KPW, g.NW, g.NB, g.RPL, pair_words(g));
 }
 
 int main()
@@ -40,12 +40,12 @@ int main()
         Geometry members[kMaxGroup], whole, alone;
         const int st = group_geometry(&d, &p, n, count, members, &whole);
         std::printf("group %d\n", st);
-        for (int i = 0; i < count && st == 0; ++i) {
+        for (int i = 0; i < count; ++i) {
             codegemm_desc one = d;
             one.out_features = n[i];
-            print("member", members[i]);
-            if (make_geometry(&one, &p, &alone)) return 3;
-            print("alone", alone);
+            if (st == 0) print("member", members[i]);
+            if (make_geometry(&one, &p, &alone) == 0) print("alone", alone);
+            else if (st == 0) return 3;
         }
     }
     return 0;

@@ -119,3 +119,20 @@ def test_half_octets(N, extra, g):
         y = DeviceLayer(inp).gemm()
         torch.cuda.synchronize()
         assert check_against_oracle(y.cpu().numpy(), y_ref, T, case.name) < 6e-4
+
+
+@pytest.mark.parametrize("g", [32, 64, 128, 512])
+@pytest.mark.parametrize("N,B", [(28672, 257), (27001, 288), (3004, 2713)])
+def test_whole_octets(N, B, g):
+    """The same format where half octets would take one more round of workgroups: 1024 rows and 32 batch rows each.  Odd numbers of steps and
+    sub-vectors, ragged last workgroups of rows and of batch rows."""
+    K = max(g, 128) + g
+    case = synth.custom_case(K, N, 4, 1, B, seed=3800 + K, g=g)
+    print(f"[prompt] {case.name}", flush=True)
+    inp = synth.generate(case)
+    layer = DeviceLayer(inp)
+    ref = exact_on_gpu(layer, inp)
+    y = layer.gemm().double()
+    torch.cuda.synchronize()
+    assert ((y - ref).norm() / ref.norm()).item() < 3e-4               # the rounding of the output: 2.1e-4
+    assert ((y - ref).abs().max() / ref.square().mean().sqrt()).item() < 5e-3    # half a unit in the last place at 8 times the root mean square: 3.9e-3

@@ -94,3 +94,22 @@ def test_two_and_four_ranges_of_the_centroid_kernels_meet_pairwise(geometry):
     for splits, words in ((2, 1), (4, 0)):
         [(st, _, alone)] = geometry([line(8, 8192, [1000], 8, 2, 128, plan=(8, 1, splits, 4, 0, 0, 0, 0))])
         assert st == 0 and alone[0]["pairs"] == 8 * words * 1024
+
+
+def test_half_octets_take_no_extra_round(geometry):
+    """Prompts of v4 m1 with group scales: tiles of 512 rows x 64 batch rows, but of 1024 x 32 where those take fewer rounds of 256
+    workgroups (by more than the 8 % that the former are faster)."""
+    rounds = lambda N, B, granules, rows: -(-(-(--(-N // 128) // granules) * -(-B // rows)) // 256)
+    rng = random.Random(6)
+    cases = [(28672, B) for B in (224, 256, 257, 270, 288, 289, 500)] + [(int(2 ** rng.uniform(10, 15)), int(2 ** rng.uniform(5.1, 12))) for _ in range(2000)]
+    half = {}
+    for (N, B), (_, _, [alone]) in zip(cases, geometry([line(B, 4096, [N], 4, 1, 128) for N, B in cases])):
+        if alone["prompt"]:
+            half[N, B] = alone["half"]
+            assert alone["half"] == (12 * rounds(N, B, 4, 64) <= 13 * rounds(N, B, 8, 32)), (N, B)
+        else:
+            assert not alone["half"]
+    assert [half[28672, B] for B in (224, 256, 257, 270, 288, 289, 500)] == [1, 1, 0, 0, 0, 1, 1]
+    assert len(half) > 500 and all(rounds(N, B, 4, 64) <= 1.09 * rounds(N, B, 8, 32) for (N, B), h in half.items() if h)
+    for [alone] in (a for _, _, a in geometry([line(270, 4096, [28672], v, m, g) for v, m, g in ((4, 1, -1), (8, 2, 128), (4, 2, 128))])):
+        assert alone["prompt"] and not alone["half"]
