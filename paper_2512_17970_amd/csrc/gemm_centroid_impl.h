@@ -597,7 +597,7 @@ int launch_gemm_centroid_one(const Geometry& g, const GemmParams& p, hipStream_t
 template <int M, int V, int GS>
 int launch_gemm_centroid_v(const Geometry& g, const GemmParams& p, hipStream_t stream)
 {
-    // 128-row blocks with staged operands have a kernel of their own (gemm_staged_impl.h), but for one shape that does not fit
+    // 128-row blocks with staged operands have a kernel of their own (gemm_staged_impl.h), from a K on, and but for one shape that does not fit
     constexpr bool STAGED = GS <= 1 && ((V == 8 && M <= 2) || (V == 4 && M == 1)), WIDE = V == 8 && M == 1;
     constexpr int D1 = centroid_ring(M, V, 4, GS, true), D4 = centroid_ring(M, V, 4, GS, false), D2 = centroid_ring(M, V, 2, GS, false);
     switch (g.BG) {
@@ -610,14 +610,14 @@ int launch_gemm_centroid_v(const Geometry& g, const GemmParams& p, hipStream_t s
             if (g.RB == 64) return launch_gemm_centroid_one<M, V, 4, 1, 2, 4, D4, GS>(g, p, stream);
             return launch_gemm_centroid_one<M, V, 4, 1, 1, 8, D4, GS>(g, p, stream);
         case 8:
-            if constexpr (!STAGED) {
+            if constexpr (!(STAGED && V == 8 && GS == 1)) {
                 if (g.RB == 128) return launch_gemm_centroid_one<M, V, 2, 1, 2, 4, D2, GS>(g, p, stream);
             }
             if (g.RB == 64) return launch_gemm_centroid_one<M, V, 2, 1, 1, 8, D2, GS>(g, p, stream);
             if constexpr (V < 16) return launch_gemm_centroid_one<M, V, 4, 2, 1, 8, 3, GS>(g, p, stream);
             break;
         case 16:
-            if constexpr (!STAGED || (WIDE && GS == 1)) {
+            if constexpr (!STAGED || WIDE) {
                 if (g.RB == 128) return launch_gemm_centroid_one<M, V, 1, 1, 1, 8, 2, GS>(g, p, stream);
             }
             if constexpr (V < 16 && ((GS != 2 && GS != 4) || M == 1)) {

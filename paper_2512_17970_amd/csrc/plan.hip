@@ -62,23 +62,29 @@ static int centroid_min_rows(const codegemm_desc* d)
 }
 
 // Batch rows of a workgroup of the kernel that stages codes and x in LDS, or 0: the centroid kernel.  Blocks of 128 rows, fp16
-// output, one or two codebooks of short vectors, groups that hold a step of 16 chunks.  `range` is the K of a workgroup.  Measured
-// (us back to back, centroid kernel / here; 128-row blocks):
-//  * Up to 4 rows with group scales: 8192->28672 v8 m2 23.3 / 20.0, v8 m1 15.2 / 12.4, v4 m1 17.1 / 15.2, 28672->8192 v8 m2 in four
-//    ranges 23.9 / 20.0; with little K the centroid kernel's second workgroup on a compute unit makes up for it (2048->28672 8.6 /
-//    8.8, 8192->8192 in four ranges 10.5 / 10.9, with 5 % more time per lookup than now).  One scale per row ties or loses (8192->57344
-//    34.4 / 35.9, 4096->28672 11.6 / 12.1): nothing is picked or scaled there.
-//  * 5 to 16 rows, in tiles of 16 (of 8 when v8 m1 has group scales, whose 16 rows do not fit): 8192->28672 v8 m2 8 rows 21.5 / 20.3, g128
-//    24.5 / 21.1; 4096->28672 16 rows v8 m2 16.0 / 13.8, v4 m1 14.2 / 11.6, g128 14.5 / 12.4.
-//  * 17 to 32 rows: two tiles of 16 where they fit (4096->28672 v8 m2 23.2 / 20.6, v4 m1 20.0 / 16.3), one per workgroup with
-//    group scales.
+// output, one or two codebooks of short vectors, groups that hold a step of 16 chunks.  `range` is the K of a workgroup: filling the rings and
+// turning a tile over cost the same whatever K is.  Measured on default plans of 13 000 random calls, time of the centroid kernel / time here, by
+// range, up to 256 workgroups (above: the centroid kernel has two workgroups on a compute unit, the rings leave room for one):
+//  * 2 to 4 rows with group scales: v8 m1 1.05 from 3072 on, 1.18 at 6144, 1.36 at 16000; v8 m2 0.99 at 3072, 1.02 at 4096, 1.10 at 7168,
+//    1.15 at 16000; v4 m1 0.97 at 3072, 1.02 to 1.04 up to 8192, 1.10 at 16000.  (Above 256: 0.88 at 3072 and 1.00 at 6144; 0.82, 0.94 from 7168
+//    on; 0.83, 0.95 at 6144, 0.98.)  One scale per row ties or loses (8192->57344 34.4 / 35.9 us, 4096->28672 11.6 / 12.1): nothing is picked or scaled there.
+//  * 5 to 8 rows, a tile of 16 (of 8 when v8 m1 has group scales, whose 16 rows do not fit): v8 m1 0.85 to 0.96 below 6144, 1.01 there, 1.04 at
+//    8192, 1.13 at 16000, with group scales 1.01 to 1.25; v8 m2 0.95 below 1024, 1.00 there, then 1.04 to 1.13, with group scales 1.02
+//    to 1.14; v4 m1 0.91, 0.97, 1.02 (below 1024, 2048, 3072) to 1.28, with group scales 0.81, 0.94, 1.07 to 1.32.  (Above 256: v8 m1 0.79 to 0.94 below
+//    10000; v4 m1 0.93 to 1.00 from 2048 to 6144, with group scales 0.83 to 0.98.)
+//  * 9 to 16 rows: v8 m1 0.94 and 0.97 below 2048, 1.03 to 1.19 from there on; v8 m2 1.03 to 1.17, v4 m1 1.03 to 1.26.
+//  * 17 to 32 rows: two tiles of 16 where they fit (v8 m2 1.06 to 1.16, v4 m1 1.06 to 1.29), one per workgroup with group scales (1.02 to
+//    1.13, 1.03 to 1.26).
+// Up to 16 rows the kernel does not depend on the number of workgroups: a layer alone has others than in a group.
 static int staged_batch(const codegemm_desc* d, int rows, int range)
 {
     const int v = d->vec_len, m = d->num_codebooks, b = d->batch;
     const bool grouped = d->group_size > 0, wide = v == 8 && m == 1;
     if (rows != 128 || (d->flags & CODEGEMM_FLAG_Y_FP32) || short_groups(d) || !((v == 8 && m <= 2) || (v == 4 && m == 1))) return 0;
-    if (b <= 4) return b > 1 && grouped && range >= 3072 ? 4 : 0;
+    if (b <= 4) return b > 1 && grouped && range >= (v == 4 ? 7168 : wide ? 3072 : 4096) ? 4 : 0;
+    if (b <= 8 && range < (v == 4 ? 2048 : grouped ? 0 : wide ? 8192 : 1024)) return 0;
     if (wide && grouped) return b <= 8 ? 8 : 0;
+    if (wide && b <= 16 && range < 2048) return 0;
     if (b <= 16 || grouped) return 16;
     return wide ? 0 : 32;
 }

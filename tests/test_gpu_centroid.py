@@ -280,7 +280,7 @@ def test_staged_operands(v, m, g, B):
 
 def test_staged_operands_leave_the_neighbours_of_x_alone():
     """The last row of x is followed by other memory, here NaN: what a stage reads past the end of a row counts for nothing."""
-    for v, m, K, B in ((8, 2, 1032, 6), (8, 1, 1096, 13), (4, 1, 1028, 16), (8, 2, 2056, 31)):
+    for v, m, K, B in ((8, 2, 1032, 6), (8, 1, 1096, 13), (8, 1, 2120, 13), (8, 1, 8200, 7), (4, 1, 1028, 16), (4, 1, 2052, 5), (8, 2, 2056, 31)):
         inp = synth.generate(synth.custom_case(K, 130, v, m, B, seed=3500 + K))
         y_ref, T = oracle.gemm(inp.x, inp.codes, inp.codebooks, inp.scales)
         layer = DeviceLayer(inp, plan=plan_of(inp.case, 128, 1))
@@ -290,3 +290,12 @@ def test_staged_operands_leave_the_neighbours_of_x_alone():
         y = layer.gemm()
         torch.cuda.synchronize()
         check_against_oracle(y.cpu().numpy(), y_ref, T, inp.case.name)
+
+
+@pytest.mark.parametrize("v,m,g,B", [(8, 1, -1, 5), (8, 1, -1, 8), (8, 2, -1, 6), (4, 1, -1, 7), (4, 1, 128, 5), (4, 1, 256, 8), (8, 1, -1, 9), (8, 1, -1, 16)])
+def test_blocks_of_128_rows_on_either_side_of_the_staged_kernel(v, m, g, B):
+    """5 to 16 rows: with a short K operands go through registers, from a K of 1024 to 8192 on through LDS."""
+    unit = max(g, v)
+    for K in sorted({max(unit, K // unit * unit) for K in (v, 33 * v, 1000, 1030, 2000, 2500, 8000, 8700)}):
+        for splits in (1, 3):
+            run(synth.custom_case(K, 200, v, m, B, seed=3550 + K, g=g), 128, splits)

@@ -113,3 +113,18 @@ def test_half_octets_take_no_extra_round(geometry):
     assert len(half) > 500 and all(rounds(N, B, 4, 64) <= 1.09 * rounds(N, B, 8, 32) for (N, B), h in half.items() if h)
     for [alone] in (a for _, _, a in geometry([line(270, 4096, [28672], v, m, g) for v, m, g in ((4, 1, -1), (8, 2, 128), (4, 2, 128))])):
         assert alone["prompt"] and not alone["half"]
+
+
+@pytest.mark.parametrize("v,m,g,B,least", [
+    (8, 2, 128, 4, 4096), (8, 1, 128, 2, 3072), (4, 1, 128, 3, 7168), (8, 2, -1, 4, None), (8, 1, -1, 2, None), (8, 2, 64, 4, None),
+    (8, 2, -1, 5, 1024), (8, 1, -1, 8, 8192), (4, 1, -1, 6, 2048), (4, 1, 128, 7, 2048), (8, 2, 128, 8, 0), (8, 1, 128, 5, 0),
+    (8, 2, -1, 9, 0), (8, 1, -1, 16, 2048), (8, 1, 128, 12, None), (4, 1, -1, 16, 0), (4, 1, 128, 9, 0),
+    (8, 2, -1, 17, 0), (8, 1, -1, 32, None), (4, 1, 128, 24, 0), (8, 2, 128, 1, None), (8, 3, -1, 16, None)])
+def test_staged_kernel_from_a_k_on(geometry, v, m, g, B, least):
+    """128-row blocks: the K of a workgroup, whole units of 32 sub-vectors, from which on it stages its operands.  None: never."""
+    Ks = sorted({k for K in (1024, 2048, 3072, 4096, 7168, 8192, 28672) for k in (K, K - 32 * v)})
+    cases = [(k, splits, fp32) for k in Ks for splits in (1, 2) for fp32 in (0, 1)]
+    lines = [line(B, k * splits, [3000], v, m, g, fp32=fp32, plan=(8, 1, 2, 4, 0, 0, 128, splits)) for k, splits, fp32 in cases]
+    for (k, splits, fp32), (st, [member], [alone]) in zip(cases, geometry(lines)):
+        assert st == 0 and member["kpw"] * 32 * v == k and same(member, alone)
+        assert member["staged"] == (not fp32 and least is not None and k >= least), (k, splits, fp32)
