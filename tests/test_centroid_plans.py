@@ -151,3 +151,10 @@ def test_default_plan_keeps_the_other_kernels_where_they_win():
     for B in (2, 8, 32, 500):
         assert plan(B, 8192, 28672, 8, 2).centroid_rows != 0
     assert plan(2, 512, (1 << 24), 8, 1).centroid_rows == 0             # more blocks than a grid has
+
+
+def test_two_rounds_of_tall_blocks_or_three_of_lower_ones():
+    """5 to 8 rows, v8 m2, more than 256 blocks of 128 rows: lower blocks from a K on where a third round of them costs less."""
+    for B, K, N, rows in ((6, 3864, 33410, 128), (8, 5216, 42881, 128), (8, 6240, 40871, 128), (6, 8224, 33591, 64), (6, 27216, 37725, 64)):
+        p = cg.codegemm_default_plan(cg.Desc.make(B, K, N, 8, 2))
+        assert (p.centroid_rows, p.centroid_splits) == (rows, 1), (B, K, N, p)
