@@ -426,8 +426,9 @@ def sweep_report(torch, cg, synth, cases, launch):
 def kernel_of(plan, batch):
     """Name of the kernel that a layer runs under its plan."""
     if plan.centroid_rows and plan.psum_dtype == 0:
-        # by block height, format and output: batches of 128-row blocks with staged operands, large ones of many workgroups
-        return "cg::gemm_centroid_kernel" + (" or cg::gemm_staged_kernel" if batch > 1 else "") + (" or cg::gemm_prompt_kernel" if batch > 32 else "")
+        # 128-row blocks stage their operands from a K on that depends on format and batch, large batches of many workgroups are prompts
+        staged = plan.centroid_rows == 128 and batch > 1
+        return "cg::gemm_centroid_kernel" + (" or cg::gemm_staged_kernel" if staged else "") + (" or cg::gemm_prompt_kernel" if batch > 32 else "")
     return "cg::gemm_batch_kernel" if plan.batch_group == 4 else "cg::gemm_kernel"
 
 

@@ -23,7 +23,7 @@ constexpr int kGranuleRows = 128;   // rows per packed unit: 16 half-wavefronts 
 // more than 256 row blocks x batch groups AND several K ranges get a smaller stride.
 constexpr int kCounterStride = 64;
 constexpr int kCounterAreaWords = 16384;   // 64 KB
-// Behind the counters: 64-bit words of the pairwise reduction between K ranges (2, 4 or 8 of them), which every call
+// Behind the counters: 64-bit words of the pairwise reduction between K ranges (2 or 4 of them), which every call
 // finds and leaves all zero like the counters.  Calls whose words do not fit use the ticket and the fp32 partials.
 constexpr size_t kPairAreaBytes = 2u << 20;
 constexpr int kMaxLds = 160 * 1024; // LDS per workgroup on gfx950

@@ -565,10 +565,14 @@ __global__ void __launch_bounds__(RW * KW * 64) gemm_centroid_kernel(CG_HEAD_PAR
 }
 
 // Steps in the load ring of the kernels with one tile of batch rows: four, but three or two where that is what brings a lane's
-// registers down to 128.  One or two codebooks of short vectors take 64 KB of LDS, so two workgroups then share a compute unit, and
-// each fills the other's first loads, table and exchange (v8 m2 g128, 4 rows, two rounds of 128-row blocks at 57344 rows: 134
-// registers 46.4 us, 122 registers 38.2; v4 m1 g128, 8 rows, 4096->28672, 164 and 124: 13.3 and 12.6).  Where both depths fit, the
-// deeper one wins (8B block, v4 m1 g128, one row: three steps 30.4 us, four 28.8).
+// registers down to 128.  One or two codebooks of short vectors take 64 KB of LDS, so in launches of more than 256 workgroups two then share
+// a compute unit, and each fills the other's first loads, table and exchange (8192->57344 v8 m2 g128, 4 rows: 134 registers 45.1 us,
+// 122 registers 40.4).  Time of four steps / time here, 3800 random sizes: above 256 workgroups 1.05 to 1.24 with a K below 8192, 1.00 to 1.15
+// beyond.  It wins with one workgroup on a compute unit too, by some 0.4 us a call (why is not known): 32-row blocks 1.05 to 1.08
+// below K = 3072, 0.99 to 1.09 above; 64-row blocks 1.05 to 1.08 and 0.96 to 1.09; 128-row blocks of two codebooks 1.04 to 1.06 and 1.00 to 1.06, of
+// one 1.01 and 0.94 to 1.01 (v8 fp32 output with group scales is the format below 0.96; its sums move to the totals once a turn, so that the
+// depth has to be the same at any number of workgroups).  5 to 8 rows, 64-row blocks, v4 m1: 1.07, with group scales 1.14.  Where both depths fit,
+// the deeper one wins (8B block, v4 m1 g128, one row: three steps 30.4 us, four 28.8).
 __host__ __device__ constexpr int centroid_ring(int m, int v, int sb, int gs, bool one)
 {
     const bool shared = v < 16 && m <= 2;              // the table leaves room for a second workgroup

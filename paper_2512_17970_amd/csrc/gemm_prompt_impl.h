@@ -4,18 +4,18 @@
 //
 // A lookup is paid once per 64 codes whatever the batch, so with NT tiles of 16 batch rows per
 // wavefront the matrix cores take over as the bound (NT = 4: 32 lookups, 64 for v = 4, and 128 MFMAs
-// per step and codebook; counters at 8192^2 v8 m2 batch 2048: matrix cores 83 % busy, LDS 33 %), at the clock
-// that their power leaves: 1.87 GHz there, 2.37 with x = 0, which takes 298 us instead of 367.  Each
-// of the 8 wavefronts owns 128 rows and streams through the whole of K, there is nothing to sum
-// across wavefronts or workgroups, and x is staged in LDS for all of them: one step (16 chunks of 16 bytes, 128 elements) of 16 NT batch rows, double-buffered, one barrier per
-// step.  Measured: 8192^2 v8 m2 at batch 2048 352 us, 64 launches of 32 rows 2584 (the two
-// codebooks make it 550 GFLOP of MFMAs: 1.56 PFLOP/s; this instruction alone, in registers, reaches
-// 1.87 on this card).
+// per step and codebook; counters at 8192^2 v8 m2 batch 2048: matrix cores 85 % busy, LDS 29 %), at the clock
+// that their power leaves: 1.87 GHz there, 2.37 with x = 0.  Each of the 8 wavefronts owns 128 rows and streams
+// through the whole of K, there is nothing to sum across wavefronts or workgroups, and x is staged in LDS for all of
+// them: one step (16 chunks of 16 bytes, 128 elements) of 16 NT batch rows, double-buffered, one barrier per step.
+// Measured in one run: 8192^2 v8 m2 at batch 2048 375 us (357 on other boxes), 281 with x = 0, 64 launches of 32 rows 1231.
+// The two codebooks make it 550 GFLOP of MFMAs: 1.47 to 1.54 PFLOP/s; this instruction alone, in registers, reaches 1.87.
 //
 // UR: rows of an octet that a wavefront takes, 8 or (v4 m1 with group scales) 4.  With sums of their own beside the accumulators there are
 // registers for two tiles of 8 rows, and then v = 4, which needs two lookups per MFMA operand, is bound by the LDS (4.5 cycles per
 // MFMA and compute unit, an MFMA takes 4).  Four tiles of 4 rows hold as many sums and make it 3: two neighbouring wavefronts share a
-// granule, each with its half of every octet.  4096->28672 v4 m1 g128, batch 500: 124 -> 118 us; g32, whose chains are shorter: 218 -> 152.
+// granule, each with its half of every octet.  4096->28672 v4 m1 g128, batch 500: 129 -> 123 us, g32 159 -> 148.  Where it makes one more round
+// of workgroups UR stays 8 (make_geometry).
 //
 // Chunk 4 q + j of row r lies at place (4 j + q) ^ (r % 16) of its 256-byte row: the operand reads of a round take lanes of all four q
 // in one LDS cycle, and with the chunks in order (place (4 q + j) ^ (r % 16)) these were 2-way conflicts (3.5 against 1.9 ns per read).
@@ -242,7 +242,8 @@ __global__ void __launch_bounds__(512) gemm_prompt_kernel(CG_HEAD_PARAMS, const 
         }
     };
     // Beside MFMAs, and the next codes turned late, but for v4 m2 with short groups, where both spill (2048->8192 g32, batch 512: 100
-    // us, 90 with the sums behind the MFMAs and the codes turned first).
+    // us, 90 with the sums behind the MFMAs and the codes turned first).  Other formats, time of that order / time here on random sizes: 1.00
+    // to 1.11 for v8 m1, m2 and v4 m1, v4 m2 1.20, v8 m3 1.06, m4 1.39 with long and 1.05 with short groups, though these spill more (112 registers, 93).
     constexpr bool BESIDE = !(V == 4 && M == 2 && GS == 2);
     auto add_scaled = [&](const half8_t& scales, int u) {
         const float f = (float)scales[u];
