@@ -411,6 +411,11 @@ static void choose_plan(const codegemm_desc* d, codegemm_plan* p)
     int rows = 128;
     if (d->batch <= 4) {
         rows = low_rows(d->out_features);
+        // 513 to 768 blocks of 64 rows, two or three on a compute unit, where those of 128 rows are staged, one on a unit, and take a second round
+        // (700 random sizes, 2 to 4 rows, time of 64 rows / of 128 staged / of 128 on the centroid kernel, in parts of the second: v8 m1 0.87 / 1 / 0.89
+        // at K = 3072, 0.92 / 1 / 1.05 at 8000, 0.97 / 1 / 1.19 at 25000; v8 m2 0.82 / 1 and v4 m1 0.86 / 1 from 7000 on.  769 to 1024: 1.06 to 1.20,
+        // 0.98 to 1.04 and 1.00 to 1.04.)
+        if (rows == 128 && blocks(64) > 512 && blocks(64) <= 768 && staged_batch(d, 128, nkt * kSlots * d->vec_len)) rows = 64;
     } else if (d->batch <= 8) {
         if (least == 32 && blocks(32) <= 256 && (d->vec_len == 4 ? codes / 2 : codes) <= 10000000) rows = 32;
         else if (blocks(64) <= 256) rows = 64;
@@ -421,9 +426,9 @@ static void choose_plan(const codegemm_desc* d, codegemm_plan* p)
     }
     // K ranges.  Up to 4 batch rows: powers of two (others meet through the ticket, 1 us more than two or four pairwise:
     // three ranges are 10 % slower than two or four at any K), up to 256 workgroups, as long as a range is worth its
-    // exchange.  One / two ranges break even at K = 4300 (time ratio 0.88 at 512 to 1500, 0.98 at 4096, 1.05 at 5000, 1.2
-    // at 14000), two / four at 6500 (0.92 up to 3000, 1.02 at 8192, 1.1 at 14000), four / eight at 9000 (1.02, 1.06 at
-    // 14000, 1.14 from 16000), for 16 to 128 blocks and all formats alike.  More rows: 256 workgroups as long as every
+    // exchange.  One / two ranges break even at K = 4400 (time ratio 0.83 to 0.87 up to 2500, 0.94 at 3500, 1.05 at 6500, 1.2
+    // at 14000), two / four at 6000 (0.87 up to 2000, 0.97 at 4500, 1.06 at 7500, 1.12 at 14000), four / eight at 10000 (0.91 up to 9000, 1.09 at
+    // 14000, 1.12 from 18000), for 16 to 128 blocks and all formats alike.  More rows: 256 workgroups as long as every
     // wavefront keeps a step (4096^2 at batch 8: two ranges 6.5, one 6.8; 2048^2: two 5.6, four, with half of the
     // wavefronts idle, 6.2).
     const int nb = (int)blocks(rows);

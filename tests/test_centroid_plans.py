@@ -158,3 +158,14 @@ def test_two_rounds_of_tall_blocks_or_three_of_lower_ones():
     for B, K, N, rows in ((6, 3864, 33410, 128), (8, 5216, 42881, 128), (8, 6240, 40871, 128), (6, 8224, 33591, 64), (6, 27216, 37725, 64)):
         p = cg.codegemm_default_plan(cg.Desc.make(B, K, N, 8, 2))
         assert (p.centroid_rows, p.centroid_splits) == (rows, 1), (B, K, N, p)
+
+
+@pytest.mark.parametrize("m,v,K,least", [(1, 8, 4096, 3072), (2, 8, 8192, 4096), (1, 4, 8192, 7168)])
+def test_two_rounds_of_staged_blocks_or_more_of_lower_ones(m, v, K, least):
+    """2 to 4 rows with group scales, more than 256 blocks of 128 rows: 64-row blocks while there are at most 768 of them, from the K on
+    that tall blocks are staged at.  A group of that height follows the same plan."""
+    rows = lambda B, K, N, g=128: cg.codegemm_default_plan(cg.Desc.make(B, K, N, v, m, g=g)).centroid_rows
+    for B in (2, 3, 4):
+        assert [rows(B, K, N) for N in (32768, 32769, 40000, 49152, 49153, 57344, 65536)] == [128, 64, 64, 64, 128, 128, 128]
+        assert rows(B, least, 40000) == 64 and rows(B, least - 32 * v, 40000) == 128
+        assert rows(B, K, 40000, -1) == 128

@@ -219,3 +219,9 @@ def test_grouped_at_few_rows_and_long_k(K, Ns, m, B):
     """Group scales, 2 to 4 rows: the default plan of the sum takes 128-row blocks in two or four K ranges, and so do the members alone."""
     plan = run_group(K, list(Ns), 8, m, B, 128, seed=7700)
     assert plan.centroid_rows == 128 and plan.centroid_splits == (2 if m == 1 else 4)
+
+
+def test_grouped_at_few_rows_and_more_than_a_round():
+    """The default plan of the sum takes 64-row blocks, where 128-row blocks would be staged in two rounds, and so do the members alone."""
+    plan = run_group(3072, [20000, 20000], 8, 1, 4, 128, seed=7710)
+    assert (plan.centroid_rows, plan.centroid_splits) == (64, 1)

@@ -51,7 +51,7 @@ def same(member, alone):
 def test_group_members_and_single_calls_run_alike(geometry):
     rng = random.Random(5)
     problems = []
-    for B, K, Ns, v, m, g in ((4, 28672, (4096, 4096), 8, 2, 128), (4, 12288, (12288, 1536, 1536), 8, 1, 128), (3, 16384, (8192, 1024, 1024), 8, 2, 128)):
+    for B, K, Ns, v, m, g in ((4, 28672, (4096, 4096), 8, 2, 128), (4, 12288, (12288, 1536, 1536), 8, 1, 128), (3, 16384, (8192, 1024, 1024), 8, 2, 128), (4, 4096, (20000, 20000), 8, 1, 128)):
         problems.append((B, K, Ns, v, m, g, 0, None, None))
     for _ in range(4000):
         v, m = rng.choice([(8, 1), (8, 2), (8, 2), (8, 3), (4, 1), (4, 2), (16, 2), (16, 4)])
