@@ -269,7 +269,7 @@ def test_fp32_output_is_no_further_from_64_bits_than_the_psumbook_kernels(v, m, 
 def test_staged_operands(v, m, g, B):
     """128-row blocks, fp16 output: codes and x pass through a ring of stages (8 or 16 chunks of 16 bytes of x) in LDS.  Slices of 0, 1,
     2 .. stages per wavefront, a last stage that the rows of x end inside of (at every number of chunks, half a chunk for v = 4)
-    or that lies wholly behind them, K ranges (from 3072 elements on with up to 4 rows, else the centroid kernel), ragged N."""
+    or that lies wholly behind them, K ranges, ragged N.  (Short ones of 2 to 8 rows are the centroid kernel's: up to 8192 elements.)"""
     unit = max(g, v)
     Ks = [v, 32 * v, 3072, 3072 + 64 * v, 8192] + [2048 + c * v for c in (1, 2, 7, 9, 15, 17, 31, 33)]
     for K in sorted({max(unit, K // unit * unit) for K in Ks}):
@@ -299,3 +299,13 @@ def test_blocks_of_128_rows_on_either_side_of_the_staged_kernel(v, m, g, B):
     for K in sorted({max(unit, K // unit * unit) for K in (v, 33 * v, 1000, 1030, 2000, 2500, 8000, 8700)}):
         for splits in (1, 3):
             run(synth.custom_case(K, 200, v, m, B, seed=3550 + K, g=g), 128, splits)
+
+
+@pytest.mark.parametrize("v,m,g,B,least", [(8, 2, 128, 2, 4096), (8, 2, 256, 4, 4096), (8, 1, 128, 3, 3072), (8, 1, 256, 4, 3072), (4, 1, 128, 4, 7168), (4, 1, 256, 2, 7168), (8, 1, -1, 6, 8192)])
+def test_staged_operands_of_few_rows(v, m, g, B, least):
+    """From the K on that these formats are staged at: odd numbers of steps, slices of unequal length, a last unit that K ends inside of, K ranges."""
+    step = max(g, 8 * v)
+    for K in (least, least + step, least + 3 * step, least + 13 * step):
+        run(synth.custom_case(K, 200, v, m, B, seed=3580 + K, g=g), 128, 1)
+    for splits in (2, 3):
+        run(synth.custom_case(splits * least + 5 * step, 200, v, m, B, seed=3590 + splits, g=g), 128, splits)
