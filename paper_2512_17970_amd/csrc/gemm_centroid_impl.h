@@ -86,6 +86,53 @@ __device__ __forceinline__ void row_exchange(uint32_t& a, uint32_t& b)
     b = r[1];
 }
 
+// Row scale of the output rows of this thread (all of them are row tid % RB of the block), requested while K is streamed: asked for at the
+// end it is the one load that a call still waits for (0.3 to 0.7 us).
+template <int RB>
+__device__ __forceinline__ uint32_t row_scale_bits(const Member& mm, int tid, int blk)
+{
+    const int nn = blk * RB + tid % RB;
+    return reinterpret_cast<const uint16_t*>(mm.scales)[nn < mm.N ? nn : 0];
+}
+
+// Sums over the SLICES partials that the wavefronts have left in LDS, [slice][batch row][RB + 4] (the pad spreads the batch rows over the
+// banks), and the end of the workgroup's work.  Each thread adds up the outputs that it then stores; all tiles of batch rows
+// together: one barrier in front and one behind, where a tile at a time with its totals in LDS took 0.5 (8 rows) to 1.7 us (16 rows in
+// 32-row blocks) of a call.
+template <int THREADS, int BT, int RB, int SLICES>
+struct SliceSums {
+    static constexpr int kStride = RB + 4;
+    static constexpr size_t kBytes = (size_t)SLICES * BT * kStride * sizeof(float);
+    static constexpr size_t kLds = kBytes + 64;        // .. and the ticket's flag
+    static_assert(THREADS % RB == 0, "one row of W per thread");
+    static __device__ __forceinline__ void finish(const GemmParams& p, const Member& mm, float* parts, uint32_t scale_bits, int tid, int blk, int ks, int b0)
+    {
+        constexpr int PER_THREAD = (BT * RB + THREADS - 1) / THREADS;
+        float mine[PER_THREAD];
+        CG_STAMP(16);
+        __syncthreads();
+        CG_STAMP(17);
+        const float* src = parts + tid / RB * kStride + tid % RB;
+#pragma unroll
+        for (int i = 0; i < PER_THREAD; ++i) {
+            const int b = tid / RB + i * (THREADS / RB);
+            mine[i] = 0.0f;
+            if (b < BT && b0 + b < p.B) {
+                float t[SLICES];                       // added in pairs: fewer roundings on the way of each
+#pragma unroll
+                for (int k = 0; k < SLICES; ++k) t[k] = src[(k * BT + i * (THREADS / RB)) * kStride];
+#pragma unroll
+                for (int w = SLICES / 2; w > 0; w /= 2)
+#pragma unroll
+                    for (int k = 0; k < w; ++k) t[k] += t[k + w];
+                mine[i] = t[0];
+            }
+        }
+        const uint32_t bits[1] = {scale_bits};
+        finish_values<THREADS, BT, RB>(p, mm, mine, bits, reinterpret_cast<uint32_t*>(reinterpret_cast<unsigned char*>(parts) + kBytes), tid, blk, ks, b0);
+    }
+};
+
 // SB: sub-vectors along the columns of the operands (16 / SB octets per wavefront, 16 / SB batch rows per tile).
 // NT: tiles of batch rows.  RW x KW wavefronts: RW blocks of 128 / SB rows, KW slices of K.  D: steps in the load
 // ring.  GS: 0 one scale per row; 1 group scales, a step (16 chunks) lies in one group; 2 groups of 4 or 8 chunks (a
@@ -340,6 +387,8 @@ __global__ void __launch_bounds__(RW * KW * 64) gemm_centroid_kernel(CG_HEAD_PAR
         load_x(xr[d], s_beg + d);
         if constexpr (SCALED) load_scales(sc[d], s_beg + d);
     }
+    uint32_t scale_bits = 0x3c00u;
+    if constexpr (!SCALED) scale_bits = row_scale_bits<RB>(mm, tid, blk);
     __builtin_amdgcn_sched_barrier(0);
 
     // replicate the centroids
@@ -519,19 +568,13 @@ __global__ void __launch_bounds__(RW * KW * 64) gemm_centroid_kernel(CG_HEAD_PAR
     }
     if constexpr (SHORT) move_up();
 
-    // Sum over the wavefronts' K slices, one tile of batch rows at a time: partials in LDS
-    // [slice][batch row][RB + 4] (ONE: the four sub-vectors of a slice apart), totals behind
-    // them as [batch row][RB].
-    constexpr int STRIDE = RB + 4;                     // floats; the pad spreads the batch rows over the banks
+    // Sum over the wavefronts' K slices: partials in LDS (ONE: the four sub-vectors of a slice apart), all tiles of batch rows at once.
     constexpr int SLICES = ONE ? 4 * KW : KW;
+    typedef SliceSums<THREADS, BT, RB, SLICES> Sums;
     float* parts = reinterpret_cast<float*>(smem);
-    float* totals = parts + SLICES * BPT * STRIDE;
-    uint32_t* flag = reinterpret_cast<uint32_t*>(totals + BT * RB);
     __syncthreads();                                   // everyone is done with the table
 #pragma unroll
-    for (int nt = 0; nt < NT; ++nt) {
-        const int nb = min(p.B - b0 - BPT * nt, BPT);  // rows of this tile
-        if (nt > 0) __syncthreads();                   // the previous tile's partials have been read
+    for (int nt = 0; nt < NT; ++nt)
 #pragma unroll
         for (int t = 0; t < TL; ++t) {
             float v[8];
@@ -541,27 +584,14 @@ __global__ void __launch_bounds__(RW * KW * 64) gemm_centroid_kernel(CG_HEAD_PAR
                 if constexpr (SB >= 2 && !ONE) v[u] = dpp_add<0xb1, 0xf>(v[u]);
                 if constexpr (SB == 4 && !ONE) v[u] = dpp_add<0x4e, 0xf>(v[u]);
             }
-            const int b = ONE ? 0 : TL * q + t;
-            if (ONE ? (lane & 3) == q : b < nb && (lane & (SB - 1)) == 0) {
-                float* dst = parts + ((ONE ? kw * 4 + q : kw) * BPT + b) * STRIDE + (rw * OCT + col_o) * 8;
+            const int b = ONE ? 0 : BPT * nt + TL * q + t;
+            if (ONE ? (lane & 3) == q : b0 + b < p.B && (lane & (SB - 1)) == 0) {
+                float* dst = parts + ((ONE ? kw * 4 + q : kw) * BT + b) * Sums::kStride + (rw * OCT + col_o) * 8;
                 *reinterpret_cast<float4_t*>(dst) = float4_t{v[0], v[1], v[2], v[3]};
                 *reinterpret_cast<float4_t*>(dst + 4) = float4_t{v[4], v[5], v[6], v[7]};
             }
         }
-        __syncthreads();
-        for (int o = tid; o < nb * RB; o += THREADS) {
-            const int b = o / RB, n = o % RB;
-            float t[SLICES];                           // added in pairs: fewer roundings on the way of each
-#pragma unroll
-            for (int k = 0; k < SLICES; ++k) t[k] = parts[(k * BPT + b) * STRIDE + n];
-#pragma unroll
-            for (int w = SLICES / 2; w > 0; w /= 2)
-#pragma unroll
-                for (int k = 0; k < w; ++k) t[k] += t[k + w];
-            totals[(BPT * nt + b) * RB + n] = t[0];
-        }
-    }
-    finish_block<THREADS, BT, RB>(p, mm, totals, flag, tid, blk, ks, b0);
+    Sums::finish(p, mm, parts, scale_bits, tid, blk, ks, b0);
 }
 
 // Steps in the load ring of the kernels with one tile of batch rows: four, but three or two where that is what brings a lane's
@@ -587,7 +617,7 @@ int launch_gemm_centroid_one(const Geometry& g, const GemmParams& p, hipStream_t
     auto fn = gemm_centroid_kernel<M, V, SB, NT, RW, KW, D, GS, ONE>;
     constexpr int RB = 128 / SB * RW, BPT = ONE ? 1 : 16 / SB;
     if (g.RB != RB || g.BG != BPT * NT) return CODEGEMM_UNSUPPORTED;
-    constexpr size_t stage = (size_t)((ONE ? 4 * KW : KW) * BPT * (RB + 4) + BPT * NT * RB) * sizeof(float) + 64;
+    constexpr size_t stage = SliceSums<RW * KW * kWave, BPT * NT, RB, ONE ? 4 * KW : KW>::kLds;
     constexpr size_t table = CentroidTable<M, V>::kBytes;
     constexpr size_t lds = stage > table ? stage : table;
     static_assert(lds <= (size_t)kMaxLds, "LDS");

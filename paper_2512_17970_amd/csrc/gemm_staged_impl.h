@@ -189,6 +189,8 @@ __global__ void __launch_bounds__(512) gemm_staged_kernel(CG_HEAD_PARAMS, const 
     };
 #pragma unroll
     for (int d = 0; d < D; ++d) request(s_beg + d, d);
+    uint32_t scale_bits = 0x3c00u;
+    if constexpr (!GS) scale_bits = row_scale_bits<RB>(mm, tid, blk);
 
     if constexpr (V == 4) {
         wait_requests<S::loads(0, D)>();
@@ -340,43 +342,25 @@ __global__ void __launch_bounds__(512) gemm_staged_kernel(CG_HEAD_PARAMS, const 
     }
     wait_requests<0>();                                 // those past the end: the LDS is used again
 
-    // Sum over the wavefronts' K slices as in the centroid kernel: partials in LDS [slice][batch row][RB + 4], totals behind them.
-    // Lane (i16, q): rows 8 i16 .. + 7, batch rows 16 nt + 4 q + e.
-    constexpr int STRIDE = RB + 4;
+    // Sum over the wavefronts' K slices as in the centroid kernel.  Lane (i16, q): rows 8 i16 .. + 7, batch rows 16 nt + 4 q + e.
+    typedef SliceSums<THREADS, BT, RB, KW> Sums;
     float* parts = reinterpret_cast<float*>(smem);
-    float* totals = parts + KW * BR * STRIDE;
-    uint32_t* flag = reinterpret_cast<uint32_t*>(totals + BT * RB);
     __syncthreads();                                    // everyone is done with the table
 #pragma unroll
-    for (int nt = 0; nt < NT; ++nt) {
-        const int nb = min(p.B - b0 - BR * nt, BR);    // rows of this tile
-        if (nt > 0) __syncthreads();                   // the previous tile's partials have been read
+    for (int nt = 0; nt < NT; ++nt)
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
             const int b = 4 * q + e;
-            if (b < nb) {
+            if (b < BR && b0 + BR * nt + b < p.B) {
                 float v[8];
 #pragma unroll
                 for (int u = 0; u < 8; ++u) v[u] = GS ? sum[GS ? nt : 0][GS ? u : 0][e] : acc[nt][u][e];
-                float* dst = parts + (wave * BR + b) * STRIDE + i16 * 8;
+                float* dst = parts + (wave * BT + BR * nt + b) * Sums::kStride + i16 * 8;
                 *reinterpret_cast<float4_t*>(dst) = float4_t{v[0], v[1], v[2], v[3]};
                 *reinterpret_cast<float4_t*>(dst + 4) = float4_t{v[4], v[5], v[6], v[7]};
             }
         }
-        __syncthreads();
-        for (int o = tid; o < nb * RB; o += THREADS) {
-            const int b = o / RB, n = o % RB;
-            float t[KW];
-#pragma unroll
-            for (int k = 0; k < KW; ++k) t[k] = parts[(k * BR + b) * STRIDE + n];
-#pragma unroll
-            for (int h = KW / 2; h > 0; h /= 2)
-#pragma unroll
-                for (int k = 0; k < h; ++k) t[k] += t[k + h];
-            totals[(BR * nt + b) * RB + n] = t[0];
-        }
-    }
-    finish_block<THREADS, BT, RB>(p, mm, totals, flag, tid, blk, ks, b0);
+    Sums::finish(p, mm, parts, scale_bits, tid, blk, ks, b0);
 }
 
 template <int M, int V, int GS, int BR, int NT, int D>
@@ -385,7 +369,7 @@ int launch_gemm_staged_one(const Geometry& g, const GemmParams& p, hipStream_t s
     auto fn = gemm_staged_kernel<M, V, GS, BR, NT, D>;
     typedef StagedShape<M, V, GS, BR, NT, D> S;
     if (g.RB != kGranuleRows || g.BG != BR * NT) return CODEGEMM_UNSUPPORTED;
-    constexpr size_t stage = (size_t)(S::kWaves * BR * (kGranuleRows + 4) + BR * NT * kGranuleRows) * sizeof(float) + 64;
+    constexpr size_t stage = SliceSums<S::kWaves * kWave, BR * NT, kGranuleRows, S::kWaves>::kLds;
     constexpr size_t lds = stage > S::kLds ? stage : S::kLds;
     static_assert(lds <= (size_t)kMaxLds, "LDS");
     int st = set_max_lds(reinterpret_cast<const void*>(fn), lds);
