@@ -103,8 +103,9 @@ __device__ __forceinline__ Member member_of(const GemmParams& p, int grid_blk)
 // the feature falls back to loading them, which the compiler arranges.
 #define CG_HEAD_PARAMS const void* hx, const uint8_t* hpacked, const void* hcodebooks, const uint8_t* hgscales, \
                        int hK, int hNKT, int hKPW, int hB, int hNGR, int hmisc
-#define CG_HEAD_ARGS(p) (p).x, (p).mem[0].packed, (p).mem[0].codebooks, (p).mem[0].gscales, (p).K, (p).NKT, (p).KPW, (p).B, \
-                        (p).mem[0].NGR, ((p).ngrp | ((p).gshift << 8) | ((p).GPU << 16))
+#define CG_HEAD_ARGS_WITH(p, gscales, rows) (p).x, (p).mem[0].packed, (p).mem[0].codebooks, gscales, (p).K, (p).NKT, (p).KPW, (p).B, \
+                                           rows, ((p).ngrp | ((p).gshift << 8) | ((p).GPU << 16))
+#define CG_HEAD_ARGS(p) CG_HEAD_ARGS_WITH(p, (p).mem[0].gscales, (p).mem[0].NGR)
 
 // The argument struct with the early fields taken from the leading scalars (member 0 starts at row block 0).
 __device__ __forceinline__ GemmParams with_head(const GemmParams& pk, CG_HEAD_PARAMS)
