@@ -398,12 +398,12 @@ __global__ void __launch_bounds__(RW * KW * 64) gemm_centroid_kernel(CG_HEAD_PAR
         const int e = TPE > 1 ? tid / TPE : tid + k * THREADS;
         if (e < ENTRIES) {
             const int h = e % T::kHalves, code = (e / T::kHalves) % kCentroids, c = e / (T::kHalves * kCentroids);
-            const uint32_t row = lds0 + (uint32_t)(T::plane(c, h) * 65536 + code * 256 + T::region(c));
-            // columns this thread fills, rotated by row so that a wavefront's stores spread over the banks
+            // columns this thread fills, beginning at another one in every row so that a wavefront's stores spread over the banks
             const int cols = T::columns(c), mine = cols / TPE;
-            const int c0 = (TPE > 1 ? (tid % TPE) * mine + tid / TPE : lane);
+            const int c0 = TPE > 1 ? (tid % TPE) * mine + (tid / TPE & (mine - 1)) : lane & (cols - 1);
+            const uint32_t first = lds0 + (uint32_t)(T::plane(c, h) * 65536 + code * 256 + T::region(c) + c0 * T::kEntry);
             for (int j = 0; j < mine; ++j) {
-                const uint32_t a = row + (uint32_t)((c0 + j) & (cols - 1)) * T::kEntry;
+                const uint32_t a = first ^ (uint32_t)(j * T::kEntry);
                 if constexpr (V == 4) *reinterpret_cast<lds_half4*>(static_cast<uintptr_t>(a)) = fill[k];
                 else *reinterpret_cast<lds_half8*>(static_cast<uintptr_t>(a)) = fill[k];
             }
@@ -601,7 +601,7 @@ __global__ void __launch_bounds__(RW * KW * 64) gemm_centroid_kernel(CG_HEAD_PAR
 // beyond.  It wins with one workgroup on a compute unit too, by some 0.4 us a call (why is not known): 32-row blocks 1.05 to 1.08
 // below K = 3072, 0.99 to 1.09 above; 64-row blocks 1.05 to 1.08 and 0.96 to 1.09; 128-row blocks of two codebooks 1.04 to 1.06 and 1.00 to 1.06, of
 // one 1.01 and 0.94 to 1.01 (v8 fp32 output with group scales is the format below 0.96; its sums move to the totals once a turn, so that the
-// depth has to be the same at any number of workgroups).  5 to 8 rows, 64-row blocks, v4 m1: 1.07, with group scales 1.14.  Where both depths fit,
+// depth has to be the same at any number of workgroups).  5 to 8 rows, v4 m1: 1.07, with group scales 1.14.  Where both depths fit,
 // the deeper one wins (8B block, v4 m1 g128, one row: three steps 30.4 us, four 28.8).
 __host__ __device__ constexpr int centroid_ring(int m, int v, int sb, int gs, bool one)
 {
@@ -631,7 +631,8 @@ int launch_gemm_centroid_one(const Geometry& g, const GemmParams& p, hipStream_t
 template <int M, int V, int GS>
 int launch_gemm_centroid_v(const Geometry& g, const GemmParams& p, hipStream_t stream)
 {
-    // 128-row blocks with staged operands have a kernel of their own (gemm_staged_impl.h), from a K on, and but for one shape that does not fit
+    // From 5 rows on fp16 output of one or two codebooks has a kernel of its own (gemm_staged_impl.h), but for two shapes that do not fit there
+    // and short K
     constexpr bool STAGED = GS <= 1 && ((V == 8 && M <= 2) || (V == 4 && M == 1)), WIDE = V == 8 && M == 1;
     constexpr int D1 = centroid_ring(M, V, 4, GS, true), D4 = centroid_ring(M, V, 4, GS, false), D2 = centroid_ring(M, V, 2, GS, false);
     switch (g.BG) {
@@ -644,20 +645,22 @@ int launch_gemm_centroid_v(const Geometry& g, const GemmParams& p, hipStream_t s
             if (g.RB == 64) return launch_gemm_centroid_one<M, V, 4, 1, 2, 4, D4, GS>(g, p, stream);
             return launch_gemm_centroid_one<M, V, 4, 1, 1, 8, D4, GS>(g, p, stream);
         case 8:
-            if constexpr (!(STAGED && V == 8 && GS == 1)) {
+            if constexpr (!STAGED || V == 4 || GS == 0) {
                 if (g.RB == 128) return launch_gemm_centroid_one<M, V, 2, 1, 2, 4, D2, GS>(g, p, stream);
             }
-            if (g.RB == 64) return launch_gemm_centroid_one<M, V, 2, 1, 1, 8, D2, GS>(g, p, stream);
-            if constexpr (V < 16) return launch_gemm_centroid_one<M, V, 4, 2, 1, 8, 3, GS>(g, p, stream);
+            if constexpr (!STAGED) {
+                if (g.RB == 64) return launch_gemm_centroid_one<M, V, 2, 1, 1, 8, D2, GS>(g, p, stream);
+                if constexpr (V < 16) return launch_gemm_centroid_one<M, V, 4, 2, 1, 8, 3, GS>(g, p, stream);
+            }
             break;
         case 16:
             if constexpr (!STAGED || WIDE) {
                 if (g.RB == 128) return launch_gemm_centroid_one<M, V, 1, 1, 1, 8, 2, GS>(g, p, stream);
             }
-            if constexpr (V < 16 && ((GS != 2 && GS != 4) || M == 1)) {
+            if constexpr (!STAGED && V < 16 && ((GS != 2 && GS != 4) || M == 1)) {
                 if (g.RB == 64) return launch_gemm_centroid_one<M, V, 2, 2, 1, 8, 2, GS>(g, p, stream);
             }
-            if constexpr (V < 16 && (GS == 0 || M == 1)) {
+            if constexpr (!STAGED && V < 16 && (GS == 0 || M == 1)) {
                 if (g.RB == 32) return launch_gemm_centroid_one<M, V, 4, 4, 1, 8, 2, GS>(g, p, stream);
             }
             break;

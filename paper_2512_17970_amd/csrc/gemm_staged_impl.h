@@ -1,5 +1,5 @@
-// The centroid kernel with codes and activations staged in LDS: blocks of 128 rows, fp16 output, one or two codebooks of short
-// vectors.  Included by gemm_prompt_impl.h; table, lookups and columns as in gemm_centroid_impl.h.
+// The centroid kernel with codes and activations staged in LDS: fp16 output, one or two codebooks of short
+// vectors; blocks of 128 rows, and from 5 batch rows on of 64 and 32.  Included by gemm_prompt_impl.h; table, lookups and columns as in gemm_centroid_impl.h.
 //
 // Why a second kernel.  The chip runs out of power before it runs out of anything else here: with lookups, MFMAs and the stream of
 // codes at work its clock falls from 2.4 to 1.2-1.6 GHz (s_memtime against the 100 MHz counter; 8192->57344 v8 m2 with four rows
@@ -15,12 +15,19 @@
 //
 // Measured (us, back to back; before -> here): see staged_batch in plan.hip.
 //
-// A wavefront's stage is 8 pieces of 16 bytes of the codes of each of the 16 octets (two rounds of 4 chunks, four for v8 m1), the
-// x of these chunks and, with group scales, 256 bytes of scales; it keeps D of them.  DMA instruction e of a stage takes octets
-// 8 e .. 8 e + 7: lane -> octet 8 e + lane / 8, piece (lane % 8) ^ (octet / 2) (turn()), which lands at place `lane`, so that the 16 lanes
-// of a read, which take the same piece of 16 octets, touch 16 different columns of 16 bytes (one octet per run of 64 bytes, the
-// plain order, is a 2-way conflict, and 64-byte runs stream 117 MB in 31 us where 128-byte runs take 24).  The lookups have no conflicts; those
-// that are left, a tenth of the LDS cycles (v8 m2 g128, four rows), are in the reads of codes, two halves of 8 bytes, and of x.
+// Lower blocks (SPLIT = 2, 4).  The 16 columns are 8 octets x 2 halves or 4 octets x 4 quarters of their rows: lane (octet, part) reads the
+// 4 or 2 bytes of its rows from the staged entry and takes 4 or 2 lookups per chunk, each of which feeds one MFMA for 16 batch rows whatever the
+// height, where columns of octets x sub-vectors take two (64 rows) or four (32 rows) and discard as much of the result.  us, centroid
+// kernel -> here: v8 m2 16 rows 4096^2 8.7 -> 5.8, 4096->6144 9.4 -> 5.9; 32 rows 14336->4096 18.8 -> 13.4; v4 m1 g128 8 rows 14336->4096 9.9 -> 7.9.
+// 16 wavefronts, of twice the K slices or of two row groups, are slower (5.9 -> 6.6, 6.2 us: each has the same code in front of and behind its
+// loop), and so are three or four stages (5.7 -> 6.1 us, 8 rows) and stages of twice the size for two tiles of short codes (4 to 10 %).
+//
+// A wavefront's stage is 8 or 16 pieces of 16 bytes of the codes of each octet (two rounds of 4 chunks, four for v8 m1 and 32-row blocks), the
+// x of these chunks and, with group scales, 16 bytes of scales per octet; it keeps D of them.  DMA instruction e of a stage takes 64 pieces: lane ->
+// octet and place in its run, which holds piece place ^ turn(octet), so that the 16 lanes of a read, which take the same piece of all octets,
+// touch different columns of 16 bytes (128 rows in the plain order, one octet per run of 64 bytes, is a 2-way conflict, and 64-byte runs stream
+// 117 MB in 31 us where 128-byte runs take 24).  The lookups have no conflicts; those
+// that are left, a tenth of the LDS cycles (v8 m2 g128, four rows, 128-row blocks), are in the reads of codes, two halves of 8 bytes, and of x.
 // Only the wavefront itself reads its stages, so nothing but its own count of outstanding requests orders them: no barrier
 // in the loop.  The compiler does not see these requests (inline assembly without outputs), and waits are written out.
 //
@@ -70,7 +77,7 @@ struct StagedShape {
     static constexpr int kOctets = 16 / SPLIT;         // octets of a block
     static constexpr int kRows = 8 / SPLIT;            // rows of an octet that one lane takes
     static constexpr bool kHalf = V == 8 && M == 1;    // a piece holds two chunks
-    static constexpr int kRounds = kHalf || (SPLIT == 4 && NT == 1) ? 4 : 2;   // rounds (4 chunks of 16 bytes of x) per stage
+    static constexpr int kRounds = NT == 1 && (kHalf || SPLIT == 4) ? 4 : 2;   // rounds (4 chunks of 16 bytes of x) per stage
     static constexpr int kChunks = 4 * kRounds;
     static constexpr int kPieces = kHalf ? kChunks / 2 : kChunks;              // of an octet
     static constexpr int kCodeLoads = (kOctets * kPieces + 63) / 64;
@@ -93,7 +100,7 @@ struct StagedShape {
     static constexpr int kStep = 4 / kRounds;          // stages per step of 16 chunks
     // Piece `pos` of octet o lies at place pos ^ turn(o) of the octet's run, so that 16 lanes which take the same piece of all octets
     // touch different columns of 16 bytes (pieces of two octets share 256 bytes where a run is 128).
-    static __host__ __device__ constexpr int turn(int o) { return (kPieces == 16 ? o : o >> 1) * SPLIT & (kPieces - 1); }
+    static __host__ __device__ constexpr int turn(int o) { return (kPieces == 16 ? o : kPieces == 8 ? o >> 1 : o >> 2) * SPLIT & (kPieces - 1); }
     // Requests of stage t (counted from a step's first; scales come with that one), and of stages t .. t + n - 1.
     static constexpr int loads(int t) { return kCodeLoads + kXLoads + (GS && t % kStep == 0 ? 1 : 0); }
     static constexpr int loads(int t, int n) { int k = 0; for (int j = 0; j < n; ++j) k += loads(t + j); return k; }
@@ -420,6 +427,22 @@ template <int M, int V, int GS>
 int launch_gemm_staged(const Geometry& g, const GemmParams& p, hipStream_t stream)
 {
     constexpr bool WIDE = V == 8 && M == 1;
+    if (g.RB == 64) {
+        switch (g.BG) {
+            case 8: return launch_gemm_staged_one<M, V, GS, 2, 8, 1, 2>(g, p, stream);
+            case 16: return launch_gemm_staged_one<M, V, GS, 2, 16, 1, 2>(g, p, stream);
+            case 32: if constexpr (!WIDE) return launch_gemm_staged_one<M, V, GS, 2, 16, 2, 2>(g, p, stream);
+        }
+        return CODEGEMM_UNSUPPORTED;
+    }
+    if (g.RB == 32) {
+        switch (g.BG) {
+            case 8: return launch_gemm_staged_one<M, V, GS, 4, 8, 1, 2>(g, p, stream);
+            case 16: return launch_gemm_staged_one<M, V, GS, 4, 16, 1, 2>(g, p, stream);
+            case 32: if constexpr (!WIDE) return launch_gemm_staged_one<M, V, GS, 4, 16, 2, 2>(g, p, stream);
+        }
+        return CODEGEMM_UNSUPPORTED;
+    }
     switch (g.BG) {
         case 4:
             if constexpr (GS == 1) return launch_gemm_staged_one<M, V, GS, 1, 4, 1, 2>(g, p, stream);

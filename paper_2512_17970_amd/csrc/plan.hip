@@ -61,32 +61,46 @@ static int centroid_min_rows(const codegemm_desc* d)
     return d->batch <= 4 ? 32 : d->batch <= 8 ? 64 : 128;      // v = 16: one MFMA per lookup (registers)
 }
 
-// Batch rows of a workgroup of the kernel that stages codes and x in LDS, or 0: the centroid kernel.  Blocks of 128 rows, fp16
-// output, one or two codebooks of short vectors, groups that hold a step of 16 chunks.  `range` is the K of a workgroup: filling the rings and
-// turning a tile over cost the same whatever K is.  Measured on default plans of 13 000 random calls, time of the centroid kernel / time here, by
-// range, up to 256 workgroups (above: the centroid kernel has two workgroups on a compute unit, the rings leave room for one):
-//  * 2 to 4 rows with group scales: v8 m1 1.05 from 3072 on, 1.18 at 6144, 1.36 at 16000; v8 m2 0.99 at 3072, 1.02 at 4096, 1.10 at 7168,
-//    1.15 at 16000; v4 m1 0.97 at 3072, 1.02 to 1.04 up to 8192, 1.10 at 16000.  (Above 256: 0.88 at 3072 and 1.00 at 6144; 0.82, 0.94 from 7168
-//    on; 0.83, 0.95 at 6144, 0.98.)  One scale per row ties or loses (8192->57344 34.4 / 35.9 us, 4096->28672 11.6 / 12.1): nothing is picked or scaled there.
-//  * 5 to 8 rows, a tile of 16 (of 8 when v8 m1 has group scales, whose 16 rows do not fit): v8 m1 0.85 to 0.96 below 6144, 1.01 there, 1.04 at
-//    8192, 1.13 at 16000, with group scales 1.01 to 1.25; v8 m2 0.95 below 1024, 1.00 there, then 1.04 to 1.13, with group scales 1.02
-//    to 1.14; v4 m1 0.91, 0.97, 1.02 (below 1024, 2048, 3072) to 1.28, with group scales 0.81, 0.94, 1.07 to 1.32.  (Above 256: v8 m1 0.79 to 0.94 below
-//    10000; v4 m1 0.93 to 1.00 from 2048 to 6144, with group scales 0.83 to 0.98.)
-//  * 9 to 16 rows: v8 m1 0.94 and 0.97 below 2048, 1.03 to 1.19 from there on; v8 m2 1.03 to 1.17, v4 m1 1.03 to 1.26.
-//  * 17 to 32 rows: two tiles of 16 where they fit (v8 m2 1.06 to 1.16, v4 m1 1.06 to 1.29), one per workgroup with group scales (1.02 to
-//    1.13, 1.03 to 1.26).
-// Up to 16 rows the kernel does not depend on the number of workgroups: a layer alone has others than in a group.
+// Batch rows of a workgroup of the kernel that stages codes and x in LDS, or 0: the centroid kernel.  fp16 output, one or two codebooks of
+// short vectors, groups that hold a step of 16 chunks.  `range` is the K of a workgroup.  Measured on 59 000 random sizes under every block height
+// and 1 to 8 K ranges, time of the centroid kernel / time here, by range, up to 256 workgroups (above: the centroid kernel has two workgroups on
+// a compute unit, the rings leave room for one):
+//  * 2 to 4 rows: 128-row blocks with group scales, where the centroid kernel picks one result element of four and scales it: v8 m1 1.10 at 2048,
+//    1.21 at 5000, 1.38 at 12000 (above 256 workgroups 0.81 at 1500, 0.91, 1.03, 1.17); v8 m2 1.03, 1.12, 1.20 (0.77, 0.86, 0.92, 1.01); v4 m1 1.02, 1.07,
+//    1.14 (0.78, 0.89, 0.95, 1.01).  The lines are 3072, 4096 and 7168.  Without group scales 0.9 to 1.07 (v8 m1 1.2 from 8192 on), and lower blocks
+//    lose at any K but the longest (64 rows 0.83 to 1.02, v8 m1 with group scales 1.16; 32 rows 0.8 to 0.97): there the centroid kernel's 16
+//    columns are all at work, and its rings hold a whole short slice.
+//  * 5 to 8 rows: 32-row blocks v8 m2 1.06 to 1.31, others 1.0 to 1.18; 64-row blocks 1.01 to 1.28; 128-row blocks v8 m2 1.10 to 1.19, v8 m1 with
+//    group scales 1.12 to 1.40, without 1.05, 1.00, 1.06, 1.13, 1.29 (0.86 and 0.93 at 1500 and 3000, 1.00 at 6000, 1.19): from 8192 on; v4 m1 1.03, 1.08,
+//    1.13, 1.22, 1.36 (0.88, 0.90, 0.97, 1.07): from 2048 on, and so with group scales.
+//  * 9 to 32 rows: 32-row blocks 1.2 to 2.0, 64-row blocks 1.14 to 1.8, 128-row blocks 1.1 to 1.4: a lookup there pays one MFMA for 16 rows at any
+//    height, where the centroid kernel's columns are octets x sub-vectors and take two or four.  17 to 32 rows are two tiles of 16 in one
+//    workgroup but for v8 m1, and 128-row blocks with group scales (registers): one tile per workgroup; v8 m1 has no such 128-row kernel.
+// It does not depend on the number of workgroups: a layer alone has others than in a group.
 static int staged_batch(const codegemm_desc* d, int rows, int range)
 {
     const int v = d->vec_len, m = d->num_codebooks, b = d->batch;
     const bool grouped = d->group_size > 0, wide = v == 8 && m == 1;
-    if (rows != 128 || (d->flags & CODEGEMM_FLAG_Y_FP32) || short_groups(d) || !((v == 8 && m <= 2) || (v == 4 && m == 1))) return 0;
-    if (b <= 4) return b > 1 && grouped && range >= (v == 4 ? 7168 : wide ? 3072 : 4096) ? 4 : 0;
+    if ((d->flags & CODEGEMM_FLAG_Y_FP32) || short_groups(d) || !((v == 8 && m <= 2) || (v == 4 && m == 1))) return 0;
+    if (b <= 4) return rows == 128 && b > 1 && grouped && range >= (v == 4 ? 7168 : wide ? 3072 : 4096) ? 4 : 0;
+    if (rows < 128) return b <= 8 ? 8 : b <= 16 || wide ? 16 : 32;
     if (b <= 8 && range < (v == 4 ? 2048 : grouped ? 0 : wide ? 8192 : 1024)) return 0;
     if (wide && grouped) return b <= 8 ? 8 : 0;
     if (wide && b <= 16 && range < 2048) return 0;
     if (b <= 16 || grouped) return 16;
     return wide ? 0 : 32;
+}
+
+// Batch rows of a workgroup of whichever of the two runs.  Above kBatchPerLaunch rows, where a layer has no group to agree with, two tiles of 16
+// become workgroups of their own while these are one round: half of the work each in place of an idle half of the chip (6232->2777 v4 m1, 73
+// rows, 64-row blocks: 132 workgroups 16.4 us, 220 13.0).
+static int batch_rows(const codegemm_desc* d, int rows, int splits, bool* is_staged = nullptr)
+{
+    const int nkt = ceil_div(d->in_features / d->vec_len, kSlots), units = ceil_div(nkt, splits < nkt ? splits : nkt);
+    int staged = staged_batch(d, rows, units * kSlots * d->vec_len);
+    if (staged == 32 && d->batch > kBatchPerLaunch && (long long)ceil_div(d->out_features, rows) * ceil_div(d->batch, 16) * ceil_div(nkt, units) <= 256) staged = 16;
+    if (is_staged) *is_staged = staged != 0;
+    return staged ? staged : centroid_batch(d, rows);
 }
 
 // 2 to 4 rows with group scales: blocks of 128 rows in two or four K ranges on the staged kernel instead of lower ones on the
@@ -363,36 +377,43 @@ static bool prefer_centroid(const codegemm_desc* d)
     return !(batch > 16 && fp32 && K < 1024);
 }
 
-// Microseconds of a call of 5 to 32 rows in blocks of `rows` rows and `splits` K ranges, for the formats of the staged kernel: a
-// fixed part, a workgroup's K at a rate per format and kernel, once per round of 256 workgroups, and the exchange between the
-// ranges (two and four pairwise where their words fit, else by the ticket).  Fitted to 8000 random sizes under every height and
-// 1, 2, 3, 4, 6 and 8 ranges, some 60 000 times, with a staged kernel 3 to 9 % slower than now; the spread of one format and height about its
-// line is 3 to 9 %.  On 5200 other sizes and the kernels as they are, the plans it leads to take 1.011 of the time of the best of these
-// plans (the rule alone 1.024), and the same form fitted to them 1.011 as well: the lines lie up to 15 % too high, but side by side.  One
-// moved: v8 m2 with up to 8 rows in 128-row blocks, 1.82, where two rounds of them lost to three of 64 rows too soon (5216->42881, 8 rows 33.1 us, 30.3).
+// Microseconds of a call of 5 rows and more in blocks of `rows` rows and `splits` K ranges, for the formats of the staged kernel: a fixed part
+// per call and round of 256 workgroups, a workgroup's K at a rate per format, batch and height, and the exchange between the ranges (two and
+// four pairwise where their words fit, else by the ticket).  A round that is not full streams faster (what bounds it is the chip's power): a
+// quarter of the stream's time follows the workgroups and not the rounds.  Fitted to 17 000 random sizes of 5 to 700 rows that are no prompts, under
+// every height and 1, 2, 3, 4, 6 and 8 ranges; the spread about it is 9 %.  On 9000 other sizes the plans that it leads to take 1.006 (5 to 8 rows), 1.005
+// (9 to 16), 1.011 (17 to 32) and 1.007 (more) of the time of the best of these plans, the rules of choose_plan alone 1.010, 1.027, 1.066 and 1.054.
 static float batch_cost(const codegemm_desc* d, int rows, int splits)
 {
-    // us per 1024 elements of K: blocks of 32, 64 and 128 rows with up to 8 rows / more; two tiles of 16 in one workgroup
-    struct Rate { float h[3][2], two; };
-    static const Rate rates[3][2] = {                  // v4 m1, v8 m1, v8 m2; one scale per row / group scales
-        {{{{0.47f, 0.93f}, {0.95f, 1.28f}, {1.30f, 1.51f}}, 2.15f}, {{{0.59f, 1.24f}, {1.08f, 1.40f}, {1.47f, 1.48f}}, 0.0f}},
-        {{{{0.41f, 0.89f}, {0.63f, 1.01f}, {1.00f, 1.10f}}, 2.44f}, {{{0.57f, 1.11f}, {0.75f, 1.20f}, {1.08f, 1.40f}}, 0.0f}},
-        {{{{0.68f, 1.43f}, {1.02f, 1.59f}, {1.75f, 1.82f}}, 2.84f}, {{{0.85f, 1.71f}, {1.17f, 1.84f}, {1.94f, 1.98f}}, 0.0f}}};
-    static const float fixed[3][2] = {{1.8f, 2.7f}, {2.3f, 3.1f}, {3.25f, 3.8f}};
-    const int b = d->batch, height = rows == 32 ? 0 : rows == 64 ? 1 : 2, more = b > 8;
-    const bool two = rows == 128 && b > 16 && d->group_size < 0;
-    const int nkt = ceil_div(d->in_features / d->vec_len, kSlots), tiles = b <= 16 || two ? 1 : 2;
-    const int units = ceil_div(nkt, splits < nkt ? splits : nkt);
+    // us per 1024 elements of K: [v4 m1, v8 m1, v8 m2][one scale per row, group scales][up to 8, 16, more rows][blocks of 32, 64, 128 rows]
+    static const float rates[3][2][3][3] = {
+        {{{0.57f, 0.99f, 1.46f}, {0.76f, 1.18f, 1.64f}, {1.60f, 1.95f, 2.81f}},
+         {{0.62f, 1.08f, 1.70f}, {0.76f, 1.13f, 1.69f}, {1.34f, 1.66f, 1.50f}}},
+        {{{0.49f, 0.66f, 1.14f}, {0.64f, 0.83f, 1.23f}, {0.64f, 0.76f, 3.31f}},
+         {{0.56f, 0.76f, 1.18f}, {0.68f, 0.87f, 1.92f}, {0.66f, 0.78f, 1.64f}}},
+        {{{0.69f, 1.17f, 1.78f}, {0.81f, 1.27f, 1.84f}, {1.59f, 2.12f, 3.64f}},
+         {{0.77f, 1.36f, 2.32f}, {1.29f, 1.41f, 2.36f}, {1.83f, 2.15f, 2.05f}}}};
+    // us: a call, a round, the exchange of two and of four ranges pairwise, and of any number by the ticket
+    static const float call[3] = {1.24f, 1.28f, 1.56f};
+    static const float round[3][3] = {{2.53f, 2.49f, 3.21f}, {2.47f, 2.65f, 3.45f}, {2.33f, 2.87f, 3.97f}};
+    static const float two[3][3] = {{0.61f, 0.65f, 0.91f}, {0.71f, 0.79f, 1.06f}, {0.85f, 0.90f, 1.33f}};
+    static const float four[3][3] = {{1.08f, 1.14f, 1.59f}, {1.20f, 1.42f, 1.77f}, {1.37f, 1.55f, 2.07f}};
+    static const float ticket[3][3] = {{1.97f, 1.99f, 3.08f}, {2.10f, 2.94f, 4.30f}, {2.97f, 3.81f, 5.85f}};
+    const bool wide = d->vec_len == 8 && d->num_codebooks == 1;
+    const int b = d->batch, tile = batch_rows(d, rows, splits), h = rows == 32 ? 0 : rows == 64 ? 1 : 2;
+    // (v8 m1, and 128-row blocks with group scales, have the rates of two tiles of 16 rows in the last column)
+    const int c = b <= 8 ? 0 : b <= 16 || (b > kBatchPerLaunch && tile == 16 && !wide && (rows < 128 || d->group_size < 0)) ? 1 : 2;
+    const int nkt = ceil_div(d->in_features / d->vec_len, kSlots);
+    const int units = ceil_div(nkt, splits < nkt ? splits : nkt), range = units * kSlots * d->vec_len;
     splits = ceil_div(nkt, units);
-    const Rate& r = rates[d->vec_len == 4 ? 0 : d->num_codebooks][d->group_size > 0];
-    const float stream = (two ? r.two : r.h[height][more]) * (float)(units * kSlots * d->vec_len) * (1.0f / 1024) + (two ? 5.9f : fixed[height][more]);
-    const long long workgroups = (long long)ceil_div(d->out_features, rows) * tiles * splits;
+    const long long workgroups = (long long)ceil_div(d->out_features, rows) * ceil_div(b, tile) * splits;
+    const float rounds = (float)((workgroups + 255) / 256), full = (float)workgroups * (1.0f / 256);
     const bool pairs = (splits == 2 || splits == 4) &&
                        (long long)b * (splits - 1) * ceil_div(d->out_features, kGranuleRows) * kGranuleRows * 8 <= (long long)kPairAreaBytes;
-    float exchange = 0.0f;
-    if (pairs) exchange = splits == 2 ? (rows == 128 && more ? 1.7f : 0.8f) : !more ? 1.3f : rows == 128 ? 2.0f : 1.5f;
-    else if (splits > 1) exchange = !more ? (rows == 128 ? 2.75f : 2.0f) + 0.1f * splits : rows < 128 ? 2.9f : two ? 5.5f : 4.0f;
-    return 2.5f + (float)((workgroups + 255) / 256) * stream + exchange;
+    // (more than 8 ranges were not timed: 0.1 us each, as the batched kernel's ticket takes)
+    const float exchange = splits == 1 ? 0.0f : pairs ? (splits == 2 ? two : four)[c][h] : ticket[c][h] + 0.1f * (float)(splits > 8 ? splits - 8 : 0);
+    const float stream = rates[d->vec_len == 4 ? 0 : d->num_codebooks][d->group_size > 0][c][h] * (float)range * (1.0f / 1024);
+    return call[c] + rounds * round[c][h] + (0.73f * rounds + 0.27f * full) * stream + exchange;
 }
 
 static void choose_plan(const codegemm_desc* d, codegemm_plan* p)
@@ -448,17 +469,24 @@ static void choose_plan(const codegemm_desc* d, codegemm_plan* p)
     if (splits > room) splits = (int)room;
     if (splits > nkt) splits = nkt;
     if (splits < 1) splits = 1;
-    // 5 to 32 rows of the staged kernel's formats: another height or number of ranges where the costs say that it is worth 8 %, more
-    // than they err.  On the sizes they were fitted to that is 1.6 % (17 to 32 rows) to 0.8 % in the mean, up to a factor of 1.6
-    // (8400->4096 v8 m2, 32 rows: 128-row blocks in seven ranges 24.0 us, 64-row blocks in two 14.6).  On 5200 others 1.2 %; 24 lose 3 % or
-    // more, 5 of them 8 to 15 % (four pairwise ranges in place of eight or more by the ticket, K from 10000 on and few rows).
-    if (d->batch > 4 && d->batch <= kBatchPerLaunch && !(d->flags & CODEGEMM_FLAG_Y_FP32) && !short_groups(d) &&
-        ((d->vec_len == 8 && d->num_codebooks <= 2) || (d->vec_len == 4 && d->num_codebooks == 1))) {
+    // 5 rows and more of the staged kernel's formats: another height or number of ranges where the costs say that it is worth 3 %.  Against the
+    // rules alone that is 0.4 % in the mean at 5 to 8 rows, 2 % at 9 to 16, 5 % at 17 to 32 and 4 % above, up to a factor of 2.9; 0.8, 0.6, 1.7 and 2 % of the
+    // sizes lose 3 % or more by it (the costs are 9 % off either way).  v8 m2 with up to 8 rows and two rounds of 128-row blocks keeps three rounds
+    // of 64 rows from K = 8192 on, the plan that such layers already hold: a tie at first (33591 rows, 6 batch rows, K = 8224 32.8 / 32.5 us), 4 %
+    // slower at 27216 (93.1 / 89.6).
+    const bool three_rounds = d->vec_len == 8 && d->num_codebooks == 2 && d->group_size < 0 && d->batch > 4 && d->batch <= 8 &&
+                              !(d->flags & CODEGEMM_FLAG_Y_FP32) && d->in_features >= 8192 && blocks(128) > 256 && blocks(64) <= 768;
+    if (three_rounds) rows = 64;
+    if (!three_rounds && d->batch > 4 && !(d->flags & CODEGEMM_FLAG_Y_FP32) && !short_groups(d) && ((d->vec_len == 8 && d->num_codebooks <= 2) || (d->vec_len == 4 && d->num_codebooks == 1))) {
+        // v8 m1 without group scales, 17 rows and more: 128-row blocks take 32 rows there and lower ones 16, so these win (0.5 to 0.85 of the time) up to 128
+        // tiles of 128 x 32 and lose beyond (1.3 at K = 1000, 1.1 at 3000, 1.03 to 1.08 from 4096 on), whatever K is
+        const bool tall = d->vec_len == 8 && d->num_codebooks == 1 && d->group_size < 0 && d->batch > 16 && blocks(128) > 128;
         const int most = nkt * (d->vec_len == 4 ? 1 : 2) / 8;
-        float least_cost = (d->batch > 16 ? 0.95f : 0.92f) * batch_cost(d, rows, splits);
-        for (int r = least; r <= 128; r *= 2)
+        float least_cost = 0.97f * batch_cost(d, rows, splits);
+        for (int r = tall ? 128 : least; r <= 128; r *= 2)
             for (int n : {1, 2, 3, 4, 6, 8}) {
-                if (n > 1 && (n * blocks(r) > 256 || n > most || n > room || n > nkt)) break;
+                const long long workgroups = (long long)n * ceil_div(d->out_features, r) * ceil_div(d->batch, batch_rows(d, r, n));
+                if (n > 1 && (workgroups > 256 || n > most || n > room || n > nkt)) break;
                 const float cost = batch_cost(d, r, n);
                 if (cost >= least_cost) continue;
                 least_cost = cost;
@@ -515,9 +543,8 @@ int make_geometry(const codegemm_desc* d, const codegemm_plan* plan, Geometry* g
         if (g->B > kBatchPerLaunch && g->NKS > room) g->NKS = ranges(room > 0 ? room : 1);
     }
     g->KPW = ceil_div(g->NKT, g->NKS);
-    const int staged = g->RB ? staged_batch(d, g->RB, g->KPW * kSlots * g->v) : 0;
-    g->staged = staged != 0;
-    if (staged) g->BG = staged;
+    g->staged = false;
+    if (g->RB) g->BG = batch_rows(d, g->RB, g->NKS, &g->staged);
     // The prompt kernel's workgroups take 1024 rows of W and 64 (with group scales 32) batch rows, or half of the rows and twice the batch rows,
     // and all of K: worth it once they are enough to fill the chip.  fp32 output needs shorter sums than it has (8192^2 v8 m1 g128 batch 512: 2.9e-7
     // of 64 bits, tiles of the centroid kernel 0.95e-7, Psumbook kernels 1.24e-7; 141, 156 and 493 us).

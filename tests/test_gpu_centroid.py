@@ -104,6 +104,18 @@ def test_fewer_steps_than_wavefronts(K, N, B):
     run(synth.custom_case(K, N, 8, 2, B, seed=3200), 128, 1, True)
 
 
+@pytest.mark.parametrize("B,rows", [(5, 32), (8, 64), (9, 32), (16, 64), (16, 32), (17, 64), (32, 32), (37, 64)])
+@pytest.mark.parametrize("v,m,g", [(8, 2, -1), (8, 1, -1), (4, 1, -1), (8, 2, 128), (8, 1, 256), (4, 1, 128)])
+def test_low_staged_blocks_at_every_length_of_a_slice(v, m, g, B, rows):
+    """fp16 output, blocks of 32 and 64 rows from 5 batch rows on: slices of no stage, one, two, three and many, stages that reach past
+    the end of K, heights that end in the first and the last octet of a block and of a granule.  The error is the rounding of the output (run)."""
+    unit = max(g, v)
+    for elements in (unit, 64, 8 * 128, 8 * 128 + 64, 9 * 128, 17 * 128 + 32, 24 * 128, 41 * 128 + 96, 8192):
+        K = max(unit, elements // unit * unit)
+        for N in (rows - 7, 128 + rows + 1):
+            run(synth.custom_case(K, N, v, m, B, seed=3220 + N, g=g), rows, 1 + (K > 4000))
+
+
 @pytest.mark.parametrize("B", [1, 4, 8, 16, 32])
 def test_integer_cases_are_exact(B):
     """+-1 and 0/2 codebooks with small integer activations: every sum is an integer that fp32 holds, in any order."""
