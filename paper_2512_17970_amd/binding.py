@@ -12,6 +12,11 @@ import ctypes
 import os
 from typing import Optional
 
+try:
+    from . import _calls                      # csrc/python_calls.cpp: the two calls of a decoding loop without ctypes
+except ImportError:                           # not built yet: load() says so
+    _calls = None
+
 _PKG = os.path.dirname(os.path.abspath(__file__))
 _LIB_PATH = os.path.join(_PKG, "libcodegemm.so")
 _lib: Optional[ctypes.CDLL] = None
@@ -96,6 +101,7 @@ def load() -> ctypes.CDLL:
     if not os.path.exists(_LIB_PATH):
         raise ImportError(f"{_LIB_PATH} is missing: run `python -c 'import __graft_entry__ as g; g.build()'` "
                           "(or python paper_2512_17970_amd/build.py) first; there is no CPU fallback")
+    from . import _calls as calls              # built with the library, so it may be there only now
     lib = ctypes.CDLL(_LIB_PATH)
     vp, i, sz = ctypes.c_void_p, ctypes.c_int, ctypes.c_size_t
     dp, pp = ctypes.POINTER(Desc), ctypes.POINTER(Plan)
@@ -135,6 +141,7 @@ def load() -> ctypes.CDLL:
     lib.codegemm_dequant_gemm.restype = i
     lib.codegemm_status_string.argtypes = [i]
     lib.codegemm_status_string.restype = ctypes.c_char_p
+    calls.use(ctypes.cast(lib.codegemm_gemm, vp).value, ctypes.cast(lib.codegemm_gemm_grouped, vp).value)
     _lib = lib
     return lib
 
@@ -224,11 +231,14 @@ def codegemm_psumbook_build(desc: Desc, x, codebooks, psumbook, use_mfma: bool =
                                           1 if use_mfma else 0, stream), "codegemm_psumbook_build")
 
 
-def codegemm_gemm(desc: Desc, plan: Optional[Plan], x, packed_codes, codebooks, scales, y,
-                  workspace, workspace_bytes: int, stream: int = 0) -> None:
+def _gemm(desc: Desc, plan: Optional[Plan], x, packed_codes, codebooks, scales, y,
+          workspace, workspace_bytes: int, stream: int = 0) -> None:
     _check(load().codegemm_gemm(ctypes.byref(desc), _plan(plan), _ptr(x), _ptr(packed_codes), _ptr(codebooks),
                                 _ptr(scales), _ptr(y), _ptr(workspace), workspace_bytes,
                                 stream), "codegemm_gemm")
+
+
+codegemm_gemm = _calls.codegemm_gemm if _calls else _gemm
 
 
 def codegemm_static_workspace_limit() -> int:
@@ -245,7 +255,7 @@ def codegemm_grouped_workspace_bytes(desc: Desc, plan: Plan, out_features) -> in
     return int(load().codegemm_grouped_workspace_bytes(ctypes.byref(desc), _plan(plan), arr, len(out_features)))
 
 
-def codegemm_gemm_grouped(desc: Desc, plan: Plan, x, members, workspace, workspace_bytes: int, stream: int = 0) -> None:
+def _gemm_grouped(desc: Desc, plan: Plan, x, members, workspace, workspace_bytes: int, stream: int = 0) -> None:
     """members: sequence of (out_features, packed_codes, codebooks, scales, y), tensors or raw device addresses."""
     arr = (GroupMember * len(members))()
     for k, (n, packed, codebooks, scales, y) in enumerate(members):
@@ -257,6 +267,11 @@ def codegemm_gemm_grouped(desc: Desc, plan: Plan, x, members, workspace, workspa
         arr[k].y = _ptr(y)
     _check(load().codegemm_gemm_grouped(ctypes.byref(desc), _plan(plan), _ptr(x), arr, len(members),
                                         _ptr(workspace), workspace_bytes, stream), "codegemm_gemm_grouped")
+
+
+codegemm_gemm_grouped = _calls.codegemm_gemm_grouped if _calls else _gemm_grouped
+if _calls:
+    _calls.prepare(Desc, Plan, _gemm, _gemm_grouped, _check)
 
 
 def codegemm_dequant_gemm(desc: Desc, x, codes, codebooks, scales, y, stream: int = 0) -> None:

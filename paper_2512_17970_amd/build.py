@@ -4,6 +4,7 @@ from __future__ import annotations
 import glob
 import os
 import subprocess
+import sysconfig
 
 PKG = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(PKG)
@@ -11,6 +12,7 @@ CSRC = os.path.join(PKG, "csrc")
 LIB = os.path.join(PKG, "libcodegemm.so")
 TRACE_LIB = os.path.join(PKG, "libcodegemm_trace.so")   # diagnostic build: kernels stamp their phases
 ABLATE_MASKS = (6, 8, 14)       # ablation builds made by default: no gather + no build, no exchange, all three
+CALLS = os.path.join(PKG, "_calls" + sysconfig.get_config_var("EXT_SUFFIX"))   # Python extension with the calls of a decoding loop
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 
 # Packed-FP32 instruction selection is switched off for every device compile.
@@ -30,6 +32,15 @@ def ablate_lib(mask: int) -> str:
     return os.path.join(PKG, f"libcodegemm_ablate_{mask}.so")
 
 
+def build_calls(verbose: bool = False) -> str:
+    cmd = ["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-fvisibility=hidden", "-Wall", "-Wno-missing-field-initializers", "-I", os.path.join(ROOT, "include"),
+           "-I", sysconfig.get_paths()["include"], os.path.join(CSRC, "python_calls.cpp"), "-o", CALLS]
+    if verbose:
+        print(" ".join(cmd), flush=True)
+    subprocess.run(cmd, check=True)
+    return CALLS
+
+
 def build(verbose: bool = False, jobs: int = 8, trace: bool = False, ablate: int = 0) -> str:
     """Compiles every .hip file to an object (in parallel) and links the shared library.
     trace=True builds the diagnostic library instead (same ABI plus codegemm_set_trace;
@@ -37,6 +48,8 @@ def build(verbose: bool = False, jobs: int = 8, trace: bool = False, ablate: int
     ablate=mask builds an ablation library (same ABI, deliberately wrong outputs: parts of the
     batch-1 gather kernel compiled out, see csrc/gemm_impl.h); only the translation units of
     that kernel are recompiled, the rest comes from the production build, which must exist."""
+    if not trace and not ablate:
+        build_calls(verbose)
     out_dir = os.path.join(PKG, "_build", f"ablate_{ablate}" if ablate else ("trace" if trace else "main"))
     os.makedirs(out_dir, exist_ok=True)
     extra = ["-DCODEGEMM_TRACE"] if trace else ([f"-DCODEGEMM_ABLATE={ablate}"] if ablate else [])
