@@ -633,7 +633,7 @@ int launch_gemm_centroid_v(const Geometry& g, const GemmParams& p, hipStream_t s
 {
     // From 5 rows on fp16 output of one or two codebooks has a kernel of its own (gemm_staged_impl.h), but for two shapes that do not fit there
     // and short K
-    constexpr bool STAGED = GS <= 1 && ((V == 8 && M <= 2) || (V == 4 && M == 1)), WIDE = V == 8 && M == 1;
+    constexpr bool STAGED = GS <= 2 && ((V == 8 && M <= 2) || (V == 4 && M == 1)), WIDE = V == 8 && M == 1;
     constexpr int D1 = centroid_ring(M, V, 4, GS, true), D4 = centroid_ring(M, V, 4, GS, false), D2 = centroid_ring(M, V, 2, GS, false);
     switch (g.BG) {
         case 1:
@@ -645,7 +645,7 @@ int launch_gemm_centroid_v(const Geometry& g, const GemmParams& p, hipStream_t s
             if (g.RB == 64) return launch_gemm_centroid_one<M, V, 4, 1, 2, 4, D4, GS>(g, p, stream);
             return launch_gemm_centroid_one<M, V, 4, 1, 1, 8, D4, GS>(g, p, stream);
         case 8:
-            if constexpr (!STAGED || V == 4 || GS == 0) {
+            if constexpr (!STAGED || V == 4 || GS == 0 || (WIDE && GS == 2)) {
                 if (g.RB == 128) return launch_gemm_centroid_one<M, V, 2, 1, 2, 4, D2, GS>(g, p, stream);
             }
             if constexpr (!STAGED) {

@@ -370,7 +370,7 @@ int launch_gemm_centroid_mv(const Geometry& g, const GemmParams& p, hipStream_t 
             return launch_gemm_prompt_one<M, V, prompt_tiles(M, V, GS != 0), GS, 8>(g, p, stream);
         }
     }
-    if constexpr (GS <= 1 && ((V == 8 && M <= 2) || (V == 4 && M == 1))) {
+    if constexpr (GS <= 2 && ((V == 8 && M <= 2) || (V == 4 && M == 1))) {
         if (g.staged) return launch_gemm_staged<M, V, GS>(g, p, stream);
     }
     return launch_gemm_centroid_v<M, V, GS>(g, p, stream);

@@ -19,6 +19,8 @@
 // 4 or 2 bytes of its rows from the staged entry and takes 4 or 2 lookups per chunk, each of which feeds one MFMA for 16 batch rows whatever the
 // height, where columns of octets x sub-vectors take two (64 rows) or four (32 rows) and discard as much of the result.  us, centroid
 // kernel -> here: v8 m2 16 rows 4096^2 8.7 -> 5.8, 4096->6144 9.4 -> 5.9; 32 rows 14336->4096 18.8 -> 13.4; v4 m1 g128 8 rows 14336->4096 9.9 -> 7.9.
+// Short groups (GS = 2): a round's 4 chunks are neighbours, so each round closes its sums with a scale of its own, a row's beside the MFMAs of
+// the row after it; a stage's scales, one set per round, are one more request.  64-row blocks, v8 m1 g32 16 rows: 2.3 times the centroid kernel's speed.
 // 16 wavefronts, of twice the K slices or of two row groups, are slower (5.9 -> 6.6, 6.2 us: each has the same code in front of and behind its
 // loop), and so are three or four stages (5.7 -> 6.1 us, 8 rows) and stages of twice the size for two tiles of short codes (4 to 10 %).
 //
@@ -87,7 +89,8 @@ struct StagedShape {
     static constexpr int kXTile = BR * kChunks * 16;
     static constexpr int kScalesAt = kXAt + NT * kXTile;
     static constexpr bool kZeros = BR == 8;            // a row of zeros for the batch rows that an MFMA has and the tile has not (4: copies do as well)
-    static constexpr int kZeroAt = kScalesAt + (GS ? kOctets * 16 : 0);
+    static constexpr int kScales = GS == 2 ? kRounds : 1;                      // of a row: per round, or per step in its first stage
+    static constexpr int kZeroAt = kScalesAt + (GS ? kScales * kOctets * 16 : 0);
     static constexpr int kStage = kZeroAt + (kZeros ? 16 : 0);
     static constexpr int kRing = kStage * D;
     // The rings lie behind the table: a lookup's address is then the byte-permute alone, without an addition per lookup.
@@ -102,7 +105,7 @@ struct StagedShape {
     // touch different columns of 16 bytes (pieces of two octets share 256 bytes where a run is 128).
     static __host__ __device__ constexpr int turn(int o) { return (kPieces == 16 ? o : kPieces == 8 ? o >> 1 : o >> 2) * SPLIT & (kPieces - 1); }
     // Requests of stage t (counted from a step's first; scales come with that one), and of stages t .. t + n - 1.
-    static constexpr int loads(int t) { return kCodeLoads + kXLoads + (GS && t % kStep == 0 ? 1 : 0); }
+    static constexpr int loads(int t) { return kCodeLoads + kXLoads + (GS == 2 || (GS == 1 && t % kStep == 0) ? 1 : 0); }
     static constexpr int loads(int t, int n) { int k = 0; for (int j = 0; j < n; ++j) k += loads(t + j); return k; }
     static constexpr int kTurn = D % 2 ? 2 * D : D;    // stages per turn of the loop: whole steps, registers in pairs
     // Waits until stage t + 1 has landed, stages t + 2 .. t + D being outstanding.
@@ -132,7 +135,7 @@ __global__ void __launch_bounds__(512) gemm_staged_kernel(CG_HEAD_PARAMS, const 
     typedef CentroidTable<M, V> T;
     typedef StagedShape<M, V, GS, SPLIT, BR, NT, D> S;
     static_assert((V == 8 && M <= 2) || (V == 4 && M == 1), "the table takes 64 KB, a chunk 8 or 16 bytes of codes");
-    static_assert(GS <= 1, "a step of 16 chunks lies in one group");
+    static_assert(GS <= 2, "0 one scale per row, 1 a step of 16 chunks lies in one group, 2 groups of 4 or 8 chunks");
     static_assert(NT == 1 || BR == 16, "tiles of 16 rows");
     constexpr int KW = S::kWaves, THREADS = KW * kWave, OCT = S::kOctets, U = S::kRows, RB = 8 * OCT;
     constexpr int BT = BR * NT;
@@ -161,7 +164,7 @@ __global__ void __launch_bounds__(512) gemm_staged_kernel(CG_HEAD_PARAMS, const 
     const uint32_t ring = lds0 + (uint32_t)(S::kRingAt + wave * S::kRing);
 
     // This wavefront's stages of the workgroup's K range (whole steps with group scales).
-    constexpr int ALIGN = GS ? SPS : 1;
+    constexpr int ALIGN = GS == 1 ? SPS : 1;
     const int total = nq * SPU / ALIGN;
     const int s_beg = total * wave / KW * ALIGN, s_end = total * (wave + 1) / KW * ALIGN;
 
@@ -188,6 +191,8 @@ __global__ void __launch_bounds__(512) gemm_staged_kernel(CG_HEAD_PARAMS, const 
         const int row = e * S::kXRows + lane / S::kChunks;
         x_voff[e] = row * p.K * 2 + ((lane & (S::kChunks - 1)) ^ ((row & 15) / (16 / S::kChunks))) * 16;
     }
+    constexpr int SUBS = V == 4 ? 2 : 1;               // sub-vectors of a chunk
+    const int s_voff = GS == 2 ? ((lane / OCT * (4 * SUBS)) >> p.gshift) * 256 + lane % OCT * 16 : 0;     // scales of round lane / OCT
     // Stage s into its slot.
     auto request = [&](int s, int t) {                 // t = s - s_beg, or as much as matters of it
         const uint32_t at = ring + (uint32_t)(t % D * S::kStage);
@@ -204,7 +209,10 @@ __global__ void __launch_bounds__(512) gemm_staged_kernel(CG_HEAD_PARAMS, const 
             constexpr int LANES = BT < S::kXRows ? BT * S::kChunks : 64;
             if (LANES == 64 || lane < LANES) load_to_lds<false>(at + S::kXAt + e * 1024, x_voff[e] + x_add, x_rsrc, 0);
         }
-        if (GS && t % SPS == 0) {
+        if constexpr (GS == 2) {                       // a group of 4 or 8 chunks: a stage begins with one
+            const int unit_group = ((s % SPU) * (S::kChunks * SUBS)) >> p.gshift;
+            if (lane < S::kScales * OCT) load_to_lds<false>(at + S::kScalesAt, s_voff, s_rsrc, ((s / SPU) * p.GPU + unit_group) * 256);
+        } else if (GS && t % SPS == 0) {
             const int sub = V == 4 ? 0 : (s % SPU) / SPS * 16;             // first sub-vector of the step in its unit
             if (lane < OCT) load_to_lds<false>(at + S::kScalesAt, lane * 16, s_rsrc, ((s / SPU) * p.GPU + (sub >> p.gshift)) * 256);
         }
@@ -315,15 +323,16 @@ __global__ void __launch_bounds__(512) gemm_staged_kernel(CG_HEAD_PARAMS, const 
             return *reinterpret_cast<const lds_half8*>(static_cast<uintptr_t>(__builtin_amdgcn_perm(w[r][c * (WR / M) + u / 4], base[c], sel)));
         }
     };
-    auto add_scaled = [&](const scales_t& scales) {
+    auto add_scaled = [&](const scales_t& scales, int u) {
+        const float f = (float)scales[u];
 #pragma unroll
-        for (int u = 0; u < U; ++u) {
-            const float f = (float)scales[u];
+        for (int nt = 0; nt < NT; ++nt)
 #pragma unroll
-            for (int nt = 0; nt < NT; ++nt)
+            for (int e = 0; e < 4; ++e) sum[GS ? nt : 0][GS ? u : 0][e] = __builtin_fmaf(f, acc[nt][u][e], sum[GS ? nt : 0][GS ? u : 0][e]);
+    };
+    auto read_scales = [&](scales_t (&dst)[S::kScales], int d) {
 #pragma unroll
-                for (int e = 0; e < 4; ++e) sum[GS ? nt : 0][GS ? u : 0][e] = __builtin_fmaf(f, acc[nt][u][e], sum[GS ? nt : 0][GS ? u : 0][e]);
-        }
+        for (int r = 0; r < S::kScales; ++r) dst[r] = *reinterpret_cast<const lds_scales*>(static_cast<uintptr_t>(s_at + (uint32_t)(d * S::kStage + r * OCT * 16)));
     };
 
     S::template wait_but<1>(asked - 1);                // the first stage
@@ -334,10 +343,10 @@ __global__ void __launch_bounds__(512) gemm_staged_kernel(CG_HEAD_PARAMS, const 
     constexpr int LOOKUPS = NSB * U, AHEAD = LOOKUPS < 8 ? LOOKUPS : 8;
     uint32_t w[2][R][WR];
     half8_t xv[2][R][NT], a[AHEAD];
-    scales_t scales, scales_next;
+    scales_t scales[S::kScales], scales_next[S::kScales];
     read_codes(w[0], 0);
     read_x(xv[0], 0, s_beg);
-    if constexpr (GS) scales_next = *reinterpret_cast<const lds_scales*>(static_cast<uintptr_t>(s_at));
+    if constexpr (GS) read_scales(scales_next, 0);
 #pragma unroll
     for (int n = 0; n < AHEAD; ++n) a[n] = fetch(w[0], n / U, n % U);
     asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");  // slot 0 has been read
@@ -348,22 +357,30 @@ __global__ void __launch_bounds__(512) gemm_staged_kernel(CG_HEAD_PARAMS, const 
         for (int t = 0; t < TURN; ++t) {
             const int s = s0 + t, n = (t + 1) % D;
             if (s < s_end) {
-                const bool opens = GS && t % SPS == 0, closes = GS && t % SPS == SPS - 1;   // of a step
-                if (opens) scales = scales_next;
+                const bool opens = GS == 2 || (GS && t % SPS == 0), closes = GS == 2 || (GS && t % SPS == SPS - 1);   // of a step
+                if (opens) {
+#pragma unroll
+                    for (int r = 0; r < S::kScales; ++r) scales[r] = scales_next[r];
+                }
                 if (s + D < s_end) S::wait(t);         // stage s + 1 has landed
                 else wait_requests<0>();
                 read_codes(w[(t + 1) & 1], n);
                 read_x(xv[(t + 1) & 1], n, s + 1);
-                if (closes) scales_next = *reinterpret_cast<const lds_scales*>(static_cast<uintptr_t>(s_at + (uint32_t)(n * S::kStage)));
+                if (closes) read_scales(scales_next, n);
                 __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
                 for (int l = 0; l < LOOKUPS; ++l) {
                     const int k = l / U, u = l % U, next = l + AHEAD;
+                    const bool first = GS == 2 ? k % M == 0 : opens && k == 0;
 #pragma unroll
                     for (int nt = 0; nt < NT; ++nt)
-                        acc[nt][u] = __builtin_amdgcn_mfma_f32_16x16x32_f16(xv[t & 1][k / M][nt], a[l % AHEAD], opens && k == 0 ? float4_t{} : acc[nt][u], 0, 0, 0);
+                        acc[nt][u] = __builtin_amdgcn_mfma_f32_16x16x32_f16(xv[t & 1][k / M][nt], a[l % AHEAD], first ? float4_t{} : acc[nt][u], 0, 0, 0);
                     __builtin_amdgcn_sched_barrier(0);             // the lookup after its operand's last use: no second set of registers
                     a[l % AHEAD] = next < LOOKUPS ? fetch(w[t & 1], next / U, next % U) : fetch(w[(t + 1) & 1], (next - LOOKUPS) / U, next % U);
+                    if constexpr (GS == 2) {           // a row's sum is scaled beside the MFMAs of the row after it
+                        if (u > 0 && k % M == M - 1) add_scaled(scales[k / M], u - 1);
+                        if (u == 0 && k % M == 0 && k > 0) add_scaled(scales[k / M - 1], U - 1);
+                    }
                     __builtin_amdgcn_sched_barrier(0);
                 }
                 // the values are here: what they were read from may be overwritten
@@ -371,9 +388,15 @@ __global__ void __launch_bounds__(512) gemm_staged_kernel(CG_HEAD_PARAMS, const 
                 for (int r = 0; r < R; ++r)
 #pragma unroll
                     for (int nt = 0; nt < NT; ++nt) asm volatile("" : "+v"(xv[(t + 1) & 1][r][nt]));
-                if (closes) asm volatile("" : "+v"(scales_next));
+                if (closes) {
+#pragma unroll
+                    for (int r = 0; r < S::kScales; ++r) asm volatile("" : "+v"(scales_next[r]));
+                }
                 if (s + 1 + D < s_end) request(s + 1 + D, t + 1 + D);
-                if (closes) add_scaled(scales);
+                if (closes) {
+#pragma unroll
+                    for (int u = GS == 2 ? U - 1 : 0; u < U; ++u) add_scaled(scales[S::kScales - 1], u);
+                }
             }
         }
     }

@@ -51,8 +51,14 @@ static bool short_groups(const codegemm_desc* d)
 {
     return d->group_size > 0 && (d->group_size < (d->vec_len == 4 ? 32 : 16) * d->vec_len || (d->flags & CODEGEMM_FLAG_Y_FP32));
 }
+// Formats that the kernel with staged operands has (gemm_staged_impl.h).
+static bool staged_format(const codegemm_desc* d)
+{
+    return !(d->flags & CODEGEMM_FLAG_Y_FP32) && ((d->vec_len == 8 && d->num_codebooks <= 2) || (d->vec_len == 4 && d->num_codebooks == 1));
+}
 static int centroid_min_rows(const codegemm_desc* d)
 {
+    if (staged_format(d)) return 32;
     if (d->vec_len < 16) {
         if (d->batch <= 8 || d->num_codebooks == 1) return 32;
         if (d->group_size < 0) return d->flags & CODEGEMM_FLAG_Y_FP32 ? 64 : 32;
@@ -61,8 +67,7 @@ static int centroid_min_rows(const codegemm_desc* d)
     return d->batch <= 4 ? 32 : d->batch <= 8 ? 64 : 128;      // v = 16: one MFMA per lookup (registers)
 }
 
-// Batch rows of a workgroup of the kernel that stages codes and x in LDS, or 0: the centroid kernel.  fp16 output, one or two codebooks of
-// short vectors, groups that hold a step of 16 chunks.  `range` is the K of a workgroup.  Measured on 59 000 random sizes under every block height
+// Batch rows of a workgroup of the kernel that stages codes and x in LDS, or 0: the centroid kernel.  `range` is the K of a workgroup.  Measured on 59 000 random sizes under every block height
 // and 1 to 8 K ranges, time of the centroid kernel / time here, by range, up to 256 workgroups (above: the centroid kernel has two workgroups on
 // a compute unit, the rings leave room for one):
 //  * 2 to 4 rows: 128-row blocks with group scales, where the centroid kernel picks one result element of four and scales it: v8 m1 1.10 at 2048,
@@ -76,16 +81,19 @@ static int centroid_min_rows(const codegemm_desc* d)
 //  * 9 to 32 rows: 32-row blocks 1.2 to 2.0, 64-row blocks 1.14 to 1.8, 128-row blocks 1.1 to 1.4: a lookup there pays one MFMA for 16 rows at any
 //    height, where the centroid kernel's columns are octets x sub-vectors and take two or four.  17 to 32 rows are two tiles of 16 in one
 //    workgroup but for v8 m1, and 128-row blocks with group scales (registers): one tile per workgroup; v8 m1 has no such 128-row kernel.
+//  * Groups of 4 and 8 chunks, which take a scaled sum per round either way (12 000 other sizes): 32-row blocks 1.1 to 1.25 at 5 to 8 rows and 1.3 to 1.7
+//    beyond, 64-row blocks 1.2 to 1.4 and 1.7 to 2.9 (the centroid kernel spills there), 128-row blocks 1.05 to 1.3 and 1.25 to 1.4; v8 m1 has no 128-row
+//    kernel (47 registers of spills).
 // It does not depend on the number of workgroups: a layer alone has others than in a group.
 static int staged_batch(const codegemm_desc* d, int rows, int range)
 {
     const int v = d->vec_len, m = d->num_codebooks, b = d->batch;
     const bool grouped = d->group_size > 0, wide = v == 8 && m == 1;
-    if ((d->flags & CODEGEMM_FLAG_Y_FP32) || short_groups(d) || !((v == 8 && m <= 2) || (v == 4 && m == 1))) return 0;
-    if (b <= 4) return rows == 128 && b > 1 && grouped && range >= (v == 4 ? 7168 : wide ? 3072 : 4096) ? 4 : 0;
+    if (!staged_format(d)) return 0;
+    if (b <= 4) return rows == 128 && b > 1 && !short_groups(d) && grouped && range >= (v == 4 ? 7168 : wide ? 3072 : 4096) ? 4 : 0;
     if (rows < 128) return b <= 8 ? 8 : b <= 16 || wide ? 16 : 32;
     if (b <= 8 && range < (v == 4 ? 2048 : grouped ? 0 : wide ? 8192 : 1024)) return 0;
-    if (wide && grouped) return b <= 8 ? 8 : 0;
+    if (wide && grouped) return b <= 8 && !short_groups(d) ? 8 : 0;
     if (wide && b <= 16 && range < 2048) return 0;
     if (b <= 16 || grouped) return 16;
     return wide ? 0 : 32;
@@ -383,16 +391,21 @@ static bool prefer_centroid(const codegemm_desc* d)
 // quarter of the stream's time follows the workgroups and not the rounds.  Fitted to 17 000 random sizes of 5 to 700 rows that are no prompts, under
 // every height and 1, 2, 3, 4, 6 and 8 ranges; the spread about it is 9 %.  On 9000 other sizes the plans that it leads to take 1.006 (5 to 8 rows), 1.005
 // (9 to 16), 1.011 (17 to 32) and 1.007 (more) of the time of the best of these plans, the rules of choose_plan alone 1.010, 1.027, 1.066 and 1.054.
+// Short groups: rates of 11 000 sizes of their own, the other numbers the same; 1.003, 1.004 and 1.011 (17 and more), the rules 1.032, 1.094 and 1.071.
 static float batch_cost(const codegemm_desc* d, int rows, int splits)
 {
-    // us per 1024 elements of K: [v4 m1, v8 m1, v8 m2][one scale per row, group scales][up to 8, 16, more rows][blocks of 32, 64, 128 rows]
-    static const float rates[3][2][3][3] = {
+    // us per 1024 elements of K: [v4 m1, v8 m1, v8 m2][one scale per row, groups that hold a step, short groups][up to 8, 16, more rows][blocks of
+    // 32, 64, 128 rows]
+    static const float rates[3][3][3][3] = {
         {{{0.57f, 0.99f, 1.46f}, {0.76f, 1.18f, 1.64f}, {1.60f, 1.95f, 2.81f}},
-         {{0.62f, 1.08f, 1.70f}, {0.76f, 1.13f, 1.69f}, {1.34f, 1.66f, 1.50f}}},
+         {{0.62f, 1.08f, 1.70f}, {0.76f, 1.13f, 1.69f}, {1.34f, 1.66f, 1.50f}},
+         {{0.67f, 1.15f, 1.90f}, {0.85f, 1.28f, 1.85f}, {1.47f, 1.92f, 1.69f}}},
         {{{0.49f, 0.66f, 1.14f}, {0.64f, 0.83f, 1.23f}, {0.64f, 0.76f, 3.31f}},
-         {{0.56f, 0.76f, 1.18f}, {0.68f, 0.87f, 1.92f}, {0.66f, 0.78f, 1.64f}}},
+         {{0.56f, 0.76f, 1.18f}, {0.68f, 0.87f, 1.92f}, {0.66f, 0.78f, 1.64f}},
+         {{0.61f, 0.93f, 2.56f}, {0.72f, 1.03f, 2.62f}, {0.73f, 0.92f, 2.21f}}},
         {{{0.69f, 1.17f, 1.78f}, {0.81f, 1.27f, 1.84f}, {1.59f, 2.12f, 3.64f}},
-         {{0.77f, 1.36f, 2.32f}, {1.29f, 1.41f, 2.36f}, {1.83f, 2.15f, 2.05f}}}};
+         {{0.77f, 1.36f, 2.32f}, {1.29f, 1.41f, 2.36f}, {1.83f, 2.15f, 2.05f}},
+         {{0.81f, 1.35f, 2.45f}, {0.93f, 1.44f, 2.50f}, {1.60f, 2.39f, 2.28f}}}};
     // us: a call, a round, the exchange of two and of four ranges pairwise, and of any number by the ticket
     static const float call[3] = {1.24f, 1.28f, 1.56f};
     static const float round[3][3] = {{2.53f, 2.49f, 3.21f}, {2.47f, 2.65f, 3.45f}, {2.33f, 2.87f, 3.97f}};
@@ -412,7 +425,7 @@ static float batch_cost(const codegemm_desc* d, int rows, int splits)
                        (long long)b * (splits - 1) * ceil_div(d->out_features, kGranuleRows) * kGranuleRows * 8 <= (long long)kPairAreaBytes;
     // (more than 8 ranges were not timed: 0.1 us each, as the batched kernel's ticket takes)
     const float exchange = splits == 1 ? 0.0f : pairs ? (splits == 2 ? two : four)[c][h] : ticket[c][h] + 0.1f * (float)(splits > 8 ? splits - 8 : 0);
-    const float stream = rates[d->vec_len == 4 ? 0 : d->num_codebooks][d->group_size > 0][c][h] * (float)range * (1.0f / 1024);
+    const float stream = rates[d->vec_len == 4 ? 0 : d->num_codebooks][short_groups(d) ? 2 : d->group_size > 0][c][h] * (float)range * (1.0f / 1024);
     return call[c] + rounds * round[c][h] + (0.73f * rounds + 0.27f * full) * stream + exchange;
 }
 
@@ -477,7 +490,7 @@ static void choose_plan(const codegemm_desc* d, codegemm_plan* p)
     const bool three_rounds = d->vec_len == 8 && d->num_codebooks == 2 && d->group_size < 0 && d->batch > 4 && d->batch <= 8 &&
                               !(d->flags & CODEGEMM_FLAG_Y_FP32) && d->in_features >= 8192 && blocks(128) > 256 && blocks(64) <= 768;
     if (three_rounds) rows = 64;
-    if (!three_rounds && d->batch > 4 && !(d->flags & CODEGEMM_FLAG_Y_FP32) && !short_groups(d) && ((d->vec_len == 8 && d->num_codebooks <= 2) || (d->vec_len == 4 && d->num_codebooks == 1))) {
+    if (!three_rounds && d->batch > 4 && staged_format(d)) {
         // v8 m1 without group scales, 17 rows and more: 128-row blocks take 32 rows there and lower ones 16, so these win (0.5 to 0.85 of the time) up to 128
         // tiles of 128 x 32 and lose beyond (1.3 at K = 1000, 1.1 at 3000, 1.03 to 1.08 from 4096 on), whatever K is
         const bool tall = d->vec_len == 8 && d->num_codebooks == 1 && d->group_size < 0 && d->batch > 16 && blocks(128) > 128;

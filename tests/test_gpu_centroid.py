@@ -105,7 +105,7 @@ def test_fewer_steps_than_wavefronts(K, N, B):
 
 
 @pytest.mark.parametrize("B,rows", [(5, 32), (8, 64), (9, 32), (16, 64), (16, 32), (17, 64), (32, 32), (37, 64)])
-@pytest.mark.parametrize("v,m,g", [(8, 2, -1), (8, 1, -1), (4, 1, -1), (8, 2, 128), (8, 1, 256), (4, 1, 128)])
+@pytest.mark.parametrize("v,m,g", [(8, 2, -1), (8, 1, -1), (4, 1, -1), (8, 2, 128), (8, 1, 256), (4, 1, 128), (8, 2, 32), (8, 2, 64), (8, 1, 32), (8, 1, 64), (4, 1, 32), (4, 1, 64)])
 def test_low_staged_blocks_at_every_length_of_a_slice(v, m, g, B, rows):
     """fp16 output, blocks of 32 and 64 rows from 5 batch rows on: slices of no stage, one, two, three and many, stages that reach past
     the end of K, heights that end in the first and the last octet of a block and of a granule.  The error is the rounding of the output (run)."""
