@@ -188,6 +188,7 @@ __global__ void __launch_bounds__(RW * KW * 64) gemm_centroid_kernel(CG_HEAD_PAR
     constexpr int kOutOfRange = 0x7ffffff0;
     constexpr uint32_t kRsrcFlags = 0x00020000u;
     static_assert((KW & (KW - 1)) == 0, "slices are added in pairs");
+    static_assert(THREADS == 512, "a pass over the table's entries is one codebook (v = 16) or two");
     static_assert(RB <= kGranuleRows, "rows of a workgroup lie in one granule");
 
     extern __shared__ __align__(16) unsigned char smem[];
@@ -219,17 +220,16 @@ __global__ void __launch_bounds__(RW * KW * 64) gemm_centroid_kernel(CG_HEAD_PAR
         else return (NEAR ? 4 * SB : SB) * j;
     };
 
-    // Table entries of this thread, requested first: everything waits for them.
+    // Table entries of this thread, requested first: everything waits for them.  A pass takes THREADS entries, whole codebooks with as many
+    // columns each; where fewer are left, several threads share the columns of one.
     constexpr int ENTRIES = M * kCentroids * T::kHalves;                // to replicate
-    constexpr int TPE = 2 * ENTRIES <= THREADS ? 2 : 1;                 // threads that share one entry's columns
-    constexpr int EPT = (ENTRIES + THREADS - 1) / THREADS;              // entries per thread
+    constexpr int EPT = (ENTRIES + THREADS - 1) / THREADS;              // passes
+    auto sharing = [](int k) constexpr -> int { return ENTRIES - k * THREADS < THREADS ? THREADS / (ENTRIES - k * THREADS) : 1; };
     typedef typename Frag<V == 4 ? 4 : 16>::type entry_t;               // 8 or 16 bytes
     entry_t fill[EPT];
 #pragma unroll
-    for (int k = 0; k < EPT; ++k) {
-        const int e = TPE > 1 ? min(tid / TPE, ENTRIES - 1) : min(tid + k * THREADS, ENTRIES - 1);
-        fill[k] = reinterpret_cast<const entry_t*>(mm.codebooks)[e];    // entry e = (codebook, centroid, half) in memory order
-    }
+    for (int k = 0; k < EPT; ++k)
+        fill[k] = reinterpret_cast<const entry_t*>(mm.codebooks)[k * THREADS + tid / sharing(k)];      // entry e = (codebook, centroid, half) in memory order
 
     // This wavefront's steps [s_beg, s_end) of the workgroup's K range.
     const int total = nq * SPU;
@@ -395,18 +395,17 @@ __global__ void __launch_bounds__(RW * KW * 64) gemm_centroid_kernel(CG_HEAD_PAR
     const uint32_t lds0 = (uint32_t)reinterpret_cast<uintptr_t>((lds_float*)smem);
 #pragma unroll
     for (int k = 0; k < EPT; ++k) {
-        const int e = TPE > 1 ? tid / TPE : tid + k * THREADS;
-        if (e < ENTRIES) {
-            const int h = e % T::kHalves, code = (e / T::kHalves) % kCentroids, c = e / (T::kHalves * kCentroids);
-            // columns this thread fills, beginning at another one in every row so that a wavefront's stores spread over the banks
-            const int cols = T::columns(c), mine = cols / TPE;
-            const int c0 = TPE > 1 ? (tid % TPE) * mine + (tid / TPE & (mine - 1)) : lane & (cols - 1);
-            const uint32_t first = lds0 + (uint32_t)(T::plane(c, h) * 65536 + code * 256 + T::region(c) + c0 * T::kEntry);
-            for (int j = 0; j < mine; ++j) {
-                const uint32_t a = first ^ (uint32_t)(j * T::kEntry);
-                if constexpr (V == 4) *reinterpret_cast<lds_half4*>(static_cast<uintptr_t>(a)) = fill[k];
-                else *reinterpret_cast<lds_half8*>(static_cast<uintptr_t>(a)) = fill[k];
-            }
+        const int share = sharing(k), e = k * THREADS + tid / share;
+        const int h = e % T::kHalves, code = (e / T::kHalves) % kCentroids, c = e / (T::kHalves * kCentroids);
+        // columns this thread fills, beginning at another one in every row so that a wavefront's stores spread over the banks
+        const int cols = T::columns(k * THREADS / (T::kHalves * kCentroids)), mine = cols / share;
+        const int c0 = tid % share * mine + (tid / share & (mine - 1));
+        const uint32_t first = lds0 + (uint32_t)(T::plane(c, h) * 65536 + code * 256 + T::region(c) + c0 * T::kEntry);
+#pragma unroll
+        for (int j = 0; j < mine; ++j) {
+            const uint32_t a = first ^ (uint32_t)(j * T::kEntry);
+            if constexpr (V == 4) *reinterpret_cast<lds_half4*>(static_cast<uintptr_t>(a)) = fill[k];
+            else *reinterpret_cast<lds_half8*>(static_cast<uintptr_t>(a)) = fill[k];
         }
     }
 

@@ -341,14 +341,18 @@ static int low_rows(int n) { return ceil_div(n, 32) <= 256 ? 32 : ceil_div(n, 64
 //    output on blocks of 64 and 128 rows that fill less than three quarters of the chip, from a work of 128 x 8192 on
 //    (two rows, v8 m1 g128: 0.75 to 0.97 at K = 8300 to 28000 and 16400 to 18000 rows), and v16 with three or four codebooks, whose lookups read 32
 //    bytes (two rows, v16 m4: 1.2 below K = 4000, 0.95 to 1.05 at 8000, 0.8 to 0.9 from 16000 on).
-//  * Groups shorter than a step cost a flush inside it.  With several codebooks only 128-row blocks are left from nine
-//    rows on, too few of them on small matrices (v8 m2 g32 2048^2, batch 16: 8.7/10.3 us), and v = 16 loses at two rows.
+//  * Groups shorter than a step cost a flush inside it.  With several codebooks the register-loading kernel has only 128-row
+//    blocks for them from nine rows on, too few of them on small matrices (v8 m2 g32 2048^2, batch 16: 8.7/10.3 us), and
+//    v = 16 loses at two rows.  v8 m2 has staged blocks of 32 rows and wins from 1.1 million codes on (batch 16, Psumbook / staged
+//    kernel: 853 rows of K = 5376 12.2/6.1 us, 3000 of 3072 13.0/5.9; batch 9 to 32 of six such shapes 1.5 to 2.2); 2048^2,
+//    just below, was not moved.
 //  * fp32 output pays for its short chains of sums: v = 16 loses on small matrices, at two rows (m2 8192^2 8.4/9.4) and
 //    with three and four codebooks, and above 8 rows its 16 products per sum leave it less exact than the Psumbook
 //    kernels (1.04 to 1.08 of their error below K = 8192).
 //  * 5 to 32 rows: v16 on small matrices (0.76 to 0.97; m4 at batch 16: 4096^2 14.8/16.0, 8192^2 31.7/20.6), blocks of v8
 //    that are too few when they have to be 128 rows (group scales: up to 1100 rows; fp32 output: 1500), and short K with
-//    fp32 output above 16 rows.
+//    fp32 output above 16 rows.  The staged kernel's blocks of 32 rows are enough of them at any height (v8 m2 g128, batch 16,
+//    Psumbook / staged: 1024 rows of K = 8192 13.0/5.7 us, 1100 of 4096 10.6/5.3).
 //  * More: everywhere (33 to 64 rows 2.4, to 128 3.2, to 512 4.4, to 2048 6 and more; no size of 17 000 lost 1 %).
 static bool prefer_centroid(const codegemm_desc* d)
 {
@@ -357,7 +361,7 @@ static bool prefer_centroid(const codegemm_desc* d)
     const bool fp32 = d->flags & CODEGEMM_FLAG_Y_FP32, grouped = d->group_size > 0;
     const long long codes = (long long)m * N * (K / v);
     if (short_groups(d)) {
-        if (batch > 8 && batch <= kBatchPerLaunch && m > 1 && codes < 4000000) return false;
+        if (batch > 8 && batch <= kBatchPerLaunch && m > 1 && codes < (staged_format(d) ? 1100000 : 4000000)) return false;
         if (v == 16 && batch == 2 && m > 2) return false;
     }
     if (fp32 && v == 16 && (batch > 8 || codes < 6000000 || batch == 2 || m > 2)) return false;
@@ -381,7 +385,7 @@ static bool prefer_centroid(const codegemm_desc* d)
         if (m >= 3 && (batch <= 8 ? n64 <= 64 : batch < 24 && codes < 10000000)) return false;
         return batch <= 8 || codes >= (batch <= 16 ? 6000000 : 4000000);
     }
-    if (batch > 8 && v == 8 && m >= 2 && (grouped ? n64 <= 18 : fp32 && n64 < 24)) return false;
+    if (batch > 8 && v == 8 && m >= 2 && !staged_format(d) && (grouped ? n64 <= 18 : fp32 && n64 < 24)) return false;
     return !(batch > 16 && fp32 && K < 1024);
 }
 
