@@ -104,32 +104,9 @@ struct SliceSums {
     static constexpr int kStride = RB + 4;
     static constexpr size_t kBytes = (size_t)SLICES * BT * kStride * sizeof(float);
     static constexpr size_t kLds = kBytes + 64;        // .. and the ticket's flag
-    static_assert(THREADS % RB == 0, "one row of W per thread");
     static __device__ __forceinline__ void finish(const GemmParams& p, const Member& mm, float* parts, uint32_t scale_bits, int tid, int blk, int ks, int b0)
     {
-        constexpr int PER_THREAD = (BT * RB + THREADS - 1) / THREADS;
-        float mine[PER_THREAD];
-        CG_STAMP(16);
-        __syncthreads();
-        CG_STAMP(17);
-        const float* src = parts + tid / RB * kStride + tid % RB;
-#pragma unroll
-        for (int i = 0; i < PER_THREAD; ++i) {
-            const int b = tid / RB + i * (THREADS / RB);
-            mine[i] = 0.0f;
-            if (b < BT && b0 + b < p.B) {
-                float t[SLICES];                       // added in pairs: fewer roundings on the way of each
-#pragma unroll
-                for (int k = 0; k < SLICES; ++k) t[k] = src[(k * BT + i * (THREADS / RB)) * kStride];
-#pragma unroll
-                for (int w = SLICES / 2; w > 0; w /= 2)
-#pragma unroll
-                    for (int k = 0; k < w; ++k) t[k] += t[k + w];
-                mine[i] = t[0];
-            }
-        }
-        const uint32_t bits[1] = {scale_bits};
-        finish_values<THREADS, BT, RB>(p, mm, mine, bits, reinterpret_cast<uint32_t*>(reinterpret_cast<unsigned char*>(parts) + kBytes), tid, blk, ks, b0);
+        finish_block<THREADS, BT, RB, SLICES>(p, mm, parts, reinterpret_cast<uint32_t*>(reinterpret_cast<unsigned char*>(parts) + kBytes), tid, blk, ks, b0, scale_bits);
     }
 };
 

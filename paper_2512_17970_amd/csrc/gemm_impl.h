@@ -399,21 +399,61 @@ __device__ __forceinline__ float halfwave_transpose_sum(float (&v)[NV], int lane
     return v[0] + __shfl_xor(v[0], 16, kWave);
 }
 
-// End of a workgroup's work, shared by all kernels with K ranges.  Output o = tid + i * NT of the workgroup's BG x ROWS row totals
-// over its K range is in mine[i], the fp16 bits of its row's scale in scale_bits[i] (one register where all of a thread's outputs
-// are of one row of W).  With one K range they are scaled and stored.  Otherwise each workgroup stores its totals as fp32
-// partials, takes a ticket on the row block's counter, and the last one to arrive adds the partials of all K ranges in
-// range order, scales and stores y.  Ends with the kernel: every path returns.
-template <int NT, int BG, int ROWS, int PER_THREAD, int SCALES>
-__device__ __forceinline__ void finish_values(const GemmParams& p, const Member& mm, float (&mine)[PER_THREAD], const uint32_t (&scale_bits)[SCALES],
-                                              uint32_t* flag, int tid, int blk, int ks, int b0)
+// Sum of SLICES values `stride` floats apart, added in pairs: fewer roundings on the way of each.
+template <int SLICES>
+__device__ __forceinline__ float pairwise_sum(const float* src, int stride)
 {
-    static_assert(SCALES == PER_THREAD || (SCALES == 1 && NT % ROWS == 0), "one scale per output, or one row of W per thread");
+    float t[SLICES];
+#pragma unroll
+    for (int k = 0; k < SLICES; ++k) t[k] = src[k * stride];
+#pragma unroll
+    for (int w = SLICES / 2; w > 0; w /= 2)
+#pragma unroll
+        for (int k = 0; k < w; ++k) t[k] += t[k + w];
+    return t[0];
+}
+
+// End of a workgroup's work, shared by all kernels with K ranges.  `stage` (LDS) holds the
+// workgroup's BG x ROWS row totals over its K range (the gather kernels), or SLICES partial sums of each as
+// [slice][batch row][ROWS + 4], and row_scale is the fp16 bits of the scale of row tid % ROWS (the centroid kernels).
+// With one K range they are scaled and stored.  Otherwise each workgroup stores its totals as fp32 partials, takes a ticket on
+// the row block's counter, and the last one to arrive adds the partials of all K ranges in
+// range order, scales and stores y.  Ends with the kernel: every path returns.
+// (One function, the two sources inside it: handed over as arrays by a caller, the totals cost the batched kernels 20 to 80 instructions for row
+// addresses, with 14 + 2 wavefronts 0.4 % of a call in the mean of 2900 random sizes and up to 3 %.)
+template <int NT, int BG, int ROWS, int SLICES = 0>
+__device__ __forceinline__ void finish_block(const GemmParams& p, const Member& mm, const float* stage, uint32_t* flag,
+                                             int tid, int blk, int ks, int b0, uint32_t row_scale = 0)
+{
+    CG_STAMP(16);
+    __syncthreads();
+    CG_STAMP(17);
+
+    constexpr int PER_THREAD = (BG * ROWS + NT - 1) / NT;             // outputs per thread
     const int n_base = blk * ROWS;
+    float mine[PER_THREAD];
+    uint32_t scale_bits[SLICES > 0 ? 1 : PER_THREAD] = {row_scale};
+#pragma unroll
+    for (int i = 0; i < PER_THREAD; ++i) {
+        const int o = tid + i * NT;
+        const int nn = n_base + o % ROWS;
+        if constexpr (SLICES > 0) {
+            static_assert(NT % ROWS == 0, "one row of W per thread");
+            constexpr int STEP = NT / ROWS;             // batch rows
+            const float* src = stage + tid / ROWS * (ROWS + 4) + tid % ROWS;
+            const int b = tid / ROWS + i * STEP;
+            mine[i] = 0.0f;
+            if (b < BG && b0 + b < p.B) mine[i] = pairwise_sum<SLICES>(src + i * STEP * (ROWS + 4), BG * (ROWS + 4));
+        } else {
+            mine[i] = (o < BG * ROWS) ? stage[o] : 0.0f;
+            // requested before any ticket round trip; with group scales the totals are already scaled
+            scale_bits[i] = mm.scales ? reinterpret_cast<const uint16_t*>(mm.scales)[nn < mm.N ? nn : 0] : 0x3c00u;
+        }
+    }
     // The scale is first touched where it is used (the pin keeps its conversion, and with it
     // the wait for the load, from being hoisted in front of the partial-sum stores).
     auto scale_of = [&](int i) -> float {
-        uint32_t b = scale_bits[SCALES == 1 ? 0 : i];
+        uint32_t b = scale_bits[SLICES > 0 ? 0 : i];
         asm volatile("" : "+v"(b));
         return (float)__builtin_bit_cast(_Float16, (uint16_t)b);
     };
@@ -577,29 +617,6 @@ __device__ __forceinline__ void finish_values(const GemmParams& p, const Member&
         store_y(row, nn, sum * scale_of(i));
     }
     CG_STAMP(3);
-}
-
-// The same with the totals in `stage` (LDS), which the workgroup has just written.
-template <int NT, int BG, int ROWS>
-__device__ __forceinline__ void finish_block(const GemmParams& p, const Member& mm, const float* stage, uint32_t* flag,
-                                             int tid, int blk, int ks, int b0)
-{
-    CG_STAMP(16);
-    __syncthreads();
-    CG_STAMP(17);
-
-    constexpr int PER_THREAD = (BG * ROWS + NT - 1) / NT;             // outputs per thread
-    float mine[PER_THREAD];
-    uint32_t scale_bits[PER_THREAD];
-#pragma unroll
-    for (int i = 0; i < PER_THREAD; ++i) {
-        const int o = tid + i * NT;
-        const int nn = blk * ROWS + o % ROWS;
-        mine[i] = (o < BG * ROWS) ? stage[o] : 0.0f;
-        // requested before any ticket round trip; with group scales the totals are already scaled
-        scale_bits[i] = mm.scales ? reinterpret_cast<const uint16_t*>(mm.scales)[nn < mm.N ? nn : 0] : 0x3c00u;
-    }
-    finish_values<NT, BG, ROWS>(p, mm, mine, scale_bits, flag, tid, blk, ks, b0);
 }
 
 // acc + scale * psum for group scales, acc + psum otherwise.
