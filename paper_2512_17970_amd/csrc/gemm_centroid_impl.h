@@ -86,8 +86,8 @@ __device__ __forceinline__ void row_exchange(uint32_t& a, uint32_t& b)
     b = r[1];
 }
 
-// Row scale of the output rows of this thread (all of them are row tid % RB of the block), requested while K is streamed: asked for at the
-// end it is the one load that a call still waits for (0.3 to 0.7 us).
+// Row scale of the output rows of this thread (all of them are row tid % RB of the block), requested in front of the sums over the wavefronts: asked for
+// behind them it is the one load that a call still waits for (0.3 to 0.7 us).
 template <int RB>
 __device__ __forceinline__ uint32_t row_scale_bits(const Member& mm, int tid, int blk)
 {
@@ -99,16 +99,29 @@ __device__ __forceinline__ uint32_t row_scale_bits(const Member& mm, int tid, in
 // banks), and the end of the workgroup's work.  Each thread adds up the outputs that it then stores; all tiles of batch rows
 // together: one barrier in front and one behind, where a tile at a time with its totals in LDS took 0.5 (8 rows) to 1.7 us (16 rows in
 // 32-row blocks) of a call.
-template <int THREADS, int BT, int RB, int SLICES>
+template <int THREADS, int BT, int RB, int SLICES, bool TERNARY = false>
 struct SliceSums {
     static constexpr int kStride = RB + 4;
     static constexpr size_t kBytes = (size_t)SLICES * BT * kStride * sizeof(float);
     static constexpr size_t kLds = kBytes + 64;        // .. and the ticket's flag
     static __device__ __forceinline__ void finish(const GemmParams& p, const Member& mm, float* parts, uint32_t scale_bits, int tid, int blk, int ks, int b0)
     {
-        finish_block<THREADS, BT, RB, SLICES>(p, mm, parts, reinterpret_cast<uint32_t*>(reinterpret_cast<unsigned char*>(parts) + kBytes), tid, blk, ks, b0, scale_bits);
+        finish_block<THREADS, BT, RB, SLICES, TERNARY>(p, mm, parts, reinterpret_cast<uint32_t*>(reinterpret_cast<unsigned char*>(parts) + kBytes), tid, blk, ks, b0, scale_bits);
     }
 };
+
+// The one pass costs some instances of gemm_centroid_kernel, whose registers are all taken, values of the loop that go to scratch.  (Percent of a call's time, on
+// random sizes with 9 batch rows and more, against sums a tile at a time; lowest and highest in brackets.)
+//  * fp32 output, v8 m1 with group scales, 32-row blocks (27 spills for 11): 2 to 4 % more (-5 to 14).  It keeps sums a tile at a time.
+//  * 128-row blocks of fp16 output v16 m4 (19 for 18) 5 % more (0 to 12), of v16 m3 with groups that hold a step and of fp32 output v4 m2 with group
+//    scales 0 % (-4 to 7).  What outputs beyond the batch do not add, written as a conditional expression in place of a branch, gives them another
+//    assignment of registers: 1 to 3 % less, 2 % less and 2 % less (none more than 1 % more).  Other instances spill more by it (fp32 output v8 m4 and
+//    v4 m2, v8 m4 with group scales: 1 to 13 % more time).
+__host__ __device__ constexpr bool sums_tiled(int m, int v, int sb, int nt, int gs) { return m == 1 && v == 8 && sb == 4 && nt == 4 && gs == 4; }
+__host__ __device__ constexpr bool sums_ternary(int m, int v, int sb, int gs)
+{
+    return sb == 1 && ((m == 4 && v == 16 && gs == 0) || (m == 3 && v == 16 && gs == 1) || (m == 2 && v == 4 && gs == 4));
+}
 
 // SB: sub-vectors along the columns of the operands (16 / SB octets per wavefront, 16 / SB batch rows per tile).
 // NT: tiles of batch rows.  RW x KW wavefronts: RW blocks of 128 / SB rows, KW slices of K.  D: steps in the load
@@ -164,6 +177,10 @@ __global__ void __launch_bounds__(RW * KW * 64) gemm_centroid_kernel(CG_HEAD_PAR
     constexpr int TURNS = ADDS >= AIM ? 0 : D * ADDS >= AIM ? 1 : D * ADDS >= AIM / 2 ? 2 : 4;
     constexpr int kOutOfRange = 0x7ffffff0;
     constexpr uint32_t kRsrcFlags = 0x00020000u;
+    constexpr bool TILED = sums_tiled(M, V, SB, NT, GS);
+    // The row scale is asked for behind the loop, in front of the wavefronts' sums: with the first codes it held a register through the loop and
+    // made calls 1 to 3 % longer.  Here that register happens to leave the loop fewer spills (7 for 12): 0.88 of the time, 9 batch rows and more.
+    constexpr bool EARLY = GS == 3 && V == 4 && M == 2 && SB == 1;
     static_assert((KW & (KW - 1)) == 0, "slices are added in pairs");
     static_assert(THREADS == 512, "a pass over the table's entries is one codebook (v = 16) or two");
     static_assert(RB <= kGranuleRows, "rows of a workgroup lie in one granule");
@@ -365,7 +382,7 @@ __global__ void __launch_bounds__(RW * KW * 64) gemm_centroid_kernel(CG_HEAD_PAR
         if constexpr (SCALED) load_scales(sc[d], s_beg + d);
     }
     uint32_t scale_bits = 0x3c00u;
-    if constexpr (!SCALED) scale_bits = row_scale_bits<RB>(mm, tid, blk);
+    if constexpr (EARLY) scale_bits = row_scale_bits<RB>(mm, tid, blk);
     __builtin_amdgcn_sched_barrier(0);
 
     // replicate the centroids
@@ -544,13 +561,18 @@ __global__ void __launch_bounds__(RW * KW * 64) gemm_centroid_kernel(CG_HEAD_PAR
     }
     if constexpr (SHORT) move_up();
 
-    // Sum over the wavefronts' K slices: partials in LDS (ONE: the four sub-vectors of a slice apart), all tiles of batch rows at once.
+    // Sum over the wavefronts' K slices: partials in LDS (ONE: the four sub-vectors of a slice apart), all tiles of batch rows at once or (TILED) one
+    // by one, the totals then behind them as [batch row][RB].
     constexpr int SLICES = ONE ? 4 * KW : KW;
-    typedef SliceSums<THREADS, BT, RB, SLICES> Sums;
+    constexpr int ROWS = TILED ? BPT : BT;
+    typedef SliceSums<THREADS, ROWS, RB, SLICES, sums_ternary(M, V, SB, GS)> Sums;
     float* parts = reinterpret_cast<float*>(smem);
+    float* totals = parts + SLICES * ROWS * Sums::kStride;
     __syncthreads();                                   // everyone is done with the table
+    if constexpr (!SCALED && !EARLY && !TILED) scale_bits = row_scale_bits<RB>(mm, tid, blk);
 #pragma unroll
-    for (int nt = 0; nt < NT; ++nt)
+    for (int nt = 0; nt < NT; ++nt) {
+        if (TILED && nt > 0) __syncthreads();          // the previous tile's partials have been read
 #pragma unroll
         for (int t = 0; t < TL; ++t) {
             float v[8];
@@ -562,12 +584,20 @@ __global__ void __launch_bounds__(RW * KW * 64) gemm_centroid_kernel(CG_HEAD_PAR
             }
             const int b = ONE ? 0 : BPT * nt + TL * q + t;
             if (ONE ? (lane & 3) == q : b0 + b < p.B && (lane & (SB - 1)) == 0) {
-                float* dst = parts + ((ONE ? kw * 4 + q : kw) * BT + b) * Sums::kStride + (rw * OCT + col_o) * 8;
+                float* dst = parts + ((ONE ? kw * 4 + q : kw) * ROWS + b % ROWS) * Sums::kStride + (rw * OCT + col_o) * 8;
                 *reinterpret_cast<float4_t*>(dst) = float4_t{v[0], v[1], v[2], v[3]};
                 *reinterpret_cast<float4_t*>(dst + 4) = float4_t{v[4], v[5], v[6], v[7]};
             }
         }
-    Sums::finish(p, mm, parts, scale_bits, tid, blk, ks, b0);
+        if constexpr (TILED) {
+            __syncthreads();
+            const int nb = min(p.B - b0 - BPT * nt, BPT);
+            for (int o = tid; o < nb * RB; o += THREADS)
+                totals[BPT * nt * RB + o] = pairwise_sum<SLICES>(parts + o / RB * Sums::kStride + o % RB, BPT * Sums::kStride);
+        }
+    }
+    if constexpr (TILED) finish_block<THREADS, BT, RB>(p, mm, totals, reinterpret_cast<uint32_t*>(totals + BT * RB), tid, blk, ks, b0);
+    else Sums::finish(p, mm, parts, scale_bits, tid, blk, ks, b0);
 }
 
 // Steps in the load ring of the kernels with one tile of batch rows: four, but three or two where that is what brings a lane's
@@ -593,7 +623,8 @@ int launch_gemm_centroid_one(const Geometry& g, const GemmParams& p, hipStream_t
     auto fn = gemm_centroid_kernel<M, V, SB, NT, RW, KW, D, GS, ONE>;
     constexpr int RB = 128 / SB * RW, BPT = ONE ? 1 : 16 / SB;
     if (g.RB != RB || g.BG != BPT * NT) return CODEGEMM_UNSUPPORTED;
-    constexpr size_t stage = SliceSums<RW * KW * kWave, BPT * NT, RB, ONE ? 4 * KW : KW>::kLds;
+    constexpr bool TILED = sums_tiled(M, V, SB, NT, GS);
+    constexpr size_t stage = SliceSums<RW * KW * kWave, TILED ? BPT : BPT * NT, RB, ONE ? 4 * KW : KW>::kLds + (TILED ? BPT * NT * RB * sizeof(float) : 0);
     constexpr size_t table = CentroidTable<M, V>::kBytes;
     constexpr size_t lds = stage > table ? stage : table;
     static_assert(lds <= (size_t)kMaxLds, "LDS");

@@ -415,13 +415,13 @@ __device__ __forceinline__ float pairwise_sum(const float* src, int stride)
 
 // End of a workgroup's work, shared by all kernels with K ranges.  `stage` (LDS) holds the
 // workgroup's BG x ROWS row totals over its K range (the gather kernels), or SLICES partial sums of each as
-// [slice][batch row][ROWS + 4], and row_scale is the fp16 bits of the scale of row tid % ROWS (the centroid kernels).
+// [slice][batch row][ROWS + 4], and row_scale is the fp16 bits of the scale of row tid % ROWS (the centroid kernels; TERNARY: see sums_ternary).
 // With one K range they are scaled and stored.  Otherwise each workgroup stores its totals as fp32 partials, takes a ticket on
 // the row block's counter, and the last one to arrive adds the partials of all K ranges in
 // range order, scales and stores y.  Ends with the kernel: every path returns.
 // (One function, the two sources inside it: handed over as arrays by a caller, the totals cost the batched kernels 20 to 80 instructions for row
 // addresses, with 14 + 2 wavefronts 0.4 % of a call in the mean of 2900 random sizes and up to 3 %.)
-template <int NT, int BG, int ROWS, int SLICES = 0>
+template <int NT, int BG, int ROWS, int SLICES = 0, bool TERNARY = false>
 __device__ __forceinline__ void finish_block(const GemmParams& p, const Member& mm, const float* stage, uint32_t* flag,
                                              int tid, int blk, int ks, int b0, uint32_t row_scale = 0)
 {
@@ -439,11 +439,14 @@ __device__ __forceinline__ void finish_block(const GemmParams& p, const Member& 
         const int nn = n_base + o % ROWS;
         if constexpr (SLICES > 0) {
             static_assert(NT % ROWS == 0, "one row of W per thread");
-            constexpr int STEP = NT / ROWS;             // batch rows
-            const float* src = stage + tid / ROWS * (ROWS + 4) + tid % ROWS;
-            const int b = tid / ROWS + i * STEP;
-            mine[i] = 0.0f;
-            if (b < BG && b0 + b < p.B) mine[i] = pairwise_sum<SLICES>(src + i * STEP * (ROWS + 4), BG * (ROWS + 4));
+            const int b = o / ROWS;
+            const bool used = b < BG && b0 + b < p.B;
+            const float* src = stage + b * (ROWS + 4) + o % ROWS;
+            if constexpr (TERNARY) mine[i] = used ? pairwise_sum<SLICES>(src, BG * (ROWS + 4)) : 0.0f;
+            else {
+                mine[i] = 0.0f;
+                if (used) mine[i] = pairwise_sum<SLICES>(src, BG * (ROWS + 4));
+            }
         } else {
             mine[i] = (o < BG * ROWS) ? stage[o] : 0.0f;
             // requested before any ticket round trip; with group scales the totals are already scaled

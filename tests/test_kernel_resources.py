@@ -59,3 +59,17 @@ def _one(kernels, name, *args):
 def test_epilogue_of_the_batched_kernel(kernels, args, code):
     """14 + 2 wavefronts, bytes of code: 440 more, row addresses in the epilogue, cost up to 2 % of a call.  (The limits lie 150 above.)"""
     assert _one(kernels, "gemm_batch_kernel", *args)[2] <= code
+
+
+# <M, V, SB, NT, RW, KW, D, GS, ONE> of gemm_centroid_kernel
+@pytest.mark.parametrize("args,registers", [((1, 16, 4, 1, rw, 8 // rw, 4, 3, one), 128) for rw in (1, 2, 4) for one in (False, True)])
+def test_two_workgroups_share_a_compute_unit(kernels, args, registers):
+    """512 threads and a table of 64 KB: up to 128 registers leave room for a second workgroup, 130 do not."""
+    assert _one(kernels, "gemm_centroid_kernel", *args)[0] <= registers
+
+
+@pytest.mark.parametrize("args,spills", [((4, 16, 1, 1, 1, 8, 2, 0, False), 18), ((1, 8, 4, 4, 1, 8, 2, 4, False), 11), ((2, 4, 2, 2, 1, 8, 2, 3, False), 0),
+                                         ((4, 8, 2, 2, 1, 8, 2, 3, False), 0), ((2, 4, 1, 1, 1, 8, 2, 3, False), 7)])
+def test_spilled_registers(kernels, args, spills):
+    """Instances that were up to 12 % slower with some more."""
+    assert _one(kernels, "gemm_centroid_kernel", *args)[1] <= spills
