@@ -14,7 +14,7 @@ from typing import Optional
 
 try:
     from . import _calls                      # csrc/python_calls.cpp: the two calls of a decoding loop without ctypes
-except ImportError:                           # not built yet: load() says so
+except ImportError:                           # not built (yet), or for another Python: the ctypes forms below serve
     _calls = None
 
 _PKG = os.path.dirname(os.path.abspath(__file__))
@@ -101,7 +101,6 @@ def load() -> ctypes.CDLL:
     if not os.path.exists(_LIB_PATH):
         raise ImportError(f"{_LIB_PATH} is missing: run `python -c 'import __graft_entry__ as g; g.build()'` "
                           "(or python paper_2512_17970_amd/build.py) first; there is no CPU fallback")
-    from . import _calls as calls              # built with the library, so it may be there only now
     lib = ctypes.CDLL(_LIB_PATH)
     vp, i, sz = ctypes.c_void_p, ctypes.c_int, ctypes.c_size_t
     dp, pp = ctypes.POINTER(Desc), ctypes.POINTER(Plan)
@@ -141,7 +140,8 @@ def load() -> ctypes.CDLL:
     lib.codegemm_dequant_gemm.restype = i
     lib.codegemm_status_string.argtypes = [i]
     lib.codegemm_status_string.restype = ctypes.c_char_p
-    calls.use(ctypes.cast(lib.codegemm_gemm, vp).value, ctypes.cast(lib.codegemm_gemm_grouped, vp).value)
+    if _calls:
+        _calls.use(ctypes.cast(lib.codegemm_gemm, vp).value, ctypes.cast(lib.codegemm_gemm_grouped, vp).value)
     _lib = lib
     return lib
 

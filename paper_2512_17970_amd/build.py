@@ -3,6 +3,7 @@ from __future__ import annotations
 
 import glob
 import os
+import shutil
 import subprocess
 import sysconfig
 
@@ -33,8 +34,13 @@ def ablate_lib(mask: int) -> str:
 
 
 def build_calls(verbose: bool = False) -> str:
+    """The extension; without a C++ compiler or Python's headers there is none, and the binding makes its calls through ctypes."""
+    include = sysconfig.get_paths()["include"]
+    if not shutil.which("g++") or not os.path.exists(os.path.join(include, "Python.h")):
+        print(f"no g++ or no {include}/Python.h: built without {os.path.basename(CALLS)}", flush=True)
+        return ""
     cmd = ["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-fvisibility=hidden", "-Wall", "-Wno-missing-field-initializers", "-I", os.path.join(ROOT, "include"),
-           "-I", sysconfig.get_paths()["include"], os.path.join(CSRC, "python_calls.cpp"), "-o", CALLS]
+           "-I", include, os.path.join(CSRC, "python_calls.cpp"), "-o", CALLS]
     if verbose:
         print(" ".join(cmd), flush=True)
     subprocess.run(cmd, check=True)

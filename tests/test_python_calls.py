@@ -1,6 +1,9 @@
 """The extension's codegemm_gemm and codegemm_gemm_grouped against their ctypes forms: the same arguments reach the library in every form of a
 call that these take, and the same exceptions leave it."""
 import ctypes
+import os
+import subprocess
+import sys
 
 import pytest
 
@@ -115,3 +118,34 @@ def test_a_list_that_shrinks_while_it_is_read(calls):
     members[0] = (1, Clearing(), 2, 3, 4)
     cg.codegemm_gemm_grouped(DESC, PLAN, 1, members, 9, 4096)
     assert [len(s[3]) for s in seen] == [1]
+
+
+WITHOUT = """
+import ctypes, sys
+sys.modules["paper_2512_17970_amd._calls"] = None          # what an import finds where the extension has not been built
+import paper_2512_17970_amd as cg
+from paper_2512_17970_amd import binding
+assert binding._calls is None and cg.codegemm_gemm is binding._gemm and cg.codegemm_gemm_grouped is binding._gemm_grouped
+desc = cg.Desc.make(1, 512, 512, 8, 1)
+for call in (lambda: cg.codegemm_gemm(desc, None, 16, 16, 16, 16, 16, None, 0), lambda: cg.codegemm_gemm_grouped(desc, None, None, [(512, 16, 16, 16, 16)], 16, 0)):
+    try:
+        call()
+    except cg.CodegemmError as e:
+        assert e.status == -1, e
+    else:
+        raise AssertionError("no error")
+print(cg.codegemm_workspace_bytes(desc))
+"""
+
+
+def test_the_library_without_the_extension():
+    root = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+    out = subprocess.run([sys.executable, "-c", WITHOUT], cwd=root, capture_output=True, text=True)
+    assert out.returncode == 0 and int(out.stdout) == cg.codegemm_workspace_bytes(cg.Desc.make(1, 512, 512, 8, 1)), out.stderr
+
+
+def test_a_build_without_a_compiler_or_headers(monkeypatch, tmp_path, capsys):
+    from paper_2512_17970_amd import build
+    monkeypatch.setattr(build.subprocess, "run", lambda *a, **k: pytest.fail("nothing to run"))
+    monkeypatch.setattr(build.sysconfig, "get_paths", lambda: {"include": str(tmp_path)})
+    assert build.build_calls() == "" and "Python.h" in capsys.readouterr().out
