@@ -2,7 +2,7 @@
 // such a call spends 2.8 us in the interpreter and in argument conversion before it reaches the library, of the 8 us that
 // an eager call of a small layer takes in all (its kernels take 3); here 0.6.  Only the plain form of a call is handled: positional
 // arguments, Desc and Plan themselves, tensors (anything with data_ptr()), integer addresses or None.  Every other form, and every
-// error, goes to the ctypes functions, which then do and raise what they always did.
+// argument that the plain form refuses, goes to the ctypes functions, which then do and raise what they always did.
 #define PY_SSIZE_T_CLEAN
 #include <Python.h>
 
@@ -37,19 +37,22 @@ struct View {
     ~View() { if (held) PyBuffer_Release(&b); }
 };
 
-// Address of a tensor, an integer or None.
-bool address(PyObject* o, void** at)
+enum Form { kPlain, kOther, kRaised };
+
+// Address of a tensor, an integer or None.  What a data_ptr() raises is the caller's to see, but for AttributeError, which sends the
+// ctypes forms on to int(o).
+Form address(PyObject* o, void** at)
 {
-    if (o == Py_None) { *at = nullptr; return true; }
+    if (o == Py_None) { *at = nullptr; return kPlain; }
     if (PyLong_CheckExact(o)) *at = PyLong_AsVoidPtr(o);
     else {
         PyObject* n = PyObject_CallMethodNoArgs(o, data_ptr);
-        if (!n) return false;
-        if (!PyLong_CheckExact(n)) { Py_DECREF(n); return false; }
+        if (!n) return PyErr_ExceptionMatches(PyExc_AttributeError) ? kOther : kRaised;
+        if (!PyLong_CheckExact(n)) { Py_DECREF(n); return kOther; }
         *at = PyLong_AsVoidPtr(n);
         Py_DECREF(n);
     }
-    return *at != nullptr || !PyErr_Occurred();
+    return *at != nullptr || !PyErr_Occurred() ? kPlain : kOther;
 }
 
 bool size(PyObject* o, size_t* n)
@@ -84,9 +87,10 @@ PyObject* gemm(PyObject*, PyObject* const* a, Py_ssize_t n, PyObject* names)
     View desc, plan;
     void *at[6], *stream = nullptr;
     size_t bytes;
-    bool plain = gemm_at && !names && (n == 9 || n == 10) && structures(a[0], a[1], &desc, &plan);
-    for (int k = 0; plain && k < 6; ++k) plain = address(a[2 + k], &at[k]);
-    if (!plain || !size(a[8], &bytes) || (n == 10 && !(PyLong_CheckExact(a[9]) && address(a[9], &stream)))) return slowly(slow_gemm, a, n, names);
+    Form form = gemm_at && !names && (n == 9 || n == 10) && structures(a[0], a[1], &desc, &plan) ? kPlain : kOther;
+    for (int k = 0; form == kPlain && k < 6; ++k) form = address(a[2 + k], &at[k]);
+    if (form == kRaised) return nullptr;
+    if (form == kOther || !size(a[8], &bytes) || (n == 10 && !(PyLong_CheckExact(a[9]) && address(a[9], &stream) == kPlain))) return slowly(slow_gemm, a, n, names);
     const gemm_t call = gemm_at;
     int status;
     Py_BEGIN_ALLOW_THREADS
@@ -104,19 +108,19 @@ PyObject* gemm_grouped(PyObject*, PyObject* const* a, Py_ssize_t n, PyObject* na
     size_t bytes;
     codegemm_group_member group[kMaxMembers] = {};
     int32_t count = 0;
-    bool plain = grouped_at && !names && (n == 6 || n == 7) && structures(a[0], a[1], &desc, &plan) && address(a[2], &x) &&
-                 (PyList_CheckExact(a[3]) || PyTuple_CheckExact(a[3])) && PySequence_Fast_GET_SIZE(a[3]) <= kMaxMembers;
+    Form form = grouped_at && !names && (n == 6 || n == 7) && structures(a[0], a[1], &desc, &plan) &&
+                (PyList_CheckExact(a[3]) || PyTuple_CheckExact(a[3])) && PySequence_Fast_GET_SIZE(a[3]) <= kMaxMembers ? kPlain : kOther;
     // (a data_ptr() may run any Python, so the list is asked for its length again, and members are held while they are read)
-    for (; plain && count < PySequence_Fast_GET_SIZE(a[3]) && count < kMaxMembers; ++count) {
+    for (; form == kPlain && count < PySequence_Fast_GET_SIZE(a[3]) && count < kMaxMembers; ++count) {
         PyObject* m = PySequence_Fast_GET_ITEM(a[3], count);
         Py_INCREF(m);
-        plain = PyTuple_CheckExact(m) && PyTuple_GET_SIZE(m) == 5 && PyLong_CheckExact(PyTuple_GET_ITEM(m, 0));
-        if (plain) {
+        form = kOther;
+        if (PyTuple_CheckExact(m) && PyTuple_GET_SIZE(m) == 5 && PyLong_CheckExact(PyTuple_GET_ITEM(m, 0))) {
             const long rows = PyLong_AsLong(PyTuple_GET_ITEM(m, 0));
             void* at[4];
-            plain = rows >= INT32_MIN && rows <= INT32_MAX && !(rows == -1 && PyErr_Occurred());
-            for (int k = 0; plain && k < 4; ++k) plain = address(PyTuple_GET_ITEM(m, 1 + k), &at[k]);
-            if (plain) {
+            if (rows >= INT32_MIN && rows <= INT32_MAX && !(rows == -1 && PyErr_Occurred())) form = kPlain;
+            for (int k = 0; form == kPlain && k < 4; ++k) form = address(PyTuple_GET_ITEM(m, 1 + k), &at[k]);
+            if (form == kPlain) {
                 group[count].out_features = (int32_t)rows;
                 group[count].packed_codes = static_cast<const uint8_t*>(at[0]);
                 group[count].codebooks = at[1];
@@ -126,7 +130,10 @@ PyObject* gemm_grouped(PyObject*, PyObject* const* a, Py_ssize_t n, PyObject* na
         }
         Py_DECREF(m);
     }
-    if (!plain || !address(a[4], &workspace) || !size(a[5], &bytes) || (n == 7 && !(PyLong_CheckExact(a[6]) && address(a[6], &stream))))
+    if (form == kPlain) form = address(a[2], &x);
+    if (form == kPlain) form = address(a[4], &workspace);
+    if (form == kRaised) return nullptr;
+    if (form == kOther || !size(a[5], &bytes) || (n == 7 && !(PyLong_CheckExact(a[6]) && address(a[6], &stream) == kPlain)))
         return slowly(slow_grouped, a, n, names);
     const grouped_t call = grouped_at;
     int status;

@@ -120,6 +120,44 @@ def test_a_list_that_shrinks_while_it_is_read(calls):
     assert [len(s[3]) for s in seen] == [1]
 
 
+@pytest.mark.parametrize("error", [KeyboardInterrupt, SystemExit, MemoryError, RuntimeError, OverflowError])
+def test_what_a_data_ptr_raises_once(calls, error):
+    """An interrupt in data_ptr() is not lost, and no data_ptr() that raised is called again."""
+    seen, _ = calls
+
+    class Once:
+        asked = 0
+
+        def data_ptr(self):
+            self.asked += 1
+            if self.asked == 1:
+                raise error("once")
+            return 0x40
+
+    for at in range(6):
+        for call in (cg.codegemm_gemm, binding._gemm):
+            once, args = Once(), [1, 2, 3, 4, 5, 6]
+            args[at] = once
+            with pytest.raises(error):
+                call(DESC, PLAN, *args, 4096, 0)
+            assert once.asked == 1 and not seen
+    for at in range(6):
+        for call in (cg.codegemm_gemm_grouped, binding._gemm_grouped):
+            once, args = Once(), [1, 2, 3, 4, 5, 6]
+            args[at] = once
+            with pytest.raises(error):
+                call(DESC, PLAN, args[0], [(1, 2, 3, 4, 5), (1, *args[1:5])], args[5], 4096)
+            assert once.asked == 1 and not seen
+
+
+def test_which_of_two_errors_is_raised(calls):
+    """Members are looked at before x."""
+    x, y = Tensor(KeyError("x")), Tensor(ValueError("y"))
+    for call in (cg.codegemm_gemm_grouped, binding._gemm_grouped):
+        with pytest.raises(ValueError):
+            call(DESC, PLAN, x, [(1, 2, 3, 4, y)], 6, 4096)
+
+
 WITHOUT = """
 import ctypes, sys
 sys.modules["paper_2512_17970_amd._calls"] = None          # what an import finds where the extension has not been built
