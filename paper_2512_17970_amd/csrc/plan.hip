@@ -342,10 +342,9 @@ static int low_rows(int n) { return ceil_div(n, 32) <= 256 ? 32 : ceil_div(n, 64
 //    (two rows, v8 m1 g128: 0.75 to 0.97 at K = 8300 to 28000 and 16400 to 18000 rows), and v16 with three or four codebooks, whose lookups read 32
 //    bytes (two rows, v16 m4: 1.2 below K = 4000, 0.95 to 1.05 at 8000, 0.8 to 0.9 from 16000 on).
 //  * Groups shorter than a step cost a flush inside it.  With several codebooks the register-loading kernel has only 128-row
-//    blocks for them from nine rows on, too few of them on small matrices (v8 m2 g32 2048^2, batch 16: 8.7/10.3 us), and
-//    v = 16 loses at two rows.  v8 m2 has staged blocks of 32 rows and wins from 1.1 million codes on (batch 16, Psumbook / staged
-//    kernel: 853 rows of K = 5376 12.2/6.1 us, 3000 of 3072 13.0/5.9; batch 9 to 32 of six such shapes 1.5 to 2.2); 2048^2,
-//    just below, was not moved.
+//    blocks for them from nine rows on, too few of them on small matrices (v8 m3 and fp32 output below 4 million codes), and v = 16 loses at two
+//    rows.  v8 m2 with fp16 output has staged blocks of 32 rows at any size (2400 random sizes of 30 000 to 1.1 million codes, g 32 and 64, 9 to 32
+//    rows, Psumbook / staged kernel: 1.31 to 2.61, 1.74 in the mean; 2048^2 g32, 9, 16 and 32 rows: 7.5/4.6, 7.8/4.7 and 10.5/5.9 us).
 //  * fp32 output pays for its short chains of sums: v = 16 loses on small matrices, at two rows (m2 8192^2 8.4/9.4) and
 //    with three and four codebooks, and above 8 rows its 16 products per sum leave it less exact than the Psumbook
 //    kernels (1.04 to 1.08 of their error below K = 8192).
@@ -361,7 +360,7 @@ static bool prefer_centroid(const codegemm_desc* d)
     const bool fp32 = d->flags & CODEGEMM_FLAG_Y_FP32, grouped = d->group_size > 0;
     const long long codes = (long long)m * N * (K / v);
     if (short_groups(d)) {
-        if (batch > 8 && batch <= kBatchPerLaunch && m > 1 && codes < (staged_format(d) ? 1100000 : 4000000)) return false;
+        if (batch > 8 && batch <= kBatchPerLaunch && m > 1 && !staged_format(d) && codes < 4000000) return false;
         if (v == 16 && batch == 2 && m > 2) return false;
     }
     if (fp32 && v == 16 && (batch > 8 || codes < 6000000 || batch == 2 || m > 2)) return false;

@@ -146,11 +146,22 @@ def test_default_plan_keeps_the_other_kernels_where_they_win():
     assert fp32(1, 4096, 4096, 8, 2).centroid_rows == 0 and fp32(1, 4096, 4096, 8, 1).centroid_rows == 32
     assert fp32(4, 8192, 8192, 16, 4).centroid_rows == 0 and fp32(16, 8192, 8192, 16, 2).centroid_rows == 0 and fp32(4, 8192, 8192, 16, 2).centroid_rows == 32
     assert plan(4, 8192, 8192, 8, 2, 16).centroid_rows == 0             # groups smaller than an MFMA's contraction
-    assert plan(16, 2048, 2048, 8, 2, 32).centroid_rows == 0 and plan(16, 2048, 2048, 8, 1, 32).centroid_rows != 0
+    assert plan(16, 2048, 2048, 8, 3, 32).centroid_rows == 0 and plan(16, 2048, 2048, 8, 1, 32).centroid_rows != 0
     assert plan(2, 8192, 8192, 16, 4, 64).centroid_rows == 0 and plan(4, 8192, 8192, 16, 4, 64).centroid_rows != 0
     for B in (2, 8, 32, 500):
         assert plan(B, 8192, 28672, 8, 2).centroid_rows != 0
     assert plan(2, 512, (1 << 24), 8, 1).centroid_rows == 0             # more blocks than a grid has
+
+
+@pytest.mark.parametrize("g", [32, 64])
+def test_small_matrices_with_short_groups(g):
+    """v8 m2, fp16 output: low staged blocks at every size (2048^2 g32, 16 rows: Psumbook kernels 7.8 us, staged 4.7; 5376->768 9.7, 6.0; 512->627 g64,
+    24 rows 6.7, 4.2).  fp32 output has no such blocks."""
+    for B in (8, 9, 16, 17, 32, 33):
+        for K, N in ((512, 627), (1024, 1024), (2048, 2048), (4096, 1024), (5376, 768), (16384, 128)):
+            assert cg.codegemm_default_plan(cg.Desc.make(B, K, N, 8, 2, g=g)).centroid_rows == 32, (B, K, N)
+            if 9 <= B <= 32:
+                assert cg.codegemm_default_plan(cg.Desc.make(B, K, N, 8, 2, g=g, y_fp32=True)).centroid_rows == 0, (B, K, N)
 
 
 def test_two_rounds_of_tall_blocks_or_three_of_lower_ones():
