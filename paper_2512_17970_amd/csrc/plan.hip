@@ -487,13 +487,9 @@ static void choose_plan(const codegemm_desc* d, codegemm_plan* p)
     if (splits < 1) splits = 1;
     // 5 rows and more of the staged kernel's formats: another height or number of ranges where the costs say that it is worth 3 %.  Against the
     // rules alone that is 0.4 % in the mean at 5 to 8 rows, 2 % at 9 to 16, 5 % at 17 to 32 and 4 % above, up to a factor of 2.9; 0.8, 0.6, 1.7 and 2 % of the
-    // sizes lose 3 % or more by it (the costs are 9 % off either way).  v8 m2 with up to 8 rows and two rounds of 128-row blocks keeps three rounds
-    // of 64 rows from K = 8192 on, the plan that such layers already hold: a tie at first (33591 rows, 6 batch rows, K = 8224 32.8 / 32.5 us), 4 %
-    // slower at 27216 (93.1 / 89.6).
-    const bool three_rounds = d->vec_len == 8 && d->num_codebooks == 2 && d->group_size < 0 && d->batch > 4 && d->batch <= 8 &&
-                              !(d->flags & CODEGEMM_FLAG_Y_FP32) && d->in_features >= 8192 && blocks(128) > 256 && blocks(64) <= 768;
-    if (three_rounds) rows = 64;
-    if (!three_rounds && d->batch > 4 && staged_format(d)) {
+    // sizes lose 3 % or more by it (the costs are 9 % off either way).  Two rounds of 128-row blocks and three of 64 rows
+    // tie (v8 m2, 5 to 8 rows, 1200 sizes with K from 8192 on, time of 64 / of 128 rows: 1.003 in regions of 3 ms, 0.94 to 1.05; 1.014 in short ones).
+    if (d->batch > 4 && staged_format(d)) {
         // v8 m1 without group scales, 17 rows and more: 128-row blocks take 32 rows there and lower ones 16, so these win (0.5 to 0.85 of the time) up to 128
         // tiles of 128 x 32 and lose beyond (1.3 at K = 1000, 1.1 at 3000, 1.03 to 1.08 from 4096 on), whatever K is
         const bool tall = d->vec_len == 8 && d->num_codebooks == 1 && d->group_size < 0 && d->batch > 16 && blocks(128) > 128;
