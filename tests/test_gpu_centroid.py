@@ -16,6 +16,8 @@ from gpu_util import DeviceLayer, Guarded, check_against_oracle, dev, exact_on_g
 def least_rows(B, v=8, m=2, g=-1, fp32=False):
     if v == 16:
         return 32 if B <= 4 else 64 if B <= 8 else 128
+    if not fp32 and (v, m) in ((8, 1), (8, 2), (4, 1)):                 # the staged kernel's
+        return 32
     return 32 if B <= 8 or m == 1 or (g < 0 and not fp32) else 64 if g < 0 or (g >= 128 and not fp32) else 128
 
 
@@ -152,22 +154,25 @@ def test_fp32_output_keeps_chains_of_sums_short(v, m, g, B, rows):
 @pytest.mark.parametrize("B,row", [(3, 1), (6, 4), (13, 0), (20, 19), (70, 33)])
 def test_non_finite_activations_stay_in_their_row(B, row):
     """The batch rows share instructions (and, up to 8 rows, result tiles whose other elements are discarded): an
-    infinity or NaN in one row of x reaches that row of y alone."""
-    case = synth.custom_case(8 * 32 * 4, 300, 8, 2, B, seed=3300)
-    inp = synth.generate(case)
-    clean = DeviceLayer(inp, plan=plan_of(case, 128, 1)).gemm().clone()
-    inp.x = inp.x.copy()
-    inp.x[row, ::97] = np.inf
-    inp.x[row, 5] = np.nan
-    y = DeviceLayer(inp, plan=plan_of(case, 128, 1)).gemm()
-    torch.cuda.synchronize()
-    others = [b for b in range(B) if b != row]
-    assert torch.equal(y[others], clean[others])
-    assert not bool(torch.isfinite(y[row]).any().item())
+    infinity or NaN in one row of x reaches that row of y alone.  At every block height: 64 and 32 rows are staged from 5 batch rows on, with a row
+    of zeros beside up to 8."""
+    for rows, g in ((128, -1), (64, -1), (32, -1), (64, 32), (32, 128)):
+        case = synth.custom_case(8 * 32 * 4, 300, 8, 2, B, seed=3300, g=g)
+        inp = synth.generate(case)
+        clean = DeviceLayer(inp, plan=plan_of(case, rows, 1)).gemm().clone()
+        inp.x = inp.x.copy()
+        inp.x[row, ::97] = np.inf
+        inp.x[row, 5] = np.nan
+        y = DeviceLayer(inp, plan=plan_of(case, rows, 1)).gemm()
+        torch.cuda.synchronize()
+        others = [b for b in range(B) if b != row]
+        assert torch.equal(y[others], clean[others]), (rows, g)
+        assert not bool(torch.isfinite(y[row]).any().item()), (rows, g)
 
 
 @pytest.mark.parametrize("B,rows,splits,g", [(1, 32, 1, -1), (1, 64, 2, 128), (4, 32, 3, -1), (8, 64, 4, -1), (6, 32, 1, 128),
-                                             (16, 128, 2, 128), (16, 32, 2, -1), (3, 32, 1, 32), (11, 128, 2, 64), (13, 64, 1, 128), (32, 128, 5, -1), (32, 64, 2, -1)])
+                                             (16, 128, 2, 128), (16, 32, 2, -1), (3, 32, 1, 32), (11, 128, 2, 64), (13, 64, 1, 128), (32, 128, 5, -1), (32, 64, 2, -1),
+                                             (9, 32, 2, 32), (16, 64, 4, 64), (32, 32, 3, 32), (20, 64, 2, 32), (7, 32, 4, 64)])
 def test_grouped_members_equal_their_single_calls(B, rows, splits, g):
     K, Ns = 2048, [300, 130, 65]
     desc = cg.Desc.make(B, K, sum(Ns), 8, 2, g=g)
@@ -237,6 +242,9 @@ def test_replays_from_a_hip_graph():
     """Captured calls give the eager bits on every replay, with eager calls on the same workspace in between."""
     layers = [DeviceLayer(synth.generate(synth.custom_case(K, N, 8, 2, B, seed=3500 + B)), plan=None)
               for K, N, B in ((4096, 1000, 4), (2048, 700, 16), (1024, 4200, 1))]
+    for rows, splits, B, g in ((32, 2, 6, -1), (64, 4, 16, 32), (32, 3, 24, 64), (64, 1, 12, 128)):                   # low staged blocks
+        case = synth.custom_case(4096, 300, 8, 2, B, seed=3510 + B, g=g)
+        layers.append(DeviceLayer(synth.generate(case), plan=plan_of(case, rows, splits)))
     eager = [l.gemm().clone() for l in layers]
     outs = [torch.empty_like(e) for e in eager]
     graph = torch.cuda.CUDAGraph()
@@ -277,7 +285,8 @@ def test_fp32_output_is_no_further_from_64_bits_than_the_psumbook_kernels(v, m, 
 
 
 @pytest.mark.parametrize("v,m,g,B", [(8, 2, -1, 5), (8, 2, -1, 16), (8, 2, -1, 17), (8, 2, -1, 33), (4, 1, -1, 7), (4, 1, -1, 32), (8, 1, -1, 16), (8, 2, 128, 2), (8, 2, 256, 4),
-                                     (8, 2, 128, 9), (8, 1, 128, 3), (8, 1, 256, 8), (4, 1, 128, 4), (4, 1, 128, 16), (4, 1, 256, 20)])
+                                     (8, 2, 128, 9), (8, 1, 128, 3), (8, 1, 256, 8), (4, 1, 128, 4), (4, 1, 128, 16), (4, 1, 256, 20),
+                                     (8, 2, 32, 9), (8, 2, 32, 20), (8, 2, 64, 6), (4, 1, 32, 7), (4, 1, 32, 16), (4, 1, 64, 20)])
 def test_staged_operands(v, m, g, B):
     """128-row blocks, fp16 output: codes and x pass through a ring of stages (8 or 16 chunks of 16 bytes of x) in LDS.  Slices of 0, 1,
     2 .. stages per wavefront, a last stage that the rows of x end inside of (at every number of chunks, half a chunk for v = 4)
@@ -292,16 +301,18 @@ def test_staged_operands(v, m, g, B):
 
 def test_staged_operands_leave_the_neighbours_of_x_alone():
     """The last row of x is followed by other memory, here NaN: what a stage reads past the end of a row counts for nothing."""
-    for v, m, K, B in ((8, 2, 1032, 6), (8, 1, 1096, 13), (8, 1, 2120, 13), (8, 1, 8200, 7), (4, 1, 1028, 16), (4, 1, 2052, 5), (8, 2, 2056, 31)):
-        inp = synth.generate(synth.custom_case(K, 130, v, m, B, seed=3500 + K))
+    for v, m, K, B, g in ((8, 2, 1032, 6, -1), (8, 1, 1096, 13, -1), (8, 1, 2120, 13, -1), (8, 1, 8200, 7, -1), (4, 1, 1028, 16, -1), (4, 1, 2052, 5, -1), (8, 2, 2056, 31, -1),
+                          (8, 2, 1056, 11, 32), (8, 2, 2112, 8, 64), (4, 1, 1184, 6, 32), (4, 1, 1312, 32, 32), (8, 1, 1120, 8, 32)):
+        inp = synth.generate(synth.custom_case(K, 130, v, m, B, seed=3500 + K, g=g))
         y_ref, T = oracle.gemm(inp.x, inp.codes, inp.codebooks, inp.scales)
-        layer = DeviceLayer(inp, plan=plan_of(inp.case, 128, 1))
-        wide = torch.full((B * K + 4096,), float("nan"), dtype=torch.float16, device="cuda")
-        wide[:B * K] = torch.from_numpy(inp.x.reshape(-1)).cuda()
-        layer.x = wide[:B * K].view(B, K)
-        y = layer.gemm()
-        torch.cuda.synchronize()
-        check_against_oracle(y.cpu().numpy(), y_ref, T, inp.case.name)
+        for rows in (128, 64, 32):
+            layer = DeviceLayer(inp, plan=plan_of(inp.case, rows, 1))
+            wide = torch.full((B * K + 4096,), float("nan"), dtype=torch.float16, device="cuda")
+            wide[:B * K] = torch.from_numpy(inp.x.reshape(-1)).cuda()
+            layer.x = wide[:B * K].view(B, K)
+            y = layer.gemm()
+            torch.cuda.synchronize()
+            check_against_oracle(y.cpu().numpy(), y_ref, T, f"{inp.case.name} rows={rows}")
 
 
 @pytest.mark.parametrize("v,m,g,B", [(8, 1, -1, 5), (8, 1, -1, 8), (8, 2, -1, 6), (4, 1, -1, 7), (4, 1, 128, 5), (4, 1, 256, 8), (8, 1, -1, 9), (8, 1, -1, 16)])
