@@ -426,8 +426,8 @@ def sweep_report(torch, cg, synth, cases, launch):
 def kernel_of(plan, batch):
     """Name of the kernel that a layer runs under its plan."""
     if plan.centroid_rows and plan.psum_dtype == 0:
-        # 128-row blocks stage their operands from a K on that depends on format and batch, large batches of many workgroups are prompts
-        staged = plan.centroid_rows == 128 and batch > 1
+        # staged operands: some formats, from 5 rows on at any block height, 128-row blocks from a K on that depends on format and batch; large batches of many workgroups are prompts
+        staged = batch > 4 or (plan.centroid_rows == 128 and batch > 1)
         return "cg::gemm_centroid_kernel" + (" or cg::gemm_staged_kernel" if staged else "") + (" or cg::gemm_prompt_kernel" if batch > 32 else "")
     return "cg::gemm_batch_kernel" if plan.batch_group == 4 else "cg::gemm_kernel"
 

@@ -51,7 +51,7 @@ struct Geometry {
                     // (32 * NW * RPL in the batched kernel, BG = 4)
     int BG;         // batch rows per pass over the codes
     int RB;         // rows of a block of the centroid kernel (32, 64 or 128), or 0: one of the Psumbook kernels
-    bool staged;    // the centroid kernel with codes and x staged in LDS (RB = 128)
+    bool staged;    // the centroid kernel with codes and x staged in LDS
     bool prompt;    // the prompt kernel: RB != 0, fp16 output, more than kBatchPerLaunch batch rows and enough of them
     bool half;      // .. with two wavefronts to a granule (v = 4, one codebook, group scales)
     int NGR;        // ceil(N / 128) granules

@@ -132,7 +132,7 @@ static void fill_common(GemmParams* p, const Geometry& g, const void* x, void* w
     p->y_fp32 = g.y_fp32 ? 1 : 0;
     p->trace = nullptr;
 #ifdef CODEGEMM_TRACE
-    if (!g.RB) p->trace = reinterpret_cast<unsigned long long*>(g_trace);   // the centroid kernel has other phases and no stamps
+    if (!g.RB) p->trace = reinterpret_cast<unsigned long long*>(g_trace);   // the centroid kernels share only the stamps of a call's end
 #endif
     p->ngrp = 1;
     for (int i = 0; i < kMaxGroup; ++i) p->mem[i] = Member{};

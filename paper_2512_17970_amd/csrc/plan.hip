@@ -441,8 +441,9 @@ static void choose_plan(const codegemm_desc* d, codegemm_plan* p)
     const int least = centroid_min_rows(d);
     auto blocks = [&](int r) { return (long long)ceil_div(d->out_features, r) * ceil_div(d->batch, centroid_batch(d, r)); };
     // Block height.  Low blocks need fewer K ranges, and with them the exchange through memory; from 5 batch rows on
-    // they cost more MFMAs per lookup (32 rows: one per 4 batch rows, 64: one per 8).  So: as low as fills the chip, and
-    // only for matrices whose lookups are few beside a call's fixed part (v8 m2, us: batch 8, 2048^2 32 rows 5.6, 64 rows
+    // they cost the register-loading kernel more MFMAs per lookup (32 rows: one per 4 batch rows, 64: one per 8).  So: as low as fills the chip, and
+    // only for matrices whose lookups are few beside a call's fixed part.  (The staged formats, whose low blocks pay one MFMA at any height, only start
+    // from this choice: the costs below have the last word.  Times of the register-loading kernel, v8 m2, us: batch 8, 2048^2 32 rows 5.6, 64 rows
     // 6.6; 4096^2 6.5 / 7.8; 8192^2 13.6 / 11.1; batch 16, 4096^2 32 rows 9.0, 64 rows 9.5, 128 rows 11.3; 4096->14336
     // 64 rows 12.5, 128 rows 14.0; 14336->4096 17.0 / 14.0; batch 32, 4096^2 64 rows 10.5, 128 rows 15.8).
     int rows = 128;
